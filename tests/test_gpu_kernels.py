@@ -397,6 +397,27 @@ def test_embedding_gather_and_scatter(orc64):
     assert np.all(got[V - 5:] == 0)
 
 
+@pytest.mark.parametrize("V,d", [(70, 8), (130, 520), (33, 1032), (40, 2568)])
+def test_embedding_scatter_with_frequent_tokens(orc64, V, d):
+    """Tokens that occur often are summed by a whole block: list lengths around the switch (32 and 33), one of several
+    hundred, none, the last row of the table; column counts around the 512 of a wave.  Every element is a sum of m bf16
+    terms in fp32: within m 2^-24 of the sum of their magnitudes, whatever the order."""
+    rng = np.random.default_rng(V + d)
+    tok = np.concatenate([np.full(700, 3), np.full(32, 5), np.full(33, 6), np.full(131, V - 1), rng.integers(7, V - 2, 60)]).astype(np.int32)
+    rng.shuffle(tok)
+    dh = bf16_round(rng.standard_normal((tok.size, d)))
+    order = np.argsort(tok, kind="stable").astype(np.int32)
+    row_start = np.zeros(V + 1, np.int32)
+    row_start[1:] = np.cumsum(np.bincount(tok, minlength=V))
+    DT = torch.full((V, d), 3.0, dtype=torch.float32, device="cuda")
+    DH, RS, ORD = dev_bf16(dh), dev_i32(row_start), dev_i32(order)
+    ok(L.mt_k_embed_scatter(DT.data_ptr(), DH.data_ptr(), RS.data_ptr(), ORD.data_ptr(), V, d, None))
+    got, ref = host(DT), orc64.embed_bwd(dh, tok, V)
+    mag = orc64.embed_bwd(np.abs(dh), tok, V)
+    assert (np.abs(got - ref) <= 700 * 2.0 ** -24 * mag).all()
+    assert np.all(got[0] == 0)
+
+
 # ----------------------------------------------------------------------------- cross-entropy
 @pytest.mark.parametrize("n,V", [(9, 1024), (5, 32000), (7, 520)])
 def test_cross_entropy(orc64, n, V):
