@@ -4,6 +4,7 @@
 // All of them move 16 bytes per lane per access (8 bf16 or 4 fp32), do their
 // arithmetic in fp32 and reduce inside a 64-lane wave with cross-lane shuffles.
 // None uses atomics, so every result is bit-reproducible from run to run.
+#include <algorithm>
 #include <atomic>
 
 #include "common.h"
@@ -11,6 +12,9 @@
 namespace mt {
 
 namespace {
+
+// four floats of a caller's fp32 array, which need not be aligned to more than a float
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ void unpack8(const uint4 &u, float *f) {
     f[0] = bflo(u.x); f[1] = bfhi(u.x); f[2] = bflo(u.y); f[3] = bfhi(u.y);
@@ -67,13 +71,15 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
     const uint4 *xr = reinterpret_cast<const uint4 *>(x + row * d);
     uint4 xv[NCH];
     float ss = 0.f;
+    // all loads first and without branches (chunks past the row re-read its last one): under a branch each load would be
+    // waited for before the next is issued
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) xv[i] = xr[min(lane + 64 * i, nch - 1)];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = lane + 64 * i;
-        if (c < nch) {
-            xv[i] = xr[c];
-            float f[8];
-            unpack8(xv[i], f);
+        float f[8];
+        unpack8(xv[i], f);
+        if (lane + 64 * i < nch) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) ss += f[k] * f[k];
         }
@@ -97,118 +103,145 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
 }
 
 // ------------------------------------------------------------------ RMSNorm backward
-// Wave w walks rows w, w + W, ...  Per row: r and dot = sum_j g_j dy_j x_j, then
-// dx = r g dy - x r^3 dot / d (+ dres).  The gain gradient sum_t dy x r is kept in
-// registers per lane and column, summed over the 4 waves of the block through LDS and
-// written as one partial row per block; a second kernel adds the partial rows in order.
+// Per row: r and dot = sum_j g_j dy_j x_j, then dx = r g dy - x r^3 dot / d (+ dres).  The gain gradient sum_t dy x r is
+// kept in registers per thread and column; every block writes one partial row, a second kernel adds the partial rows.
+// HBM-bound: three tensors read, one written, once each.  A row belongs to WPR waves of the block, NCH chunks of 16 bytes
+// per thread: one wave up to 1024 elements (with all four waves on a row, half of them would be idle), four beyond, so that
+// a row of any width fits the registers next to its gain gradient.  The next row is requested before this one is reduced.
+// One wave per row at every width, loads on demand and rows beyond 4096 read twice took (gain-gradient sum included)
+// 722 us for 65 536 x 5120, 479 for x 4096, 145 for x 1024; this kernel takes 518, 398 and 102 (5.2 and 5.4 TB/s at the
+// first two; a copy reaches 4.9).
 constexpr int kNormBwdBlocks = 512;
 
-template <int NCH>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *partial, const bf16_t *dy,
-                                                          const bf16_t *x, const bf16_t *gain, const bf16_t *dres,
-                                                          int64_t n, int d, float eps) {
-    extern __shared__ float red[];  // [d]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int NCH, int WPR>
+__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *partial, const bf16_t *dy, const bf16_t *x,
+                                                          const bf16_t *gain, const bf16_t *dres, int64_t n, int d, float eps) {
+    static_assert(WPR == 1 || WPR == 4, "a row belongs to one wave or to the whole block");
+    constexpr int TPR = 64 * WPR, RPB = 4 / WPR;   // threads per row, rows per block at a time
+    __shared__ float red[2][2][4];                 // [parity of the row][sum x^2, dot][wave]
+    __shared__ float dgs[WPR == 1 ? 8 * TPR * NCH : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = threadIdx.x % TPR;
     const int nch = d >> 3;
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
     float dg[NCH][8];
+    uint4 gv[NCH], xn[NCH], yn[NCH], rn[NCH];
 #pragma unroll
-    for (int i = 0; i < NCH; ++i)
+    for (int i = 0; i < NCH; ++i) {
+        const int c = tr + TPR * i;
+        gv[i] = c < nch ? reinterpret_cast<const uint4 *>(gain)[c] : zero;
 #pragma unroll
         for (int k = 0; k < 8; ++k) dg[i][k] = 0.f;
-    const uint4 *gr = reinterpret_cast<const uint4 *>(gain);
-
-    // up to 8 chunks per lane (d <= 4096) the row stays in registers between the two passes; wider rows are read again
-    constexpr bool kKeep = NCH <= 8;
-    for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < n; row += nwaves) {
-        const uint4 *xr = reinterpret_cast<const uint4 *>(x + row * d);
-        const uint4 *dyr = reinterpret_cast<const uint4 *>(dy + row * d);
-        uint4 xk[kKeep ? NCH : 1], yk[kKeep ? NCH : 1];
+    }
+    auto fetch = [&](int64_t row) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int c = tr + TPR * i;
+            const bool ok = c < nch;
+            xn[i] = ok ? reinterpret_cast<const uint4 *>(x + row * d)[c] : zero;
+            yn[i] = ok ? reinterpret_cast<const uint4 *>(dy + row * d)[c] : zero;
+            rn[i] = ok && dres ? reinterpret_cast<const uint4 *>(dres + row * d)[c] : zero;
+        }
+    };
+    const int64_t row0 = (int64_t)blockIdx.x * RPB + (WPR == 1 ? wave : 0), stride = (int64_t)gridDim.x * RPB;
+    if (row0 < n) fetch(row0);
+    int par = 0;
+    for (int64_t row = row0; row < n; row += stride, par ^= 1) {   // WPR == 4: the same rows in every wave of the block
+        uint4 xv[NCH], yv[NCH], rv[NCH];
         float ss = 0.f, dot = 0.f;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int c = lane + 64 * i;
-            if (c < nch) {
-                float xf[8], yf[8], gf[8];
-                const uint4 xu = xr[c], yu = dyr[c];
-                if (kKeep) {
-                    xk[i] = xu;
-                    yk[i] = yu;
-                }
-                unpack8(xu, xf);
-                unpack8(yu, yf);
-                unpack8(gr[c], gf);
+            xv[i] = xn[i];
+            yv[i] = yn[i];
+            rv[i] = rn[i];
+            float xf[8], yf[8], gf[8];
+            unpack8(xv[i], xf);
+            unpack8(yv[i], yf);
+            unpack8(gv[i], gf);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    ss += xf[k] * xf[k];
-                    dot += gf[k] * yf[k] * xf[k];
-                }
+            for (int k = 0; k < 8; ++k) {
+                ss += xf[k] * xf[k];
+                dot += gf[k] * yf[k] * xf[k];
             }
         }
+        if (row + stride < n) fetch(row + stride);
         ss = wave_sum(ss);
         dot = wave_sum(dot);
+        if constexpr (WPR == 4) {
+            if (lane == 0) {
+                red[par][0][wave] = ss;
+                red[par][1][wave] = dot;
+            }
+            __syncthreads();   // one per row: the other parity's slots are rewritten only after the next row's barrier
+            ss = (red[par][0][0] + red[par][0][1]) + (red[par][0][2] + red[par][0][3]);
+            dot = (red[par][1][0] + red[par][1][1]) + (red[par][1][2] + red[par][1][3]);
+        }
         const float r = 1.0f / sqrtf(ss / (float)d + eps);
         const float cc = r * r * r * dot / (float)d;
-        uint4 *dxr = reinterpret_cast<uint4 *>(dx + row * d);
-        const uint4 *rr = dres ? reinterpret_cast<const uint4 *>(dres + row * d) : nullptr;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int c = lane + 64 * i;
-            if (c < nch) {
-                float xf[8], yf[8], gf[8], of[8];
-                unpack8(kKeep ? xk[i] : xr[c], xf);
-                unpack8(kKeep ? yk[i] : dyr[c], yf);
-                unpack8(gr[c], gf);
-                if (rr) {
-                    unpack8(rr[c], of);
-                } else {
+            const int c = tr + TPR * i;
+            float xf[8], yf[8], gf[8], of[8];
+            unpack8(xv[i], xf);
+            unpack8(yv[i], yf);
+            unpack8(gv[i], gf);
+            unpack8(rv[i], of);
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) of[k] = 0.f;
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    of[k] += r * gf[k] * yf[k] - xf[k] * cc;
-                    dg[i][k] += yf[k] * xf[k] * r;
-                }
-                dxr[c] = pack8(of);
+            for (int k = 0; k < 8; ++k) {
+                of[k] += r * gf[k] * yf[k] - xf[k] * cc;
+                dg[i][k] += yf[k] * xf[k] * r;
             }
+            if (c < nch) reinterpret_cast<uint4 *>(dx + row * d)[c] = pack8(of);
         }
     }
-    // block reduction of the gain-gradient partials in the fixed order ((w0 + w1) + w2) + w3
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+    if constexpr (WPR == 1) {   // the four waves' sums, ((w0 + w1) + w2) + w3
+        for (int w = 0; w < 4; ++w) {
+            if (wave == w)
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int c = lane + 64 * i;
-                if (c < nch)
+                for (int i = 0; i < NCH; ++i)
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        if (w == 0) red[c * 8 + k] = dg[i][k];
-                        else red[c * 8 + k] += dg[i][k];
+                        float *p = &dgs[(i * 8 + k) * TPR + tr];
+                        if (w > 0) dg[i][k] = *p + dg[i][k];
+                        *p = dg[i][k];
                     }
-            }
+            __syncthreads();
         }
-        __syncthreads();
+        if (wave != 3) return;
     }
-    for (int j = threadIdx.x; j < d; j += 256) partial[(int64_t)blockIdx.x * d + j] = red[j];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = tr + TPR * i;
+        if (c < nch) {
+            f32x4_a4 *p = reinterpret_cast<f32x4_a4 *>(partial + (int64_t)blockIdx.x * d + c * 8);
+            p[0] = f32x4_a4{dg[i][0], dg[i][1], dg[i][2], dg[i][3]};
+            p[1] = f32x4_a4{dg[i][4], dg[i][5], dg[i][6], dg[i][7]};
+        }
+    }
 }
 
-// out[j] (+)= sum over rows of partial[r][j].  A block owns 32 columns; its 8 row groups each add every 8th row in
-// order and the 8 group sums are added in order, so the result does not depend on the launch.
-__global__ __launch_bounds__(256) void colsum_kernel(float *out, const float *partial, int nrows, int d, int accumulate) {
-    __shared__ float red[8][32];
-    const int cl = threadIdx.x & 31, rg = threadIdx.x >> 5;
-    const int j = blockIdx.x * 32 + cl;
-    float s = 0.f;
-    if (j < d)
-        for (int r = rg; r < nrows; r += 8) s += partial[(int64_t)r * d + j];
+// out[j] (+)= sum over rows of partial[r][j].  A block owns 32 columns, four per lane; its 128 row groups each add every
+// 128th row in order (at most 4 of the 512 rows that the callers produce: all of them in flight together) and the group
+// sums are added in a fixed tree, so the result does not depend on the launch.  Bound by latency, not by the 10 MB: 512 x 5120 took 20.6 us
+// with one float per lane and 8 row groups, 5.0 us so.
+__global__ __launch_bounds__(1024) void colsum_kernel(float *out, const float *partial, int nrows, int d, int accumulate) {
+    __shared__ f32x4 red[128][8];
+    const int cl = threadIdx.x & 7, rg = threadIdx.x >> 3;
+    const int j = blockIdx.x * 32 + cl * 4;   // d is a multiple of 8
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (j < d) {
+#pragma unroll 4
+        for (int r = rg; r < nrows; r += 128) s += *reinterpret_cast<const f32x4_a4 *>(partial + (int64_t)r * d + j);
+    }
     red[rg][cl] = s;
     __syncthreads();
-    if (rg == 0 && j < d) {
-        float t = red[0][cl];
 #pragma unroll
-        for (int g = 1; g < 8; ++g) t += red[g][cl];
-        out[j] = accumulate ? out[j] + t : t;
+    for (int h = 64; h > 0; h >>= 1) {
+        if (rg < h) red[rg][cl] += red[rg + h][cl];
+        __syncthreads();
+    }
+    if (rg == 0 && j < d) {
+        f32x4_a4 *o = reinterpret_cast<f32x4_a4 *>(out + j);
+        *o = accumulate ? *o + red[0][cl] : red[0][cl];
     }
 }
 
@@ -543,9 +576,9 @@ hipError_t rmsnorm_fwd(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n
                        hipStream_t s) {
     if (n <= 0 || d <= 0 || (d & 7) || d > 8192) return hipErrorInvalidValue;
     const unsigned grid = blocks_for(n, 4);
-    if (d <= 2048) hipLaunchKernelGGL(rmsnorm_fwd_kernel<4>, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
-    else if (d <= 4096) hipLaunchKernelGGL(rmsnorm_fwd_kernel<8>, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
-    else hipLaunchKernelGGL(rmsnorm_fwd_kernel<16>, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
+    auto kernel = d <= 1024 ? rmsnorm_fwd_kernel<2> : d <= 2048 ? rmsnorm_fwd_kernel<4> : d <= 4096 ? rmsnorm_fwd_kernel<8>
+                : d <= 5120 ? rmsnorm_fwd_kernel<10> : rmsnorm_fwd_kernel<16>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
     return hipGetLastError();
 }
 
@@ -555,20 +588,14 @@ hipError_t rmsnorm_bwd(bf16_t *dx_out, float *dgain, const bf16_t *dy, const bf1
                        const bf16_t *dres, float *partial, int64_t n, int32_t d, float eps, hipStream_t s,
                        int accumulate_dgain) {
     if (n <= 0 || d <= 0 || (d & 7) || d > 8192) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)((n + 3) / 4 < kNormBwdBlocks ? (n + 3) / 4 : kNormBwdBlocks);
-    const size_t lds = (size_t)d * sizeof(float);
-    if (d <= 2048)
-        hipLaunchKernelGGL(rmsnorm_bwd_kernel<4>, dim3(grid), dim3(256), lds, s, dx_out, partial, dy, x, gain, dres, n,
-                           d, eps);
-    else if (d <= 4096)
-        hipLaunchKernelGGL(rmsnorm_bwd_kernel<8>, dim3(grid), dim3(256), lds, s, dx_out, partial, dy, x, gain, dres, n,
-                           d, eps);
-    else
-        hipLaunchKernelGGL(rmsnorm_bwd_kernel<16>, dim3(grid), dim3(256), lds, s, dx_out, partial, dy, x, gain, dres,
-                           n, d, eps);
+    const int rpb = d <= 1024 ? 4 : 1;   // rows a block has in hand
+    const unsigned grid = (unsigned)std::min<int64_t>((n + rpb - 1) / rpb, kNormBwdBlocks);
+    auto kernel = d <= 512 ? rmsnorm_bwd_kernel<1, 1> : d <= 1024 ? rmsnorm_bwd_kernel<2, 1> : d <= 2048 ? rmsnorm_bwd_kernel<1, 4>
+                : d <= 4096 ? rmsnorm_bwd_kernel<2, 4> : d <= 6144 ? rmsnorm_bwd_kernel<3, 4> : rmsnorm_bwd_kernel<4, 4>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, dx_out, partial, dy, x, gain, dres, n, d, eps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(d, 32)), dim3(256), 0, s, dgain, partial, (int)grid, d,
+    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(d, 32)), dim3(1024), 0, s, dgain, partial, (int)grid, d,
                        accumulate_dgain);
     return hipGetLastError();
 }
@@ -608,7 +635,7 @@ hipError_t bias_grad(float *db, const bf16_t *x, int64_t ld, int64_t n, int32_t 
                        ld, n, cols, rpb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(cols, 32)), dim3(256), 0, s, db, ws, kBiasGradRowBlocks, cols, 0);
+    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(cols, 32)), dim3(1024), 0, s, db, ws, kBiasGradRowBlocks, cols, 0);
     return hipGetLastError();
 }
 

@@ -246,6 +246,27 @@ def test_rmsnorm_backward_many_rows_gain_reduction(orc64):
     assert_rows_close(host(DG), dg_ref, 2e-5, what="rmsnorm gain gradient, 5000 rows")
 
 
+@pytest.mark.parametrize("n,d", [(1, 8), (2050, 512), (5, 520), (3, 1024), (515, 1032), (1030, 2048), (7, 2056), (514, 4104),
+                                 (9, 6144), (2, 6152), (513, 8192)])
+def test_rmsnorm_at_the_widths_where_the_kernels_change(orc64, n, d):
+    """One and four waves per row, each number of 16-byte chunks per thread, partly filled ones, more rows than blocks."""
+    rng = np.random.default_rng(n * 3 + d)
+    x, g = bf16_round(rng.standard_normal((n, d)) * 1.7), bf16_round(1 + 0.3 * rng.standard_normal(d))
+    dy, dres = bf16_round(rng.standard_normal((n, d))), bf16_round(rng.standard_normal((n, d)))
+    X, G, DY, DR = dev_bf16(x), dev_bf16(g), dev_bf16(dy), dev_bf16(dres)
+    Y, DX = torch.empty_like(X), torch.empty_like(X)
+    DG = torch.full((d + 8,), 4.0, dtype=torch.float32, device="cuda")[1:]     # 4-byte aligned only
+    ws = torch.empty(L.mt_k_rmsnorm_bwd_ws_bytes(d) // 4, dtype=torch.float32, device="cuda")
+    ok(L.mt_k_rmsnorm_fwd(Y.data_ptr(), X.data_ptr(), G.data_ptr(), n, d, 1e-5, None))
+    assert_rows_close(host(Y), orc64.rmsnorm_fwd(x, g, 1e-5), ROW1, what="rmsnorm forward")
+    ok(L.mt_k_rmsnorm_bwd(DX.data_ptr(), DG.data_ptr(), DY.data_ptr(), X.data_ptr(), G.data_ptr(), DR.data_ptr(), ws.data_ptr(),
+                          n, d, 1e-5, None))
+    dx_ref, dg_ref = orc64.rmsnorm_bwd(dy, x, g, 1e-5)
+    assert_rows_close(host(DX), dx_ref + dres, ROW1, what="rmsnorm backward + residual")
+    assert_rows_close(host(DG)[:d], dg_ref, 2e-5, what="rmsnorm gain gradient")
+    assert np.all(host(DG)[d:] == 4.0)
+
+
 # ----------------------------------------------------------------------------- RoPE
 @pytest.mark.parametrize("hd,base", [(64, 10000.0), (128, 1.0e6)])
 def test_rope_forward_and_inverse(orc64, hd, base):
