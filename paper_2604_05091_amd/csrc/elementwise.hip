@@ -221,8 +221,8 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
 
 // out[j] (+)= sum over rows of partial[r][j].  A block owns 32 columns, four per lane; its 128 row groups each add every
 // 128th row in order (at most 4 of the 512 rows that the callers produce: all of them in flight together) and the group
-// sums are added in a fixed tree, so the result does not depend on the launch.  Bound by latency, not by the 10 MB: 512 x 5120 took 20.6 us
-// with one float per lane and 8 row groups, 5.0 us so.
+// sums are added in a fixed tree, so the result does not depend on the launch.  Bound by latency, not by the 10 MB:
+// 512 x 5120 took 20.6 us with one float per lane and 8 row groups, 5.0 us so.
 __global__ __launch_bounds__(1024) void colsum_kernel(float *out, const float *partial, int nrows, int d, int accumulate) {
     __shared__ f32x4 red[128][8];
     const int cl = threadIdx.x & 7, rg = threadIdx.x >> 3;
@@ -454,23 +454,76 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
 }
 
 // ------------------------------------------------------------------ cross-entropy
-// One block per row.  Pass 1: online (max, sum exp).  Pass 2: gradient.
-__global__ __launch_bounds__(256) void cross_entropy_kernel(float *loss_rows, bf16_t *dlogits, const float *logits,
-                                                            const int32_t *labels, int V, float inv_n) {
-    __shared__ float sm[4], ssum[4];
+// One block per row: maximum and sum of exponentials, then the gradient.  HBM-bound at 6 V bytes per row if the logits are
+// read once: up to 4 NR NT of them (32 768) stay in the registers of the block's NT threads between the two passes; wider
+// rows (NR = 0) are read twice, the first time with a running maximum.  8192 rows, before (256 threads, two reads) and
+// after: V = 32 000 470 -> 312 us (5.05 TB/s), 16 384 208 -> 157, 8000 100 -> 75, 1024 13.1 -> @V1024@.
+
+template <int NT>
+__device__ __forceinline__ float block_reduce(float v, float *buf, bool is_max) {
+    v = is_max ? wave_max(v) : wave_sum(v);
+    if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float r = buf[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) r = is_max ? fmaxf(r, buf[w]) : r + buf[w];
+    return r;
+}
+
+// e: exponentials of the logits relative to the row's maximum, inv: 1 / their sum (relative to the maximum and not to the
+// log-sum-exp: the difference of two large numbers is exact, their log-sum-exp is not)
+__device__ __forceinline__ uint2 ce_grad(const float4 &e, float inv, int c, int label, float inv_n) {
+    float p0 = e.x * inv, p1 = e.y * inv, p2 = e.z * inv, p3 = e.w * inv;
+    if (label == c) p0 -= 1.f;
+    if (label == c + 1) p1 -= 1.f;
+    if (label == c + 2) p2 -= 1.f;
+    if (label == c + 3) p3 -= 1.f;
+    return make_uint2(pack2bf(p0 * inv_n, p1 * inv_n), pack2bf(p2 * inv_n, p3 * inv_n));
+}
+
+template <int NT, int NR>
+__global__ __launch_bounds__(NT) void cross_entropy_kernel(float *loss_rows, bf16_t *dlogits, const float *logits,
+                                                           const int32_t *labels, int V, float inv_n) {
+    __shared__ float smax[NT / 64], ssum[NT / 64];
     const int64_t row = blockIdx.x;
     const int label = labels[row];
     const float4 *z = reinterpret_cast<const float4 *>(logits + row * V);
     uint2 *dz = reinterpret_cast<uint2 *>(dlogits + row * V);
     const int nq = V >> 2;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (label < 0) {
         if (threadIdx.x == 0) loss_rows[row] = 0.f;
-        for (int i = threadIdx.x; i < nq; i += 256) dz[i] = make_uint2(0u, 0u);
+        for (int i = threadIdx.x; i < nq; i += NT) dz[i] = make_uint2(0u, 0u);
+        return;
+    }
+    if constexpr (NR > 0) {
+        float4 v[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = threadIdx.x + NT * k;
+            v[k] = i < nq ? z[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) mx = fmaxf(fmaxf(fmaxf(mx, v[k].x), fmaxf(v[k].y, v[k].z)), v[k].w);
+        mx = block_reduce<NT>(mx, smax, true);
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            v[k] = make_float4(__expf(v[k].x - mx), __expf(v[k].y - mx), __expf(v[k].z - mx), __expf(v[k].w - mx));
+            sum += (v[k].x + v[k].y) + (v[k].z + v[k].w);
+        }
+        sum = block_reduce<NT>(sum, ssum, false);
+        if (threadIdx.x == 0) loss_rows[row] = __logf(sum) + (mx - logits[row * V + label]);
+        const float inv = 1.0f / sum;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = threadIdx.x + NT * k;
+            if (i < nq) dz[i] = ce_grad(v[k], inv, i * 4, label, inv_n);
+        }
         return;
     }
     float mx = -INFINITY, sum = 0.f;
-    for (int i = threadIdx.x; i < nq; i += 256) {
+    for (int i = threadIdx.x; i < nq; i += NT) {
         const float4 v = z[i];
         const float m4 = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
         if (m4 > mx) {
@@ -479,30 +532,13 @@ __global__ __launch_bounds__(256) void cross_entropy_kernel(float *loss_rows, bf
         }
         sum += __expf(v.x - mx) + __expf(v.y - mx) + __expf(v.z - mx) + __expf(v.w - mx);
     }
-    // combine (mx, sum) pairs: wave, then the 4 waves
-    const float wmx = wave_max(mx);
-    sum = wave_sum(mx == -INFINITY ? 0.f : sum * __expf(mx - wmx));
-    if (lane == 0) {
-        sm[wave] = wmx;
-        ssum[wave] = sum;
-    }
-    __syncthreads();
-    const float bmx = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-    float bsum = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-        if (sm[w] != -INFINITY) bsum += ssum[w] * __expf(sm[w] - bmx);
-    const float lse = bmx + __logf(bsum);
-    if (threadIdx.x == 0) loss_rows[row] = lse - logits[row * V + label];
-    for (int i = threadIdx.x; i < nq; i += 256) {
+    const float bmx = block_reduce<NT>(mx, smax, true);
+    sum = block_reduce<NT>(mx == -INFINITY ? 0.f : sum * __expf(mx - bmx), ssum, false);
+    if (threadIdx.x == 0) loss_rows[row] = __logf(sum) + (bmx - logits[row * V + label]);
+    const float inv = 1.0f / sum;
+    for (int i = threadIdx.x; i < nq; i += NT) {
         const float4 v = z[i];
-        float p0 = __expf(v.x - lse), p1 = __expf(v.y - lse), p2 = __expf(v.z - lse), p3 = __expf(v.w - lse);
-        const int c = i * 4;
-        if (label == c) p0 -= 1.f;
-        if (label == c + 1) p1 -= 1.f;
-        if (label == c + 2) p2 -= 1.f;
-        if (label == c + 3) p3 -= 1.f;
-        dz[i] = make_uint2(pack2bf(p0 * inv_n, p1 * inv_n), pack2bf(p2 * inv_n, p3 * inv_n));
+        dz[i] = ce_grad(make_float4(__expf(v.x - bmx), __expf(v.y - bmx), __expf(v.z - bmx), __expf(v.w - bmx)), inv, i * 4, label, inv_n);
     }
 }
 
@@ -681,8 +717,12 @@ hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_sta
 hipError_t cross_entropy(float *loss_rows, bf16_t *dlogits, const float *logits, const int32_t *labels, int64_t n,
                          int32_t V, float inv_n, hipStream_t s) {
     if (n <= 0 || V <= 0 || (V & 3)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(cross_entropy_kernel, dim3((unsigned)n), dim3(256), 0, s, loss_rows, dlogits, logits, labels, V,
-                       inv_n);
+    // the smallest block, and the fewest registers per thread, that hold the row
+    const int nt = V <= 8192 ? 256 : V <= 16384 ? 512 : 1024;
+    auto kernel = V <= 1024 ? cross_entropy_kernel<256, 1> : V <= 2048 ? cross_entropy_kernel<256, 2>
+                : V <= 4096 ? cross_entropy_kernel<256, 4> : V <= 8192 ? cross_entropy_kernel<256, 8>
+                : V <= 16384 ? cross_entropy_kernel<512, 8> : V <= 32768 ? cross_entropy_kernel<1024, 8> : cross_entropy_kernel<1024, 0>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(nt), 0, s, loss_rows, dlogits, logits, labels, V, inv_n);
     return hipGetLastError();
 }
 

@@ -471,6 +471,31 @@ def test_cross_entropy(orc64, n, V):
     assert np.all(got[1] == 0)
 
 
+@pytest.mark.parametrize("V", [4, 1024, 1028, 2052, 4100, 8192, 8196, 16388, 32768, 32772])
+def test_cross_entropy_at_the_widths_where_the_kernel_changes(orc64, V):
+    """Rows that just fill, or just do not fit, the registers of each block size; a row of large negative logits."""
+    rng = np.random.default_rng(V + 1)
+    n = 6
+    z = (rng.standard_normal((n, V)) * 3).astype(np.float32)
+    z[2] -= 1.0e4
+    y = rng.integers(0, V, n).astype(np.int32)
+    y[0], y[1], y[3] = V - 1, 0, -1
+    loss_ref, dl_ref = orc64.cross_entropy(z, y)
+    Z, Y = dev_f32(z), dev_i32(y)
+    LR = torch.empty(n, dtype=torch.float32, device="cuda")
+    DZ = torch.empty((n, V), dtype=torch.bfloat16, device="cuda")
+    ok(L.mt_k_cross_entropy(LR.data_ptr(), DZ.data_ptr(), Z.data_ptr(), Y.data_ptr(), n, V, 1.0 / (n - 1), None))
+    # everything is computed relative to the row's maximum, so the size of the logits (row 2) does not matter
+    lr = host(LR)
+    zz = z.astype(np.float64)
+    want = np.log(np.exp(zz - zz.max(1, keepdims=True)).sum(1)) + zz.max(1) - zz[np.arange(n), np.maximum(y, 0)]
+    want[3] = 0
+    assert (np.abs(lr - want) <= 1e-5 * np.maximum(1, np.abs(want))).all()
+    got = host(DZ)
+    # one rounding to bf16 (2^-9), doubled; p - 1 of the label's column may cancel: 1e-6 of p = 1
+    assert (np.abs(got - dl_ref) <= 2.0 ** -8 * np.abs(dl_ref) + 1e-6 / (n - 1) * (np.arange(V)[None, :] == y[:, None]) + 1e-12).all()
+
+
 # ----------------------------------------------------------------------------- attention
 def _attention_case(orc64, B, T, Hq, Hkv, hd, seed, out_pad=0):
     """out_pad: extra elements in the row pitch of every output (4: rows are then only 8-byte aligned and the
