@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmegatrain_mi355.so")
-SOURCES = ["gemm.hip", "elementwise.hip", "attention.hip", "engine.cpp", "kernels_api.cpp", "host_ops.cpp"]
+SOURCES = ["gemm.hip", "gemm_ring.hip", "elementwise.hip", "attention.hip", "engine.cpp", "kernels_api.cpp", "host_ops.cpp"]
 HOST_ONLY = {"host_ops.cpp"}  # no device code: plain g++ (function multi-versioning for the Adam loop)
 HEADERS = ["common.h", "host_ops.h", "../../include/megatrain.h", "../../include/megatrain_kernels.h"]
 # -packed-fp32-ops off: the compiler must not form packed fp32 instructions on this target

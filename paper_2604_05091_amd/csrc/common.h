@@ -117,6 +117,11 @@ struct GemmArgs {
     int32_t group_m = 0;
 };
 hipError_t gemm_nt(const GemmArgs &g, hipStream_t s);
+// The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
+// has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced.
+enum class RingTile { none, t256x128, t128x128, t128x64, t64x64 };
+hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, hipStream_t s);
+hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, hipStream_t s);
 // true when gemm_nt would apply g.rope_* in its epilogue for this problem (large grid, K % 64 == 0, head-aligned
 // columns); otherwise a call with rope_cos set fails with hipErrorNotSupported and the caller rotates separately
 bool gemm_nt_fuses_rope(const GemmArgs &g);

@@ -7,20 +7,19 @@
 // stored ([out,in]); the input-gradient and weight-gradient products are brought to
 // the same form by transposing one or both operands with transpose_bf16 first.
 //
-// Two kernels share the tile geometry: a workgroup owns a 256 x 256 (or 128 x 128) tile of C made of
-// 32x32 MFMA blocks (v_mfma_f32_32x32x16_bf16, 16 fp32 accumulators per lane per block); K is walked in
-// steps of 64 through a double-buffered LDS stage; LDS rows are padded to 72 elements (144 B), which
-// makes the 16-byte fragment reads of consecutive lanes conflict-free.
-//   gemm_nt_w4_kernel  large grids with K % 64 == 0 (every projection of the billion-parameter
-//                      workloads): 4 waves x 128x128 quadrants, software-pipelined inside the wave.
-//   gemm_nt_kernel     everything else (ragged K, small problems): 8 waves x 128x64 (or 4 x 64x64),
-//                      load - compute - commit - barrier per step.
+// Here a workgroup owns a 256 x 256 tile of C made of 32x32 MFMA blocks (v_mfma_f32_32x32x16_bf16, 16 fp32 accumulators
+// per lane per block): 4 waves x 128x128 quadrants, K walked in steps of 64 through a double-buffered LDS stage,
+// software-pipelined inside the wave.  Reductions that are no multiple of 64 and grids that 256 x 256 tiles fill badly
+// go to the kernels with smaller tiles in gemm_ring.hip (choose_tile).
 //
 // Workgroup -> tile mapping: consecutive workgroup ids are dealt round-robin to the
 // 8 XCDs, each with a private L2.  The id is first re-numbered so that every XCD gets
 // a contiguous range of tiles, then walked in column-major groups of 8 tile rows so
 // the 32 tiles resident on one XCD form an 8 x 4 patch that shares A and B panels.
 #include <stdlib.h>
+
+#include <algorithm>
+#include <cmath>
 
 #include "common.h"
 
@@ -40,187 +39,10 @@ constexpr int kGroupM = 8;
 constexpr int kGroupMLarge = 4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-template <int BM, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    constexpr int NT = 64 * WGM * WGN;
-    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-    constexpr int A_ELEMS = BM * LDT, B_ELEMS = BN * LDT, STAGE = A_ELEMS + B_ELEMS;
-    constexpr int RS = NT / 8;                       // rows covered by one pass of the loader
-    constexpr int NA = BM / RS, NB = BN / RS;        // 16-byte chunks per thread and operand
-    static_assert(BM % RS == 0 && BN % RS == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
-
-    // ---- tile of this workgroup
-    const int nb = tiles_m * tiles_n;
-    int pid = blockIdx.x;
-    {
-        const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
-        pid = x * q + (x < r ? x : r) + pid / kXcd;
-    }
-    const int group = kGroupM * tiles_n;
-    const int first_m = (pid / group) * kGroupM;
-    const int gsz = min(tiles_m - first_m, kGroupM);
-    const int tm = first_m + (pid % group) % gsz;
-    const int tn = (pid % group) / gsz;
-    const int m0 = tm * BM, n0 = tn * BN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, hl = lane >> 5;
-
-    // ---- global -> register loader.  Thread owns 16-byte chunk (tid&7) of rows (tid>>3) + RS j.
-    // Rows past the matrix edge are clamped to the last row: they only feed C rows/columns that are
-    // never stored.  Only the K tail needs real zeros; it is handled in the last step alone.
-    const int lrow = tid >> 3, lkc = (tid & 7) * 8;
-    const bf16_t *abase = g.A + (int64_t)m0 * g.lda;
-    const bf16_t *bbase = g.B + (int64_t)n0 * g.ldb;
-    uint32_t aoff[NA], boff[NB];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) aoff[j] = (uint32_t)(min(lrow + RS * j, g.M - 1 - m0) * (int)g.lda + lkc);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) boff[j] = (uint32_t)(min(lrow + RS * j, g.N - 1 - n0) * (int)g.ldb + lkc);
-    // One register stage (native vectors, so the selects below stay value selects): while the matrix cores
-    // work on k-step t out of LDS, the loads of step t+1 are landing in these registers.
-    u32x4 ra0[NA], rb0[NB];
-    bool kok0 = true;
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // K tail: a chunk at or beyond K is read from column 0 of its row instead (always in bounds) and
-    // replaced by zeros when it is written to LDS.
-#define MT_GEMM_LOAD(RA, RB, KOK, K0)                                                                   \
-    {                                                                                                   \
-        KOK = ((K0) + lkc) < g.K;                                                                       \
-        const bf16_t *ak_ = abase + (KOK ? (K0) : -lkc), *bk_ = bbase + (KOK ? (K0) : -lkc);            \
-        _Pragma("unroll") for (int j = 0; j < NA; ++j) RA[j] = *reinterpret_cast<const u32x4 *>(ak_ + aoff[j]); \
-        _Pragma("unroll") for (int j = 0; j < NB; ++j) RB[j] = *reinterpret_cast<const u32x4 *>(bk_ + boff[j]); \
-    }
-#define MT_GEMM_COMMIT(RA, RB, KOK, BUF)                                                                \
-    {                                                                                                   \
-        bf16_t *ws_ = smem + (BUF) * STAGE + lrow * LDT + lkc;                                          \
-        bf16_t *wb_ = ws_ + A_ELEMS;                                                                    \
-        _Pragma("unroll") for (int j = 0; j < NA; ++j)                                                  \
-            *reinterpret_cast<u32x4 *>(ws_ + RS * j * LDT) = KOK ? RA[j] : zero4;                       \
-        _Pragma("unroll") for (int j = 0; j < NB; ++j)                                                  \
-            *reinterpret_cast<u32x4 *>(wb_ + RS * j * LDT) = KOK ? RB[j] : zero4;                       \
-    }
-    // Fragments of k-substep ks+1 are read while the MFMAs of substep ks run (two fragment sets); the
-    // scheduling barrier keeps the compiler from sinking the reads back next to their first use.
-#define MT_GEMM_READ_FRAGS(SET, KS)                                                                     \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                  \
-            af[SET][i] = *reinterpret_cast<const bf16x8 *>(as_ + i * 32 * LDT + (KS) * 16);             \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                  \
-            bfr[SET][j] = *reinterpret_cast<const bf16x8 *>(bs_ + j * 32 * LDT + (KS) * 16);            \
-    }
-#define MT_GEMM_COMPUTE(BUF)                                                                            \
-    {                                                                                                   \
-        const bf16_t *as_ = smem + (BUF) * STAGE + (wm * WM + l32) * LDT + hl * 8;                      \
-        const bf16_t *bs_ = smem + (BUF) * STAGE + A_ELEMS + (wn * WN + l32) * LDT + hl * 8;            \
-        bf16x8 af[2][TM], bfr[2][TN];                                                                   \
-        MT_GEMM_READ_FRAGS(0, 0);                                                                       \
-        _Pragma("unroll") for (int ks = 0; ks < BK / 16; ++ks) {                                        \
-            if (ks + 1 < BK / 16) MT_GEMM_READ_FRAGS((ks + 1) & 1, ks + 1);                             \
-            __builtin_amdgcn_sched_barrier(0);                                                          \
-            _Pragma("unroll") for (int i = 0; i < TM; ++i)                                              \
-                _Pragma("unroll") for (int j = 0; j < TN; ++j)                                          \
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], bfr[ks & 1][j],  \
-                                                                        acc[i][j], 0, 0, 0);            \
-            __builtin_amdgcn_sched_barrier(0);                                                          \
-        }                                                                                               \
-    }
-
-    const int nk = (g.K + BK - 1) / BK;
-    MT_GEMM_LOAD(ra0, rb0, kok0, 0);
-    MT_GEMM_COMMIT(ra0, rb0, kok0, 0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
-        MT_GEMM_LOAD(ra0, rb0, kok0, (kt + 1) * BK);
-        MT_GEMM_COMPUTE(0);
-        MT_GEMM_COMMIT(ra0, rb0, kok0, 1);
-        __syncthreads();
-        if (kt + 2 < nk) MT_GEMM_LOAD(ra0, rb0, kok0, (kt + 2) * BK);
-        MT_GEMM_COMPUTE(1);
-        if (kt + 2 < nk) MT_GEMM_COMMIT(ra0, rb0, kok0, 0);
-        __syncthreads();
-    }
-    if (kt < nk) MT_GEMM_COMPUTE(0);
-#undef MT_GEMM_LOAD
-#undef MT_GEMM_COMMIT
-#undef MT_GEMM_COMPUTE
-#undef MT_GEMM_READ_FRAGS
-
-    // ---- epilogue: lane holds C[row = 8 (r/4) + 4 hl + r%4][col = l32] of each 32x32 block
-    const int row_w = m0 + wm * WM + hl * 4, col_w = n0 + wn * WN + l32;
-    const bool full = (m0 + BM <= g.M) && (n0 + BN <= g.N);
-    if (g.out_fp32) {
-        float *cw = reinterpret_cast<float *>(g.C) + (int64_t)row_w * g.ldc + col_w;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int dr = i * 32 + (r >> 2) * 8 + (r & 3);
-                if (!full && row_w + dr >= g.M) continue;
-                float *cr = cw + (int64_t)dr * g.ldc;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (!full && col_w + j * 32 >= g.N) continue;
-                    float v = acc[i][j][r];
-                    if (g.accumulate) v += cr[j * 32];
-                    cr[j * 32] = v;
-                }
-            }
-    } else {
-        bf16_t *cw = reinterpret_cast<bf16_t *>(g.C) + (int64_t)row_w * g.ldc + col_w;
-        const bf16_t *rw = g.R ? g.R + (int64_t)row_w * g.ldr + col_w : nullptr;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int dr = i * 32 + (r >> 2) * 8 + (r & 3);
-                if (!full && row_w + dr >= g.M) continue;
-                bf16_t *cr = cw + (int64_t)dr * g.ldc;
-                const bf16_t *rr = rw ? rw + (int64_t)dr * g.ldr : nullptr;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (!full && col_w + j * 32 >= g.N) continue;
-                    float v = acc[i][j][r];
-                    if (g.bias) v += bf2f(g.bias[col_w + j * 32]);
-                    if (rr) v += bf2f(rr[j * 32]);
-                    cr[j * 32] = f2bf(v);
-                }
-            }
-    }
-}
-
-template <int BM, int BN, int WGM, int WGN>
-hipError_t launch(const GemmArgs &g, hipStream_t s) {
-    constexpr size_t lds = (size_t)2 * (BM + BN) * LDT * sizeof(bf16_t);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_kernel<BM, BN, WGM, WGN>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, WGM, WGN>), dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * WGM * WGN),
-                       lds, s, g, tiles_m, tiles_n);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------------------------
-// 4-wave variant for large problems with K % 64 == 0: the same 256 x 256 x 64 tile and LDS layout,
-// but every wave owns a 128 x 128 quadrant (4 x 4 MFMA blocks, 256 accumulators in AGPRs), which
-// halves the LDS bytes read per MFMA, and the whole k-step is software-pipelined inside the wave:
+// Register-staged kernel (MT_GEMM_VARIANT=5): LDS rows padded to 72 elements (144 B, conflict-free 16-byte fragment
+// reads), every wave owns a 128 x 128 quadrant (4 x 4 MFMA blocks, 256 accumulators in AGPRs), and the whole
+// k-step is software-pipelined inside the wave:
 //   phase p = 0..2 : MFMAs of k-slice p  ||  LDS reads of slice p+1  ||  a third of the staged
 //                    registers of step t+1 written to the other LDS buffer, each register refilled
 //                    at once by the global load of step t+2
@@ -1322,11 +1144,6 @@ hipError_t launch_tn_epi(const GemmArgs &g0, hipStream_t s) {
     } else {
         hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, grid, dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || g.split_k == 1) return e;
-    const int64_t quads = ((int64_t)g.M * g.N + 3) / 4;
-    hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, reinterpret_cast<float *>(g.C),
-                       g.ldc, g.split_ws, g.split_k - 1, g.M, g.N);
     return hipGetLastError();
 }
 
@@ -1345,10 +1162,66 @@ int variant_override() {
 
 }  // namespace
 
+// The fused stores exist in the 256 x 256 kernel only.  They are taken from 192 tiles on: below, the separate pass over a
+// small result costs less than the idle compute units.
 static bool takes_w4(const GemmArgs &g) {
     const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
     const int v = variant_override();
     return g.K % BK == 0 && (v == 6 || ((v == 0 || v == 5) && big_tiles >= 192));
+}
+
+// Which tile takes a problem: the one with the smallest estimated time.  A kernel with one workgroup per compute unit
+// runs rounds of n_cu tiles; a stage of 64 reduction indices costs `part` us when few compute units are busy and
+// `full` us when all are (shared bandwidth, lower clock), in between with the square of the share; a tile costs
+// `fixed` us on top (first loads, store).  The two smallest tiles share a compute unit (two and three workgroups): per
+// tile and compute unit `full` us a stage, but never less than a lone one's `part`.  All figures measured at
+// K = 1000 .. 11008 and 16 .. 1600 tiles; the estimates came out within 10 % where rows are whole cache lines.  NT in us,
+// this kernel against the 256 x 256 / 128 x 128 register-staged one it replaced:
+//   1000 x 2048 x 11008  57 (128 x 64) : 130      1024 x 1024 x 3000  17 (64 x 64) : 47
+//   3000 x 1024 x 1024   11 (64 x 64) : 20        4096 x 5120 x 5120  183 (256 x 128) : 201 (256 x 256: 1.25 rounds)
+//   1000 x 11008 x 2048  46 (256 x 256, 172 tiles) : 77
+struct TileCost {
+    RingTile tile;
+    int bm, bn, per_cu;
+    double part, full, fixed, fixed_shared;
+};
+static const TileCost kNtCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.45, 9.0, 0.0},
+                                    {RingTile::t256x128, 256, 128, 1, 0.53, 0.79, 5.0, 0.0},
+                                    {RingTile::t128x128, 128, 128, 1, 0.36, 0.43, 3.2, 0.0},
+                                    {RingTile::t128x64, 128, 64, 2, 0.33, 0.275, 2.0, 1.2},
+                                    {RingTile::t64x64, 64, 64, 3, 0.26, 0.18, 2.0, 0.5}};
+static const TileCost kTnCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.57, 10.0, 0.0},
+                                    {RingTile::t256x128, 256, 128, 1, 0.50, 0.84, 5.0, 0.0},
+                                    {RingTile::t128x128, 128, 128, 1, 0.42, 0.47, 3.0, 0.0},
+                                    {RingTile::t128x64, 128, 64, 2, 0.34, 0.29, 2.0, 1.2},
+                                    {RingTile::t64x64, 64, 64, 3, 0.23, 0.175, 2.0, 0.4}};
+constexpr int kComputeUnits = 256;
+
+static double tile_time(const TileCost &c, int64_t M, int64_t N, double stages, int split, int n_cu) {
+    const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * split;
+    if (c.per_cu > 1) {
+        const double per = std::ceil(tiles / n_cu);
+        return std::max(stages * c.part + c.fixed, per * (stages * c.full + c.fixed_shared));
+    }
+    const double rounds = std::floor(tiles / n_cu), share = (tiles - rounds * n_cu) / n_cu;
+    return rounds * (stages * c.full + c.fixed) +
+           (share > 0 ? stages * (c.part + (c.full - c.part) * share * share) + c.fixed : 0.0);
+}
+
+template <int N_COSTS>
+static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], const GemmArgs &g) {
+    const double stages = (double)((g.K + BK - 1) / BK) / g.split_k;
+    const int first = g.K % BK ? 1 : 0;   // the 256 x 256 kernel takes whole stages only
+    const TileCost *best = &costs[first];
+    double best_t = tile_time(*best, g.M, g.N, stages, g.split_k, kComputeUnits);
+    for (int i = first + 1; i < N_COSTS; ++i) {
+        const double t = tile_time(costs[i], g.M, g.N, stages, g.split_k, kComputeUnits);
+        if (t < 0.97 * best_t) {
+            best = &costs[i];
+            best_t = t;
+        }
+    }
+    return *best;
 }
 
 bool gemm_nt_fuses_rope(const GemmArgs &g) {
@@ -1385,16 +1258,16 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s) {
     if (g.bias && g.out_fp32) return hipErrorInvalidValue;
     // offsets inside one tile are 32-bit: 256 rows of either operand must stay below 2^31 elements
     if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return hipErrorInvalidValue;
-    const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-    switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = heuristic
-        case 2: return launch<256, 256, 2, 4>(g, s);
-        case 3: return launch<128, 128, 2, 2>(g, s);
-        case 5: if (g.K % BK == 0 && big_tiles >= 192) return launch_w4(g, s); break;   // register-staged 4-wave kernel
-        case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;                      // 4-wave kernel on any grid
+    if (g.rope_cos || g.glu_F || g.glu_bwd_gu) return variant_override() == 5 ? launch_w4(g, s) : launch_w4e(g, s);
+    switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = the estimate
+        case 2: return gemm_nt_ring(g, RingTile::t256x128, s);
+        case 3: return gemm_nt_ring(g, RingTile::t128x128, s);
+        case 5: if (takes_w4(g)) return launch_w4(g, s); break;             // register-staged 4-wave kernel
+        case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
         default: break;
     }
-    if (big_tiles >= 192) return (g.K % BK == 0) ? launch_w4e(g, s) : launch<256, 256, 2, 4>(g, s);
-    return launch<128, 128, 2, 2>(g, s);
+    const RingTile tile = choose_tile(kNtCosts, g).tile;
+    return tile == RingTile::none ? launch_w4e(g, s) : gemm_nt_ring(g, tile, s);
 }
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
@@ -1406,6 +1279,7 @@ int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
     const double t_step = 1.65e-6, bw = 3.5e12;
     int best = 1;
     double best_t = 0.0, t_unsplit = 0.0;
+    // ... with 256 x 256 tiles,
     for (int sp = 1; sp <= 6 && nk / sp >= 32; ++sp) {
         const double rounds = (double)((tiles * sp + n_cu - 1) / n_cu);
         const double t = rounds * (double)nk / sp * t_step + (sp > 1 ? (sp + 1) * 4.0 * (double)M * (double)N / bw : 0.0);
@@ -1420,6 +1294,20 @@ int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
             best = sp;
         }
     }
+    // ... unless smaller tiles, with a split of their own, are estimated faster by as much; a split reduction then
+    // costs its launch as well (measured 3 us).  5504 x 2048 x 16384: 256 x 128 tiles in two chunks 311 + 26 us, 256 x 256
+    // in four 358; 1024 x 1024 x 3008: 64 x 64 tiles unsplit 13 us, 256 x 256 57.
+    const auto reduction = [&](int sp) { return sp > 1 ? 3.0 + (sp + 1) * 4.0 * (double)M * (double)N / (bw * 1e-6) : 0.0; };
+    double best_us = tile_time(kTnCosts[0], M, N, (double)nk / best, best, n_cu) + reduction(best);
+    for (int sp = 1; sp <= 6 && nk / sp >= 8; ++sp)
+        for (const TileCost &c : kTnCosts) {
+            if (c.tile == RingTile::none) continue;
+            const double t = tile_time(c, M, N, (double)nk / sp, sp, n_cu) + reduction(sp);
+            if (t < 0.96 * best_us) {
+                best_us = t;
+                best = sp;
+            }
+        }
     return best;
 }
 
@@ -1434,7 +1322,15 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
     // the reduction of a split reads and writes C four floats at a time
     if (g.split_k > 1 && (!g.split_ws || ((uintptr_t)g.split_ws & 15) || (g.ldc & 3) || (g.N & 3) || ((uintptr_t)g.C & 15)))
         return hipErrorInvalidValue;
-    return launch_tn(g, s);
+    const int v = variant_override();
+    const RingTile tile = v == 5 || v == 6 ? RingTile::none : v == 2 ? RingTile::t256x128 : v == 3 ? RingTile::t128x128
+                                                                                                   : choose_tile(kTnCosts, g).tile;
+    const hipError_t e = tile == RingTile::none ? launch_tn(g, s) : gemm_tn_ring(g, tile, s);
+    if (e != hipSuccess || g.split_k == 1) return e;
+    const int64_t quads = ((int64_t)g.M * g.N + 3) / 4;
+    hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, reinterpret_cast<float *>(g.C),
+                       g.ldc, g.split_ws, g.split_k - 1, g.M, g.N);
+    return hipGetLastError();
 }
 
 }  // namespace mt

@@ -1,0 +1,414 @@
+// bf16 GEMM on the gfx950 matrix cores for grids that do not fill the chip with 256 x 256 tiles.
+//
+//   ring_nt_kernel   C[M,N] = A[M,K] . B[N,K]^T (+ bias) (+ R)     both operands with the reduction index contiguous
+//   ring_tn_kernel   C[M,N] = sum_k At[k][m] Bt[k][n]              both operands token-major (weight gradients)
+//
+// With one workgroup of four waves on a compute unit nothing but the kernel itself hides the latency of a load (1-2 us
+// to the memory-side cache), so what bounds these sizes is how many bytes a workgroup keeps in flight.  Operands go
+// from memory straight into a ring of S LDS stages of 64 reduction indices each (global_load_lds_dwordx4, no staging
+// registers); S - 1 stages are in flight while one is consumed.  A wave reads ALL fragments of the next stage while the
+// MFMAs of the present one run (two register sets), so neither the LDS latency nor the barrier (one per stage) is
+// exposed.  The path into LDS takes about 57 bytes a clock, which makes (BM + BN) * 128 / 57 clocks the floor of a
+// stage: 575 for 128 x 128 (MFMA: 515), 431 for 128 x 64 (257), 287 for 64 x 64 (129).
+#include "common.h"
+
+namespace mt {
+
+namespace {
+
+constexpr int RK = 64;         // reduction indices per stage
+constexpr int kRingXcd = 8;
+constexpr int kRingGroupM = 8;
+typedef __attribute__((address_space(3))) void *ring_lptr;
+typedef __attribute__((ext_vector_type(4))) uint32_t ru32x4;
+
+// One load of 16 bytes per lane from base + off straight into LDS at lds + 16 lane.  Assembly because the compiler puts
+// a full wait in front of every LDS read that might alias a builtin load-to-LDS; ordering is by ring_wait.
+__device__ __forceinline__ void ring_load(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
+}
+// all but the youngest N loads of this wave have landed, its LDS reads too; then the workgroup's barrier
+template <int N>
+__device__ __forceinline__ void ring_wait() {
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+template <int L, int S>
+__device__ __forceinline__ void ring_wait_steps(int steps) {   // steps: wave-uniform
+    if (S >= 6 && steps >= 4) ring_wait<4 * L <= 63 ? 4 * L : 0>();
+    else if (S >= 5 && steps >= 3) ring_wait<3 * L <= 63 ? 3 * L : 0>();
+    else if (S >= 4 && steps >= 2) ring_wait<2 * L>();
+    else if (steps >= 1) ring_wait<L>();
+    else ring_wait<0>();
+}
+
+// Workgroup -> tile: ids are dealt round-robin to the 8 XCDs; re-numbered so that an XCD gets a contiguous range, walked
+// column by column in groups of kRingGroupM tile rows.
+__device__ __forceinline__ int ring_renumber(int nb) {
+    const int q = nb / kRingXcd, r = nb % kRingXcd, x = blockIdx.x % kRingXcd;
+    return x * q + (x < r ? x : r) + (int)blockIdx.x / kRingXcd;
+}
+__device__ __forceinline__ void ring_tile(int pid, int tiles_m, int tiles_n, int *tm, int *tn) {
+    const int group = kRingGroupM * tiles_n;
+    const int first_m = (pid / group) * kRingGroupM;
+    const int gsz = min(tiles_m - first_m, kRingGroupM);
+    *tm = first_m + (pid % group) % gsz;
+    *tn = (pid % group) / gsz;
+}
+
+// The tile leaves through LDS as fp32 (the ring is free after the last stage), so that a store instruction covers whole
+// lines and bias, residual and accumulation read them the same way.  A lane owns row l32 of a 32 x 32 block and, per
+// quarter q, the columns 8 q + 4 hl .. + 3 (the MFMAs are issued with the operands swapped).  Row pitch BN + 4: the
+// 16-byte writes of consecutive rows fall on disjoint banks.
+template <int BM, int BN, int TM, int TN, bool F32>
+__device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc)[TM][TN], int m0, int n0, int wm, int wn, float *st) {
+    constexpr int P = BN + 4;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hl = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                *reinterpret_cast<f32x4 *>(st + (wm * TM * 32 + i * 32 + l32) * P + wn * TN * 32 + j * 32 + q * 8 + hl * 4) = v;
+            }
+    __syncthreads();
+    constexpr int CPL = F32 ? 4 : 8;                  // columns per lane
+    constexpr int LPR = BN / CPL, RPI = 256 / LPR;    // lanes per row, rows per pass
+    const int r0 = tid / LPR, col = n0 + (tid % LPR) * CPL;
+    if (col >= g.N) return;
+    const float *sp = st + r0 * P + (tid % LPR) * CPL;
+    if constexpr (F32) {
+        const bool vec = !(g.ldc & 3) && !((uintptr_t)g.C & 15) && col + 4 <= g.N;
+        float *cp = reinterpret_cast<float *>(g.C) + (int64_t)(m0 + r0) * g.ldc + col;
+#pragma unroll 4
+        for (int it = 0; it < BM / RPI; ++it) {
+            if (m0 + r0 + it * RPI >= g.M) break;
+            f32x4 v = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P);
+            float *c = cp + (int64_t)it * RPI * g.ldc;
+            if (vec) {
+                if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(c);
+                *reinterpret_cast<f32x4 *>(c) = v;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < g.N) c[e] = v[e] + (g.accumulate ? c[e] : 0.f);
+            }
+        }
+    } else {
+        const bool vec = !(g.ldc & 7) && !((uintptr_t)g.C & 15) && col + 8 <= g.N &&
+                         (!g.R || (!(g.ldr & 7) && !((uintptr_t)g.R & 15)));
+        float bias[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bias[e] = g.bias && col + e < g.N ? bf2f(g.bias[col + e]) : 0.f;
+        bf16_t *cp = reinterpret_cast<bf16_t *>(g.C) + (int64_t)(m0 + r0) * g.ldc + col;
+        const bf16_t *rp = g.R ? g.R + (int64_t)(m0 + r0) * g.ldr + col : nullptr;
+#pragma unroll 4
+        for (int it = 0; it < BM / RPI; ++it) {
+            if (m0 + r0 + it * RPI >= g.M) break;
+            const f32x4 lo = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P), hi = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P + 4);
+            float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += bias[e];
+            bf16_t *c = cp + (int64_t)it * RPI * g.ldc;
+            const bf16_t *r = rp ? rp + (int64_t)it * RPI * g.ldr : nullptr;
+            if (vec) {
+                if (r) {
+                    const uint4 rv = *reinterpret_cast<const uint4 *>(r);
+                    v[0] += bflo(rv.x); v[1] += bfhi(rv.x); v[2] += bflo(rv.y); v[3] += bfhi(rv.y);
+                    v[4] += bflo(rv.z); v[5] += bfhi(rv.z); v[6] += bflo(rv.w); v[7] += bfhi(rv.w);
+                }
+                *reinterpret_cast<uint4 *>(c) = uint4{pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (col + e < g.N) c[e] = f2bf(v[e] + (r ? bf2f(r[e]) : 0.f));
+            }
+        }
+    }
+}
+
+// The walk over the stages, shared by the two kernels.  LOAD(J, T, SLOT) requests load J of stage T, READ(SET, KS, F, SLOT)
+// reads fragment F of slice KS into register set SET.  Stage T lives in slot T % S.  At the top of stage T: stage T + 1
+// has landed and every wave has read its fragments of stage T (one wait, one barrier), so slot T % S takes stage T + S.
+#define RING_STAGE(CS, NS, LOADS)                                                                       \
+    {                                                                                                   \
+        const int sn_ = slot + 1 == S ? 0 : slot + 1;                                                   \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+            _Pragma("unroll") for (int m = 0; m < MPS; ++m) {                                           \
+                constexpr int ALL = 4 * MPS;                                                            \
+                const int u = ks * MPS + m;                                                             \
+                if (LOADS) {                                                                            \
+                    _Pragma("unroll") for (int j = u * LPS / ALL; j < (u + 1) * LPS / ALL; ++j) RING_LOAD(j, t + S, slot); \
+                }                                                                                       \
+                _Pragma("unroll") for (int f = m * (TM + TN) / MPS; f < (m + 1) * (TM + TN) / MPS; ++f) RING_READ(NS, ks, f, sn_); \
+                const int i = m / TN, j = m % TN;                                                       \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[CS][ks][TM + j], fr[CS][ks][i], acc[i][j], 0, 0, 0); \
+                __builtin_amdgcn_sched_barrier(0);                                                      \
+            }                                                                                           \
+        slot = sn_;                                                                                     \
+    }
+#define RING_LAST_STAGE(CS, NS)                                                                         \
+    {                                                                                                   \
+        ring_wait_steps<LPS, S>(min(t + S - 1, nk - 1) - (t + 1));                                      \
+        if (t + S < nk) {                                                                               \
+            _Pragma("unroll") for (int j = 0; j < LPS; ++j) RING_LOAD(j, t + S, slot);                  \
+        }                                                                                               \
+        RING_STAGE(CS, NS, false);                                                                      \
+    }
+#define RING_WALK()                                                                                     \
+    {                                                                                                   \
+        ring_wait_steps<LPS, S + 1>(min(S, nk) - 1);                                                    \
+        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+            _Pragma("unroll") for (int f = 0; f < TM + TN; ++f) RING_READ(0, ks, f, 0);                 \
+        int t = 0, slot = 0;                                                                            \
+        for (; t + 1 + S < nk;) {                                                                       \
+            ring_wait<(S - 2) * LPS>();                                                                 \
+            RING_STAGE(0, 1, true);                                                                     \
+            ++t;                                                                                        \
+            ring_wait<(S - 2) * LPS>();                                                                 \
+            RING_STAGE(1, 0, true);                                                                     \
+            ++t;                                                                                        \
+        }                                                                                               \
+        for (; t < nk;) {                                                                               \
+            RING_LAST_STAGE(0, 1);                                                                      \
+            if (++t == nk) break;                                                                       \
+            RING_LAST_STAGE(1, 0);                                                                      \
+            ++t;                                                                                        \
+        }                                                                                               \
+    }
+
+// LDS stage: A [BM][64] | B [BN][64] bf16, rows of 128 bytes, 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)
+// (conflict-free 16-byte fragment reads without padding).  TAIL (K % 64 != 0): the last, partial stage is walked first; it goes
+// through registers, chunks at or beyond K as zeros.
+template <int BM, int BN, int S, bool F32, bool TAIL>
+__global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
+    constexpr int TM = BM / 64, TN = BN / 64, MPS = TM * TN;         // 32 x 32 blocks of a wave (2 x 2 waves)
+    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;         // loads of a wave per stage
+    constexpr int STAGE = (BM + BN) * 128;
+    static_assert(BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
+    int tm, tn;
+    ring_tile(ring_renumber(tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hl = lane >> 5;
+
+    // wave w fills rows (BM / 4) w .. of A and (BN / 4) w .. of B, 8 rows per load; rows past the edge re-read the last one
+    const bf16_t *abase = g.A + (int64_t)m0 * g.lda, *bbase = g.B + (int64_t)n0 * g.ldb;
+    uint32_t off[LPS];
+    const int lr = lane >> 3;
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) {
+        const int r = j < LA ? wave * (BM / 4) + j * 8 + lr : wave * (BN / 4) + (j - LA) * 8 + lr;
+        const int chunk = (lane & 7) ^ ((r >> 1) & 7);
+        const int row = j < LA ? min(r, g.M - 1 - m0) : min(r, g.N - 1 - n0);
+        off[j] = (uint32_t)(row * (int)(j < LA ? g.lda : g.ldb) + chunk * 8) * 2u;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(ring_lptr)ring;
+    const uint32_t fill_a = (uint32_t)(wave * (BM / 4) * 128), fill_b = (uint32_t)(BM * 128 + wave * (BN / 4) * 128);
+    uint32_t rda[4], rdb[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        const uint32_t pos = (uint32_t)(((2 * ks + hl) ^ ((l32 >> 1) & 7)) * 16);
+        rda[ks] = (uint32_t)((wm * TM * 32 + l32) * 128) + pos;
+        rdb[ks] = (uint32_t)(BM * 128 + (wn * TN * 32 + l32) * 128) + pos;
+    }
+    bf16x8 fr[2][4][TM + TN];
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const int nk = (g.K + RK - 1) / RK;
+    const int first = TAIL ? 1 : 0;      // stage t > 0 (t >= 0 without a tail) holds reduction indices 64 (t - first) ..
+#define RING_LOAD(J, T, SLOT)                                                                           \
+    ring_load(((J) < LA ? abase : bbase) + (int64_t)((T) - first) * RK, off[J],                         \
+              lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
+#define RING_READ(SET, KS, F, SLOT)                                                                     \
+    fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 4096 : rdb[KS] + ((F) - TM) * 4096))
+    ru32x4 tv[TAIL ? LPS : 1];
+    const int kt = (nk - 1) * RK;
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) {
+            const int r = j < LA ? wave * (BM / 4) + j * 8 + lr : wave * (BN / 4) + (j - LA) * 8 + lr;
+            const int chunk = (lane & 7) ^ ((r >> 1) & 7);
+            const bool ok = kt + chunk * 8 < g.K;   // otherwise column 0 of the row is read (in bounds) and replaced
+            const char *p = reinterpret_cast<const char *>(j < LA ? abase : bbase) + off[j] + (ok ? kt * 2 : -chunk * 16);
+            tv[j] = *reinterpret_cast<const ru32x4 *>(p);
+            if (!ok) tv[j] = ru32x4{0u, 0u, 0u, 0u};
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) RING_LOAD(j, 0, 0);
+    }
+#pragma unroll
+    for (int s = 1; s < S; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int j = 0; j < LPS; ++j) RING_LOAD(j, s, s);
+        }
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j)
+            *reinterpret_cast<ru32x4 *>(ring + (j < LA ? fill_a + j * 1024 : fill_b + (j - LA) * 1024) + lane * 16) = tv[j];
+    }
+    RING_WALK();
+#undef RING_LOAD
+#undef RING_READ
+    ring_store<BM, BN, TM, TN, F32>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
+}
+
+// LDS stage: A [64][BM] | B [64][BN] bf16 as in memory; fragments are read with the transposing load, whose half-waves touch
+// four rows x 64 bytes: 64-byte column group c of row r sits at group position c ^ ring_swz(r), which puts those four on
+// disjoint banks.  A wave-load fills 1024 / (2 BM) rows.  The token range may be split over workgroups (g.split_k).
+template <int W>
+__device__ __forceinline__ int ring_swz(int r) { return W == 64 ? (r >> 1) & 1 : W == 128 ? r & 3 : r & 7; }
+
+template <int BM, int BN, int S>
+__global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
+    typedef __attribute__((address_space(3))) s16x4 *trptr;
+    constexpr int TM = BM / 64, TN = BN / 64, MPS = TM * TN;
+    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;
+    constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    static_assert(BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
+    const int n_tiles = tiles_m * tiles_n;
+    int pid = ring_renumber(n_tiles * g.split_k);
+    const int chunk = pid / n_tiles;
+    pid -= chunk * n_tiles;
+    const int nk_all = g.K / RK;
+    const int kb = (int)((int64_t)chunk * nk_all / g.split_k), nk = (int)((int64_t)(chunk + 1) * nk_all / g.split_k) - kb;
+    if (chunk > 0) {
+        g.C = g.split_ws + (int64_t)(chunk - 1) * g.M * g.N;
+        g.ldc = g.N;
+        g.accumulate = 0;
+    }
+    int tm, tn;
+    ring_tile(pid, tiles_m, tiles_n, &tm, &tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    const bf16_t *abase = g.A + (int64_t)kb * RK * g.lda, *bbase = g.B + (int64_t)kb * RK * g.ldb;
+    uint32_t off[LPS];
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) {
+        // lane l delivers to 16-byte position l % (W / 8) of its row and fetches the chunk that belongs there; chunks
+        // past the edge re-read the last one
+        constexpr int PA = BM / 8, PB = BN / 8;
+        if (j < LA) {
+            const int r = wave * 16 + j * (64 / PA) + lane / PA, p = lane % PA;
+            const int c = (((p >> 2) ^ ring_swz<BM>(r)) << 2) | (p & 3);
+            off[j] = (uint32_t)(r * (int)g.lda + min(m0 + c * 8, g.M - 8)) * 2u;
+        } else {
+            const int r = wave * 16 + (j - LA) * (64 / PB) + lane / PB, p = lane % PB;
+            const int c = (((p >> 2) ^ ring_swz<BN>(r)) << 2) | (p & 3);
+            off[j] = (uint32_t)(r * (int)g.ldb + min(n0 + c * 8, g.N - 8)) * 2u;
+        }
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(ring_lptr)ring;
+    const uint32_t fill_a = (uint32_t)(wave * 16 * BM * 2), fill_b = (uint32_t)(A_BYTES + wave * 16 * BN * 2);
+    uint32_t rd[TM + TN];
+    {
+        const int gq = lane >> 4, ii = lane & 15;
+        const int row = (gq >> 1) * 4 + (ii >> 2), inner = (gq & 1) * 16 + (ii & 3) * 4;
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f)
+            rd[f] = f < TM ? (uint32_t)((row * BM + (((wm * TM + f) ^ ring_swz<BM>(row)) * 32) + inner) * 2)
+                           : (uint32_t)(A_BYTES + (row * BN + (((wn * TN + f - TM) ^ ring_swz<BN>(row)) * 32) + inner) * 2);
+    }
+    bf16x8 fr[2][4][TM + TN];
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+#define RING_LOAD(J, T, SLOT)                                                                           \
+    ring_load((J) < LA ? abase + (int64_t)(T) * RK * g.lda : bbase + (int64_t)(T) * RK * g.ldb, off[J], \
+              lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
+#define RING_READ(SET, KS, F, SLOT)                                                                     \
+    {                                                                                                   \
+        const int ROW_ = 2 * ((F) < TM ? BM : BN);                                                  \
+        const char *p_ = ring + (SLOT) * STAGE + rd[F] + (KS) * 16 * ROW_;                              \
+        const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)(p_));                         \
+        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)(p_ + 8 * ROW_));              \
+        typedef __attribute__((ext_vector_type(8))) short s16x8_;                                       \
+        const s16x8_ v_ = {lo_[0], lo_[1], lo_[2], lo_[3], hi_[0], hi_[1], hi_[2], hi_[3]};             \
+        fr[SET][KS][F] = __builtin_bit_cast(bf16x8, v_);                                                \
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int j = 0; j < LPS; ++j) RING_LOAD(j, s, s);
+        }
+    RING_WALK();
+#undef RING_LOAD
+#undef RING_READ
+    ring_store<BM, BN, TM, TN, true>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
+}
+
+template <typename K>
+hipError_t ring_launch(K kernel, const GemmArgs &g, int bm, int bn, size_t lds, bool *attr_set, hipStream_t s) {
+    if (!*attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        *attr_set = true;
+    }
+    const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int S, bool F32, bool TAIL>
+hipError_t launch_nt_one(const GemmArgs &g, hipStream_t s) {
+    static bool attr = false;
+    return ring_launch(ring_nt_kernel<BM, BN, S, F32, TAIL>, g, BM, BN, (size_t)S * (BM + BN) * 128, &attr, s);
+}
+template <int BM, int BN, int S>
+hipError_t launch_nt(const GemmArgs &g, hipStream_t s) {
+    if (g.K % RK) return g.out_fp32 ? launch_nt_one<BM, BN, S, true, true>(g, s) : launch_nt_one<BM, BN, S, false, true>(g, s);
+    return g.out_fp32 ? launch_nt_one<BM, BN, S, true, false>(g, s) : launch_nt_one<BM, BN, S, false, false>(g, s);
+}
+template <int BM, int BN, int S>
+hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
+    static bool attr = false;
+    return ring_launch(ring_tn_kernel<BM, BN, S>, g, BM, BN, (size_t)S * (BM + BN) * 128, &attr, s);
+}
+
+}  // namespace
+
+// Three stages each: a fourth or fifth measured the same (4096^3: 118.6, 119.5, 120.6 us with 128 x 128 tiles), and three
+// of 24 or 16 KB let two or three workgroups share a compute unit.
+hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, hipStream_t s) {
+    switch (tile) {
+        case RingTile::t256x128: return launch_nt<256, 128, 3>(g, s);
+        case RingTile::t128x128: return launch_nt<128, 128, 3>(g, s);
+        case RingTile::t128x64: return launch_nt<128, 64, 3>(g, s);
+        case RingTile::t64x64: return launch_nt<64, 64, 3>(g, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, hipStream_t s) {
+    switch (tile) {
+        case RingTile::t256x128: return launch_tn<256, 128, 3>(g, s);
+        case RingTile::t128x128: return launch_tn<128, 128, 3>(g, s);
+        case RingTile::t128x64: return launch_tn<128, 64, 3>(g, s);
+        case RingTile::t64x64: return launch_tn<64, 64, 3>(g, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace mt

@@ -112,6 +112,33 @@ def test_gemm_bias_epilogue_and_bias_gradient(orc64, M, N, K):
     assert np.max(np.abs(host(DB) - want)) <= 1e-5 * np.sqrt(M) * np.max(np.abs(host(C)))
 
 
+# Sizes around the edges of the smaller tiles (64 x 64, 128 x 64, 128 x 128, 256 x 128) and of the ring of three stages:
+# one stage and less, two, three, four and more, odd counts, partial last stages; columns and pitches that are whole
+# 16-byte chunks and that are not.
+@pytest.mark.parametrize("M,N,K,pad", [(8, 8, 8, 0), (64, 64, 64, 0), (65, 63, 72, 1), (130, 200, 128, 8), (333, 72, 184, 4),
+                                       (256, 512, 256, 8), (1000, 520, 328, 0), (1000, 1030, 1000, 2), (2050, 1544, 448, 8),
+                                       (3000, 1024, 136, 0), (2304, 2056, 200, 3)])
+def test_gemm_small_tiles_edges(orc64, M, N, K, pad):
+    rng = np.random.default_rng(M * 5 + N * 3 + K)
+    lda, ldb, ldc, ldr = K + 8, K + 16, N + pad, N + 3 * pad
+    a, b = bf16_round(rng.standard_normal((M, lda))), bf16_round(rng.standard_normal((N, ldb)))
+    r, bias = bf16_round(rng.standard_normal((M, ldr))), bf16_round(rng.standard_normal(N))
+    ref = orc64.linear_fwd(np.ascontiguousarray(a[:, :K]), np.ascontiguousarray(b[:, :K]))
+    A, B, R, BI = dev_bf16(a), dev_bf16(b), dev_bf16(r), dev_bf16(bias)
+    ops = (A.data_ptr(), lda, B.data_ptr(), ldb)
+    C = torch.zeros((M, ldc), dtype=torch.bfloat16, device="cuda")
+    ok(L.mt_k_gemm_nt(*ops, C.data_ptr(), ldc, R.data_ptr(), ldr, M, N, K, 0, 0, None))
+    assert_rows_close(host(C)[:, :N], ref + r[:, :N], ROW1, what="residual")
+    ok(L.mt_k_gemm_nt_bias(*ops, C.data_ptr(), ldc, BI.data_ptr(), M, N, K, None))
+    assert_rows_close(host(C)[:, :N], ref + bias[None, :], ROW1, what="bias")
+    assert np.all(host(C)[:, N:] == 0)           # nothing written outside the N columns
+    F = torch.full((M, ldc), 3.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        ok(L.mt_k_gemm_nt(*ops, F.data_ptr(), ldc, None, 0, M, N, K, 1, acc, None))
+        assert_rows_close(host(F)[:, :N], (1 + acc) * ref, 2e-5, what="fp32")
+    assert np.all(host(F)[:, N:] == 3)
+
+
 @pytest.mark.parametrize("n,out,inn", [(2048, 136, 264), (576, 520, 1376), (64, 8, 8), (4096, 2056, 4104)])
 def test_gemm_token_major_weight_gradient(orc64, n, out, inn):
     """dW[out,in] = sum_t dy[t,out] x[t,in] straight from the token-major operands (no transposes): ragged
@@ -129,6 +156,24 @@ def test_gemm_token_major_weight_gradient(orc64, n, out, inn):
     assert rel_l2(host(DW), 2 * ref) < 5e-6
     assert_rows_close(host(DW), 2 * ref, 2e-5, what="token-major weight gradient, accumulate")
     assert L.mt_k_gemm_tn(DY.data_ptr(), ldy, X.data_ptr(), ldx, DW.data_ptr(), inn, out, inn, n - 8, 0, None) == -2
+
+
+@pytest.mark.parametrize("n,out,inn", [(64, 64, 64), (128, 72, 136), (192, 1024, 520), (320, 2048, 1544), (1024, 200, 1000),
+                                       (2112, 3080, 1032)])
+def test_gemm_token_major_weight_gradient_small_tiles(orc64, n, out, inn):
+    """The token-major product at the edges of the smaller tiles and of the ring, unsplit and split."""
+    rng = np.random.default_rng(n + 2 * out + 3 * inn)
+    dy, x = bf16_round(rng.standard_normal((n, out))), bf16_round(rng.standard_normal((n, inn)))
+    ref = orc64.linear_bwd_w(dy, x)
+    DY, X = dev_bf16(dy), dev_bf16(x)
+    WS = torch.full((2 * out * inn,), 9.0, dtype=torch.float32, device="cuda")
+    for split in (1, 2, 3):
+        if split > n // 64:
+            continue
+        DW = torch.full((out, inn), 7.0, dtype=torch.float32, device="cuda")
+        for acc in (0, 1):
+            ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, DW.data_ptr(), inn, out, inn, n, acc, split, WS.data_ptr(), None))
+            assert_rows_close(host(DW), (1 + acc) * ref, 2e-5, what=f"split {split}")
 
 
 @pytest.mark.parametrize("n,out,inn,split", [(2048, 520, 1032, 2), (4096, 264, 256, 5), (1024, 1280, 776, 3)])
