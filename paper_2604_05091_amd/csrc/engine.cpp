@@ -632,15 +632,17 @@ struct AdamHyper {
 // Adam on the part of a unit's tensors that lies inside [off, off + count) of its block (the update is
 // elementwise, so ranges that partition the block may cut through tensors)
 void adam_range(mt_handle *h, int unit, size_t off, size_t count, const AdamHyper &hp) {
+    std::vector<AdamPiece> pieces;   // one job for the whole range: small tensors do not each pay a fork and a join
     for (int i = 0; i < h->n_tensors; ++i) {
         const TensorRef &t = h->tref[i];
         if (t.unit != unit) continue;
         const size_t b = std::max(off, (size_t)t.off), e = std::min(off + count, (size_t)t.off + (size_t)t.numel);
         if (b >= e) continue;
         Unit &u = h->units[unit];
-        host_adam(h->params[i] + (b - t.off), u.h_grad + b, h->adam_m[unit] + b, h->adam_v[unit] + b,
-                  u.h_shadow ? u.h_shadow + b : nullptr, e - b, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.wd, hp.step);
+        pieces.push_back({h->params[i] + (b - t.off), u.h_grad + b, h->adam_m[unit] + b, h->adam_v[unit] + b,
+                          u.h_shadow ? u.h_shadow + b : nullptr, e - b});
     }
+    host_adam_pieces(pieces.data(), pieces.size(), hp.lr, hp.beta1, hp.beta2, hp.eps, hp.wd, hp.step);
 }
 
 // Host optimizer running beside the GPU (Algorithm 1, optimizer phase; Section 3.3: a background CPU thread
@@ -1700,12 +1702,8 @@ mt_status mt_adam_step(mt_handle *h, float lr, float beta1, float beta2, float e
     if (h->opt_partial)
         return fail(MT_ERR_STATE, "an earlier mt_train_step_adam failed part-way: restore the parameters and moments, then call mt_refresh_shadow");
     const double t0 = now_ms();
-    for (int i = 0; i < h->n_tensors; ++i) {
-        const TensorRef &t = h->tref[i];
-        Unit &u = h->units[t.unit];
-        host_adam(h->params[i], u.h_grad + t.off, h->adam_m[t.unit] + t.off, h->adam_v[t.unit] + t.off,
-                  u.h_shadow ? u.h_shadow + t.off : nullptr, t.numel, lr, beta1, beta2, eps, wd, step);
-    }
+    const AdamHyper hp = {lr, beta1, beta2, eps, wd, step};
+    for (size_t u = 0; u < h->units.size(); ++u) adam_range(h, (int)u, 0, h->units[u].numel, hp);
     h->resident[0] = h->resident[1] = -1;
     h->stats.adam_ms = now_ms() - t0;
     return MT_OK;

@@ -14,6 +14,16 @@ void parallel_for(size_t n, size_t min_chunk, const std::function<void(size_t, s
 void host_f32_to_bf16(uint16_t *out, const float *in, size_t n);
 void host_adam(float *p, const float *g, float *m, float *v, uint16_t *shadow, size_t n, float lr, float beta1,
                float beta2, float eps, float wd, int64_t step);
+// The same update on several ranges as one fork-join job.
+struct AdamPiece {
+    float *p;
+    const float *g;
+    float *m, *v;
+    uint16_t *shadow;   // may be NULL
+    size_t n;
+};
+void host_adam_pieces(const AdamPiece *pieces, size_t n_pieces, float lr, float beta1, float beta2, float eps, float wd,
+                      int64_t step);
 void host_zero(void *p, size_t bytes);  // multi-threaded first touch
 void rope_table(float *cs, float *sn, int T, int hd, double base);
 
