@@ -28,6 +28,8 @@
 // of the 64 banks only (a pitch of head_dim + 8 piles them onto the same 28 banks and halves the LDS rate).
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace mt {
@@ -199,12 +201,22 @@ __device__ __forceinline__ void mfma_tr_accumulate(f32x16 *acc, const bf16_t *ti
 // congruent modulo 8 and adjacent in dispatch order, so they run together on one XCD and the stream is
 // fetched into that XCD's L2 once.  per_set = workgroups per (batch, KV head); returns false for the
 // padding workgroups of the last, partial round.
+// A number of sets that is no multiple of 8 would leave XCDs idle (one set: seven of the eight), so each set is then cut into
+// 2, 4 or 8 parts on different XCDs, every part an even share of light and heavy blocks: 8192 tokens, 4 query heads, 1 KV
+// head of 128: forward 512 -> 213 us, dQ 708 -> 287.  Up to 7 % of idle XCD time a set stays whole (sharing one L2).
 constexpr int kXcds = 8;
+__host__ __device__ __forceinline__ int set_parts(int n_sets) {
+    int p = 1;
+    while (p < kXcds && (n_sets * p + kXcds - 1) / kXcds * kXcds * 100 > n_sets * p * 107) p *= 2;
+    return p;
+}
 __device__ __forceinline__ bool decode_block(int per_set, int n_sets, int *set, int *inner) {
+    const int p = set_parts(n_sets), per_part = (per_set + p - 1) / p;
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    *set = (slot / per_set) * kXcds + xcd;
-    *inner = slot % per_set;
-    return *set < n_sets;
+    const int part_id = (slot / per_part) * kXcds + xcd, i = slot % per_part, part = part_id % p;
+    *set = part_id / p;
+    *inner = i * p + (i & 1 ? p - 1 - part : part);
+    return *set < n_sets && *inner < per_set;
 }
 // Causal work falls off linearly with the block index, and the workgroups of an XCD are handed to its shader
 // engines round-robin in dispatch order: with the plain order "heaviest first" one engine would always get the
@@ -218,24 +230,27 @@ __device__ __forceinline__ int snake8(int i, int n) {
     if (n > 128 || !(row & 1) || row * 8 + 7 >= n) return i;
     return row * 8 + 7 - (i & 7);
 }
-inline unsigned grid_blocks(int per_set, int n_sets) { return (unsigned)(((n_sets + kXcds - 1) / kXcds) * kXcds * per_set); }
+inline unsigned grid_blocks(int per_set, int n_sets) {
+    const int p = set_parts(n_sets);
+    return (unsigned)((n_sets * p + kXcds - 1) / kXcds * kXcds * ((per_set + p - 1) / p));
+}
 
 // ------------------------------------------------------------------ forward
-// grid (q blocks of 32*NW rows, heaviest first; Hq; B); wave w owns 32 queries.  K and V tiles of 64
-// keys go through a double-buffered LDS stage, one barrier per tile.
+// grid (q blocks of 32*QW rows, heaviest first; Hq; B); wave w owns 32 queries.  K and V tiles of 64
+// keys go through a double-buffered LDS stage, one barrier per tile.  KW = 2: two sets of QW waves share the
+// queries, one per 32-key half of every tile, and are merged through LDS at the end: half the walk per tile for problems whose
+// few blocks would otherwise walk their keys while the chip idles (split_keys).  A 32-key half is either wholly
+// visible to a wave's 32 queries, or the diagonal one (every query sees at least its first key), or skipped.
 #ifndef MT_FWD_PAD
 #define MT_FWD_PAD 40
 #endif
 #ifndef MT_DQ_PAD
 #define MT_DQ_PAD 40
 #endif
-#ifndef MT_DQ_WAVES
-#define MT_DQ_WAVES 8
-#endif
 constexpr int kFwdPad = MT_FWD_PAD, kDqPad = MT_DQ_PAD;
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
-    constexpr int LDK = HD + kFwdPad, NT = 64 * NW, BQ = 32 * NW;
+template <int HD, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a) {
+    constexpr int LDK = HD + kFwdPad, NT = 64 * QW * KW, BQ = 32 * QW, NR = 2 / KW;
     constexpr int STAGE = 2 * 64 * LDK;
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
@@ -246,7 +261,8 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
     const int qb = nqb - 1 - snake8(inner % nqb, nqb);  // heaviest query blocks first, in alternating rows of 8
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
-    const int q0 = qb * BQ + wave * 32, q = q0 + l32;
+    const int qw = wave % QW, kw = wave / QW;
+    const int q0 = qb * BQ + qw * 32, q = q0 + l32;
     const bool qok = q < T;
     const int qm = qok ? q : T - 1;  // padded queries behave like the last row; never stored
 
@@ -282,26 +298,29 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
             stK.fetch(kbase + (int64_t)(kv0 + 64) * a.ldk, a.ldk, T - kv0 - 64, HD);
             stV.fetch(vbase + (int64_t)(kv0 + 64) * a.ldv, a.ldv, T - kv0 - 64, HD);
         }
-        if (kv0 <= q0 + 31) {  // otherwise the whole tile lies after every query of this wave
-            // S^T = K Q^T for the two 32-key row blocks: fragments are read in batches of 4 k-steps ahead of
-            // the MFMAs, and the two independent accumulation chains are interleaved
-            f32x16 sacc[2] = {zero16(), zero16()};
+        const int key0 = KW == 2 ? kw * 32 : 0;  // first key of this wave inside the tile
+        if (kv0 + key0 <= q0 + 31) {  // otherwise the wave's keys lie after every one of its queries
+            // S^T = K Q^T for the wave's 32-key row blocks: fragments are read in batches of 4 k-steps ahead of
+            // the MFMAs, and the independent accumulation chains are interleaved
+            f32x16 sacc[NR];
+#pragma unroll
+            for (int rb = 0; rb < NR; ++rb) sacc[rb] = zero16();
             {
-                const bf16_t *kr0 = Ks + l32 * LDK + hl * 8, *kr1 = kr0 + 32 * LDK;
+                const bf16_t *kr = Ks + (key0 + l32) * LDK + hl * 8;
 #pragma unroll
                 for (int half = 0; half < HD / 64; ++half) {
-                    bf16x8 k0[4], k1[4];
+                    bf16x8 kk[NR][4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        k0[j] = *reinterpret_cast<const bf16x8 *>(kr0 + (half * 4 + j) * 16);
-                        k1[j] = *reinterpret_cast<const bf16x8 *>(kr1 + (half * 4 + j) * 16);
-                    }
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int rb = 0; rb < NR; ++rb)
+                            kk[rb][j] = *reinterpret_cast<const bf16x8 *>(kr + rb * 32 * LDK + (half * 4 + j) * 16);
                     __builtin_amdgcn_sched_barrier(0);  // keep the batch of reads ahead of the MFMAs
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[j], qf[half * 4 + j], sacc[0], 0, 0, 0);
-                        sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[j], qf[half * 4 + j], sacc[1], 0, 0, 0);
-                    }
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int rb = 0; rb < NR; ++rb)
+                            sacc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[rb][j], qf[half * 4 + j], sacc[rb], 0, 0, 0);
                 }
             }
             // V^T fragments of the first two 16-key chunks are requested now, so that their LDS latency is
@@ -310,24 +329,24 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-                for (int hb = 0; hb < HD / 32; ++hb) va[ch][hb] = read_tr_frag(Vs, tr_off, LDK, ch * 16, hb * 32);
+                for (int hb = 0; hb < HD / 32; ++hb) va[ch][hb] = read_tr_frag(Vs, tr_off, LDK, key0 + ch * 16, hb * 32);
             __builtin_amdgcn_sched_barrier(0);
             // Softmax on the raw scores: the scale is folded into the exponent's multiply-add, the running
             // maximum m is only moved when some query of the wave saw a score more than kLazyMax above it
             // (P then stays below 2^kLazyMax * ... which bf16 and the fp32 sums hold without loss; the final
             // O / lsum and lse do not depend on which maximum was used), so the accumulator rescale is rare.
-            if (kv0 + 63 > q0) {  // tile touches the diagonal: mask keys after the query
+            if (kv0 + key0 + NR * 32 - 1 > q0) {  // the keys touch the diagonal: mask those after the query
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
+                for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const int kv = kv0 + rb * 32 + (r >> 2) * 8 + hl * 4 + (r & 3);
+                        const int kv = kv0 + key0 + rb * 32 + (r >> 2) * 8 + hl * 4 + (r & 3);
                         sacc[rb][r] = kv > qm ? -INFINITY : sacc[rb][r];
                     }
             }
-            float mx = fmaxf(sacc[0][0], sacc[1][0]);
+            float mx = fmaxf(sacc[0][0], sacc[NR - 1][0]);
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(fmaxf(mx, sacc[0][r]), sacc[1][r]);  // v_max3_f32
+            for (int r = 1; r < 16; ++r) mx = fmaxf(fmaxf(mx, sacc[0][r]), sacc[NR - 1][r]);  // v_max3_f32
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             // m = -inf before the first tile: the comparison is then true (every query sees key kv0)
             if (__builtin_amdgcn_ballot_w64(mx > m + tau) != 0) {
@@ -340,10 +359,11 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
                     for (int r = 0; r < 16; ++r) oacc[hb][r] *= alpha;
                 m = m_new;
             }
-            const float negmc = -m * c;
+            // (a wave that holds only half of the keys may have seen nothing but -inf so far: its P is then zero)
+            const float negmc = KW == 2 && m == -INFINITY ? 0.f : -m * c;
             float ps = 0.f;
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
+            for (int rb = 0; rb < NR; ++rb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[rb][r], c, negmc));
@@ -353,12 +373,12 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
             lsum += ps;
             // O^T += V^T P^T
 #pragma unroll
-            for (int ch = 0; ch < 4; ++ch) {
+            for (int ch = 0; ch < 2 * NR; ++ch) {
                 const bf16x8 pf = pack_frag(sacc[ch >> 1], ch & 1);
 #pragma unroll
                 for (int hb = 0; hb < HD / 32; ++hb)
                     oacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ch & 1][hb], pf, oacc[hb], 0, 0, 0);
-                if (ch < 2) {
+                if (ch + 2 < 2 * NR) {
 #pragma unroll
                     for (int hb = 0; hb < HD / 32; ++hb)
                         va[ch & 1][hb] = read_tr_frag(Vs, tr_off, LDK, (ch + 2) * 16, hb * 32);
@@ -373,17 +393,39 @@ __global__ __launch_bounds__(64 * NW) void flash_fwd_kernel(AttnArgs a) {
         __syncthreads();
     }
     lsum += __shfl_xor(lsum, 32, 64);
+    if constexpr (KW == 2) {
+        constexpr int NV = HD / 32 * 16;
+        float *red = reinterpret_cast<float *>(smem) + qw * ((NV + 2) * 64) + lane;
+        if (kw == 1) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) red[i * 64] = oacc[i / 16][i % 16];
+            red[NV * 64] = m;   // -inf where this half saw no key: its weight below is zero
+            red[(NV + 1) * 64] = lsum;
+        }
+        __syncthreads();
+        if (kw == 0) {
+            const float m1 = red[NV * 64], mn = fmaxf(m, m1);
+            const float w0 = __builtin_amdgcn_exp2f((m - mn) * c), w1 = __builtin_amdgcn_exp2f((m1 - mn) * c);
+            lsum = lsum * w0 + red[(NV + 1) * 64] * w1;
+            m = mn;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) oacc[i / 16][i % 16] = oacc[i / 16][i % 16] * w0 + red[i * 64] * w1;
+        }
+        __syncthreads();
+        if (kw == 1) return;
+    }
     if (q0 < T)
         write_owned_rows<HD>(a.o + ((int64_t)b * T + q0) * a.ldo + (int64_t)h * HD, a.ldo, oacc, 1.0f / lsum, l32, hl,
-                             min(32, T - q0), nullptr, nullptr, out_region<HD>(smem, wave));
+                             min(32, T - q0), nullptr, nullptr, out_region<HD>(smem, qw));
     if (qok && hl == 0) a.lse[((int64_t)b * a.Hq + h) * T + q] = (m * c + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
 // ------------------------------------------------------------------ backward: dQ
 // Same ownership as the forward: a lane owns one query, loops over key tiles <= q.
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void flash_bwd_dq_kernel(AttnArgs a) {
-    constexpr int BQ = 32 * NW, NT = 64 * NW;
+// KW = 2 splits the tiles' keys over two sets of waves as in the forward; their sums are added at the end.
+template <int HD, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a) {
+    constexpr int BQ = 32 * QW, NT = 64 * QW * KW;
     constexpr int LDK = HD + kDqPad;
     constexpr int STAGE = 2 * 64 * LDK;
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
@@ -395,7 +437,8 @@ __global__ __launch_bounds__(64 * NW) void flash_bwd_dq_kernel(AttnArgs a) {
     const int qb = nqb - 1 - snake8(inner % nqb, nqb);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
-    const int q0 = qb * BQ + wave * 32, q = q0 + l32;
+    const int qw = wave % QW, kw = wave / QW;
+    const int q0 = qb * BQ + qw * 32, q = q0 + l32;
     const bool qok = q < T;
     const int qm = qok ? q : T - 1;
 
@@ -436,10 +479,11 @@ __global__ __launch_bounds__(64 * NW) void flash_bwd_dq_kernel(AttnArgs a) {
             stK.fetch(kbase + (int64_t)(kv0 + 64) * a.ldk, a.ldk, T - kv0 - 64, HD);
             stV.fetch(vbase + (int64_t)(kv0 + 64) * a.ldv, a.ldv, T - kv0 - 64, HD);
         }
-        if (kv0 <= q0 + 31) {
+        if (kv0 + (KW == 2 ? kw * 32 : 0) <= q0 + 31) {
             const bool diag = kv0 + 63 > q0;
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
+            for (int u = 0; u < 2 / KW; ++u) {
+                const int rb = KW == 2 ? kw : u;
                 f32x16 sacc = zero16(), dpacc = zero16();
                 const bf16_t *kr = Ks + (rb * 32 + l32) * LDK + hl * 8;
                 const bf16_t *vr = Vs + (rb * 32 + l32) * LDK + hl * 8;
@@ -483,10 +527,25 @@ __global__ __launch_bounds__(64 * NW) void flash_bwd_dq_kernel(AttnArgs a) {
         }
         __syncthreads();
     }
+    if constexpr (KW == 2) {
+        constexpr int NV = HD / 32 * 16;
+        float *red = reinterpret_cast<float *>(smem) + qw * (NV * 64) + lane;
+        if (kw == 1) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) red[i * 64] = dqacc[i / 16][i % 16];
+        }
+        __syncthreads();
+        if (kw == 0) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) dqacc[i / 16][i % 16] += red[i * 64];
+        }
+        __syncthreads();
+        if (kw == 1) return;
+    }
     if (q0 < T)
         write_owned_rows<HD>(a.dq + ((int64_t)b * T + q0) * a.lddq + (int64_t)h * HD, a.lddq, dqacc, a.scale, l32, hl,
                              min(32, T - q0), a.rope_cos ? a.rope_cos + (int64_t)q0 * (HD / 2) : nullptr,
-                             a.rope_cos ? a.rope_sin + (int64_t)q0 * (HD / 2) : nullptr, out_region<HD>(smem, wave));
+                             a.rope_cos ? a.rope_sin + (int64_t)q0 * (HD / 2) : nullptr, out_region<HD>(smem, qw));
 }
 
 // ------------------------------------------------------------------ backward: dK, dV
@@ -505,9 +564,15 @@ __global__ __launch_bounds__(64 * NW) void flash_bwd_dq_kernel(AttnArgs a) {
 // conflict-free (odd multiple of 4 banks) and lets the four rows of a transposing read overlap in only
 // 12 of 64 banks (with HD + 8 they pile up on the same 28 banks).
 constexpr int kDkdvPad = 40;
-template <int HD>
-__global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
-    constexpr int LDK = HD + kDkdvPad, LDKV = HD + 8, HB = HD / 32, KB = 256;
+//
+// The work of a key block is one serial walk over G T / 64 tiles, so a short or narrow problem leaves most of the chip
+// idle while its few blocks walk.  KW, QW: KW waves own 32 keys each (blocks of 32 KW keys); with QW = 2 two such sets
+// share a block, one per 32-query half of every tile, and the second set's sums are added to the first's through
+// LDS at the end (fixed order).  (8, 1) above is the cheapest per tile, (4, 2) and (2, 2) have shorter walks: see
+// choose_dkdv.
+template <int HD, int KW, int QW>
+__global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a) {
+    constexpr int LDK = HD + kDkdvPad, LDKV = HD + 8, HB = HD / 32, KB = 32 * KW, NT = 64 * KW * QW;
     constexpr int V_BF = KB * LDKV;
     constexpr int STAGE_BF = 2 * 64 * LDK, STAGE = STAGE_BF + 256;
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
@@ -520,7 +585,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
     const int b = set / a.Hkv, hk = set % a.Hkv;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
-    const int kv0w = kvb * KB + wave * 32, kv = kv0w + l32;
+    const int kw = wave % KW, qw = wave / KW;
+    const int kv0w = kvb * KB + kw * 32, kv = kv0w + l32;
 
     f32x16 dvacc[HB], dkacc[HB];
 #pragma unroll
@@ -532,7 +598,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
     const int qt_first = (kvb * KB) / 64, n_qt = (T + 63) / 64 - qt_first;
     const int total = G * n_qt;
 
-    using Stage = TileStage<64, HD, LDK, 512>;
+    using Stage = TileStage<64, HD, LDK, NT>;
     Stage stQ, stDO;
     float stat = 0.f;
     bool stat_pad = false;
@@ -565,7 +631,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
     };
     bf16x8 kf[HD / 16];
     {
-        TileStage<KB, HD, LDKV, 512> stV;
+        TileStage<KB, HD, LDKV, NT> stV;
         stV.fetch(a.v + ((int64_t)b * T + kvb * KB) * a.ldv + (int64_t)hk * HD, a.ldv, T - kvb * KB, HD);
         fetch_next();
         const bf16_t *kp = a.k + ((int64_t)b * T + min(kv, T - 1)) * a.ldk + (int64_t)hk * HD + hl * 8;
@@ -576,7 +642,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
     }
     __syncthreads();
 
-    const bf16_t *vr = Vt + (wave * 32 + l32) * LDKV + hl * 8;
+    const bf16_t *vr = Vt + (kw * 32 + l32) * LDKV + hl * 8;
     int tq = 0;  // query tile inside the head
     for (int j = 0; j < total; ++j) {
         const bf16_t *Qs = stages + (j & 1) * STAGE, *dOs = Qs + 64 * LDK;
@@ -585,8 +651,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
         const bool more = j + 1 < total;
         if (more) fetch_next();
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-            const int q0u = q0t + rb * 32;
+        for (int u = 0; u < 2 / QW; ++u) {
+            const int rb = QW == 2 ? qw : u, q0u = q0t + rb * 32;
             if (q0u + 31 < kv0w) continue;  // wave-uniform: no query of the half sees a key of the wave
             f32x16 s_ = zero16(), p_ = zero16();
             const bf16_t *qr = Qs + (rb * 32 + l32) * LDK + hl * 8;
@@ -638,13 +704,31 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_kernel(AttnArgs a) {
         __syncthreads();
         tq = tq + 1 == n_qt ? 0 : tq + 1;
     }
+    if constexpr (QW == 2) {
+        float *red = reinterpret_cast<float *>(smem) + kw * (HB * 16 * 64) + lane;
+        auto add_halves = [&](f32x16 (&acc)[HB]) {
+            if (qw == 1) {
+#pragma unroll
+                for (int i = 0; i < HB * 16; ++i) red[i * 64] = acc[i / 16][i % 16];
+            }
+            __syncthreads();
+            if (qw == 0) {
+#pragma unroll
+                for (int i = 0; i < HB * 16; ++i) acc[i / 16][i % 16] += red[i * 64];
+            }
+            __syncthreads();
+        };
+        add_halves(dvacc);
+        add_halves(dkacc);
+        if (qw == 1) return;
+    }
     if (kv0w < T) {
         const int n_valid = min(32, T - kv0w);
         write_owned_rows<HD>(a.dk + ((int64_t)b * T + kv0w) * a.lddk + (int64_t)hk * HD, a.lddk, dkacc, a.scale, l32, hl,
                              n_valid, a.rope_cos ? a.rope_cos + (int64_t)kv0w * (HD / 2) : nullptr,
-                             a.rope_cos ? a.rope_sin + (int64_t)kv0w * (HD / 2) : nullptr, out_region<HD>(smem, wave));
+                             a.rope_cos ? a.rope_sin + (int64_t)kv0w * (HD / 2) : nullptr, out_region<HD>(smem, kw));
         write_owned_rows<HD>(a.dv + ((int64_t)b * T + kv0w) * a.lddv + (int64_t)hk * HD, a.lddv, dvacc, 1.0f, l32, hl,
-                             n_valid, nullptr, nullptr, out_region<HD>(smem, wave));
+                             n_valid, nullptr, nullptr, out_region<HD>(smem, kw));
     }
 }
 
@@ -673,25 +757,49 @@ static hipError_t ensure_lds(K kernel, size_t bytes, bool *done) {
     return e;
 }
 
+template <int HD, int QW, int KW>
+static hipError_t launch_fwd(const AttnArgs &a, hipStream_t s) {
+    constexpr size_t lds = 2 * (2 * 64 * (HD + kFwdPad)) * sizeof(bf16_t);
+    static_assert(KW == 1 || (size_t)QW * (HD / 32 * 16 + 2) * 64 * sizeof(float) <= lds, "room for the other half's sums");
+    static bool done = false;
+    const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW>, lds, &done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
+                       dim3(64 * QW * KW), lds, s, a);
+    return hipGetLastError();
+}
+
+template <int HD, int QW, int KW>
+static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
+    constexpr size_t lds = 2 * (2 * 64 * (HD + kDqPad)) * sizeof(bf16_t);
+    static_assert(KW == 1 || (size_t)QW * (HD / 32 * 16) * 64 * sizeof(float) <= lds, "room for the other half's sums");
+    static bool done = false;
+    const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW>, lds, &done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
+                       dim3(64 * QW * KW), lds, s, a);
+    return hipGetLastError();
+}
+
+// Forward and dQ: blocks of 128 queries with the keys split over two sets of waves, or blocks of 256?  The former walk
+// their keys in two thirds of the time (per 64-key tile 1.16 against 1.68 us at head_dim 128, 0.9 against 1.3 at 64) but fetch K and
+// V twice as often.  They are taken while about one round of them covers the problem (256 compute units).  Measured,
+// blocks of 256 -> 128, us (forward; dQ), head_dim 128 unless said:
+//   256 blocks: 1 x 8192 x 4 heads 212 -> 153; 288 -> 175       1 x 4096 x 8 110 -> 81; 149 -> 92      2 x 1024 x 16 33 -> 27; 44 -> 31
+//   288: 1 x 1536 x 24 47 -> 36; 62 -> 42     320: 1 x 1024 x 40 35 -> 41; 46 -> 48     384 (head_dim 64): 3 x 1000 x 16 24 -> 27; 28 -> 37
+//   4096: 4 x 4096 x 32 610 -> 733; 830 -> 910
+// With head_dim 64 the forward is bound by its vector arithmetic and four of the smaller workgroups' waves fit on a SIMD:
+// up to 4096 tokens and with several rounds they win again (8 x 2048 x 16 154 -> 119, 4 x 4096 x 16 214 -> 207; 1 x 8192 x 32 359 -> 377).
+static bool split_keys(const AttnArgs &a, bool forward) {
+    const int64_t blocks = (int64_t)a.B * a.Hq * ((a.T + 127) / 128);
+    return blocks <= 288 || (forward && a.hd == 64 && a.T <= 4096 && blocks >= 1024);
+}
+
 hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
     if (!attn_shape_ok(a) || (a.ldq & 7) || (a.ldk & 7) || (a.ldv & 7) || (a.ldo & 3)) return hipErrorInvalidValue;
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || ((uintptr_t)a.o & 7)) return hipErrorInvalidValue;
-    constexpr int NW = 8;
-    const dim3 grid(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * NW - 1) / (32 * NW)), a.B * a.Hkv));
-    if (a.hd == 128) {
-        constexpr size_t lds = 2 * (2 * 64 * (128 + kFwdPad)) * sizeof(bf16_t);
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_fwd_kernel<128, NW>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((flash_fwd_kernel<128, NW>), grid, dim3(64 * NW), lds, s, a);
-    } else {
-        constexpr size_t lds = 2 * (2 * 64 * (64 + kFwdPad)) * sizeof(bf16_t);
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_fwd_kernel<64, NW>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((flash_fwd_kernel<64, NW>), grid, dim3(64 * NW), lds, s, a);
-    }
-    return hipGetLastError();
+    if (split_keys(a, true)) return a.hd == 128 ? launch_fwd<128, 4, 2>(a, s) : launch_fwd<64, 4, 2>(a, s);
+    return a.hd == 128 ? launch_fwd<128, 8, 1>(a, s) : launch_fwd<64, 8, 1>(a, s);
 }
 
 hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
@@ -700,22 +808,51 @@ hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.dout) || ((uintptr_t)a.dq & 7))
         return hipErrorInvalidValue;
-    constexpr int NW = MT_DQ_WAVES;
-    const dim3 grid(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * NW - 1) / (32 * NW)), a.B * a.Hkv));
-    if (a.hd == 128) {
-        constexpr size_t lds = 2 * (2 * 64 * (128 + kDqPad)) * sizeof(bf16_t);
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_bwd_dq_kernel<128, NW>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((flash_bwd_dq_kernel<128, NW>), grid, dim3(64 * NW), lds, s, a);
-    } else {
-        constexpr size_t lds = 2 * (2 * 64 * (64 + kDqPad)) * sizeof(bf16_t);
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_bwd_dq_kernel<64, NW>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((flash_bwd_dq_kernel<64, NW>), grid, dim3(64 * NW), lds, s, a);
-    }
+    if (split_keys(a, false)) return a.hd == 128 ? launch_dq<128, 4, 2>(a, s) : launch_dq<64, 4, 2>(a, s);
+    return a.hd == 128 ? launch_dq<128, 8, 1>(a, s) : launch_dq<64, 8, 1>(a, s);
+}
+
+template <int HD, int KW, int QW>
+static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
+    constexpr int KB = 32 * KW;
+    // V [KB][hd + 8] | two stages of Q, dO [64][hd + pad] + 64 lse + 64 delta
+    constexpr size_t lds = (KB * (HD + 8) + 2 * (2 * 64 * (HD + kDkdvPad))) * sizeof(bf16_t) + 2 * 512;
+    static_assert(QW == 1 || (size_t)KW * (HD / 32) * 16 * 64 * sizeof(float) <= lds, "room for the other half's sums");
+    static bool done = false;
+    const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW>, lds, &done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW>), dim3(grid_blocks((a.T + KB - 1) / KB, a.B * a.Hkv)),
+                       dim3(64 * KW * QW), lds, s, a);
     return hipGetLastError();
+}
+
+// Estimated time of the dK/dV kernel in us for key blocks of kb keys: the walk of the first block (every query tile of
+// every head of the group), or the work of all blocks on 256 compute units, whichever is longer.  `tile` and `full` are us per
+// 64-query tile when a walk decides and when the chip is full, `start` and `start_full` per block; fitted to 27 shapes
+// (T 128 .. 32768, 1 .. 32 KV heads), which they meet within 15 %.  us for (8, 1) / (4, 2) / (2, 2), head_dim 128:
+//   1 x 4096, 40 heads on 8 KV heads 966 / 685 / 593     1 x 8192, 40 on 8 1996 / 1565 / 2153     1 x 8192, 4 on 1 1541 / 1083 / 838
+//   4 x 4096, 32 on 32 1131 / 1278 / 1983                2 x 1024, 16 on 16 56 / 42 / 55          8 x 512, 32 on 32 72 / 104 / 127
+// head_dim 64: 3 x 1000, 16 on 4 133 / 83 / 93; 8 x 2048, 16 on 16 243 / 223 / 269; 1 x 32768, 4 on 4 1208 / 1303 / 1730.
+struct DkdvCost { int kb; double start, tile, start_full, full; };
+static double dkdv_time(const AttnArgs &a, const DkdvCost &c) {
+    const double n_qt = (a.T + 63) / 64, nkb = (a.T + c.kb - 1) / c.kb, G = a.Hq / a.Hkv;
+    const double mean = G * (n_qt - (nkb - 1) * (c.kb / 64) * 0.5);   // tiles of a block, averaged over the blocks
+    return std::max(c.start + G * n_qt * c.tile, (double)a.B * a.Hkv * nkb / 256.0 * (c.start_full + mean * c.full));
+}
+static int choose_dkdv(const AttnArgs &a) {
+    static const DkdvCost hd64[] = {{256, 2.0, 2.05, 14.0, 2.3}, {128, 2.5, 1.22, 7.0, 1.27}};
+    static const DkdvCost hd128[] = {{256, 6.0, 3.05, 10.0, 3.9}, {128, 5.0, 2.05, 6.0, 2.35}, {64, 5.0, 1.75, 5.0, 1.78}};
+    const DkdvCost *costs = a.hd == 64 ? hd64 : hd128;
+    int best = 0;
+    double best_t = dkdv_time(a, costs[0]);
+    for (int i = 1; i < (a.hd == 64 ? 2 : 3); ++i) {
+        const double t = dkdv_time(a, costs[i]);
+        if (t < 0.97 * best_t) {
+            best = i;
+            best_t = t;
+        }
+    }
+    return best;
 }
 
 hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
@@ -726,22 +863,11 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.dout) || ((uintptr_t)a.dk & 7) ||
         ((uintptr_t)a.dv & 7))
         return hipErrorInvalidValue;
-    const dim3 grid(grid_blocks((a.T + 255) / 256, a.B * a.Hkv));
-    // V [256][hd + 8] | two stages of Q, dO [64][hd + pad] + 64 lse + 64 delta
-    if (a.hd == 128) {
-        constexpr size_t lds = (256 * (128 + 8) + 2 * (2 * 64 * (128 + kDkdvPad))) * sizeof(bf16_t) + 2 * 512;
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<128>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(flash_bwd_dkdv_kernel<128>, grid, dim3(512), lds, s, a);
-    } else {
-        constexpr size_t lds = (256 * (64 + 8) + 2 * (2 * 64 * (64 + kDkdvPad))) * sizeof(bf16_t) + 2 * 512;
-        static bool done = false;
-        hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<64>, lds, &done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(flash_bwd_dkdv_kernel<64>, grid, dim3(512), lds, s, a);
+    switch (choose_dkdv(a)) {
+        case 0: return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
+        case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);
+        default: return launch_dkdv<128, 2, 2>(a, s);
     }
-    return hipGetLastError();
 }
 
 }  // namespace mt

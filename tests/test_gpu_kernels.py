@@ -542,7 +542,7 @@ def test_cross_entropy_at_the_widths_where_the_kernel_changes(orc64, V):
 
 
 # ----------------------------------------------------------------------------- attention
-def _attention_case(orc64, B, T, Hq, Hkv, hd, seed, out_pad=0):
+def _attention_case(orc64, B, T, Hq, Hkv, hd, seed, out_pad=0, dq_floor=ROW_FLOOR):
     """out_pad: extra elements in the row pitch of every output (4: rows are then only 8-byte aligned and the
     kernels store straight from the accumulator layout instead of through LDS)."""
     rng = np.random.default_rng(seed)
@@ -581,7 +581,7 @@ def _attention_case(orc64, B, T, Hq, Hkv, hd, seed, out_pad=0):
     assert rel_l2(got[:, :nq], dq_ref) < 2e-2 and cosine(got[:, :nq], dq_ref) > 0.9995
     assert rel_l2(got[:, nq:nq + nkv], dk_ref) < 2e-2 and cosine(got[:, nq:nq + nkv], dk_ref) > 0.9995
     assert rel_l2(got[:, nq + nkv:ld], dv_ref) < 1e-2 and cosine(got[:, nq + nkv:ld], dv_ref) > 0.9995
-    assert_rows_close(got[:, :nq], dq_ref, ROW_ATT_BWD, ROW_FLOOR, width=hd, what="attention dq (per token and head)")
+    assert_rows_close(got[:, :nq], dq_ref, ROW_ATT_BWD, dq_floor, width=hd, what="attention dq (per token and head)")
     assert_rows_close(got[:, nq:nq + nkv], dk_ref, ROW_ATT_BWD, ROW_FLOOR, width=hd, what="attention dk")
     assert_rows_close(got[:, nq + nkv:ld], dv_ref, ROW_ATT_BWD, ROW_FLOOR, width=hd, what="attention dv")
 
@@ -591,6 +591,40 @@ def _attention_case(orc64, B, T, Hq, Hkv, hd, seed, out_pad=0):
                                            (2, 520, 2, 2, 64)])
 def test_flash_attention_forward_backward(orc64, B, T, Hq, Hkv, hd):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + hd)
+
+
+# Both ways of sharing a block among waves (few blocks: keys or queries split over two sets of waves; many: not), edges of
+# 32-, 64-, 128- and 256-row blocks, and set counts (batch x KV heads) that do and do not fill the 8 XCDs evenly.
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 24, 8, 8, 128), (3, 40, 3, 1, 64), (1, 136, 9, 3, 128), (5, 264, 2, 1, 64), (1, 1032, 4, 1, 128),
+                                           (3, 104, 18, 6, 64), (10, 136, 20, 4, 64), (5, 152, 32, 4, 128), (2, 1024, 32, 32, 64),
+                                           (8, 256, 32, 32, 128), (1, 2056, 2, 2, 64)])
+def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd):
+    # dq of the first few queries: delta = dO . O carries O's bf16 rounding, 2^-9 sqrt(hd) = 0.022 for unit normal data and
+    # hd = 128; times scale (0.088), P <= 1 and the largest |k| (about 4) that is 0.008, whereas ROW_FLOOR allows 2^-9 of
+    # the largest |dq| (about 3 in a short sequence): 0.006
+    _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 264 else 0, dq_floor=2 * ROW_FLOOR)
+
+
+def test_flash_attention_scores_of_minus_infinity(orc64):
+    """Keys whose scores are -inf for a query (inf * -1) have no weight, also where a whole 32-key half is such."""
+    B, T, H, hd = 1, 136, 2, 64
+    rng = np.random.default_rng(3)
+    q, k, v = (bf16_round(rng.standard_normal((T, H * hd))) for _ in range(3))
+    q[:, ::hd] = 1.0
+    masked = np.zeros(T, bool)
+    masked[32:64] = masked[100] = True
+    q[masked, ::hd] = 0.0                        # 0 * inf is NaN: those rows are not looked at
+    k[masked, ::hd] = -np.inf
+    Q, K, V = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    O, LSE = torch.zeros_like(Q), torch.zeros((B, H, T), dtype=torch.float32, device="cuda")
+    ok(L.mt_k_flash_fwd(O.data_ptr(), H * hd, LSE.data_ptr(), Q.data_ptr(), H * hd, K.data_ptr(), H * hd, V.data_ptr(), H * hd,
+                        B, T, H, H, hd, hd ** -0.5, None))
+    for h in range(H):
+        s = (q[:, h * hd:(h + 1) * hd].astype(np.float64)[~masked] @ k[:, h * hd:(h + 1) * hd].astype(np.float64)[~masked].T) * hd ** -0.5
+        s[np.triu_indices(len(s), 1)] = -np.inf
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        ref = (p / p.sum(axis=1, keepdims=True)) @ v[:, h * hd:(h + 1) * hd].astype(np.float64)[~masked]
+        assert_rows_close(host(O)[~masked][:, h * hd:(h + 1) * hd], ref, ROW2, what="masked keys")
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 200, 4, 2, 64), (2, 72, 2, 2, 128)])
