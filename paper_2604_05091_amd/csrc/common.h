@@ -74,6 +74,24 @@ __device__ __forceinline__ bf16x8 read_tr_frag(const bf16_t *tile, int lane_off,
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// acc += a b (16 x 16 x 32, bf16): lane l holds of a and of b row l & 15, reduction indices 8 (l >> 4) .. + 7, and of acc
+// column l & 15, rows 4 (l >> 4) .. + 3.  In place in the accumulation registers: through the builtin the compiler gives a large
+// set of accumulators new registers every time and moves them back.  It neither sees that this is a matrix instruction: whoever
+// reads an accumulator calls mfma16_settle first, and operands come from LDS reads (the wait for those is the
+// compiler's as usual), not from a vector instruction right in front.
+__device__ __forceinline__ void mfma16_acc(f32x4 &acc, const bf16x8 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// every accumulator has been written (16 wait states, the slowest of these instructions needs 11) and may be read
+template <int I, int J>
+__device__ __forceinline__ void mfma16_settle(f32x4 (&acc)[I][J]) {
+    asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j) asm volatile("" : "+a"(acc[i][j]));
+}
+
 #endif  // __HIPCC__
 
 // ---------------------------------------------------------------- launchers (host side)

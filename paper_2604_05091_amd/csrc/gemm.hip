@@ -7,7 +7,7 @@
 // stored ([out,in]); the input-gradient and weight-gradient products are brought to
 // the same form by transposing one or both operands with transpose_bf16 first.
 //
-// Here a workgroup owns a 256 x 256 tile of C made of 32x32 MFMA blocks (v_mfma_f32_32x32x16_bf16, 16 fp32 accumulators
+// Here a workgroup owns a 256 x 256 tile of C made of 16x16 MFMA blocks (v_mfma_f32_16x16x32_bf16, 4 fp32 accumulators
 // per lane per block): 4 waves x 128x128 quadrants, K walked in steps of 64 through a double-buffered LDS stage,
 // software-pipelined inside the wave.  Reductions that are no multiple of 64 and grids that 256 x 256 tiles fill badly
 // go to the kernels with smaller tiles in gemm_ring.hip (choose_tile).
@@ -28,32 +28,14 @@ namespace mt {
 namespace {
 
 constexpr int BK = 64;
-constexpr int LDT = BK + 8;
 constexpr int kXcd = 8;
-constexpr int kGroupM = 8;
 // Tile-row group of the large-grid (load-to-LDS) kernels: the 32 workgroups of an XCD then cover 4 x 8 tiles and a
 // group's A rows are left after two patches.  Measured inside the step against 8 (8 x 4 patches): 14B GEMM class
 // +0.9 %, 1.3B +0.9 %, 7B +0.2 %; 3 and 6 lose at 14B.  (Stand-alone timings of one GEMM repeated on the same
 // operands favour small groups far more, up to 7 % at K = 11008, but there the operands are still in the memory-side
 // cache from the previous repetition.)
 constexpr int kGroupMLarge = 4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
-// ---------------------------------------------------------------------------------------------
-// Register-staged kernel (MT_GEMM_VARIANT=5): LDS rows padded to 72 elements (144 B, conflict-free 16-byte fragment
-// reads), every wave owns a 128 x 128 quadrant (4 x 4 MFMA blocks, 256 accumulators in AGPRs), and the whole
-// k-step is software-pipelined inside the wave:
-//   phase p = 0..2 : MFMAs of k-slice p  ||  LDS reads of slice p+1  ||  a third of the staged
-//                    registers of step t+1 written to the other LDS buffer, each register refilled
-//                    at once by the global load of step t+2
-//   barrier        : all waves have read buffer t%2 and written step t+1
-//   phase 3        : MFMAs of slice 3  ||  LDS reads of slice 0 of step t+1
-// so neither the LDS writes nor the global loads ever sit between two MFMAs of one wave.  The
-// barrier is issued without a memory fence: a fence would also wait for the global loads in flight.
 constexpr int W4_BM = 256, W4_BN = 256, W4_NT = 256;
-constexpr int W4_A_BYTES = W4_BM * LDT * 2, W4_STAGE_BYTES = 2 * W4_A_BYTES;
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // bf16 results leave through LDS.  Stored straight from the accumulator layout, a store instruction touches 32
 // rows with 16 bytes each, and these partial-line writes cost 10-13 us per tile; instead every wave writes its
@@ -61,7 +43,6 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // it back row-wise, so that a store instruction covers whole 128-byte lines (16 bytes per lane, consecutive lanes
 // at consecutive addresses).  Region pitch NC + 8 elements: conflict-free for the 8-byte writes and the 16-byte reads.
 constexpr int W4_EP_PITCH = 128 + 8;
-__device__ __forceinline__ bf16_t *w4_ep_region(bf16_t *smem, int wave) { return smem + wave * 128 * W4_EP_PITCH; }
 
 // second half: rows of the wave's block from LDS to C, NC columns starting at col0; rows >= M skipped
 template <int NC>
@@ -80,72 +61,52 @@ __device__ __forceinline__ void w4_flush_rows(bf16_t *C, int64_t ldc, int M, int
 }
 
 // Epilogue of the 4-wave kernels.  The MFMAs are issued with the operands swapped (B fragment first), so each
-// 32x32 block holds C transposed: the lane owns row l32 of the block and, per group q = r/4, the four
-// consecutive columns 8 q + 4 hl + (0..3): one 8-byte (bf16) or 16-byte (fp32) store each.
-__device__ __forceinline__ void w4_store(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn,
-                                         int l32, int hl) {
+// 16x16 block holds C transposed: the lane owns row l16 of the block and its four consecutive columns
+// 4 hq + (0..3): one 8-byte (bf16) or 16-byte (fp32) store each.
+__device__ __forceinline__ void w4_store(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn,
+                                         int l16, int hq) {
     constexpr int BM = W4_BM, BN = W4_BN;
-    const int row_l = m0 + wm * 128 + l32, col_l = n0 + wn * 128 + hl * 4;
+    const int row_l = m0 + wm * 128 + l16, col_l = n0 + wn * 128 + hq * 4;
     const bool full = (m0 + BM <= g.M) && (n0 + BN <= g.N);
     const bool vec = full && !(g.ldc & 3) && !((uintptr_t)g.C & 15) && (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) &&
                      !((uintptr_t)g.bias & 7);
-    if (g.out_fp32) {
-        float *cw = reinterpret_cast<float *>(g.C);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = row_l + i * 32;
+    for (int i = 0; i < 8; ++i) {
+        const int row = row_l + i * 16;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 8; ++j) {
+            const int col = col_l + j * 16;
+            f32x4 v = acc[i][j];
+            if (g.out_fp32) {
+                float *cp = reinterpret_cast<float *>(g.C) + (int64_t)row * g.ldc + col;
+                if (vec) {
+                    if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp);
+                    *reinterpret_cast<f32x4 *>(cp) = v;
+                } else if (row < g.M) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = col_l + j * 32 + q * 8;
-                    float *cp = cw + (int64_t)row * g.ldc + col;
-                    if (vec) {
-                        f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                        if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp);
-                        *reinterpret_cast<f32x4 *>(cp) = v;
-                    } else if (row < g.M) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < g.N) cp[e] = acc[i][j][4 * q + e] + (g.accumulate ? cp[e] : 0.f);
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) cp[e] = v[e] + (g.accumulate ? cp[e] : 0.f);
                 }
-        }
-    } else {
-        bf16_t *cw = reinterpret_cast<bf16_t *>(g.C);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = row_l + i * 32;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = col_l + j * 32 + q * 8;
-                    bf16_t *cp = cw + (int64_t)row * g.ldc + col;
-                    const bf16_t *rp = g.R ? g.R + (int64_t)row * g.ldr + col : nullptr;
-                    if (vec) {
-                        float v0 = acc[i][j][4 * q], v1 = acc[i][j][4 * q + 1], v2 = acc[i][j][4 * q + 2],
-                              v3 = acc[i][j][4 * q + 3];
-                        if (g.bias) {
-                            const uint2 bv = *reinterpret_cast<const uint2 *>(g.bias + col);
-                            v0 += bflo(bv.x); v1 += bfhi(bv.x); v2 += bflo(bv.y); v3 += bfhi(bv.y);
-                        }
-                        if (rp) {
-                            const uint2 rv = *reinterpret_cast<const uint2 *>(rp);
-                            v0 += bflo(rv.x); v1 += bfhi(rv.x); v2 += bflo(rv.y); v3 += bfhi(rv.y);
-                        }
-                        uint2 o;
-                        o.x = pack2bf(v0, v1);
-                        o.y = pack2bf(v2, v3);
-                        *reinterpret_cast<uint2 *>(cp) = o;
-                    } else if (row < g.M) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (col + e < g.N)
-                                cp[e] = f2bf(acc[i][j][4 * q + e] + (g.bias ? bf2f(g.bias[col + e]) : 0.f) +
-                                             (rp ? bf2f(rp[e]) : 0.f));
+            } else {
+                bf16_t *cp = reinterpret_cast<bf16_t *>(g.C) + (int64_t)row * g.ldc + col;
+                const bf16_t *rp = g.R ? g.R + (int64_t)row * g.ldr + col : nullptr;
+                if (vec) {
+                    if (g.bias) {
+                        const uint2 bv = *reinterpret_cast<const uint2 *>(g.bias + col);
+                        v[0] += bflo(bv.x); v[1] += bfhi(bv.x); v[2] += bflo(bv.y); v[3] += bfhi(bv.y);
                     }
+                    if (rp) {
+                        const uint2 rv = *reinterpret_cast<const uint2 *>(rp);
+                        v[0] += bflo(rv.x); v[1] += bfhi(rv.x); v[2] += bflo(rv.y); v[3] += bfhi(rv.y);
+                    }
+                    *reinterpret_cast<uint2 *>(cp) = uint2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+                } else if (row < g.M) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N)
+                            cp[e] = f2bf(v[e] + (g.bias ? bf2f(g.bias[col + e]) : 0.f) + (rp ? bf2f(rp[e]) : 0.f));
                 }
+            }
         }
     }
 }
@@ -155,138 +116,113 @@ __device__ __forceinline__ void w4_store(const GemmArgs &g, const f32x16 (&acc)[
 // and residual are template parameters as well: tested per element at run time they turned every one of the 64
 // loads into a branch with its own wait.  Here a row block's 16 residual loads are in flight together.
 template <bool BIAS, bool RES>
-__device__ __forceinline__ void w4_store_full_bf16(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int wm,
-                                                   int wn, int l32, int hl, bf16_t *region) {
-    const int lane = hl * 32 + l32;
-    const int col_l = n0 + wn * 128 + hl * 4;
-    uint2 bv[16];
+__device__ __forceinline__ void w4_store_full_bf16(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm,
+                                                   int wn, int l16, int hq, bf16_t *region) {
+    const int lane = hq * 16 + l16;
+    const int col_l = n0 + wn * 128 + hq * 4;
+    uint2 bv[8];
     if constexpr (BIAS) {
 #pragma unroll
-        for (int jq = 0; jq < 16; ++jq) bv[jq] = *reinterpret_cast<const uint2 *>(g.bias + col_l + (jq >> 2) * 32 + (jq & 3) * 8);
+        for (int j = 0; j < 8; ++j) bv[j] = *reinterpret_cast<const uint2 *>(g.bias + col_l + j * 16);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bf16_t *lp = region + (i * 32 + l32) * W4_EP_PITCH + hl * 4;
+    for (int i = 0; i < 8; ++i) {
+        bf16_t *lp = region + (i * 16 + l16) * W4_EP_PITCH + hq * 4;
         // bias and residual are added in fp32, before the one rounding to bf16
-        uint2 rv[16];
+        uint2 rv[8];
         if constexpr (RES) {
             // rows past M (a ragged last row tile) re-read the last row; the second half never stores them
-            const bf16_t *rp = g.R + (int64_t)min(m0 + wm * 128 + i * 32 + l32, g.M - 1) * g.ldr + col_l;
+            const bf16_t *rp = g.R + (int64_t)min(m0 + wm * 128 + i * 16 + l16, g.M - 1) * g.ldr + col_l;
 #pragma unroll
-            for (int jq = 0; jq < 16; ++jq) rv[jq] = *reinterpret_cast<const uint2 *>(rp + (jq >> 2) * 32 + (jq & 3) * 8);
+            for (int j = 0; j < 8; ++j) rv[j] = *reinterpret_cast<const uint2 *>(rp + j * 16);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int o = j * 32 + q * 8, jq = j * 4 + q;
-                float v0 = acc[i][j][4 * q], v1 = acc[i][j][4 * q + 1], v2 = acc[i][j][4 * q + 2], v3 = acc[i][j][4 * q + 3];
-                if constexpr (BIAS) {
-                    v0 += bflo(bv[jq].x); v1 += bfhi(bv[jq].x); v2 += bflo(bv[jq].y); v3 += bfhi(bv[jq].y);
-                }
-                if constexpr (RES) {
-                    v0 += bflo(rv[jq].x); v1 += bfhi(rv[jq].x); v2 += bflo(rv[jq].y); v3 += bfhi(rv[jq].y);
-                }
-                uint2 u;
-                u.x = pack2bf(v0, v1);
-                u.y = pack2bf(v2, v3);
-                *reinterpret_cast<uint2 *>(lp + o) = u;
+        for (int j = 0; j < 8; ++j) {
+            f32x4 v = acc[i][j];
+            if constexpr (BIAS) {
+                v[0] += bflo(bv[j].x); v[1] += bfhi(bv[j].x); v[2] += bflo(bv[j].y); v[3] += bfhi(bv[j].y);
             }
+            if constexpr (RES) {
+                v[0] += bflo(rv[j].x); v[1] += bfhi(rv[j].x); v[2] += bflo(rv[j].y); v[3] += bfhi(rv[j].y);
+            }
+            *reinterpret_cast<uint2 *>(lp + j * 16) = uint2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+        }
     }
     w4_flush_rows<128>(reinterpret_cast<bf16_t *>(g.C), g.ldc, g.M, m0 + wm * 128, n0 + wn * 128, region, lane);
 }
 
-__device__ __forceinline__ void w4_store_full_f32(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int wm,
-                                                  int wn, int l32, int hl) {
-    const int row_l = m0 + wm * 128 + l32, col_l = n0 + wn * 128 + hl * 4;
+__device__ __forceinline__ void w4_store_full_f32(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm,
+                                                  int wn, int l16, int hq) {
+    const int row_l = m0 + wm * 128 + l16, col_l = n0 + wn * 128 + hq * 4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (row_l + i * 32 >= g.M) continue;   // ragged last row tile
-        float *cp = reinterpret_cast<float *>(g.C) + (int64_t)(row_l + i * 32) * g.ldc + col_l;
+    for (int i = 0; i < 8; ++i) {
+        if (row_l + i * 16 >= g.M) continue;   // ragged last row tile
+        float *cp = reinterpret_cast<float *>(g.C) + (int64_t)(row_l + i * 16) * g.ldc + col_l;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int o = j * 32 + q * 8;
-                f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp + o);
-                *reinterpret_cast<f32x4 *>(cp + o) = v;
-            }
+        for (int j = 0; j < 8; ++j) {
+            f32x4 v = acc[i][j];
+            if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp + j * 16);
+            *reinterpret_cast<f32x4 *>(cp + j * 16) = v;
+        }
     }
 }
 
 // bf16 store with the rotary embedding applied on the way out (g.rope_*): the wave's 128 columns are one head,
-// the lane holds both members (j, j + 64) of every pair of its rows: blocks j4 and j4 + 2 of acc.  Columns are
+// the lane holds both members (j, j + 64) of every pair of its rows: blocks j and j + 4 of acc.  Columns are
 // complete (N % 128 == 0, checked on the host); rows are guarded.  Heads at or beyond rope_cols (the value
 // projection) are stored unrotated.  Bias, if any, is added before the rotation.  The rows leave through LDS.
 template <bool BIAS>
-__device__ __forceinline__ void w4_store_rope(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn,
-                                              int l32, int hl, bf16_t *region) {
-    const int row_l = m0 + wm * 128 + l32, col_w = n0 + wn * 128;
+__device__ __forceinline__ void w4_store_rope(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn,
+                                              int l16, int hq, bf16_t *region) {
+    const int row_l = m0 + wm * 128 + l16, col_w = n0 + wn * 128;
     if (col_w >= g.N) return;
     const bool rot = col_w < g.rope_cols;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 8; ++i) {
         // rows past M compute values nobody stores; their table row is still a valid one
-        const int64_t tpos = (int64_t)((row_l + i * 32) % g.rope_T) * 64;
-        bf16_t *lp = region + (i * 32 + l32) * W4_EP_PITCH;
+        const int64_t tpos = (int64_t)((row_l + i * 16) % g.rope_T) * 64;
+        bf16_t *lp = region + (i * 16 + l16) * W4_EP_PITCH;
 #pragma unroll
-        for (int jp = 0; jp < 2; ++jp)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int jc = jp * 32 + q * 8 + hl * 4;  // pair index inside the head, < 64
-                float a[4], b[4];
+        for (int j = 0; j < 4; ++j) {
+            const int jc = j * 16 + hq * 4;  // pair index inside the head, < 64
+            f32x4 a = acc[i][j], b = acc[i][j + 4];
+            if constexpr (BIAS) {
+                const uint2 ba = *reinterpret_cast<const uint2 *>(g.bias + col_w + jc);
+                const uint2 bb = *reinterpret_cast<const uint2 *>(g.bias + col_w + jc + 64);
+                a[0] += bflo(ba.x); a[1] += bfhi(ba.x); a[2] += bflo(ba.y); a[3] += bfhi(ba.y);
+                b[0] += bflo(bb.x); b[1] += bfhi(bb.x); b[2] += bflo(bb.y); b[3] += bfhi(bb.y);
+            }
+            if (rot) {
+                const f32x4 c = *reinterpret_cast<const f32x4 *>(g.rope_cos + tpos + jc);
+                const f32x4 sn = *reinterpret_cast<const f32x4 *>(g.rope_sin + tpos + jc);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    a[e] = acc[i][jp][4 * q + e];
-                    b[e] = acc[i][jp + 2][4 * q + e];
+                    const float ya = a[e] * c[e] - b[e] * sn[e], yb = b[e] * c[e] + a[e] * sn[e];
+                    a[e] = ya;
+                    b[e] = yb;
                 }
-                if constexpr (BIAS) {
-                    const uint2 ba = *reinterpret_cast<const uint2 *>(g.bias + col_w + jc);
-                    const uint2 bb = *reinterpret_cast<const uint2 *>(g.bias + col_w + jc + 64);
-                    a[0] += bflo(ba.x); a[1] += bfhi(ba.x); a[2] += bflo(ba.y); a[3] += bfhi(ba.y);
-                    b[0] += bflo(bb.x); b[1] += bfhi(bb.x); b[2] += bflo(bb.y); b[3] += bfhi(bb.y);
-                }
-                if (rot) {
-                    const f32x4 c = *reinterpret_cast<const f32x4 *>(g.rope_cos + tpos + jc);
-                    const f32x4 sn = *reinterpret_cast<const f32x4 *>(g.rope_sin + tpos + jc);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float ya = a[e] * c[e] - b[e] * sn[e], yb = b[e] * c[e] + a[e] * sn[e];
-                        a[e] = ya;
-                        b[e] = yb;
-                    }
-                }
-                uint2 oa, ob;
-                oa.x = pack2bf(a[0], a[1]); oa.y = pack2bf(a[2], a[3]);
-                ob.x = pack2bf(b[0], b[1]); ob.y = pack2bf(b[2], b[3]);
-                *reinterpret_cast<uint2 *>(lp + jc) = oa;
-                *reinterpret_cast<uint2 *>(lp + jc + 64) = ob;
             }
+            *reinterpret_cast<uint2 *>(lp + jc) = uint2{pack2bf(a[0], a[1]), pack2bf(a[2], a[3])};
+            *reinterpret_cast<uint2 *>(lp + jc + 64) = uint2{pack2bf(b[0], b[1]), pack2bf(b[2], b[3])};
+        }
     }
-    w4_flush_rows<128>(reinterpret_cast<bf16_t *>(g.C), g.ldc, g.M, m0 + wm * 128, col_w, region, hl * 32 + l32);
+    w4_flush_rows<128>(reinterpret_cast<bf16_t *>(g.C), g.ldc, g.M, m0 + wm * 128, col_w, region, hq * 16 + l16);
 }
 
 // SwiGLU store (g.glu_*): the tile's 256 B rows are gate columns c .. c+63, up columns c .. c+63, gate c+64 ..,
-// up c+64 .. with c = 128 tn, so a wave holds gate (blocks 0, 1) and up (blocks 2, 3) of the same 64 columns.
+// up c+64 .. with c = 128 tn, so a wave holds gate (blocks 0..3) and up (blocks 4..7) of the same 64 columns.
 // Both go through the wave's LDS region; the row-wise second half computes the activation and stores it (and
 // gate | up if asked for) as whole lines.  Rows are guarded; columns are complete (glu_F % 128 == 0).
-__device__ __forceinline__ void w4_store_glu(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int tn, int wm, int wn,
-                                             int l32, int hl, bf16_t *region) {
-    const int lane = hl * 32 + l32;
-    // first half: gate (blocks 0, 1) to columns 0..63 of the wave's LDS region, up (blocks 2, 3) to 64..127
+__device__ __forceinline__ void w4_store_glu(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int tn, int wm, int wn,
+                                             int l16, int hq, bf16_t *region) {
+    const int lane = hq * 16 + l16;
+    // first half: gate (blocks 0..3) to columns 0..63 of the wave's LDS region, up (blocks 4..7) to 64..127
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bf16_t *lp = region + (i * 32 + l32) * W4_EP_PITCH + hl * 4;
+    for (int i = 0; i < 8; ++i) {
+        bf16_t *lp = region + (i * 16 + l16) * W4_EP_PITCH + hq * 4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint2 u;
-                u.x = pack2bf(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-                u.y = pack2bf(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                *reinterpret_cast<uint2 *>(lp + j * 32 + q * 8) = u;
-            }
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<uint2 *>(lp + j * 16) = uint2{pack2bf(acc[i][j][0], acc[i][j][1]), pack2bf(acc[i][j][2], acc[i][j][3])};
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     // second half, row-wise: a lane takes 8 consecutive columns of a row, 8 rows per pass
@@ -318,9 +254,9 @@ __device__ __forceinline__ void w4_store_glu(const GemmArgs &g, const f32x16 (&a
 // SwiGLU backward store (g.glu_bwd_*): the accumulators are ds; they go to the wave's LDS region as bf16, and the
 // row-wise second half reads 8 consecutive ds per lane, loads the forward's gate and up of the same elements
 // (16 bytes each) and stores dgate and dup, all as whole lines.  Rows >= M and column chunks >= N are skipped.
-__device__ __forceinline__ void w4_store_glu_bwd(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int wm,
-                                                 int wn, int l32, int hl, bf16_t *region) {
-    const int lane = hl * 32 + l32;
+__device__ __forceinline__ void w4_store_glu_bwd(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm,
+                                                 int wn, int l16, int hq, bf16_t *region) {
+    const int lane = hq * 16 + l16;
     const int lr = lane >> 4, lc = (lane & 15) * 8;
     const int col = n0 + wn * 128 + lc;
     const bool col_ok = col < g.N;
@@ -341,17 +277,11 @@ __device__ __forceinline__ void w4_store_glu_bwd(const GemmArgs &g, const f32x16
         uq[it] = *reinterpret_cast<const uint4 *>(gu + row * g.ld_glu_bwd + g.N);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bf16_t *lp = region + (i * 32 + l32) * W4_EP_PITCH + hl * 4;
+    for (int i = 0; i < 8; ++i) {
+        bf16_t *lp = region + (i * 16 + l16) * W4_EP_PITCH + hq * 4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint2 u;
-                u.x = pack2bf(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-                u.y = pack2bf(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                *reinterpret_cast<uint2 *>(lp + j * 32 + q * 8) = u;
-            }
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<uint2 *>(lp + j * 16) = uint2{pack2bf(acc[i][j][0], acc[i][j][1]), pack2bf(acc[i][j][2], acc[i][j][3])};
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     bf16_t *C = reinterpret_cast<bf16_t *>(g.C);
@@ -389,179 +319,55 @@ enum { EPI_GENERAL = 0, EPI_FULL_BF16 = 1, EPI_FULL_F32 = 2, EPI_ROPE = 3, EPI_G
        EPI_FULL_BF16_BIAS = 7, EPI_ROPE_BIAS = 8 };
 // region: the wave's private LDS staging block (128 rows of W4_EP_PITCH bf16), free once the k-loop's last barrier has passed
 template <int EPI>
-__device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x16 (&acc)[4][4], int m0, int n0, int tn, int wm, int wn,
-                                            int l32, int hl, bf16_t *region) {
-    if constexpr (EPI == EPI_GLU) w4_store_glu(g, acc, m0, tn, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_ROPE) w4_store_rope<false>(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_ROPE_BIAS) w4_store_rope<true>(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_GLU_BWD) w4_store_glu_bwd(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_FULL_BF16) w4_store_full_bf16<false, false>(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_FULL_BF16_RES) w4_store_full_bf16<false, true>(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_FULL_BF16_BIAS) w4_store_full_bf16<true, false>(g, acc, m0, n0, wm, wn, l32, hl, region);
-    else if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l32, hl);
-    else w4_store(g, acc, m0, n0, wm, wn, l32, hl);
+__device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int tn, int wm, int wn,
+                                            int l16, int hq, bf16_t *region) {
+    if constexpr (EPI == EPI_GLU) w4_store_glu(g, acc, m0, tn, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_ROPE) w4_store_rope<false>(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_ROPE_BIAS) w4_store_rope<true>(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_GLU_BWD) w4_store_glu_bwd(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_FULL_BF16) w4_store_full_bf16<false, false>(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_FULL_BF16_RES) w4_store_full_bf16<false, true>(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_FULL_BF16_BIAS) w4_store_full_bf16<true, false>(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l16, hq);
+    else w4_store(g, acc, m0, n0, wm, wn, l16, hq);
 }
-template <int EPI>
-__global__ __launch_bounds__(W4_NT) void gemm_nt_w4_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    constexpr int BM = W4_BM, BN = W4_BN;
-    const int nb = tiles_m * tiles_n;
-    int pid = blockIdx.x;
-    {
-        const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
-        pid = x * q + (x < r ? x : r) + pid / kXcd;
-    }
-    const int group = kGroupM * tiles_n;
-    const int first_m = (pid / group) * kGroupM;
-    const int gsz = min(tiles_m - first_m, kGroupM);
-    const int tm = first_m + (pid % group) % gsz;
-    const int tn = (pid % group) / gsz;
-    const int m0 = tm * BM, n0 = tn * BN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, hl = lane >> 5;
-
-    // loader: thread owns 16-byte chunk (tid & 7) of rows (tid >> 3) + 32 j, j < 8, of A and of B
-    const int lrow = tid >> 3, lkc = (tid & 7) * 8;
-    const bf16_t *abase = g.A + (int64_t)m0 * g.lda;
-    constexpr bool glu = EPI == EPI_GLU;
-    const bf16_t *bbase = g.B + (glu ? 0 : (int64_t)n0 * g.ldb);
-    uint32_t off[16];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        off[j] = (uint32_t)(min(lrow + 32 * j, g.M - 1 - m0) * (int)g.lda + lkc);
-        // SwiGLU pairing: tile rows in blocks of 64 = gate c.., up c.., gate c+64.., up c+64.. (c = 128 tn)
-        const int brow = glu ? ((j >> 1) & 1) * g.glu_F + tn * 128 + (j >> 2) * 64 + lrow + 32 * (j & 1)
-                             : min(lrow + 32 * j, g.N - 1 - n0);
-        off[8 + j] = (uint32_t)(brow * (int)g.ldb + lkc);
-    }
-    u32x4 st[16];
-    bf16x8 fr[2][8];   // [set][A block 0..3 | B block 0..3]
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    char *const lds = reinterpret_cast<char *>(smem);
-    const uint32_t wr_off = (uint32_t)((lrow * LDT + lkc) * 2);
-    const uint32_t rda_off = (uint32_t)(((wm * 128 + l32) * LDT + hl * 8) * 2);
-    const uint32_t rdb_off = (uint32_t)(W4_A_BYTES + ((wn * 128 + l32) * LDT + hl * 8) * 2);
-    uint32_t cur = 0;   // byte offset of the LDS buffer holding the current step
-
-#define W4_LOAD(J, K0) st[J] = *reinterpret_cast<const u32x4 *>(((J) < 8 ? abase : bbase) + (K0) + off[J]);
-#define W4_WRITE(J, BUFOFF)                                                                             \
-    *reinterpret_cast<u32x4 *>(lds + (BUFOFF) + wr_off + ((J) < 8 ? 0 : W4_A_BYTES) + ((J) & 7) * 32 * LDT * 2) = st[J];
-#define W4_READ(SET, BUFOFF, KS)                                                                        \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
-            fr[SET][i] = *reinterpret_cast<const bf16x8 *>(lds + (BUFOFF) + rda_off + i * 32 * LDT * 2 + (KS) * 32); \
-            fr[SET][4 + i] = *reinterpret_cast<const bf16x8 *>(lds + (BUFOFF) + rdb_off + i * 32 * LDT * 2 + (KS) * 32); \
-        }                                                                                               \
-    }
-#define W4_MMA(SET)                                                                                     \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                   \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[SET][4 + j], fr[SET][i], acc[i][j], 0, 0, 0); \
-    }
-    // phase P of step kt: chunks [C0, C1) of the staged registers move on
-#define W4_PHASE(P, SET, C0, C1, COMMIT, LOAD)                                                          \
-    {                                                                                                   \
-        W4_READ((SET) ^ 1, cur, (P) + 1);                                                               \
-        _Pragma("unroll") for (int c = C0; c < C1; ++c) {                                               \
-            if (COMMIT) W4_WRITE(c, nxt);                                                               \
-            if (LOAD) W4_LOAD(c, (kt + 2) * BK);                                                        \
-        }                                                                                               \
-        W4_MMA(SET);                                                                                    \
-        _Pragma("unroll") for (int c = 0; c < 8; ++c) {                                                 \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-        }                                                                                               \
-        _Pragma("unroll") for (int c = C0; c < C1; ++c) {                                               \
-            if (COMMIT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                              \
-            if (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-        }                                                                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 8 - ((C1) - (C0)), 0);                              \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-    }
-#define W4_MMA_ROWS(SET, I0, I1)                                                                        \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = I0; i < I1; ++i)                                                 \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[SET][4 + j], fr[SET][i], acc[i][j], 0, 0, 0); \
-    }
-#define W4_STEP(COMMIT, LOAD)                                                                           \
-    {                                                                                                   \
-        const uint32_t nxt = W4_STAGE_BYTES - cur;                                                      \
-        W4_PHASE(0, 0, 0, 4, COMMIT, LOAD);                                                             \
-        W4_PHASE(1, 1, 4, 8, COMMIT, LOAD);                                                             \
-        W4_PHASE(2, 0, 8, 12, COMMIT, LOAD);                                                            \
-        _Pragma("unroll") for (int c = 12; c < 16; ++c) {                                               \
-            if (COMMIT) W4_WRITE(c, nxt);                                                               \
-            if (LOAD) W4_LOAD(c, (kt + 2) * BK);                                                        \
-        }                                                                                               \
-        W4_MMA_ROWS(1, 0, 3);                                                                           \
-        _Pragma("unroll") for (int c = 12; c < 16; ++c) {                                               \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-            if (COMMIT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                              \
-            if (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                \
-        }                                                                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);                                              \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-        lds_barrier();                                                                                  \
-        if (COMMIT) W4_READ(0, nxt, 0);                                                                 \
-        W4_MMA_ROWS(1, 3, 4);                                                                           \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-        cur = nxt;                                                                                      \
-    }
-
-    const int nk = g.K / BK;
-    // prologue: step 0 into LDS buffer 0, step 1 into the staged registers
-#pragma unroll
-    for (int c = 0; c < 16; ++c) W4_LOAD(c, 0);
-#pragma unroll
-    for (int c = 0; c < 16; ++c) W4_WRITE(c, 0);
-    if (nk > 1) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) W4_LOAD(c, BK);
-    }
-    lds_barrier();
-    W4_READ(0, 0, 0);
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) W4_STEP(true, true);
-    if (kt + 1 < nk) {
-        W4_STEP(true, false);
-        ++kt;
-    }
-    W4_STEP(false, false);
-#undef W4_LOAD
-#undef W4_WRITE
-#undef W4_READ
-#undef W4_MMA
-#undef W4_MMA_ROWS
-#undef W4_PHASE
-#undef W4_STEP
-
-    w4_epilogue<EPI>(g, acc, m0, n0, tn, wm, wn, l32, hl, w4_ep_region(smem, wm * 2 + wn));
-}
-
 // ---------------------------------------------------------------------------------------------
-// Load-to-LDS variant with full k-steps of 64: a wave-load fills 8 rows of 128 bytes (whole cache lines per request),
-// two LDS slots of 64 KB (A 256 x 64 | B 256 x 64 bf16), chunk c of row r stored at position c ^ ((r >> 1) & 7).
-//   step t:  k-slice 0: MFMAs  ||  LDS reads of slice 1  ||  the B-row loads of step t + 1
-//            k-slices 1, 2: MFMAs, the LDS reads one slice ahead
+// The main loop.  Operands go from memory straight into LDS (no staging registers, no LDS store instructions): full
+// k-steps of 64, a wave-load fills 8 rows of 128 bytes (whole cache lines per request), two slots of 64 KB
+// (A 256 x 64 | B 256 x 64 bf16), chunk c of row r stored at position c ^ ((r >> 1) & 7).
+//   step t:  k-slice 0 (32 indices): 64 MFMAs  ||  the 16 LDS reads of slice 1
 //            wait for the loads of step t + 1 (all that are in flight) and for the wave's last reads of the slot; barrier
-//            k-slice 3: MFMAs  ||  LDS reads of slice 0 of step t + 1  ||  the A-row loads of step t + 2 into the slot just freed
-// A load has two to four k-slices (1000-2000 MFMA clocks) to land; loads go out one per two MFMAs (64 clocks): the path
-// into LDS takes a wave's 1 KB every 16 clocks and four waves share it.  No staging registers, no LDS store
-// instructions, half the LDS instruction traffic of the register-staged kernel; measured 5-8 % faster at the 7B shapes.
+//            k-slice 1: 64 MFMAs  ||  the 16 LDS reads of slice 0 of step t + 1  ||  the 16 loads of step t + 2 into the
+//            slot just freed, one per four MFMAs (64 clocks: the path into LDS takes a wave's 1 KB every 16 clocks and
+//            four waves share it), which leaves every load at least the 1024 clocks of the next slice 0 to land
+// What bounds it is power: the chip clocks down to what its matrix cores, registers and LDS draw.  The 16x16x32 MFMA
+// moves a fifth fewer register bytes per multiplication than 32x32x16 (each accumulator is read and written once per 32
+// reduction indices instead of 16), and the 2 x 2 zigzag below changes one operand per MFMA: 8192^3 759 us -> 689 (1450 ->
+// 1597 TFLOP/s), 4096^3 101 -> 91, 16384 x 11008 x 4096 1085 -> 1024.  The accumulators are updated in place by assembly (mfma16_acc):
+// given the builtin, the register allocator renames them, 500 moves per 256 MFMAs (8192^3: 916 us).
 constexpr int WE_HALF = 256 * 64 * 2, WE_SLOT = 2 * WE_HALF, WE_ARRAY = 2 * 128 * W4_EP_PITCH * 2;
 static_assert(WE_ARRAY >= WE_SLOT, "a slot must fit into two staging blocks");
+// From 128 k-steps on (operand rows of 16 KB and more, whose lines at one k crowd onto few memory channels) a group of four
+// tile rows starts its walk over K at an eighth of K of its own, so that the XCDs, which work on different groups, read
+// different columns: 16384 x 4096 x 11008 1095 -> 1042 us, x 22016 2303 -> 2116; K = 8192, 13824 and 32000 +- 1 %.
+// The start depends on the tile row alone, so every store variant sums in the same order.
+constexpr int kStaggerSteps = 128;
+__device__ __forceinline__ int walk_start(int tm, int nk) {
+    if (nk < kStaggerSteps) return 0;
+    int h = tm >> 2;
+    h ^= h >> 1; h ^= h >> 2; h ^= h >> 4;   // any eight groups in arithmetic progression by a power of two: distinct low bits
+    return (h & 7) * (nk >> 3);
+}
+
+// MFMAs 4 U .. 4 U + 3 of a slice's 64: the four blocks (2 x 2) number U, walked in zigzag
+template <int U>
+__device__ __forceinline__ void w4_mfma_group(f32x4 (&acc)[8][8], const bf16x8 (&fr)[16]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = (U >> 2) * 2 + (e >> 1), j0 = (U & 3) * 2 + ((e & 1) ^ (e >> 1)), j = (U >> 2) & 1 ? 7 - j0 : j0;
+        mfma16_acc(acc[i][j], fr[8 + j], fr[i]);
+    }
+}
 
 template <int EPI>
 __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tiles_m, int tiles_n) {
@@ -585,7 +391,7 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, hl = lane >> 5;
+    const int l16 = lane & 15, hq = lane >> 4;
 
     // loader: wave w fills rows 64 w .. 64 w + 63 of the A half and of the B half of a slot, 8 rows per load;
     // lane l delivers to chunk position l & 7 of row l >> 3 and fetches the chunk that belongs there
@@ -603,22 +409,20 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
         off[8 + j] = (uint32_t)(brow * (int)g.ldb + chunk * 8) * 2u;
     }
     const uint32_t fill_off = (uint32_t)(wave * 64 * 128);
-    // fragment reads: k-chunk 2 ks + hl of row l32 + 32 i sits at chunk position (2 ks + hl) ^ ((l32 >> 1) & 7)
-    uint32_t rda[4], rdb[4];
+    // fragment reads: k-chunk 4 ks + hq of row l16 + 16 i sits at chunk position (4 ks + hq) ^ ((l16 >> 1) & 7)
+    uint32_t rda[2], rdb[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        const uint32_t pos = (uint32_t)(((2 * ks + hl) ^ ((l32 >> 1) & 7)) * 16);
-        rda[ks] = (uint32_t)((wm * 128 + l32) * 128) + pos;
-        rdb[ks] = (uint32_t)(WE_HALF + (wn * 128 + l32) * 128) + pos;
+    for (int ks = 0; ks < 2; ++ks) {
+        const uint32_t pos = (uint32_t)(((4 * ks + hq) ^ ((l16 >> 1) & 7)) * 16);
+        rda[ks] = (uint32_t)((wm * 128 + l16) * 128) + pos;
+        rdb[ks] = (uint32_t)(WE_HALF + (wn * 128 + l16) * 128) + pos;
     }
-    bf16x8 fr[2][8];   // [set][A block 0..3 | B block 0..3]
-    f32x16 acc[4][4];
+    bf16x8 fr[2][16];   // [set][A block 0..7 | B block 0..7]
+    f32x4 acc[8][8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // One load-to-LDS, written out as assembly: the compiler orders every later LDS read after all earlier builtin
     // load-to-LDS instructions it cannot tell apart (a full vmcnt(0) in front of reads of the other slot), which undoes
@@ -631,88 +435,51 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
                  : "v"(off[J]), "s"(((J) < 8 ? abase : bbase) + (T) * 64),                              \
                    "s"((uint32_t)(uintptr_t)(lptr)(SLOT) + ((J) < 8 ? 0u : (uint32_t)WE_HALF) + fill_off + ((J) & 7) * 1024u) \
                  : "memory")
-#define WE_FILL(SLOT, T)                                                                                \
-    {                                                                                                   \
-        WE_LOAD1(SLOT, 0, T); WE_LOAD1(SLOT, 1, T); WE_LOAD1(SLOT, 2, T); WE_LOAD1(SLOT, 3, T);         \
-        WE_LOAD1(SLOT, 4, T); WE_LOAD1(SLOT, 5, T); WE_LOAD1(SLOT, 6, T); WE_LOAD1(SLOT, 7, T);         \
-        WE_LOAD1(SLOT, 8, T); WE_LOAD1(SLOT, 9, T); WE_LOAD1(SLOT, 10, T); WE_LOAD1(SLOT, 11, T);       \
-        WE_LOAD1(SLOT, 12, T); WE_LOAD1(SLOT, 13, T); WE_LOAD1(SLOT, 14, T); WE_LOAD1(SLOT, 15, T);     \
-    }
 #define WE_READ1(SET, SLOT, KS, IDX)                                                                    \
-    fr[SET][IDX] = *reinterpret_cast<const bf16x8 *>((SLOT) + ((IDX) < 4 ? rda[KS] : rdb[KS]) + ((IDX) & 3) * 4096)
-#define WE_READ(SET, SLOT, KS)                                                                          \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
-            WE_READ1(SET, SLOT, KS, i);                                                                 \
-            WE_READ1(SET, SLOT, KS, 4 + i);                                                             \
-        }                                                                                               \
-    }
-#define WE_MMA1(SET, I, J) acc[I][J] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[SET][4 + (J)], fr[SET][I], acc[I][J], 0, 0, 0)
-#define WE_MMA(SET)                                                                                     \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                   \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) WE_MMA1(SET, i, j);                           \
-    }
-    // 16 MFMAs of SET with the 8 fragment reads of (RSET, SLOT, KS) one per MFMA in front
-#define WE_SLICE(SET, RSET, SLOT, KS)                                                                   \
-    {                                                                                                   \
-        WE_READ(RSET, SLOT, KS);                                                                        \
-        WE_MMA(SET);                                                                                    \
-        _Pragma("unroll") for (int c = 0; c < 8; ++c) {                                                 \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-        }                                                                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);                                              \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-    }
+    fr[SET][IDX] = *reinterpret_cast<const bf16x8 *>((SLOT) + ((IDX) < 8 ? rda[KS] : rdb[KS]) + ((IDX) & 7) * 2048)
 #define WE_WAIT(N) asm volatile("s_waitcnt vmcnt(" #N ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
-    // two MFMAs of slice SET (numbers 2 U and 2 U + 1) with one fragment read of (RSET, RSLOT, KS) and, if LD, one load
-    // (J of step TL into LSLOT) in front; pinned in this order.  The loads are spaced two MFMAs (64 clocks) apart: the
-    // path into LDS takes a wave's 1 KB load every 16 clocks and is shared by four waves.
-#define WE_PAIR(SET, RSET, RSLOT, KS, U, LSLOT, J, TL)                                                  \
+    // four MFMAs of slice SET with one fragment read of (RSET, RSLOT, KS) and, if LD, load U of step TL into LSLOT in front;
+    // pinned in this order.  The B fragments are read first: the next slice's first four MFMAs need B 0, 1 and A 0, 1.
+#define WE_GROUP(SET, RSET, RSLOT, KS, U, LD, LSLOT, TL)                                                \
     {                                                                                                   \
-        if ((J) >= 0) WE_LOAD1(LSLOT, ((J) < 0 ? 0 : (J)), TL);                                         \
-        WE_READ1(RSET, RSLOT, KS, ((U) >> 1) + ((U) & 1) * 4);                                          \
-        WE_MMA1(SET, (U) >> 1, ((U) & 1) * 2);                                                          \
-        WE_MMA1(SET, (U) >> 1, ((U) & 1) * 2 + 1);                                                      \
+        if (LD) WE_LOAD1(LSLOT, U, TL);                                                                 \
+        WE_READ1(RSET, RSLOT, KS, ((U) < 8 ? 8 + (U) : (U) - 8));                                       \
+        w4_mfma_group<U>(acc, fr[SET]);                                                                 \
         __builtin_amdgcn_sched_barrier(0);                                                              \
     }
-    // a slice whose MFMA pairs 0..7 carry the loads J0..J7 (of step TL into LSLOT; -1 = none)
-#define WE_SLICE_LD(SET, RSET, RSLOT, KS, LSLOT, TL, J0, J1, J2, J3, J4, J5, J6, J7)                    \
+#define WE_SLICE(SET, RSET, RSLOT, KS, LD, LSLOT, TL)                                                   \
     {                                                                                                   \
-        WE_PAIR(SET, RSET, RSLOT, KS, 0, LSLOT, J0, TL); WE_PAIR(SET, RSET, RSLOT, KS, 1, LSLOT, J1, TL); \
-        WE_PAIR(SET, RSET, RSLOT, KS, 2, LSLOT, J2, TL); WE_PAIR(SET, RSET, RSLOT, KS, 3, LSLOT, J3, TL); \
-        WE_PAIR(SET, RSET, RSLOT, KS, 4, LSLOT, J4, TL); WE_PAIR(SET, RSET, RSLOT, KS, 5, LSLOT, J5, TL); \
-        WE_PAIR(SET, RSET, RSLOT, KS, 6, LSLOT, J6, TL); WE_PAIR(SET, RSET, RSLOT, KS, 7, LSLOT, J7, TL); \
+        WE_GROUP(SET, RSET, RSLOT, KS, 0, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 1, LD, LSLOT, TL);   \
+        WE_GROUP(SET, RSET, RSLOT, KS, 2, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 3, LD, LSLOT, TL);   \
+        WE_GROUP(SET, RSET, RSLOT, KS, 4, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 5, LD, LSLOT, TL);   \
+        WE_GROUP(SET, RSET, RSLOT, KS, 6, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 7, LD, LSLOT, TL);   \
+        WE_GROUP(SET, RSET, RSLOT, KS, 8, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 9, LD, LSLOT, TL);   \
+        WE_GROUP(SET, RSET, RSLOT, KS, 10, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 11, LD, LSLOT, TL); \
+        WE_GROUP(SET, RSET, RSLOT, KS, 12, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 13, LD, LSLOT, TL); \
+        WE_GROUP(SET, RSET, RSLOT, KS, 14, LD, LSLOT, TL); WE_GROUP(SET, RSET, RSLOT, KS, 15, LD, LSLOT, TL); \
     }
-    // step T out of CUR.  The A rows of step T + 1 were requested into NXT during the last slice of step T - 1; its B
-    // rows follow during slice 0 here; the A rows of step T + 2 go into CUR during the last slice.  Past the end of K
-    // the last step is requested again (kl clamps it): the same instruction stream for every step, no branches around
-    // the MFMAs; the extra data lands in a free slot and is never read.
-    // step T out of CUR.  Loads 0..7 (the A rows) of step T + 2 go into CUR during the last slice, right after the barrier
-    // that frees it; loads 8..15 (the B rows) follow during slice 0 of the next step.  Later than that they miss the
-    // next barrier (measured: 5 + 5 + 6 over three slices is 3 % slower), all 16 in one slice back up behind the load
-    // path (5 % slower).
+    // step T out of CUR.  Past the end of K the last step is requested again (clamped): the same instruction stream for
+    // every step, no branches around the MFMAs; the extra data lands in a free slot and is never read.
 #define WE_STEP(CUR, NXT, T)                                                                            \
     {                                                                                                   \
-        const int t1_ = min((T) + 1, nk - 1), t2_ = min((T) + 2, nk - 1);                               \
-        WE_SLICE_LD(0, 1, CUR, 1, NXT, t1_, 8, 9, 10, 11, 12, 13, 14, 15);                              \
-        WE_SLICE(1, 0, CUR, 2);                                                                         \
-        WE_SLICE(0, 1, CUR, 3);                                                                         \
+        const int t2_ = at(min((T) + 2, nk - 1));                                                       \
+        WE_SLICE(0, 1, CUR, 1, false, CUR, 0);                                                          \
         WE_WAIT(0);                                                                                     \
-        WE_SLICE_LD(1, 0, NXT, 0, CUR, t2_, 0, 1, 2, 3, 4, 5, 6, 7);                                    \
+        WE_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
     }
 
-    const int nk = g.K / BK;
-    WE_FILL(sl0, 0);
+    const int nk = g.K / BK, start = walk_start(tm, nk);
+    const auto at = [&](int t) { return t + start - (t + start >= nk ? nk : 0); };   // k-step walked as number t
     {
-        // the A rows of step 1, which the schedule would have requested during "step -1"
-        const int t1_ = min(1, nk - 1);
-        WE_LOAD1(sl1, 0, t1_); WE_LOAD1(sl1, 1, t1_); WE_LOAD1(sl1, 2, t1_); WE_LOAD1(sl1, 3, t1_);
-        WE_LOAD1(sl1, 4, t1_); WE_LOAD1(sl1, 5, t1_); WE_LOAD1(sl1, 6, t1_); WE_LOAD1(sl1, 7, t1_);
+        const int t0_ = at(0), t1_ = at(min(1, nk - 1));
+#pragma unroll
+        for (int j = 0; j < 16; ++j) WE_LOAD1(sl0, j, t0_);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) WE_LOAD1(sl1, j, t1_);
     }
-    WE_WAIT(8);
-    WE_READ(0, sl0, 0);
+    WE_WAIT(16);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) WE_READ1(0, sl0, 0, u);
     int kt = 0;
     for (; kt + 2 <= nk; kt += 2) {
         WE_STEP(sl0, sl1, kt);
@@ -721,19 +488,15 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
     if (kt < nk) WE_STEP(sl0, sl1, kt);
     WE_WAIT(0);   // the loads requested past the end have landed before the store staging reuses the arrays
 #undef WE_LOAD1
-#undef WE_FILL
 #undef WE_READ1
-#undef WE_READ
-#undef WE_MMA1
-#undef WE_MMA
-#undef WE_SLICE
 #undef WE_WAIT
-#undef WE_PAIR
-#undef WE_SLICE_LD
+#undef WE_GROUP
+#undef WE_SLICE
 #undef WE_STEP
+    mfma16_settle(acc);
     // every wave has passed the last step's barrier, i.e. has read its last fragments: the arrays are free
     bf16_t *region = reinterpret_cast<bf16_t *>((wave < 2 ? sl0 : sl1) + (wave & 1) * (128 * W4_EP_PITCH * 2));
-    w4_epilogue<EPI>(g, acc, m0, n0, tn, wm, wn, l32, hl, region);
+    w4_epilogue<EPI>(g, acc, m0, n0, tn, wm, wn, l16, hq, region);
 }
 
 // MT_GROUP_M (diagnostics): forces the tile-row group of the large-grid kernels
@@ -754,35 +517,6 @@ hipError_t launch_w4e_epi(const GemmArgs &g0, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int EPI>
-hipError_t launch_w4_epi(const GemmArgs &g, hipStream_t s) {
-    constexpr size_t lds = (size_t)2 * W4_STAGE_BYTES;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_w4_kernel<EPI>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    // with the SwiGLU pairing a tile covers 128 gate and the matching 128 up columns
-    const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = EPI == EPI_GLU ? g.glu_F / 128 : (g.N + W4_BN - 1) / W4_BN;
-    hipLaunchKernelGGL(gemm_nt_w4_kernel<EPI>, dim3((unsigned)(tiles_m * tiles_n)), dim3(W4_NT), lds, s, g, tiles_m, tiles_n);
-    return hipGetLastError();
-}
-
-hipError_t launch_w4(const GemmArgs &g, hipStream_t s) {
-    if (g.glu_F > 0) return launch_w4_epi<EPI_GLU>(g, s);
-    if (g.rope_cos) return g.bias ? launch_w4_epi<EPI_ROPE_BIAS>(g, s) : launch_w4_epi<EPI_ROPE>(g, s);
-    if (g.glu_bwd_gu) return launch_w4_epi<EPI_GLU_BWD>(g, s);
-    // every column tile complete and every access of the store aligned: the vector stores (rows are guarded)
-    const bool full = g.N % W4_BN == 0 && !(g.ldc & 7) && !((uintptr_t)g.C & 15) &&
-                      (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) && !((uintptr_t)g.bias & 7);
-    if (!full || (g.bias && g.R)) return launch_w4_epi<EPI_GENERAL>(g, s);
-    if (g.out_fp32) return launch_w4_epi<EPI_FULL_F32>(g, s);
-    if (g.R) return launch_w4_epi<EPI_FULL_BF16_RES>(g, s);
-    return g.bias ? launch_w4_epi<EPI_FULL_BF16_BIAS>(g, s) : launch_w4_epi<EPI_FULL_BF16>(g, s);
-}
-
 hipError_t launch_w4e(const GemmArgs &g, hipStream_t s) {
     if (g.glu_F > 0) return launch_w4e_epi<EPI_GLU>(g, s);
     if (g.rope_cos) return g.bias ? launch_w4e_epi<EPI_ROPE_BIAS>(g, s) : launch_w4e_epi<EPI_ROPE>(g, s);
@@ -798,165 +532,14 @@ hipError_t launch_w4e(const GemmArgs &g, hipStream_t s) {
 
 // ---------------------------------------------------------------------------------------------
 // Weight-gradient form: C[M,N] = sum_k At[k][m] Bt[k][n] with both operands token-major ([K, M] and [K, N]),
-// i.e. dW = dY^T X straight from the activations as the other kernels produce them.  Same tile, waves and
-// in-wave pipeline as gemm_nt_w4_kernel; the LDS tiles are [64 k][256 m] (pitch 296 elements: rows 20 banks
-// apart, the spacing that keeps the transposing reads nearly conflict-free) and the MFMA operands are read
-// with ds_read_b64_tr_b16 (read_tr_frag), which hands a lane eight reduction indices of one output row: two
-// reads per fragment instead of one.  fp32 output only.
-constexpr int TN_LDT = 256 + 40;
-constexpr int TN_TILE_BYTES = BK * TN_LDT * 2, TN_STAGE_BYTES = 2 * TN_TILE_BYTES;
-
-template <int EPI>
-__global__ __launch_bounds__(W4_NT) void gemm_tn_w4_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    constexpr int BM = W4_BM, BN = W4_BN;
-    const int n_tiles = tiles_m * tiles_n, nb = n_tiles * g.split_k;
-    int pid = blockIdx.x;
-    {
-        const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
-        pid = x * q + (x < r ? x : r) + pid / kXcd;
-    }
-    // split reduction: units are ordered chunk-major, so the workgroups running together still form tile patches
-    // that walk the same K range; chunk 0 owns C, the others a slice of the workspace
-    const int chunk = pid / n_tiles;
-    pid -= chunk * n_tiles;
-    const int nk_all = g.K / BK;
-    const int kb = (int)((int64_t)chunk * nk_all / g.split_k), ke = (int)((int64_t)(chunk + 1) * nk_all / g.split_k);
-    if (chunk > 0) {
-        g.C = g.split_ws + (int64_t)(chunk - 1) * g.M * g.N;
-        g.ldc = g.N;
-        g.accumulate = 0;
-    }
-    const int group = kGroupM * tiles_n;
-    const int first_m = (pid / group) * kGroupM;
-    const int gsz = min(tiles_m - first_m, kGroupM);
-    const int tm = first_m + (pid % group) % gsz;
-    const int tn = (pid % group) / gsz;
-    const int m0 = tm * BM, n0 = tn * BN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, hl = lane >> 5;
-    const int tr_off = tr_lane_offset(lane, TN_LDT);
-
-    // loader: thread owns the 16-byte chunk (tid & 31) (8 consecutive m or n) of the k rows (tid >> 5) + 8 j.
-    // Chunks past the matrix edge re-read the last chunk; they only feed outputs that are never stored.
-    const int lk = tid >> 5, lc = (tid & 31) * 8;
-    const bf16_t *abase = g.A + min(m0 + lc, g.M - 8) + (int64_t)kb * BK * g.lda;
-    const bf16_t *bbase = g.B + min(n0 + lc, g.N - 8) + (int64_t)kb * BK * g.ldb;
-    u32x4 st[16];
-    bf16x8 fr[2][8];
-    f32x16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    char *const lds = reinterpret_cast<char *>(smem);
-    const uint32_t wr_off = (uint32_t)((lk * TN_LDT + lc) * 2);
-    uint32_t cur = 0;
-
-#define TN_LOAD(J, K0)                                                                                  \
-    st[J] = *reinterpret_cast<const u32x4 *>(                                                           \
-        ((J) < 8 ? abase + (int64_t)((K0) + lk + 8 * ((J) & 7)) * g.lda : bbase + (int64_t)((K0) + lk + 8 * ((J) & 7)) * g.ldb));
-#define TN_WRITE(J, BUFOFF)                                                                             \
-    *reinterpret_cast<u32x4 *>(lds + (BUFOFF) + wr_off + ((J) < 8 ? 0 : TN_TILE_BYTES) + ((J) & 7) * 8 * TN_LDT * 2) = st[J];
-#define TN_READ(SET, BUFOFF, KS)                                                                        \
-    {                                                                                                   \
-        const bf16_t *ta_ = reinterpret_cast<const bf16_t *>(lds + (BUFOFF));                           \
-        const bf16_t *tb_ = reinterpret_cast<const bf16_t *>(lds + (BUFOFF) + TN_TILE_BYTES);           \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
-            fr[SET][i] = read_tr_frag(ta_, tr_off, TN_LDT, (KS) * 16, wm * 128 + i * 32);               \
-            fr[SET][4 + i] = read_tr_frag(tb_, tr_off, TN_LDT, (KS) * 16, wn * 128 + i * 32);           \
-        }                                                                                               \
-    }
-#define TN_MMA_ROWS(SET, I0, I1)                                                                        \
-    {                                                                                                   \
-        _Pragma("unroll") for (int i = I0; i < I1; ++i)                                                 \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                               \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[SET][4 + j], fr[SET][i], acc[i][j], 0, 0, 0); \
-    }
-#define TN_PHASE(P, SET, C0, C1, COMMIT, LOAD)                                                          \
-    {                                                                                                   \
-        TN_READ((SET) ^ 1, cur, (P) + 1);                                                               \
-        _Pragma("unroll") for (int c = C0; c < C1; ++c) {                                               \
-            if (COMMIT) TN_WRITE(c, nxt);                                                               \
-            if (LOAD) TN_LOAD(c, (kt + 2) * BK);                                                        \
-        }                                                                                               \
-        TN_MMA_ROWS(SET, 0, 4);                                                                         \
-        _Pragma("unroll") for (int c = 0; c < 8; ++c) {                                                 \
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                          \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-        }                                                                                               \
-        _Pragma("unroll") for (int c = C0; c < C1; ++c) {                                               \
-            if (COMMIT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                              \
-            if (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-        }                                                                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 8 - ((C1) - (C0)), 0);                              \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-    }
-#define TN_STEP(COMMIT, LOAD)                                                                           \
-    {                                                                                                   \
-        const uint32_t nxt = TN_STAGE_BYTES - cur;                                                      \
-        TN_PHASE(0, 0, 0, 4, COMMIT, LOAD);                                                             \
-        TN_PHASE(1, 1, 4, 8, COMMIT, LOAD);                                                             \
-        TN_PHASE(2, 0, 8, 12, COMMIT, LOAD);                                                            \
-        _Pragma("unroll") for (int c = 12; c < 16; ++c) {                                               \
-            if (COMMIT) TN_WRITE(c, nxt);                                                               \
-            if (LOAD) TN_LOAD(c, (kt + 2) * BK);                                                        \
-        }                                                                                               \
-        TN_MMA_ROWS(1, 0, 3);                                                                           \
-        _Pragma("unroll") for (int c = 12; c < 16; ++c) {                                               \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                          \
-            if (COMMIT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                              \
-            if (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                \
-        }                                                                                               \
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);                                              \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-        lds_barrier();                                                                                  \
-        if (COMMIT) TN_READ(0, nxt, 0);                                                                 \
-        TN_MMA_ROWS(1, 3, 4);                                                                           \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-        cur = nxt;                                                                                      \
-    }
-
-    const int nk = ke - kb;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) TN_LOAD(c, 0);
-#pragma unroll
-    for (int c = 0; c < 16; ++c) TN_WRITE(c, 0);
-    if (nk > 1) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) TN_LOAD(c, BK);
-    }
-    lds_barrier();
-    TN_READ(0, 0, 0);
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) TN_STEP(true, true);
-    if (kt + 1 < nk) {
-        TN_STEP(true, false);
-        ++kt;
-    }
-    TN_STEP(false, false);
-#undef TN_LOAD
-#undef TN_WRITE
-#undef TN_READ
-#undef TN_MMA_ROWS
-#undef TN_PHASE
-#undef TN_STEP
-    if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l32, hl);
-    else w4_store(g, acc, m0, n0, wm, wn, l32, hl);
-}
-
-// The same product with the loads written straight into LDS, as in gemm_nt_w4e_kernel: two slots of 64 KB
-// (A [64 k][256 m] | B [64 k][256 n] bf16, rows of 512 bytes, unpadded), a wave-load fills two k rows, loads spaced two
-// MFMAs apart, one barrier per k-step.  The transposing reads touch 8 k rows x 64 bytes per instruction; the 64-byte
-// column group cg of k row r is stored at group position cg ^ (r & 7), which puts the four rows that half a wave reads
-// together on disjoint banks (unswizzled they would all sit on the same 16).
+// i.e. dW = dY^T X straight from the activations as the other kernels produce them.  Same tile, waves, loads and
+// schedule as gemm_nt_w4e_kernel; the LDS slots are A [64 k][256 m] | B [64 k][256 n] bf16 (rows of 512 bytes, unpadded), a
+// wave-load fills two k rows, and the MFMA operands are read with ds_read_b64_tr_b16, which hands a lane four reduction
+// indices of one output row: two reads per fragment.  A read instruction touches rows 8 q + 0..3 (and + 4 in the second
+// one), 32 bytes each; the 32-byte column group c of k row r is stored at group position c ^ tn_swz(r), which puts the
+// eight rows that half a wave reads together on disjoint banks.  fp32 output only.
 constexpr int WT_HALF = 64 * 256 * 2, WT_SLOT = 2 * WT_HALF;
+__device__ __forceinline__ int tn_swz(int r) { return ((r & 3) << 1) | ((r >> 3) & 1); }
 
 template <int EPI>
 __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tiles_m, int tiles_n) {
@@ -993,7 +576,7 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, hl = lane >> 5;
+    const int l16 = lane & 15, hq = lane >> 4;
 
     // loader: wave w fills k rows 16 w .. 16 w + 15 of the A half and of the B half of a slot, two rows per load;
     // lane l delivers to the 16-byte position l & 31 of row l >> 5 and fetches the chunk that belongs there.
@@ -1004,32 +587,28 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int r = wave * 16 + j * 2 + (lane >> 5);
-        const int c16 = ((((lane & 31) >> 2) ^ (r & 7)) << 2) | (lane & 3);
+        const int c16 = ((((lane & 31) >> 1) ^ tn_swz(r)) << 1) | (lane & 1);
         off[j] = (uint32_t)(r * (int)g.lda + min(m0 + c16 * 8, g.M - 8)) * 2u;
         off[8 + j] = (uint32_t)(r * (int)g.ldb + min(n0 + c16 * 8, g.N - 8)) * 2u;
     }
     const uint32_t fill_off = (uint32_t)(wave * 16 * 512);
-    // transposing fragment reads (see read_tr_frag): lane (g, i) of a wave supplies k row (g >> 1) * 4 + (i >> 2) of the
-    // slice (and that row + 8), columns (g & 1) * 16 + (i & 3) * 4 .. + 3 of the block's 32; block b of the wave's
-    // quadrant is column group cg = 4 wm + b (A) or 4 wn + b (B), stored at group position cg ^ (row & 7)
-    uint32_t rd[8];
+    // transposing fragment reads: lane (hq, i = l16) supplies k row 8 hq + (i >> 2) of the slice (and that row + 4), columns
+    // (i & 3) * 4 .. + 3 of the block's 16; block b of the wave's quadrant is column group 8 wm + b (A) or 8 wn + b (B)
+    uint32_t rd[16];
     {
-        const int gq = lane >> 4, ii = lane & 15;
-        const int row = (gq >> 1) * 4 + (ii >> 2), inner = (gq & 1) * 16 + (ii & 3) * 4;
+        const int row = hq * 8 + (l16 >> 2), inner = (l16 & 3) * 8;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            rd[b] = (uint32_t)((row * 256 + (((wm * 4 + b) ^ (row & 7)) * 32) + inner) * 2);
-            rd[4 + b] = (uint32_t)(WT_HALF + (row * 256 + (((wn * 4 + b) ^ (row & 7)) * 32) + inner) * 2);
+        for (int b = 0; b < 8; ++b) {
+            rd[b] = (uint32_t)(row * 512 + ((wm * 8 + b) ^ tn_swz(row)) * 32 + inner);
+            rd[8 + b] = (uint32_t)(WT_HALF + row * 512 + ((wn * 8 + b) ^ tn_swz(row)) * 32 + inner);
         }
     }
-    bf16x8 fr[2][8];
-    f32x16 acc[4][4];
+    bf16x8 fr[2][16];
+    f32x4 acc[8][8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // one load-to-LDS as assembly, ordered by hand (see gemm_nt_w4e_kernel); a k-step advances both operands by 64 rows
 #define WT_LOAD1(SLOT, J, T)                                                                            \
@@ -1040,59 +619,50 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
                  : "memory")
 #define WT_READ1(SET, SLOT, KS, IDX)                                                                    \
     {                                                                                                   \
-        const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)((SLOT) + rd[IDX] + (KS) * 8192));        \
-        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)((SLOT) + rd[IDX] + (KS) * 8192 + 4096)); \
+        const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)((SLOT) + rd[IDX] + (KS) * 16384));        \
+        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)((SLOT) + rd[IDX] + (KS) * 16384 + 2048)); \
         typedef __attribute__((ext_vector_type(8))) short s16x8_;                                       \
         const s16x8_ v_ = {lo_[0], lo_[1], lo_[2], lo_[3], hi_[0], hi_[1], hi_[2], hi_[3]};             \
         fr[SET][IDX] = __builtin_bit_cast(bf16x8, v_);                                                  \
     }
-#define WT_READ(SET, SLOT, KS)                                                                          \
-    {                                                                                                   \
-        WT_READ1(SET, SLOT, KS, 0); WT_READ1(SET, SLOT, KS, 4); WT_READ1(SET, SLOT, KS, 1); WT_READ1(SET, SLOT, KS, 5); \
-        WT_READ1(SET, SLOT, KS, 2); WT_READ1(SET, SLOT, KS, 6); WT_READ1(SET, SLOT, KS, 3); WT_READ1(SET, SLOT, KS, 7); \
-    }
-#define WT_MMA1(SET, I, J) acc[I][J] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[SET][4 + (J)], fr[SET][I], acc[I][J], 0, 0, 0)
 #define WT_WAIT(N) asm volatile("s_waitcnt vmcnt(" #N ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
-    // two MFMAs of slice SET with one fragment (two reads) of (RSET, RSLOT, KS) and, if J >= 0, load J of step TL into
-    // LSLOT in front; pinned in this order
-#define WT_PAIR(SET, RSET, RSLOT, KS, U, LSLOT, J, TL)                                                  \
+#define WT_GROUP(SET, RSET, RSLOT, KS, U, LD, LSLOT, TL)                                                \
     {                                                                                                   \
-        if ((J) >= 0) WT_LOAD1(LSLOT, ((J) < 0 ? 0 : (J)), TL);                                         \
-        WT_READ1(RSET, RSLOT, KS, ((U) >> 1) + ((U) & 1) * 4);                                          \
-        WT_MMA1(SET, (U) >> 1, ((U) & 1) * 2);                                                          \
-        WT_MMA1(SET, (U) >> 1, ((U) & 1) * 2 + 1);                                                      \
+        if (LD) WT_LOAD1(LSLOT, U, TL);                                                                 \
+        WT_READ1(RSET, RSLOT, KS, ((U) < 8 ? 8 + (U) : (U) - 8));                                       \
+        w4_mfma_group<U>(acc, fr[SET]);                                                                 \
         __builtin_amdgcn_sched_barrier(0);                                                              \
     }
-#define WT_SLICE(SET, RSET, RSLOT, KS, LSLOT, TL, J0, J1, J2, J3, J4, J5, J6, J7)                       \
+#define WT_SLICE(SET, RSET, RSLOT, KS, LD, LSLOT, TL)                                                   \
     {                                                                                                   \
-        WT_PAIR(SET, RSET, RSLOT, KS, 0, LSLOT, J0, TL); WT_PAIR(SET, RSET, RSLOT, KS, 1, LSLOT, J1, TL); \
-        WT_PAIR(SET, RSET, RSLOT, KS, 2, LSLOT, J2, TL); WT_PAIR(SET, RSET, RSLOT, KS, 3, LSLOT, J3, TL); \
-        WT_PAIR(SET, RSET, RSLOT, KS, 4, LSLOT, J4, TL); WT_PAIR(SET, RSET, RSLOT, KS, 5, LSLOT, J5, TL); \
-        WT_PAIR(SET, RSET, RSLOT, KS, 6, LSLOT, J6, TL); WT_PAIR(SET, RSET, RSLOT, KS, 7, LSLOT, J7, TL); \
+        WT_GROUP(SET, RSET, RSLOT, KS, 0, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 1, LD, LSLOT, TL);   \
+        WT_GROUP(SET, RSET, RSLOT, KS, 2, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 3, LD, LSLOT, TL);   \
+        WT_GROUP(SET, RSET, RSLOT, KS, 4, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 5, LD, LSLOT, TL);   \
+        WT_GROUP(SET, RSET, RSLOT, KS, 6, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 7, LD, LSLOT, TL);   \
+        WT_GROUP(SET, RSET, RSLOT, KS, 8, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 9, LD, LSLOT, TL);   \
+        WT_GROUP(SET, RSET, RSLOT, KS, 10, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 11, LD, LSLOT, TL); \
+        WT_GROUP(SET, RSET, RSLOT, KS, 12, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 13, LD, LSLOT, TL); \
+        WT_GROUP(SET, RSET, RSLOT, KS, 14, LD, LSLOT, TL); WT_GROUP(SET, RSET, RSLOT, KS, 15, LD, LSLOT, TL); \
     }
-    // step T out of CUR: the schedule of gemm_nt_w4e_kernel
 #define WT_STEP(CUR, NXT, T)                                                                            \
     {                                                                                                   \
-        const int t1_ = min((T) + 1, nk - 1), t2_ = min((T) + 2, nk - 1);                               \
-        WT_SLICE(0, 1, CUR, 1, NXT, t1_, 8, 9, 10, 11, 12, 13, 14, 15);                                 \
-        WT_SLICE(1, 0, CUR, 2, NXT, t1_, -1, -1, -1, -1, -1, -1, -1, -1);                               \
-        WT_SLICE(0, 1, CUR, 3, NXT, t1_, -1, -1, -1, -1, -1, -1, -1, -1);                               \
+        const int t2_ = min((T) + 2, nk - 1);                                                           \
+        WT_SLICE(0, 1, CUR, 1, false, CUR, 0);                                                          \
         WT_WAIT(0);                                                                                     \
-        WT_SLICE(1, 0, NXT, 0, CUR, t2_, 0, 1, 2, 3, 4, 5, 6, 7);                                       \
+        WT_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
     }
 
     const int nk = ke - kb;
     {
-        WT_LOAD1(sl0, 0, 0); WT_LOAD1(sl0, 1, 0); WT_LOAD1(sl0, 2, 0); WT_LOAD1(sl0, 3, 0);
-        WT_LOAD1(sl0, 4, 0); WT_LOAD1(sl0, 5, 0); WT_LOAD1(sl0, 6, 0); WT_LOAD1(sl0, 7, 0);
-        WT_LOAD1(sl0, 8, 0); WT_LOAD1(sl0, 9, 0); WT_LOAD1(sl0, 10, 0); WT_LOAD1(sl0, 11, 0);
-        WT_LOAD1(sl0, 12, 0); WT_LOAD1(sl0, 13, 0); WT_LOAD1(sl0, 14, 0); WT_LOAD1(sl0, 15, 0);
         const int t1_ = min(1, nk - 1);
-        WT_LOAD1(sl1, 0, t1_); WT_LOAD1(sl1, 1, t1_); WT_LOAD1(sl1, 2, t1_); WT_LOAD1(sl1, 3, t1_);
-        WT_LOAD1(sl1, 4, t1_); WT_LOAD1(sl1, 5, t1_); WT_LOAD1(sl1, 6, t1_); WT_LOAD1(sl1, 7, t1_);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) WT_LOAD1(sl0, j, 0);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) WT_LOAD1(sl1, j, t1_);
     }
-    WT_WAIT(8);
-    WT_READ(0, sl0, 0);
+    WT_WAIT(16);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) WT_READ1(0, sl0, 0, u);
     int kt = 0;
     for (; kt + 2 <= nk; kt += 2) {
         WT_STEP(sl0, sl1, kt);
@@ -1102,14 +672,13 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
     WT_WAIT(0);
 #undef WT_LOAD1
 #undef WT_READ1
-#undef WT_READ
-#undef WT_MMA1
 #undef WT_WAIT
-#undef WT_PAIR
+#undef WT_GROUP
 #undef WT_SLICE
 #undef WT_STEP
-    if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l32, hl);
-    else w4_store(g, acc, m0, n0, wm, wn, l32, hl);
+    mfma16_settle(acc);
+    if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l16, hq);
+    else w4_store(g, acc, m0, n0, wm, wn, l16, hq);
 }
 
 // C (pitch ldc) += ws[0] + ws[1] + ... (n_ws slices of M x N floats, pitch N), added in that order
@@ -1123,27 +692,13 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(float *C, int64_t ldc
     *reinterpret_cast<f32x4 *>(C + row * ldc + col) = v;
 }
 
-int variant_override();
-
 template <int EPI>
 hipError_t launch_tn_epi(const GemmArgs &g0, hipStream_t s) {
     GemmArgs g = g0;
     if (group_m_override() > 0) g.group_m = group_m_override();
     const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = (g.N + W4_BN - 1) / W4_BN;
     const dim3 grid((unsigned)(tiles_m * tiles_n * g.split_k));
-    if (variant_override() == 5) {   // diagnostic: the register-staged kernel
-        constexpr size_t lds = (size_t)2 * TN_STAGE_BYTES;
-        static bool attr_set = false;
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_w4_kernel<EPI>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
-        hipLaunchKernelGGL(gemm_tn_w4_kernel<EPI>, grid, dim3(W4_NT), lds, s, g, tiles_m, tiles_n);
-    } else {
-        hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, grid, dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
-    }
+    hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, grid, dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
     return hipGetLastError();
 }
 
@@ -1167,7 +722,7 @@ int variant_override() {
 static bool takes_w4(const GemmArgs &g) {
     const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
     const int v = variant_override();
-    return g.K % BK == 0 && (v == 6 || ((v == 0 || v == 5) && big_tiles >= 192));
+    return g.K % BK == 0 && (v == 6 || (v == 0 && big_tiles >= 192));
 }
 
 // Which tile takes a problem: the one with the smallest estimated time.  A kernel with one workgroup per compute unit
@@ -1185,12 +740,12 @@ struct TileCost {
     int bm, bn, per_cu;
     double part, full, fixed, fixed_shared;
 };
-static const TileCost kNtCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.45, 9.0, 0.0},
+static const TileCost kNtCosts[] = {{RingTile::none, 256, 256, 1, 0.95, 1.30, 9.0, 0.0},
                                     {RingTile::t256x128, 256, 128, 1, 0.53, 0.79, 5.0, 0.0},
                                     {RingTile::t128x128, 128, 128, 1, 0.36, 0.43, 3.2, 0.0},
                                     {RingTile::t128x64, 128, 64, 2, 0.33, 0.275, 2.0, 1.2},
                                     {RingTile::t64x64, 64, 64, 3, 0.26, 0.18, 2.0, 0.5}};
-static const TileCost kTnCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.57, 10.0, 0.0},
+static const TileCost kTnCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.46, 10.0, 0.0},
                                     {RingTile::t256x128, 256, 128, 1, 0.50, 0.84, 5.0, 0.0},
                                     {RingTile::t128x128, 128, 128, 1, 0.42, 0.47, 3.0, 0.0},
                                     {RingTile::t128x64, 128, 64, 2, 0.34, 0.29, 2.0, 1.2},
@@ -1258,11 +813,10 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s) {
     if (g.bias && g.out_fp32) return hipErrorInvalidValue;
     // offsets inside one tile are 32-bit: 256 rows of either operand must stay below 2^31 elements
     if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return hipErrorInvalidValue;
-    if (g.rope_cos || g.glu_F || g.glu_bwd_gu) return variant_override() == 5 ? launch_w4(g, s) : launch_w4e(g, s);
+    if (g.rope_cos || g.glu_F || g.glu_bwd_gu) return launch_w4e(g, s);
     switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = the estimate
         case 2: return gemm_nt_ring(g, RingTile::t256x128, s);
         case 3: return gemm_nt_ring(g, RingTile::t128x128, s);
-        case 5: if (takes_w4(g)) return launch_w4(g, s); break;             // register-staged 4-wave kernel
         case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
         default: break;
     }
@@ -1323,7 +877,7 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
     if (g.split_k > 1 && (!g.split_ws || ((uintptr_t)g.split_ws & 15) || (g.ldc & 3) || (g.N & 3) || ((uintptr_t)g.C & 15)))
         return hipErrorInvalidValue;
     const int v = variant_override();
-    const RingTile tile = v == 5 || v == 6 ? RingTile::none : v == 2 ? RingTile::t256x128 : v == 3 ? RingTile::t128x128
+    const RingTile tile = v == 6 ? RingTile::none : v == 2 ? RingTile::t256x128 : v == 3 ? RingTile::t128x128
                                                                                                    : choose_tile(kTnCosts, g).tile;
     const hipError_t e = tile == RingTile::none ? launch_tn(g, s) : gemm_tn_ring(g, tile, s);
     if (e != hipSuccess || g.split_k == 1) return e;

@@ -8,7 +8,7 @@
 // from memory straight into a ring of S LDS stages of 64 reduction indices each (global_load_lds_dwordx4, no staging
 // registers); S - 1 stages are in flight while one is consumed.  A wave reads ALL fragments of the next stage while the
 // MFMAs of the present one run (two register sets), so neither the LDS latency nor the barrier (one per stage) is
-// exposed.  The path into LDS takes about 57 bytes a clock, which makes (BM + BN) * 128 / 57 clocks the floor of a
+// exposed.  16 x 16 x 32 MFMAs with accumulators updated in place, as in the 256 x 256 kernel.  The path into LDS takes about 57 bytes a clock, which makes (BM + BN) * 128 / 57 clocks the floor of a
 // stage: 575 for 128 x 128 (MFMA: 515), 431 for 128 x 64 (257), 287 for 64 x 64 (129).
 #include "common.h"
 
@@ -57,22 +57,18 @@ __device__ __forceinline__ void ring_tile(int pid, int tiles_m, int tiles_n, int
 }
 
 // The tile leaves through LDS as fp32 (the ring is free after the last stage), so that a store instruction covers whole
-// lines and bias, residual and accumulation read them the same way.  A lane owns row l32 of a 32 x 32 block and, per
-// quarter q, the columns 8 q + 4 hl .. + 3 (the MFMAs are issued with the operands swapped).  Row pitch BN + 4: the
-// 16-byte writes of consecutive rows fall on disjoint banks.
+// lines and bias, residual and accumulation read them the same way.  A lane owns row l16 of a 16 x 16 block and its columns
+// 4 hq .. + 3 (the MFMAs are issued with the operands swapped).  Row pitch BN + 4: the 16-byte writes of consecutive rows
+// fall on disjoint banks.
 template <int BM, int BN, int TM, int TN, bool F32>
-__device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc)[TM][TN], int m0, int n0, int wm, int wn, float *st) {
+__device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)[TM][TN], int m0, int n0, int wm, int wn, float *st) {
     constexpr int P = BN + 4;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hl = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, hq = lane >> 4;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                *reinterpret_cast<f32x4 *>(st + (wm * TM * 32 + i * 32 + l32) * P + wn * TN * 32 + j * 32 + q * 8 + hl * 4) = v;
-            }
+            *reinterpret_cast<f32x4 *>(st + (wm * TM * 16 + i * 16 + l16) * P + wn * TN * 16 + j * 16 + hq * 4) = acc[i][j];
     __syncthreads();
     constexpr int CPL = F32 ? 4 : 8;                  // columns per lane
     constexpr int LPR = BN / CPL, RPI = 256 / LPR;    // lanes per row, rows per pass
@@ -135,16 +131,16 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc
 #define RING_STAGE(CS, NS, LOADS)                                                                       \
     {                                                                                                   \
         const int sn_ = slot + 1 == S ? 0 : slot + 1;                                                   \
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                \
             _Pragma("unroll") for (int m = 0; m < MPS; ++m) {                                           \
-                constexpr int ALL = 4 * MPS;                                                            \
+                constexpr int ALL = 2 * MPS;                                                            \
                 const int u = ks * MPS + m;                                                             \
                 if (LOADS) {                                                                            \
                     _Pragma("unroll") for (int j = u * LPS / ALL; j < (u + 1) * LPS / ALL; ++j) RING_LOAD(j, t + S, slot); \
                 }                                                                                       \
                 _Pragma("unroll") for (int f = m * (TM + TN) / MPS; f < (m + 1) * (TM + TN) / MPS; ++f) RING_READ(NS, ks, f, sn_); \
-                const int i = m / TN, j = m % TN;                                                       \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[CS][ks][TM + j], fr[CS][ks][i], acc[i][j], 0, 0, 0); \
+                const int i = m / TN, j = i & 1 ? TN - 1 - m % TN : m % TN;                             \
+                mfma16_acc(acc[i][j], fr[CS][ks][TM + j], fr[CS][ks][i]);                               \
                 __builtin_amdgcn_sched_barrier(0);                                                      \
             }                                                                                           \
         slot = sn_;                                                                                     \
@@ -160,7 +156,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc
 #define RING_WALK()                                                                                     \
     {                                                                                                   \
         ring_wait_steps<LPS, S + 1>(min(S, nk) - 1);                                                    \
-        _Pragma("unroll") for (int ks = 0; ks < 4; ++ks)                                                \
+        _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                \
             _Pragma("unroll") for (int f = 0; f < TM + TN; ++f) RING_READ(0, ks, f, 0);                 \
         int t = 0, slot = 0;                                                                            \
         for (; t + 1 + S < nk;) {                                                                       \
@@ -177,6 +173,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc
             RING_LAST_STAGE(1, 0);                                                                      \
             ++t;                                                                                        \
         }                                                                                               \
+        mfma16_settle(acc);                                                                             \
     }
 
 // LDS stage: A [BM][64] | B [BN][64] bf16, rows of 128 bytes, 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)
@@ -185,7 +182,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x16 (&acc
 template <int BM, int BN, int S, bool F32, bool TAIL>
 __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(1024))) char ring[];
-    constexpr int TM = BM / 64, TN = BN / 64, MPS = TM * TN;         // 32 x 32 blocks of a wave (2 x 2 waves)
+    constexpr int TM = BM / 32, TN = BN / 32, MPS = TM * TN;         // 16 x 16 blocks of a wave (2 x 2 waves)
     constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;         // loads of a wave per stage
     constexpr int STAGE = (BM + BN) * 128;
     static_assert(BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
@@ -194,7 +191,7 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     const int m0 = tm * BM, n0 = tn * BN;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hl = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, hq = lane >> 4;
 
     // wave w fills rows (BM / 4) w .. of A and (BN / 4) w .. of B, 8 rows per load; rows past the edge re-read the last one
     const bf16_t *abase = g.A + (int64_t)m0 * g.lda, *bbase = g.B + (int64_t)n0 * g.ldb;
@@ -209,21 +206,19 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(ring_lptr)ring;
     const uint32_t fill_a = (uint32_t)(wave * (BM / 4) * 128), fill_b = (uint32_t)(BM * 128 + wave * (BN / 4) * 128);
-    uint32_t rda[4], rdb[4];
+    uint32_t rda[2], rdb[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        const uint32_t pos = (uint32_t)(((2 * ks + hl) ^ ((l32 >> 1) & 7)) * 16);
-        rda[ks] = (uint32_t)((wm * TM * 32 + l32) * 128) + pos;
-        rdb[ks] = (uint32_t)(BM * 128 + (wn * TN * 32 + l32) * 128) + pos;
+    for (int ks = 0; ks < 2; ++ks) {
+        const uint32_t pos = (uint32_t)(((4 * ks + hq) ^ ((l16 >> 1) & 7)) * 16);
+        rda[ks] = (uint32_t)((wm * TM * 16 + l16) * 128) + pos;
+        rdb[ks] = (uint32_t)(BM * 128 + (wn * TN * 16 + l16) * 128) + pos;
     }
-    bf16x8 fr[2][4][TM + TN];
-    f32x16 acc[TM][TN];
+    bf16x8 fr[2][2][TM + TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (g.K + RK - 1) / RK;
     const int first = TAIL ? 1 : 0;      // stage t > 0 (t >= 0 without a tail) holds reduction indices 64 (t - first) ..
@@ -231,7 +226,7 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     ring_load(((J) < LA ? abase : bbase) + (int64_t)((T) - first) * RK, off[J],                         \
               lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
-    fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 4096 : rdb[KS] + ((F) - TM) * 4096))
+    fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 2048 : rdb[KS] + ((F) - TM) * 2048))
     ru32x4 tv[TAIL ? LPS : 1];
     const int kt = (nk - 1) * RK;
     if constexpr (TAIL) {
@@ -265,17 +260,18 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     ring_store<BM, BN, TM, TN, F32>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
 }
 
-// LDS stage: A [64][BM] | B [64][BN] bf16 as in memory; fragments are read with the transposing load, whose half-waves touch
-// four rows x 64 bytes: 64-byte column group c of row r sits at group position c ^ ring_swz(r), which puts those four on
-// disjoint banks.  A wave-load fills 1024 / (2 BM) rows.  The token range may be split over workgroups (g.split_k).
+// LDS stage: A [64][BM] | B [64][BN] bf16 as in memory; fragments are read with the transposing load: lane (hq, i) supplies k
+// row 8 hq + (i >> 2) (and + 4) of the 32-row slice, 8 bytes at column 4 (i & 3) of the block's 16.  Half a wave reads rows 0 .. 3
+// and 8 .. 11, 32 bytes each: 32-byte column group c of row r sits at group position c ^ ring_swz(r), which puts those
+// eight on disjoint banks.  A wave-load fills 1024 / (2 BM) rows.  The token range may be split over workgroups (g.split_k).
 template <int W>
-__device__ __forceinline__ int ring_swz(int r) { return W == 64 ? (r >> 1) & 1 : W == 128 ? r & 3 : r & 7; }
+__device__ __forceinline__ int ring_swz(int r) { return ((W == 64 ? (r >> 1) & 1 : r & 3) << 1) | ((r >> 3) & 1); }
 
 template <int BM, int BN, int S>
 __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     typedef __attribute__((address_space(3))) s16x4 *trptr;
-    constexpr int TM = BM / 64, TN = BN / 64, MPS = TM * TN;
+    constexpr int TM = BM / 32, TN = BN / 32, MPS = TM * TN;
     constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     static_assert(BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
@@ -306,11 +302,11 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
         constexpr int PA = BM / 8, PB = BN / 8;
         if (j < LA) {
             const int r = wave * 16 + j * (64 / PA) + lane / PA, p = lane % PA;
-            const int c = (((p >> 2) ^ ring_swz<BM>(r)) << 2) | (p & 3);
+            const int c = (((p >> 1) ^ ring_swz<BM>(r)) << 1) | (p & 1);
             off[j] = (uint32_t)(r * (int)g.lda + min(m0 + c * 8, g.M - 8)) * 2u;
         } else {
             const int r = wave * 16 + (j - LA) * (64 / PB) + lane / PB, p = lane % PB;
-            const int c = (((p >> 2) ^ ring_swz<BN>(r)) << 2) | (p & 3);
+            const int c = (((p >> 1) ^ ring_swz<BN>(r)) << 1) | (p & 1);
             off[j] = (uint32_t)(r * (int)g.ldb + min(n0 + c * 8, g.N - 8)) * 2u;
         }
     }
@@ -318,21 +314,18 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
     const uint32_t fill_a = (uint32_t)(wave * 16 * BM * 2), fill_b = (uint32_t)(A_BYTES + wave * 16 * BN * 2);
     uint32_t rd[TM + TN];
     {
-        const int gq = lane >> 4, ii = lane & 15;
-        const int row = (gq >> 1) * 4 + (ii >> 2), inner = (gq & 1) * 16 + (ii & 3) * 4;
+        const int i = lane & 15, row = (lane >> 4) * 8 + (i >> 2), inner = (i & 3) * 8;
 #pragma unroll
         for (int f = 0; f < TM + TN; ++f)
-            rd[f] = f < TM ? (uint32_t)((row * BM + (((wm * TM + f) ^ ring_swz<BM>(row)) * 32) + inner) * 2)
-                           : (uint32_t)(A_BYTES + (row * BN + (((wn * TN + f - TM) ^ ring_swz<BN>(row)) * 32) + inner) * 2);
+            rd[f] = f < TM ? (uint32_t)(row * BM * 2 + ((wm * TM + f) ^ ring_swz<BM>(row)) * 32 + inner)
+                           : (uint32_t)(A_BYTES + row * BN * 2 + ((wn * TN + f - TM) ^ ring_swz<BN>(row)) * 32 + inner);
     }
-    bf16x8 fr[2][4][TM + TN];
-    f32x16 acc[TM][TN];
+    bf16x8 fr[2][2][TM + TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
 #define RING_LOAD(J, T, SLOT)                                                                           \
     ring_load((J) < LA ? abase + (int64_t)(T) * RK * g.lda : bbase + (int64_t)(T) * RK * g.ldb, off[J], \
@@ -340,9 +333,9 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
     {                                                                                                   \
         const int ROW_ = 2 * ((F) < TM ? BM : BN);                                                  \
-        const char *p_ = ring + (SLOT) * STAGE + rd[F] + (KS) * 16 * ROW_;                              \
+        const char *p_ = ring + (SLOT) * STAGE + rd[F] + (KS) * 32 * ROW_;                              \
         const s16x4 lo_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)(p_));                         \
-        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)(p_ + 8 * ROW_));              \
+        const s16x4 hi_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((trptr)(p_ + 4 * ROW_));              \
         typedef __attribute__((ext_vector_type(8))) short s16x8_;                                       \
         const s16x8_ v_ = {lo_[0], lo_[1], lo_[2], lo_[3], hi_[0], hi_[1], hi_[2], hi_[3]};             \
         fr[SET][KS][F] = __builtin_bit_cast(bf16x8, v_);                                                \
