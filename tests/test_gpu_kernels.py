@@ -238,6 +238,17 @@ def test_gemm_rejects_bad_arguments():
     assert L.mt_k_gemm_nt(A.data_ptr(), 64, A.data_ptr(), 64, C.data_ptr(), 64, None, 0, 0, 64, 64, 0, 0, None) == -1
 
 
+@pytest.mark.parametrize("R,C", [(8, 8), (128, 64), (120, 72), (136, 56), (264, 136), (1000, 520)])
+def test_transpose_block_edges(R, C):
+    """Edges of the 128 x 64 blocks, pitches wider than the matrix: every element, nothing outside it."""
+    rng = np.random.default_rng(R + C)
+    x = bf16_round(rng.standard_normal((R, C + 16)))
+    X = dev_bf16(x)
+    out = torch.full((C, R + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    ok(L.mt_k_transpose(X.data_ptr(), out.data_ptr(), R, C, C + 16, R + 8, 1, 1, 0, 0, 0, 0, None))
+    assert np.array_equal(host(out)[:, :R], x[:, :C].T) and np.all(host(out)[:, R:] == 7)
+
+
 def test_batched_head_transpose():
     rng = np.random.default_rng(3)
     B, T, H, hd, ld = 2, 72, 3, 64, 3 * 64 + 128
