@@ -35,6 +35,16 @@ constexpr int kXcd = 8;
 // operands favour small groups far more, up to 7 % at K = 11008, but there the operands are still in the memory-side
 // cache from the previous repetition.)
 constexpr int kGroupMLarge = 4;
+constexpr int kRound = 256;   // workgroups of one round: a compute unit holds one of these kernels' workgroups
+// position in the tile order -> tile
+__device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int group_m, int *tm, int *tn) {
+    const int gm = group_m > 0 ? group_m : kGroupMLarge;
+    const int group = gm * tiles_n;
+    const int first_m = (pid / group) * gm;
+    const int gsz = min(tiles_m - first_m, gm);
+    *tm = first_m + (pid % group) % gsz;
+    *tn = (pid % group) / gsz;
+}
 constexpr int W4_BM = 256, W4_BN = 256, W4_NT = 256;
 
 // bf16 results leave through LDS.  Stored straight from the accumulator layout, a store instruction touches 32
@@ -380,12 +390,8 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
         const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
         pid = x * q + (x < r ? x : r) + pid / kXcd;
     }
-    const int gm = g.group_m > 0 ? g.group_m : kGroupMLarge;
-    const int group = gm * tiles_n;
-    const int first_m = (pid / group) * gm;
-    const int gsz = min(tiles_m - first_m, gm);
-    const int tm = first_m + (pid % group) % gsz;
-    const int tn = (pid % group) / gsz;
+    int tm, tn;
+    tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
     const int m0 = tm * W4_BM, n0 = tn * W4_BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -548,29 +554,31 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
     typedef __attribute__((address_space(3))) void *lptr;
     typedef __attribute__((address_space(3))) s16x4 *trptr;
     constexpr int BM = W4_BM, BN = W4_BN;
-    const int n_tiles = tiles_m * tiles_n, nb = n_tiles * g.split_k;
-    int pid = blockIdx.x;
+    // Split reduction: only the tiles of the last, partial round of kRound workgroups are split (all of them if there is no
+    // full round); their units are ordered chunk-major, so the workgroups running together still form tile patches that
+    // walk the same K range.  Chunk 0 owns C, the others a slice of the workspace.
+    const int n_tiles = tiles_m * tiles_n, n_whole = g.split_k > 1 ? n_tiles / kRound * kRound : n_tiles, n_tail = n_tiles - n_whole;
+    const bool whole = (int)blockIdx.x < n_whole;
+    int pid = blockIdx.x - (whole ? 0 : n_whole), chunk = 0;
     {
+        const int nb = whole ? n_whole : n_tail * g.split_k;
         const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
         pid = x * q + (x < r ? x : r) + pid / kXcd;
     }
-    // split reduction: units are ordered chunk-major, so the workgroups running together still form tile patches
-    // that walk the same K range; chunk 0 owns C, the others a slice of the workspace
-    const int chunk = pid / n_tiles;
-    pid -= chunk * n_tiles;
+    if (!whole) {
+        chunk = pid / n_tail;
+        pid += n_whole - chunk * n_tail;
+    }
+    const int split = whole ? 1 : g.split_k;
     const int nk_all = g.K / BK;
-    const int kb = (int)((int64_t)chunk * nk_all / g.split_k), ke = (int)((int64_t)(chunk + 1) * nk_all / g.split_k);
+    const int kb = (int)((int64_t)chunk * nk_all / split), ke = (int)((int64_t)(chunk + 1) * nk_all / split);
     if (chunk > 0) {
         g.C = g.split_ws + (int64_t)(chunk - 1) * g.M * g.N;
         g.ldc = g.N;
         g.accumulate = 0;
     }
-    const int gm = g.group_m > 0 ? g.group_m : kGroupMLarge;
-    const int group = gm * tiles_n;
-    const int first_m = (pid / group) * gm;
-    const int gsz = min(tiles_m - first_m, gm);
-    const int tm = first_m + (pid % group) % gsz;
-    const int tn = (pid % group) / gsz;
+    int tm, tn;
+    tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -691,14 +699,35 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(float *C, int64_t ldc
     for (int k = 0; k < n_ws; ++k) v += *reinterpret_cast<const f32x4 *>(ws + (int64_t)k * total + idx);
     *reinterpret_cast<f32x4 *>(C + row * ldc + col) = v;
 }
+// the same for the tiles from position `first` of the tile order on; a block takes 32 rows of a tile (a wave a whole row)
+__global__ __launch_bounds__(256) void split_reduce_tiles_kernel(float *C, int64_t ldc, const float *ws, int n_ws, int M, int N,
+                                                                 int first, int tiles_m, int tiles_n, int group_m) {
+    int tm, tn;
+    tile_of(first + blockIdx.x / 8, tiles_m, tiles_n, group_m, &tm, &tn);
+    const int64_t total = (int64_t)M * N;
+    const int col = tn * W4_BN + (threadIdx.x & 63) * 4;
+    if (col >= N) return;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+        const int64_t row = tm * W4_BM + (blockIdx.x & 7) * 32 + it * 4 + (threadIdx.x >> 6);
+        if (row >= M) return;
+        f32x4 v = *reinterpret_cast<const f32x4 *>(C + row * ldc + col);
+        for (int k = 0; k < n_ws; ++k) v += *reinterpret_cast<const f32x4 *>(ws + k * total + row * N + col);
+        *reinterpret_cast<f32x4 *>(C + row * ldc + col) = v;
+    }
+}
 
 template <int EPI>
 hipError_t launch_tn_epi(const GemmArgs &g0, hipStream_t s) {
     GemmArgs g = g0;
     if (group_m_override() > 0) g.group_m = group_m_override();
     const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = (g.N + W4_BN - 1) / W4_BN;
-    const dim3 grid((unsigned)(tiles_m * tiles_n * g.split_k));
-    hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, grid, dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
+    const int n_tiles = tiles_m * tiles_n, n_whole = g.split_k > 1 ? n_tiles / kRound * kRound : n_tiles, n_tail = n_tiles - n_whole;
+    hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, dim3((unsigned)(n_whole + n_tail * g.split_k)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || n_tail == 0) return e;
+    hipLaunchKernelGGL(split_reduce_tiles_kernel, dim3((unsigned)n_tail * 8), dim3(256), 0, s, reinterpret_cast<float *>(g.C), g.ldc,
+                       g.split_ws, g.split_k - 1, g.M, g.N, n_whole, tiles_m, tiles_n, g.group_m);
     return hipGetLastError();
 }
 
@@ -752,8 +781,10 @@ static const TileCost kTnCosts[] = {{RingTile::none, 256, 256, 1, 0.90, 1.46, 10
                                     {RingTile::t64x64, 64, 64, 3, 0.23, 0.175, 2.0, 0.4}};
 constexpr int kComputeUnits = 256;
 
-static double tile_time(const TileCost &c, int64_t M, int64_t N, double stages, int split, int n_cu) {
-    const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * split;
+static double tile_count(const TileCost &c, int64_t M, int64_t N) {
+    return (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn);
+}
+static double tile_time(const TileCost &c, double tiles, double stages, int n_cu) {
     if (c.per_cu > 1) {
         const double per = std::ceil(tiles / n_cu);
         return std::max(stages * c.part + c.fixed, per * (stages * c.full + c.fixed_shared));
@@ -762,15 +793,24 @@ static double tile_time(const TileCost &c, int64_t M, int64_t N, double stages, 
     return rounds * (stages * c.full + c.fixed) +
            (share > 0 ? stages * (c.part + (c.full - c.part) * share * share) + c.fixed : 0.0);
 }
+// weight gradient with its reduction split: the 256 x 256 kernel splits the tiles of the last round only, the others all of them; the
+// partial results are read and added at about 3.5 TB/s, by a launch of its own (3 us)
+static double tn_time(const TileCost &c, int64_t M, int64_t N, double stages, int split, int n_cu) {
+    const double tiles = tile_count(c, M, N);
+    if (split == 1) return tile_time(c, tiles, stages, n_cu);
+    const double whole = c.tile == RingTile::none ? std::floor(tiles / kRound) * kRound : 0.0, cut = tiles - whole;
+    const double floats = c.tile == RingTile::none ? cut * c.bm * c.bn : (double)M * N;
+    return tile_time(c, whole, stages, n_cu) + tile_time(c, cut * split, stages / split, n_cu) + 3.0 + (split + 1) * 4.0 * floats / 3.5e6;
+}
 
 template <int N_COSTS>
 static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], const GemmArgs &g) {
-    const double stages = (double)((g.K + BK - 1) / BK) / g.split_k;
+    const double stages = (double)((g.K + BK - 1) / BK);
     const int first = g.K % BK ? 1 : 0;   // the 256 x 256 kernel takes whole stages only
     const TileCost *best = &costs[first];
-    double best_t = tile_time(*best, g.M, g.N, stages, g.split_k, kComputeUnits);
+    double best_t = tn_time(*best, g.M, g.N, stages, g.split_k, kComputeUnits);
     for (int i = first + 1; i < N_COSTS; ++i) {
-        const double t = tile_time(costs[i], g.M, g.N, stages, g.split_k, kComputeUnits);
+        const double t = tn_time(costs[i], g.M, g.N, stages, g.split_k, kComputeUnits);
         if (t < 0.97 * best_t) {
             best = &costs[i];
             best_t = t;
@@ -826,42 +866,24 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s) {
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
     if (M <= 0 || N <= 0 || K < BK || n_cu <= 0) return 1;
-    const int64_t tiles = ((M + W4_BM - 1) / W4_BM) * ((N + W4_BN - 1) / W4_BN);
     const int64_t nk = K / BK;
-    // one 64-deep k-step of a 256 x 256 tile takes about 1.65 us; the reduction moves (split + 1) M N floats at
-    // about 3.5 TB/s; a round of workgroups costs the same whether it is full or not
-    const double t_step = 1.65e-6, bw = 3.5e12;
+    // A split has to win by 2.5 % in the estimate, a finer one by another 1 %.  22016 x 4096 x 16384 (5.4 rounds of 256 x 256 tiles):
+    // unsplit 2301 us, the last round in two 2123 (all tiles in two: 2394); 7168 x 5120 x 4096 (2.2 rounds) 258, in three 228;
+    // 11008 x 2048 x 16384 664, 556; 5120 x 13824 x 16384 1888, 1728; 7168 x 5120 x 65536 4499, in four 3417 (all in five: 3970).
     int best = 1;
-    double best_t = 0.0, t_unsplit = 0.0;
-    // ... with 256 x 256 tiles,
-    for (int sp = 1; sp <= 6 && nk / sp >= 32; ++sp) {
-        const double rounds = (double)((tiles * sp + n_cu - 1) / n_cu);
-        const double t = rounds * (double)nk / sp * t_step + (sp > 1 ? (sp + 1) * 4.0 * (double)M * (double)N / bw : 0.0);
-        if (sp == 1) {
-            best_t = t_unsplit = t;
-            continue;
+    double best_t = 0.0;
+    for (int sp = 1; sp <= 6; ++sp) {
+        double t = 0.0;
+        for (const TileCost &c : kTnCosts) {
+            if (sp > 1 && nk / sp < (c.tile == RingTile::none ? 16 : 8)) continue;
+            const double tc = tn_time(c, M, N, (double)nk, sp, n_cu);
+            if (t == 0.0 || tc < t) t = tc;
         }
-        // a split has to win by 4 % in this estimate: measured, a partly filled last round costs less than a full one
-        // (fewer busy compute units clock higher), e.g. 7B down-projection gradient 2.69 rounds: 5.05 ms unsplit, 5.11 split
-        if (t < 0.96 * t_unsplit && t < best_t) {
+        if (sp == 1 || (t > 0.0 && t < (best == 1 ? 0.975 : 0.99) * best_t)) {
             best_t = t;
             best = sp;
         }
     }
-    // ... unless smaller tiles, with a split of their own, are estimated faster by as much; a split reduction then
-    // costs its launch as well (measured 3 us).  5504 x 2048 x 16384: 256 x 128 tiles in two chunks 311 + 26 us, 256 x 256
-    // in four 358; 1024 x 1024 x 3008: 64 x 64 tiles unsplit 13 us, 256 x 256 57.
-    const auto reduction = [&](int sp) { return sp > 1 ? 3.0 + (sp + 1) * 4.0 * (double)M * (double)N / (bw * 1e-6) : 0.0; };
-    double best_us = tile_time(kTnCosts[0], M, N, (double)nk / best, best, n_cu) + reduction(best);
-    for (int sp = 1; sp <= 6 && nk / sp >= 8; ++sp)
-        for (const TileCost &c : kTnCosts) {
-            if (c.tile == RingTile::none) continue;
-            const double t = tile_time(c, M, N, (double)nk / sp, sp, n_cu) + reduction(sp);
-            if (t < 0.96 * best_us) {
-                best_us = t;
-                best = sp;
-            }
-        }
     return best;
 }
 
@@ -879,7 +901,8 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
     const int v = variant_override();
     const RingTile tile = v == 6 ? RingTile::none : v == 2 ? RingTile::t256x128 : v == 3 ? RingTile::t128x128
                                                                                                    : choose_tile(kTnCosts, g).tile;
-    const hipError_t e = tile == RingTile::none ? launch_tn(g, s) : gemm_tn_ring(g, tile, s);
+    if (tile == RingTile::none) return launch_tn(g, s);
+    const hipError_t e = gemm_tn_ring(g, tile, s);
     if (e != hipSuccess || g.split_k == 1) return e;
     const int64_t quads = ((int64_t)g.M * g.N + 3) / 4;
     hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, reinterpret_cast<float *>(g.C),

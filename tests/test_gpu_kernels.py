@@ -201,6 +201,24 @@ def test_gemm_weight_gradient_with_split_reduction(orc64, n, out, inn, split):
     assert L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, DW.data_ptr(), inn, out, inn, n, 0, 2, None, None) != 0
 
 
+@pytest.mark.parametrize("n,out,inn,split", [(1024, 4352, 4360, 2), (1216, 4104, 4352, 5)])
+def test_gemm_weight_gradient_split_last_round(n, out, inn, split):
+    """More than 256 tiles of 256 x 256: only those of the last round are split, and only they may differ (by the order of fp32
+    sums) from the unsplit product; with and without accumulation."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
+    ref = DY.double().T @ X.double()
+    # sums of n products of unit normals: each addition rounds to 2^-24 of a partial sum of at most about 5 sqrt(n)
+    tol = n * 2.0 ** -24 * 5 * n ** 0.5
+    WS = torch.full(((split - 1) * out * inn,), 9.0, dtype=torch.float32, device="cuda")
+    whole, cut = (torch.full((out, inn), 7.0, dtype=torch.float32, device="cuda") for _ in range(2))
+    for acc in (0, 1):
+        for dw, sp in ((whole, 1), (cut, split)):
+            ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, dw.data_ptr(), inn, out, inn, n, acc, sp, WS.data_ptr(), None))
+            assert float((dw.double() - (1 + acc) * ref).abs().max()) <= 2 * tol
+    assert float((whole == cut).float().mean()) > 0.5   # 256 of at most 306 tiles are the same work
+
+
 def test_split_choice_for_the_benchmark_shapes():
     """The split the step picks: none where the tiles fill whole rounds of 256 workgroups (7B q|k|v and output
     projections), one where the last round would be mostly empty (14B shapes)."""
