@@ -92,6 +92,22 @@ __device__ __forceinline__ void mfma16_settle(f32x4 (&acc)[I][J]) {
         for (int j = 0; j < J; ++j) asm volatile("" : "+a"(acc[i][j]));
 }
 
+// Tile-row group of the 256 x 256 GEMM kernels: the 32 workgroups of an XCD then cover 4 x 8 tiles and a
+// group's A rows are left after two patches.  Measured inside the step against 8 (8 x 4 patches): 14B GEMM class
+// +0.9 %, 1.3B +0.9 %, 7B +0.2 %; 3 and 6 lose at 14B.  (Stand-alone timings of one GEMM repeated on the same
+// operands favour small groups far more, up to 7 % at K = 11008, but there the operands are still in the memory-side
+// cache from the previous repetition.)
+constexpr int kGroupMLarge = 4;
+// position in the tile order of those kernels -> tile
+__device__ __forceinline__ void gemm_tile_of(int pid, int tiles_m, int tiles_n, int group_m, int *tm, int *tn) {
+    const int gm = group_m > 0 ? group_m : kGroupMLarge;
+    const int group = gm * tiles_n;
+    const int first_m = (pid / group) * gm;
+    const int gsz = min(tiles_m - first_m, gm);
+    *tm = first_m + (pid % group) % gsz;
+    *tn = (pid % group) / gsz;
+}
+
 #endif  // __HIPCC__
 
 // ---------------------------------------------------------------- launchers (host side)
@@ -138,7 +154,8 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
 // has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced.
 enum class RingTile { none, t256x128, t128x128, t128x64, t64x64 };
-hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, hipStream_t s);
+// first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
+hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
 hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, hipStream_t s);
 // true when gemm_nt would apply g.rope_* in its epilogue for this problem (large grid, K % 64 == 0, head-aligned
 // columns); otherwise a call with rope_cos set fails with hipErrorNotSupported and the caller rotates separately

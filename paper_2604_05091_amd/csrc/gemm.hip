@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <iterator>
 
 #include "common.h"
 
@@ -29,22 +30,7 @@ namespace {
 
 constexpr int BK = 64;
 constexpr int kXcd = 8;
-// Tile-row group of the large-grid (load-to-LDS) kernels: the 32 workgroups of an XCD then cover 4 x 8 tiles and a
-// group's A rows are left after two patches.  Measured inside the step against 8 (8 x 4 patches): 14B GEMM class
-// +0.9 %, 1.3B +0.9 %, 7B +0.2 %; 3 and 6 lose at 14B.  (Stand-alone timings of one GEMM repeated on the same
-// operands favour small groups far more, up to 7 % at K = 11008, but there the operands are still in the memory-side
-// cache from the previous repetition.)
-constexpr int kGroupMLarge = 4;
 constexpr int kRound = 256;   // workgroups of one round: a compute unit holds one of these kernels' workgroups
-// position in the tile order -> tile
-__device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int group_m, int *tm, int *tn) {
-    const int gm = group_m > 0 ? group_m : kGroupMLarge;
-    const int group = gm * tiles_n;
-    const int first_m = (pid / group) * gm;
-    const int gsz = min(tiles_m - first_m, gm);
-    *tm = first_m + (pid % group) % gsz;
-    *tn = (pid % group) / gsz;
-}
 constexpr int W4_BM = 256, W4_BN = 256, W4_NT = 256;
 
 // bf16 results leave through LDS.  Stored straight from the accumulator layout, a store instruction touches 32
@@ -384,14 +370,14 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
     __shared__ __attribute__((aligned(1024))) char sl0[WE_ARRAY];
     __shared__ __attribute__((aligned(1024))) char sl1[WE_ARRAY];
     typedef __attribute__((address_space(3))) void *lptr;
-    const int nb = tiles_m * tiles_n;
+    const int nb = (int)gridDim.x;   // all tiles, or the first rounds of them
     int pid = blockIdx.x;
     {
         const int q = nb / kXcd, r = nb % kXcd, x = pid % kXcd;
         pid = x * q + (x < r ? x : r) + pid / kXcd;
     }
     int tm, tn;
-    tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
+    gemm_tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
     const int m0 = tm * W4_BM, n0 = tn * W4_BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -514,27 +500,29 @@ int group_m_override() {
     return v;
 }
 
+// every column tile complete and every access of the store aligned: the vector stores (rows are guarded)
+bool whole_line_store(const GemmArgs &g) {
+    return g.N % W4_BN == 0 && !(g.ldc & 7) && !((uintptr_t)g.C & 15) &&
+           (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) && !((uintptr_t)g.bias & 7) && !(g.bias && g.R);
+}
+
+// n_tiles > 0: only that many tiles of the tile order
 template <int EPI>
-hipError_t launch_w4e_epi(const GemmArgs &g0, hipStream_t s) {
-    GemmArgs g = g0;
+hipError_t launch_w4e_epi(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
     const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = EPI == EPI_GLU ? g.glu_F / 128 : (g.N + W4_BN - 1) / W4_BN;
-    if (group_m_override() > 0) g.group_m = group_m_override();
-    hipLaunchKernelGGL(gemm_nt_w4e_kernel<EPI>, dim3((unsigned)(tiles_m * tiles_n)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
+    hipLaunchKernelGGL(gemm_nt_w4e_kernel<EPI>, dim3((unsigned)(n_tiles > 0 ? n_tiles : tiles_m * tiles_n)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
     return hipGetLastError();
 }
 
-hipError_t launch_w4e(const GemmArgs &g, hipStream_t s) {
+hipError_t launch_w4e(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
     if (g.glu_F > 0) return launch_w4e_epi<EPI_GLU>(g, s);
     if (g.rope_cos) return g.bias ? launch_w4e_epi<EPI_ROPE_BIAS>(g, s) : launch_w4e_epi<EPI_ROPE>(g, s);
     if (g.glu_bwd_gu) return launch_w4e_epi<EPI_GLU_BWD>(g, s);
-    const bool full = g.N % W4_BN == 0 && !(g.ldc & 7) && !((uintptr_t)g.C & 15) &&
-                      (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) && !((uintptr_t)g.bias & 7);
-    if (!full || (g.bias && g.R)) return launch_w4e_epi<EPI_GENERAL>(g, s);
-    if (g.out_fp32) return launch_w4e_epi<EPI_FULL_F32>(g, s);
-    if (g.R) return launch_w4e_epi<EPI_FULL_BF16_RES>(g, s);
-    return g.bias ? launch_w4e_epi<EPI_FULL_BF16_BIAS>(g, s) : launch_w4e_epi<EPI_FULL_BF16>(g, s);
+    if (!whole_line_store(g)) return launch_w4e_epi<EPI_GENERAL>(g, s, n_tiles);
+    if (g.out_fp32) return launch_w4e_epi<EPI_FULL_F32>(g, s, n_tiles);
+    if (g.R) return launch_w4e_epi<EPI_FULL_BF16_RES>(g, s, n_tiles);
+    return g.bias ? launch_w4e_epi<EPI_FULL_BF16_BIAS>(g, s, n_tiles) : launch_w4e_epi<EPI_FULL_BF16>(g, s, n_tiles);
 }
-
 
 // ---------------------------------------------------------------------------------------------
 // Weight-gradient form: C[M,N] = sum_k At[k][m] Bt[k][n] with both operands token-major ([K, M] and [K, N]),
@@ -578,7 +566,7 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
         g.accumulate = 0;
     }
     int tm, tn;
-    tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
+    gemm_tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
     const int m0 = tm * BM, n0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -703,7 +691,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(float *C, int64_t ldc
 __global__ __launch_bounds__(256) void split_reduce_tiles_kernel(float *C, int64_t ldc, const float *ws, int n_ws, int M, int N,
                                                                  int first, int tiles_m, int tiles_n, int group_m) {
     int tm, tn;
-    tile_of(first + blockIdx.x / 8, tiles_m, tiles_n, group_m, &tm, &tn);
+    gemm_tile_of(first + blockIdx.x / 8, tiles_m, tiles_n, group_m, &tm, &tn);
     const int64_t total = (int64_t)M * N;
     const int col = tn * W4_BN + (threadIdx.x & 63) * 4;
     if (col >= N) return;
@@ -803,6 +791,9 @@ static double tn_time(const TileCost &c, int64_t M, int64_t N, double stages, in
     return tile_time(c, whole, stages, n_cu) + tile_time(c, cut * split, stages / split, n_cu) + 3.0 + (split + 1) * 4.0 * floats / 3.5e6;
 }
 
+// The 256 x 256 kernel's guarded store (ragged columns, unaligned rows) writes partial lines: this much more per tile.
+constexpr double kGuardedStore = 14.0;
+
 template <int N_COSTS>
 static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], const GemmArgs &g) {
     const double stages = (double)((g.K + BK - 1) / BK);
@@ -840,7 +831,9 @@ bool gemm_nt_fuses_glu_bwd(const GemmArgs &g) {
            !((uintptr_t)g.glu_bwd_gu & 15);
 }
 
-hipError_t gemm_nt(const GemmArgs &g, hipStream_t s) {
+hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
+    GemmArgs g = g0;
+    if (group_m_override() > 0) g.group_m = group_m_override();
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
     if (g.glu_bwd_gu && !gemm_nt_fuses_glu_bwd(g)) return hipErrorNotSupported;
     if ((g.rope_cos || g.rope_sin) && !gemm_nt_fuses_rope(g)) return hipErrorNotSupported;
@@ -855,13 +848,38 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s) {
     if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return hipErrorInvalidValue;
     if (g.rope_cos || g.glu_F || g.glu_bwd_gu) return launch_w4e(g, s);
     switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = the estimate
-        case 2: return gemm_nt_ring(g, RingTile::t256x128, s);
-        case 3: return gemm_nt_ring(g, RingTile::t128x128, s);
+        case 2: return gemm_nt_ring(g, RingTile::t256x128, -1, s);
+        case 3: return gemm_nt_ring(g, RingTile::t128x128, -1, s);
         case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
         default: break;
     }
-    const RingTile tile = choose_tile(kNtCosts, g).tile;
-    return tile == RingTile::none ? launch_w4e(g, s) : gemm_nt_ring(g, tile, s);
+    TileCost costs[sizeof kNtCosts / sizeof kNtCosts[0]];
+    std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
+    if (!whole_line_store(g)) costs[0].fixed += kGuardedStore;
+    const TileCost &one = choose_tile(costs, g);
+    // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
+    // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
+    // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
+    const double stages = (double)((g.K + BK - 1) / BK), tiles = tile_count(costs[0], g.M, g.N);
+    const int whole = (int)(std::floor(tiles / kRound) * kRound), rest = (int)tiles - whole;
+    if (g.K % BK == 0 && whole > 0 && rest > 0) {
+        double best_t = 0.97 * tn_time(one, g.M, g.N, stages, 1, kComputeUnits);
+        const TileCost *small = nullptr;
+        for (const TileCost &c : costs) {
+            if (c.tile == RingTile::none) continue;
+            const double t = tile_time(costs[0], whole, stages, kComputeUnits) + 3.0 +
+                             tile_time(c, (double)rest * (256 / c.bm) * (256 / c.bn), stages, kComputeUnits);
+            if (t < best_t) {
+                best_t = t;
+                small = &c;
+            }
+        }
+        if (small) {
+            const hipError_t e = launch_w4e(g, s, whole);
+            return e == hipSuccess ? gemm_nt_ring(g, small->tile, whole, s) : e;
+        }
+    }
+    return one.tile == RingTile::none ? launch_w4e(g, s) : gemm_nt_ring(g, one.tile, -1, s);
 }
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {

@@ -179,16 +179,27 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
 // LDS stage: A [BM][64] | B [BN][64] bf16, rows of 128 bytes, 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)
 // (conflict-free 16-byte fragment reads without padding).  TAIL (K % 64 != 0): the last, partial stage is walked first; it goes
 // through registers, chunks at or beyond K as zeros.
+// first >= 0: the workgroups cover the 256 x 256 tiles (tiles_m x tiles_n of them) from position `first` of that kernel's tile
+// order on, each cut into (256 / BM) (256 / BN) of the tiles here.
 template <int BM, int BN, int S, bool F32, bool TAIL>
-__global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, int tiles_n, int first) {
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     constexpr int TM = BM / 32, TN = BN / 32, MPS = TM * TN;         // 16 x 16 blocks of a wave (2 x 2 waves)
     constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;         // loads of a wave per stage
     constexpr int STAGE = (BM + BN) * 128;
     static_assert(BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
     int tm, tn;
-    ring_tile(ring_renumber(tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+    if (first < 0) {
+        ring_tile(ring_renumber(tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+    } else {
+        constexpr int CM = 256 / BM, CN = 256 / BN;
+        const int pid = ring_renumber((int)gridDim.x), cut = pid % (CM * CN);
+        gemm_tile_of(first + pid / (CM * CN), tiles_m, tiles_n, g.group_m, &tm, &tn);
+        tm = tm * CM + cut % CM;
+        tn = tn * CN + cut / CM;
+    }
     const int m0 = tm * BM, n0 = tn * BN;
+    if (m0 >= g.M || n0 >= g.N) return;   // a cut of a ragged edge tile that lies outside
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, hq = lane >> 4;
@@ -221,9 +232,9 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (g.K + RK - 1) / RK;
-    const int first = TAIL ? 1 : 0;      // stage t > 0 (t >= 0 without a tail) holds reduction indices 64 (t - first) ..
+    const int partial = TAIL ? 1 : 0;    // stage t >= partial holds reduction indices 64 (t - partial) ..
 #define RING_LOAD(J, T, SLOT)                                                                           \
-    ring_load(((J) < LA ? abase : bbase) + (int64_t)((T) - first) * RK, off[J],                         \
+    ring_load(((J) < LA ? abase : bbase) + (int64_t)((T) - partial) * RK, off[J],                       \
               lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
     fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 2048 : rdb[KS] + ((F) - TM) * 2048))
@@ -353,43 +364,51 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
 }
 
 template <typename K>
-hipError_t ring_launch(K kernel, const GemmArgs &g, int bm, int bn, size_t lds, bool *attr_set, hipStream_t s) {
-    if (!*attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        *attr_set = true;
-    }
-    const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g, tiles_m, tiles_n);
-    return hipGetLastError();
+hipError_t ring_attr(K kernel, size_t lds, bool *attr_set) {
+    if (*attr_set) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    *attr_set = e == hipSuccess;
+    return e;
 }
 
 template <int BM, int BN, int S, bool F32, bool TAIL>
-hipError_t launch_nt_one(const GemmArgs &g, hipStream_t s) {
+hipError_t launch_nt_one(const GemmArgs &g, int first, hipStream_t s) {
     static bool attr = false;
-    return ring_launch(ring_nt_kernel<BM, BN, S, F32, TAIL>, g, BM, BN, (size_t)S * (BM + BN) * 128, &attr, s);
+    constexpr size_t lds = (size_t)S * (BM + BN) * 128;
+    const hipError_t e = ring_attr(ring_nt_kernel<BM, BN, S, F32, TAIL>, lds, &attr);
+    if (e != hipSuccess) return e;
+    const int bm = first < 0 ? BM : 256, bn = first < 0 ? BN : 256;
+    const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
+    const int blocks = first < 0 ? tiles_m * tiles_n : (tiles_m * tiles_n - first) * (256 / BM) * (256 / BN);
+    hipLaunchKernelGGL((ring_nt_kernel<BM, BN, S, F32, TAIL>), dim3((unsigned)blocks), dim3(256), lds, s, g, tiles_m, tiles_n, first);
+    return hipGetLastError();
 }
 template <int BM, int BN, int S>
-hipError_t launch_nt(const GemmArgs &g, hipStream_t s) {
-    if (g.K % RK) return g.out_fp32 ? launch_nt_one<BM, BN, S, true, true>(g, s) : launch_nt_one<BM, BN, S, false, true>(g, s);
-    return g.out_fp32 ? launch_nt_one<BM, BN, S, true, false>(g, s) : launch_nt_one<BM, BN, S, false, false>(g, s);
+hipError_t launch_nt(const GemmArgs &g, int first, hipStream_t s) {
+    if (g.K % RK) return g.out_fp32 ? launch_nt_one<BM, BN, S, true, true>(g, first, s) : launch_nt_one<BM, BN, S, false, true>(g, first, s);
+    return g.out_fp32 ? launch_nt_one<BM, BN, S, true, false>(g, first, s) : launch_nt_one<BM, BN, S, false, false>(g, first, s);
 }
 template <int BM, int BN, int S>
 hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
     static bool attr = false;
-    return ring_launch(ring_tn_kernel<BM, BN, S>, g, BM, BN, (size_t)S * (BM + BN) * 128, &attr, s);
+    constexpr size_t lds = (size_t)S * (BM + BN) * 128;
+    const hipError_t e = ring_attr(ring_tn_kernel<BM, BN, S>, lds, &attr);
+    if (e != hipSuccess) return e;
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    hipLaunchKernelGGL((ring_tn_kernel<BM, BN, S>), dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g, tiles_m, tiles_n);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 // Three stages each: a fourth or fifth measured the same (4096^3: 118.6, 119.5, 120.6 us with 128 x 128 tiles), and three
 // of 24 or 16 KB let two or three workgroups share a compute unit.
-hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, hipStream_t s) {
+hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s) {
     switch (tile) {
-        case RingTile::t256x128: return launch_nt<256, 128, 3>(g, s);
-        case RingTile::t128x128: return launch_nt<128, 128, 3>(g, s);
-        case RingTile::t128x64: return launch_nt<128, 64, 3>(g, s);
-        case RingTile::t64x64: return launch_nt<64, 64, 3>(g, s);
+        case RingTile::t256x128: return launch_nt<256, 128, 3>(g, first, s);
+        case RingTile::t128x128: return launch_nt<128, 128, 3>(g, first, s);
+        case RingTile::t128x64: return launch_nt<128, 64, 3>(g, first, s);
+        case RingTile::t64x64: return launch_nt<64, 64, 3>(g, first, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -139,6 +139,24 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad):
     assert np.all(host(F)[:, N:] == 3)
 
 
+@pytest.mark.parametrize("M,N,K", [(4096, 5120, 128), (4360, 4352, 64), (4100, 4616, 192), (3000, 5632, 320)])
+def test_gemm_rest_of_the_rounds_in_smaller_tiles(M, N, K):
+    """A little more than 256 tiles of 256 x 256: the full round in those, the rest in smaller ones; complete and ragged edges."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A, B, R = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, K), (N, K), (M, N)))
+    ref = A.double() @ B.double().T
+    C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    for res in (None, R):
+        ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), N, res.data_ptr() if res is not None else None, N, M, N, K, 0, 0, None))
+        want = ref if res is None else ref + R.double()
+        # one rounding to bf16 (2^-9 of the value) after fp32 sums
+        assert bool(((C.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * K ** 0.5).all())
+    F = torch.full((M, N), 3.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, F.data_ptr(), N, None, 0, M, N, K, 1, acc, None))
+        assert float((F.double() - (1 + acc) * ref).abs().max()) <= K * 2.0 ** -24 * 10 * K ** 0.5
+
+
 @pytest.mark.parametrize("n,out,inn", [(2048, 136, 264), (576, 520, 1376), (64, 8, 8), (4096, 2056, 4104)])
 def test_gemm_token_major_weight_gradient(orc64, n, out, inn):
     """dW[out,in] = sum_t dy[t,out] x[t,in] straight from the token-major operands (no transposes): ragged
