@@ -14,8 +14,8 @@
 //
 // Workgroup -> tile mapping: consecutive workgroup ids are dealt round-robin to the
 // 8 XCDs, each with a private L2.  The id is first re-numbered so that every XCD gets
-// a contiguous range of tiles, then walked in column-major groups of 8 tile rows so
-// the 32 tiles resident on one XCD form an 8 x 4 patch that shares A and B panels.
+// a contiguous range of tiles, then walked in column-major groups of kGroupMLarge tile rows
+// so the 32 tiles resident on one XCD form a 4 x 8 patch that shares A and B panels.
 #include <stdlib.h>
 
 #include <algorithm>
