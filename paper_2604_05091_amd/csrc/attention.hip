@@ -351,7 +351,9 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a) {
             // m = -inf before the first tile: the comparison is then true (every query sees key kv0)
             if (__builtin_amdgcn_ballot_w64(mx > m + tau) != 0) {
                 const float m_new = fmaxf(m, mx);
-                const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c);
+                // (of a wave with half of the keys, queries that have seen nothing but -inf come along with the others: there
+                // is nothing to rescale yet, and -inf - -inf would make a NaN of it)
+                const float alpha = KW == 2 && m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * c);
                 lsum *= alpha;
 #pragma unroll
                 for (int hb = 0; hb < HD / 32; ++hb)

@@ -674,6 +674,36 @@ def test_flash_attention_scores_of_minus_infinity(orc64):
         assert_rows_close(host(O)[~masked][:, h * hd:(h + 1) * hd], ref, ROW2, what="masked keys")
 
 
+@pytest.mark.parametrize("first", [0, 32])
+def test_flash_attention_scores_of_minus_infinity_for_some_queries(orc64, first):
+    """The scores of 32 keys (one half of the first 64-key tile) overflow to -inf for every other query of a wave only.
+    Every query that also sees another key has a finite result, whatever its neighbours see."""
+    B, T, H, hd = 1, 136, 2, 64
+    rng = np.random.default_rng(first + 5)
+    q, k, v = (bf16_round(rng.standard_normal((T, H * hd))) for _ in range(3))
+    masked = np.zeros(T, bool)
+    masked[first:first + 32] = True
+    q[:, ::hd], k[:, ::hd] = 0.0, 0.0
+    q[::2, ::hd] = k[masked, ::hd] = bf16_round(np.float32(1.0e30))
+    k[masked, ::hd] *= -1
+    defined = np.arange(T) % 2 == 1
+    defined |= np.array([(~masked[:t + 1]).any() for t in range(T)])
+    Q, K, V = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    O, LSE = torch.zeros_like(Q), torch.zeros((B, H, T), dtype=torch.float32, device="cuda")
+    ok(L.mt_k_flash_fwd(O.data_ptr(), H * hd, LSE.data_ptr(), Q.data_ptr(), H * hd, K.data_ptr(), H * hd, V.data_ptr(), H * hd,
+                        B, T, H, H, hd, hd ** -0.5, None))
+    for h in range(H):
+        cols = slice(h * hd, (h + 1) * hd)
+        s = (q[:, cols].astype(np.float64) @ k[:, cols].astype(np.float64).T) * hd ** -0.5
+        s[np.triu_indices(T, 1)] = -np.inf
+        s[s < -1.0e38] = -np.inf
+        p = np.exp(s[defined] - s[defined].max(axis=1, keepdims=True))
+        ref = (p / p.sum(axis=1, keepdims=True)) @ v[:, cols].astype(np.float64)
+        lse = s[defined].max(axis=1) + np.log(p.sum(axis=1))
+        assert_rows_close(host(O)[defined][:, cols], ref, ROW2, what="queries with and without -inf scores")
+        assert np.abs(host(LSE)[0, h, defined] - lse).max() <= 1e-4 * np.abs(lse).max()
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 200, 4, 2, 64), (2, 72, 2, 2, 128)])
 def test_flash_attention_outputs_with_8_byte_aligned_rows(orc64, B, T, Hq, Hkv, hd):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + hd + 1, out_pad=4)
