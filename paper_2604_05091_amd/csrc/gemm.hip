@@ -343,17 +343,6 @@ __device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x4 (&acc
 // given the builtin, the register allocator renames them, 500 moves per 256 MFMAs (8192^3: 916 us).
 constexpr int WE_HALF = 256 * 64 * 2, WE_SLOT = 2 * WE_HALF, WE_ARRAY = 2 * 128 * W4_EP_PITCH * 2;
 static_assert(WE_ARRAY >= WE_SLOT, "a slot must fit into two staging blocks");
-// From 128 k-steps on (operand rows of 16 KB and more, whose lines at one k crowd onto few memory channels) a group of four
-// tile rows starts its walk over K at an eighth of K of its own, so that the XCDs, which work on different groups, read
-// different columns: 16384 x 4096 x 11008 1095 -> 1042 us, x 22016 2303 -> 2116; K = 8192, 13824 and 32000 +- 1 %.
-// The start depends on the tile row alone, so every store variant sums in the same order.
-constexpr int kStaggerSteps = 128;
-__device__ __forceinline__ int walk_start(int tm, int nk) {
-    if (nk < kStaggerSteps) return 0;
-    int h = tm >> 2;
-    h ^= h >> 1; h ^= h >> 2; h ^= h >> 4;   // any eight groups in arithmetic progression by a power of two: distinct low bits
-    return (h & 7) * (nk >> 3);
-}
 
 // MFMAs 4 U .. 4 U + 3 of a slice's 64: the four blocks (2 x 2) number U, walked in zigzag
 template <int U>
@@ -460,7 +449,7 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
         WE_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
     }
 
-    const int nk = g.K / BK, start = walk_start(tm, nk);
+    const int nk = g.K / BK, start = gemm_walk_start(tm, nk);
     const auto at = [&](int t) { return t + start - (t + start >= nk ? nk : 0); };   // k-step walked as number t
     {
         const int t0_ = at(0), t1_ = at(min(1, nk - 1));

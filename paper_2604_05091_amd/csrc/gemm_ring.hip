@@ -232,9 +232,12 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (g.K + RK - 1) / RK;
-    const int partial = TAIL ? 1 : 0;    // stage t >= partial holds reduction indices 64 (t - partial) ..
+    // first reduction index of the stage walked as number t: with TAIL number 0 is the partial stage (below), otherwise the walk
+    // starts where the 256 x 256 kernel's does
+    const int start = TAIL ? -1 : gemm_walk_start(m0 >> 8, nk);
+    const auto k_of = [&](int t) { return (int64_t)(t + start - (t + start >= nk ? nk : 0)) * RK; };
 #define RING_LOAD(J, T, SLOT)                                                                           \
-    ring_load(((J) < LA ? abase : bbase) + (int64_t)((T) - partial) * RK, off[J],                       \
+    ring_load(((J) < LA ? abase : bbase) + k_of(T), off[J],                                             \
               lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
     fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 2048 : rdb[KS] + ((F) - TM) * 2048))

@@ -469,6 +469,28 @@ def test_gemm_with_swiglu_backward_in_the_store(orc64, M, F, K):
                                      None) == -2
 
 
+def test_fused_stores_equal_the_separate_route_in_long_reductions():
+    """From 128 reduction steps on the walk over K starts at a place that depends on the row: the same one in every kernel, also
+    where the separate route covers part of the result with smaller tiles."""
+    M, N, K = 3000, 5632, 8192
+    g = torch.Generator(device="cuda").manual_seed(9)
+    A, W = (torch.randn((r, K), device="cuda", generator=g).to(torch.bfloat16) for r in (M, N))
+    GU = torch.randn((M, 2 * N), device="cuda", generator=g).to(torch.bfloat16)
+    bf = lambda cols: torch.zeros((M, cols), dtype=torch.bfloat16, device="cuda")
+    C, F = bf(N), N // 2
+    ok(L.mt_k_gemm_nt(A.data_ptr(), K, W.data_ptr(), K, C.data_ptr(), N, None, 0, M, N, K, 0, 0, None))
+    S, S2, DGU, DGU2, Q = bf(F), bf(F), bf(2 * N), bf(2 * N), bf(N)
+    ok(L.mt_k_gemm_nt_swiglu(A.data_ptr(), K, W.data_ptr(), K, None, 0, S.data_ptr(), F, M, F, K, None))
+    ok(L.mt_k_swiglu_fwd(S2.data_ptr(), C.data_ptr(), M, F, None))
+    assert torch.equal(S, S2)
+    ok(L.mt_k_gemm_nt_swiglu_bwd(A.data_ptr(), K, W.data_ptr(), K, DGU.data_ptr(), 2 * N, GU.data_ptr(), 2 * N, M, N, K, None))
+    ok(L.mt_k_swiglu_bwd(DGU2.data_ptr(), C.data_ptr(), GU.data_ptr(), M, N, None))
+    assert torch.equal(DGU, DGU2)
+    cs, sn = torch.ones((M, 64), device="cuda"), torch.zeros((M, 64), device="cuda")   # rotation by 0
+    ok(L.mt_k_gemm_nt_rope(A.data_ptr(), K, W.data_ptr(), K, Q.data_ptr(), N, None, cs.data_ptr(), sn.data_ptr(), M, N, M, N, K, None))
+    assert torch.equal(Q, C)
+
+
 # ----------------------------------------------------------------------------- SwiGLU
 def test_swiglu_forward_backward(orc64):
     rng = np.random.default_rng(6)
