@@ -153,23 +153,25 @@ struct GemmArgs {
     // ds [M, N] (N = F, the gradient of the activation, rounded to bf16 as a stored ds would be); with the forward's
     // gate | up in glu_bwd_gu [M, 2N] the kernel stores C [M, 2N] = dgate | dup instead of ds
     const bf16_t *glu_bwd_gu = nullptr; int64_t ld_glu_bwd = 0;
-    // optional split of the reduction (gemm_tn only): the K range is cut into split_k chunks that run as separate
-    // workgroups (all tiles of chunk 0, then all tiles of chunk 1, ...), chunk 0 stores to C, chunk s > 0 to
-    // split_ws + (s - 1) M N (fp32, pitch N), and a second kernel adds them to C in that order.  For tile counts
-    // that fill the last round of workgroups badly (see gemm_tn_pick_split).
+    // optional split of the reduction (gemm_tn only) for tile counts that fill the last round of workgroups badly (see
+    // gemm_tn_pick_split): the K range is cut into split_k chunks that run as separate workgroups, for the tiles of the last
+    // round (256 x 256 kernel) or for all tiles (smaller ones); chunk 0 stores to C, chunk s > 0 to split_ws + (s - 1) M N
+    // (fp32, pitch N; where a tile is not split, left as it is), and a second kernel adds them to C in that order.  With
+    // split_k > 1, and in the kernels with smaller tiles always, every output is made of as many partial sums as its size
+    // asks for (1 to 6), whether they have a workgroup each or share one.
     int32_t split_k = 1;
     float *split_ws = nullptr;
-    // tile order of the large-grid kernels: tile rows per group (a group is walked column by column); 0 = the
-    // launcher chooses (gemm_pick_group_m)
+    // tile order of the large-grid kernels: tile rows per group (a group is walked column by column); 0 = kGroupMLarge
     int32_t group_m = 0;
 };
 hipError_t gemm_nt(const GemmArgs &g, hipStream_t s);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
-// has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced.
+// has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced; every
+// output is the sum of at least partial_sums partial sums.
 enum class RingTile { none, t256x128, t128x128, t128x64, t64x64 };
 // first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
 hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
-hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, hipStream_t s);
+hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s);
 // true when gemm_nt would apply g.rope_* in its epilogue for this problem (large grid, K % 64 == 0, head-aligned
 // columns); otherwise a call with rope_cos set fails with hipErrorNotSupported and the caller rotates separately
 bool gemm_nt_fuses_rope(const GemmArgs &g);
@@ -183,7 +185,7 @@ bool gemm_nt_fuses_glu_bwd(const GemmArgs &g);
 // the operands and use gemm_nt).
 hipError_t gemm_tn(const GemmArgs &g, hipStream_t s);
 // Reduction split for gemm_tn that minimises the estimated time of an M x N x K weight-gradient product on n_cu
-// compute units, 1 = none; the workspace it needs is (split - 1) * M * N floats.
+// compute units without summing it in longer chains than its size allows, 1 = none; the workspace is (split - 1) * M * N floats.
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu);
 
 // out[b][c][r] = in[b][r][c] for r < rows, c < cols (bf16); leading dimensions in elements.

@@ -312,7 +312,7 @@ __device__ __forceinline__ void w4_store_glu_bwd(const GemmArgs &g, const f32x4 
 // The epilogue is a template parameter: one kernel that carries all of them keeps so much guarded store code alive
 // that the compiler moves accumulators through scratch memory on the way out (measured: 13-16 us per tile).
 enum { EPI_GENERAL = 0, EPI_FULL_BF16 = 1, EPI_FULL_F32 = 2, EPI_ROPE = 3, EPI_GLU = 4, EPI_GLU_BWD = 5, EPI_FULL_BF16_RES = 6,
-       EPI_FULL_BF16_BIAS = 7, EPI_ROPE_BIAS = 8 };
+       EPI_FULL_BF16_BIAS = 7, EPI_ROPE_BIAS = 8, EPI_QUADS_F32 = 9 };
 // region: the wave's private LDS staging block (128 rows of W4_EP_PITCH bf16), free once the k-loop's last barrier has passed
 template <int EPI>
 __device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int tn, int wm, int wn,
@@ -524,17 +524,60 @@ hipError_t launch_w4e(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
 constexpr int WT_HALF = 64 * 256 * 2, WT_SLOT = 2 * WT_HALF;
 __device__ __forceinline__ int tn_swz(int r) { return ((r & 3) << 1) | ((r >> 3) & 1); }
 
+// fp32 store of a tile with aligned rows.  FULL: complete column tiles, otherwise whole groups of four columns (N is a multiple of
+// 8).  What it adds to is requested four row blocks (of 8 loads) ahead; rows and columns past the edge re-read the last ones.  One
+// instruction stream with and without accumulation (sums that start at +0 stay what they are when +0 is added): two would
+// both keep the accumulators alive, and the compiler then copies all of them out and spills.
+template <bool FULL>
+__device__ __forceinline__ void tn_store(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn, int l16, int hq) {
+    constexpr int AHEAD = 4;
+    const int row_l = m0 + wm * 128 + l16, col_l = n0 + wn * 128 + hq * 4;
+    float *C = reinterpret_cast<float *>(g.C);
+    f32x4 c[AHEAD][8];
+    const auto fetch = [&](int i) {
+        int row = min(row_l + i * 16, g.M - 1);
+        asm volatile("" : "+v"(row));   // addresses are worked out here, not kept in registers during the walk
+        const float *cp = C + (int64_t)row * g.ldc;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            c[i % AHEAD][j] = *reinterpret_cast<const f32x4 *>(cp + (FULL ? col_l + j * 16 : min(col_l + j * 16, g.N - 4)));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+        if (g.accumulate) fetch(i);
+        else
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        int row = row_l + i * 16;
+        asm volatile("" : "+v"(row));
+        float *cp = C + (int64_t)row * g.ldc + col_l;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            f32x4 v = acc[i][j];
+            asm volatile("" : "+a"(v));   // leaves the accumulation registers here, not with all the others in front
+            v += c[i % AHEAD][j];
+            if (row < g.M && (FULL || col_l + j * 16 < g.N)) *reinterpret_cast<f32x4 *>(cp + j * 16) = v;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + AHEAD < 8 && g.accumulate) fetch(i + AHEAD);
+    }
+}
+
 template <int EPI>
-__global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tiles_m, int tiles_n, int n_whole, int sums, int sums_tail) {
     __shared__ __attribute__((aligned(1024))) char sl0[WT_SLOT];
     __shared__ __attribute__((aligned(1024))) char sl1[WT_SLOT];
     typedef __attribute__((address_space(3))) void *lptr;
     typedef __attribute__((address_space(3))) s16x4 *trptr;
     constexpr int BM = W4_BM, BN = W4_BN;
-    // Split reduction: only the tiles of the last, partial round of kRound workgroups are split (all of them if there is no
-    // full round); their units are ordered chunk-major, so the workgroups running together still form tile patches that
-    // walk the same K range.  Chunk 0 owns C, the others a slice of the workspace.
-    const int n_tiles = tiles_m * tiles_n, n_whole = g.split_k > 1 ? n_tiles / kRound * kRound : n_tiles, n_tail = n_tiles - n_whole;
+    // Split reduction.  The first n_whole tiles walk the whole reduction.  The others (those of the last, partial round, if any)
+    // have a workgroup for each of split_k chunks; these units are ordered chunk-major, so the workgroups running together
+    // still form tile patches that walk the same K range; chunk 0 owns C, the others a slice of the workspace.  Either kind is
+    // summed in pieces (sums of them, sums_tail in a chunk) that are added to C or the slice one after the other.
+    const int n_tail = tiles_m * tiles_n - n_whole;
     const bool whole = (int)blockIdx.x < n_whole;
     int pid = blockIdx.x - (whole ? 0 : n_whole), chunk = 0;
     {
@@ -546,9 +589,10 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
         chunk = pid / n_tail;
         pid += n_whole - chunk * n_tail;
     }
-    const int split = whole ? 1 : g.split_k;
+    const int pieces = whole ? sums : g.split_k * sums_tail;
+    int piece = whole ? 0 : chunk * sums_tail;
+    const int piece_end = piece + (whole ? sums : sums_tail);
     const int nk_all = g.K / BK;
-    const int kb = (int)((int64_t)chunk * nk_all / split), ke = (int)((int64_t)(chunk + 1) * nk_all / split);
     if (chunk > 0) {
         g.C = g.split_ws + (int64_t)(chunk - 1) * g.M * g.N;
         g.ldc = g.N;
@@ -566,8 +610,7 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
     // loader: wave w fills k rows 16 w .. 16 w + 15 of the A half and of the B half of a slot, two rows per load;
     // lane l delivers to the 16-byte position l & 31 of row l >> 5 and fetches the chunk that belongs there.
     // Chunks past the matrix edge re-read the last chunk; they only feed outputs that are never stored.
-    const bf16_t *abase = g.A + (int64_t)kb * BK * g.lda;
-    const bf16_t *bbase = g.B + (int64_t)kb * BK * g.ldb;
+    const bf16_t *abase, *bbase;   // first k row of the piece
     uint32_t off[16];   // byte offsets from abase (0..7) / bbase (8..15)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -590,10 +633,6 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
     }
     bf16x8 fr[2][16];
     f32x4 acc[8][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // one load-to-LDS as assembly, ordered by hand (see gemm_nt_w4e_kernel); a k-step advances both operands by 64 rows
 #define WT_LOAD1(SLOT, J, T)                                                                            \
@@ -637,33 +676,49 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
         WT_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
     }
 
-    const int nk = ke - kb;
-    {
-        const int t1_ = min(1, nk - 1);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) WT_LOAD1(sl0, j, 0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) WT_LOAD1(sl1, j, t1_);
+    int nk;
+    // a piece's first two steps are requested; the slots are free: the barrier that ended the piece before lies behind every read
+#define WT_BEGIN()                                                                                      \
+    {                                                                                                   \
+        const int kb_ = (int)((int64_t)piece * nk_all / pieces);                                        \
+        nk = (int)((int64_t)(piece + 1) * nk_all / pieces) - kb_;                                       \
+        abase = g.A + (int64_t)kb_ * BK * g.lda;                                                        \
+        bbase = g.B + (int64_t)kb_ * BK * g.ldb;                                                        \
+        const int t1_ = min(1, nk - 1);                                                                 \
+        _Pragma("unroll") for (int j = 0; j < 16; ++j) WT_LOAD1(sl0, j, 0);                             \
+        _Pragma("unroll") for (int j = 0; j < 16; ++j) WT_LOAD1(sl1, j, t1_);                           \
     }
-    WT_WAIT(16);
+    WT_BEGIN();
+    for (;;) {
 #pragma unroll
-    for (int u = 0; u < 16; ++u) WT_READ1(0, sl0, 0, u);
-    int kt = 0;
-    for (; kt + 2 <= nk; kt += 2) {
-        WT_STEP(sl0, sl1, kt);
-        WT_STEP(sl1, sl0, kt + 1);
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        WT_WAIT(16);   // (the stores of the piece before are younger than these loads and may be waited for as well)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) WT_READ1(0, sl0, 0, u);
+        int kt = 0;
+        for (; kt + 2 <= nk; kt += 2) {
+            WT_STEP(sl0, sl1, kt);
+            WT_STEP(sl1, sl0, kt + 1);
+        }
+        if (kt < nk) WT_STEP(sl0, sl1, kt);
+        WT_WAIT(0);
+        mfma16_settle(acc);
+        const bool more = EPI != EPI_GENERAL && ++piece < piece_end;   // (a split has aligned rows)
+        if (more) WT_BEGIN();   // their flight covers the store
+        if constexpr (EPI == EPI_GENERAL) w4_store(g, acc, m0, n0, wm, wn, l16, hq);
+        else tn_store<EPI == EPI_FULL_F32>(g, acc, m0, n0, wm, wn, l16, hq);
+        if (!more) break;
+        g.accumulate = 1;
     }
-    if (kt < nk) WT_STEP(sl0, sl1, kt);
-    WT_WAIT(0);
+#undef WT_BEGIN
 #undef WT_LOAD1
 #undef WT_READ1
 #undef WT_WAIT
 #undef WT_GROUP
 #undef WT_SLICE
 #undef WT_STEP
-    mfma16_settle(acc);
-    if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l16, hq);
-    else w4_store(g, acc, m0, n0, wm, wn, l16, hq);
 }
 
 // C (pitch ldc) += ws[0] + ws[1] + ... (n_ws slices of M x N floats, pitch N), added in that order
@@ -692,25 +747,6 @@ __global__ __launch_bounds__(256) void split_reduce_tiles_kernel(float *C, int64
         for (int k = 0; k < n_ws; ++k) v += *reinterpret_cast<const f32x4 *>(ws + k * total + row * N + col);
         *reinterpret_cast<f32x4 *>(C + row * ldc + col) = v;
     }
-}
-
-template <int EPI>
-hipError_t launch_tn_epi(const GemmArgs &g0, hipStream_t s) {
-    GemmArgs g = g0;
-    if (group_m_override() > 0) g.group_m = group_m_override();
-    const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = (g.N + W4_BN - 1) / W4_BN;
-    const int n_tiles = tiles_m * tiles_n, n_whole = g.split_k > 1 ? n_tiles / kRound * kRound : n_tiles, n_tail = n_tiles - n_whole;
-    hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, dim3((unsigned)(n_whole + n_tail * g.split_k)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || n_tail == 0) return e;
-    hipLaunchKernelGGL(split_reduce_tiles_kernel, dim3((unsigned)n_tail * 8), dim3(256), 0, s, reinterpret_cast<float *>(g.C), g.ldc,
-                       g.split_ws, g.split_k - 1, g.M, g.N, n_whole, tiles_m, tiles_n, g.group_m);
-    return hipGetLastError();
-}
-
-hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
-    const bool full = g.N % W4_BN == 0 && !(g.ldc & 3) && !((uintptr_t)g.C & 15);
-    return full ? launch_tn_epi<EPI_FULL_F32>(g, s) : launch_tn_epi<EPI_GENERAL>(g, s);
 }
 
 int variant_override() {
@@ -770,27 +806,65 @@ static double tile_time(const TileCost &c, double tiles, double stages, int n_cu
     return rounds * (stages * c.full + c.fixed) +
            (share > 0 ? stages * (c.part + (c.full - c.part) * share * share) + c.fixed : 0.0);
 }
-// weight gradient with its reduction split: the 256 x 256 kernel splits the tiles of the last round only, the others all of them; the
-// partial results are read and added at about 3.5 TB/s, by a launch of its own (3 us)
+// How many partial sums every output of a weight gradient is made of at the least.  A long chain of fp32 additions loses
+// precision, so this number never falls below that of the plainest split there is, all 256 x 256 tiles into the same number of
+// workgroups, where it pays by a model of its own: a k-step 1.65 us, the reduction 3.5 TB/s, a gain of 4 %.  Relative error
+// against 64 bits for normal data in that many sums and in one: 2048 x 1024 x 16384 3.2e-7 (6 sums) and 8.2e-7, 7168 x 5120 x 32768
+// 5.1e-7 (5) and 1.2e-6.
+static int tn_partial_sums(int64_t M, int64_t N, int64_t K, int n_cu) {
+    const int64_t tiles = ((M + W4_BM - 1) / W4_BM) * ((N + W4_BN - 1) / W4_BN), nk = K / BK;
+    int best = 1;
+    double best_t = 0.0;
+    for (int sp = 1; sp <= 6 && nk / sp >= 32; ++sp) {
+        const double t = (double)((tiles * sp + n_cu - 1) / n_cu) * (double)nk / sp * 1.65e-6 +
+                         (sp > 1 ? (sp + 1) * 4.0 * (double)M * (double)N / 3.5e12 : 0.0);
+        if (sp == 1) best_t = 0.96 * t;
+        else if (t < best_t) {
+            best_t = t;
+            best = sp;
+        }
+    }
+    return best;
+}
+
+// Weight gradient with its reduction split.  The 256 x 256 kernel leaves the tiles of the last round to a workgroup per chunk, or
+// walks the whole reduction of every tile in one workgroup; the others have a workgroup per chunk for every tile.  Partial
+// results in the workspace are read and added at about 3.5 TB/s, by a launch of its own (3 us).  Every unit makes as many
+// partial sums as its precision asks for (an unsplit product of 256 x 256 tiles a single one: its caller chose that).
+// A round of 256 x 256 tiles adds a further partial sum to C in 28 us, a single one, which finds C in the memory-side cache, in 16.
+constexpr double kPiece = 28.0, kPieceAlone = 16.0;
+struct TnRoute { double time; int n_whole, sums, sums_tail; };
+static TnRoute tn_big_route(const TileCost &c, int64_t M, int64_t N, double stages, int split, int n_cu) {
+    const double tiles = tile_count(c, M, N), full = std::floor(tiles / kRound) * kRound, cut = tiles - full;
+    const int sums = split == 1 ? 1 : tn_partial_sums(M, N, (int64_t)stages * BK, n_cu), sums_tail = (sums + split - 1) / split;
+    const TnRoute whole = {tile_time(c, tiles, stages, n_cu) + (sums - 1) * (tiles == n_cu ? kPieceAlone : std::ceil(tiles / n_cu) * kPiece),
+                           (int)tiles, sums, 1};
+    if (split == 1 || cut == 0.0) return whole;
+    const TnRoute tail = {tile_time(c, full, stages, n_cu) + (sums - 1) * (full == n_cu ? kPieceAlone : full / n_cu * kPiece) +
+                              tile_time(c, cut * split, stages / split, n_cu) + (sums_tail - 1) * std::ceil(cut * split / n_cu) * kPieceAlone + 3.0 +
+                              (split + 1) * 4.0 * cut * c.bm * c.bn / 3.5e6, (int)full, sums, sums_tail};
+    return tail.time < whole.time ? tail : whole;
+}
 static double tn_time(const TileCost &c, int64_t M, int64_t N, double stages, int split, int n_cu) {
-    const double tiles = tile_count(c, M, N);
-    if (split == 1) return tile_time(c, tiles, stages, n_cu);
-    const double whole = c.tile == RingTile::none ? std::floor(tiles / kRound) * kRound : 0.0, cut = tiles - whole;
-    const double floats = c.tile == RingTile::none ? cut * c.bm * c.bn : (double)M * N;
-    return tile_time(c, whole, stages, n_cu) + tile_time(c, cut * split, stages / split, n_cu) + 3.0 + (split + 1) * 4.0 * floats / 3.5e6;
+    if (c.tile == RingTile::none) return tn_big_route(c, M, N, stages, split, n_cu).time;
+    const double t = tile_time(c, tile_count(c, M, N) * split, stages / split, n_cu);
+    if (split == 1) return t;
+    // the tiles that share a compute unit gain nothing from a split: 184 x 4248 x 13312 in five 54 us (256 x 128 tiles in six: 37),
+    // 1952 x 200 x 2048 in four 12.3 (unsplit 9.0); their estimate carries the unsplit walk of a tile once more
+    return t + 3.0 + (split + 1) * 4.0 * (double)M * (double)N / 3.5e6 + (c.per_cu > 1 ? stages * c.part + c.fixed : 0.0);
 }
 
 // The 256 x 256 kernel's guarded store (ragged columns, unaligned rows) writes partial lines: this much more per tile.
 constexpr double kGuardedStore = 14.0;
 
 template <int N_COSTS>
-static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], const GemmArgs &g) {
-    const double stages = (double)((g.K + BK - 1) / BK);
-    const int first = g.K % BK ? 1 : 0;   // the 256 x 256 kernel takes whole stages only
+static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], int64_t M, int64_t N, int64_t K, int split) {
+    const double stages = (double)((K + BK - 1) / BK);
+    const int first = K % BK ? 1 : 0;   // the 256 x 256 kernel takes whole stages only
     const TileCost *best = &costs[first];
-    double best_t = tn_time(*best, g.M, g.N, stages, g.split_k, kComputeUnits);
+    double best_t = tn_time(*best, M, N, stages, split, kComputeUnits);
     for (int i = first + 1; i < N_COSTS; ++i) {
-        const double t = tn_time(costs[i], g.M, g.N, stages, g.split_k, kComputeUnits);
+        const double t = tn_time(costs[i], M, N, stages, split, kComputeUnits);
         if (t < 0.97 * best_t) {
             best = &costs[i];
             best_t = t;
@@ -845,7 +919,7 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
     TileCost costs[sizeof kNtCosts / sizeof kNtCosts[0]];
     std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
     if (!whole_line_store(g)) costs[0].fixed += kGuardedStore;
-    const TileCost &one = choose_tile(costs, g);
+    const TileCost &one = choose_tile(costs, g.M, g.N, g.K, 1);
     // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
     // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
     // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
@@ -874,25 +948,45 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
     if (M <= 0 || N <= 0 || K < BK || n_cu <= 0) return 1;
     const int64_t nk = K / BK;
+    const int sums = tn_partial_sums(M, N, K, n_cu);
     // A split has to win by 1.5 % in the estimate, a finer one by another 1 % (27648 x 5120 x 16384, 8.4 rounds: 1.8 % estimated, 3506 ->
-    // 3325 us measured).  22016 x 4096 x 16384 (5.4 rounds of 256 x 256 tiles):
-    // unsplit 2301 us, the last round in two 2123 (all tiles in two: 2394); 7168 x 5120 x 4096 (2.2 rounds) 258, in three 228;
-    // 11008 x 2048 x 16384 664, 556; 5120 x 13824 x 16384 1888, 1728; 7168 x 5120 x 65536 4499, in four 3417 (all in five: 3970).
-    int best = 1;
+    // 3325 us measured).  22016 x 4096 x 16384 (5.4 rounds of 256 x 256 tiles): unsplit 2301 us, the last round in two 2123 (all tiles
+    // in two: 2394); 7168 x 5120 x 4096 (2.2 rounds) 258, in three 228.  With as many partial sums in the full rounds as the size asks
+    // for: 7168 x 5120 x 32768 (five) 1902 (a workgroup per chunk everywhere: 2081), 5128 x 4096 x 8192 (three) 300 (374),
+    // 11008 x 2048 x 16384 (two) 568 (657).
+    int best = 0;
     double best_t = 0.0;
     for (int sp = 1; sp <= 6; ++sp) {
-        double t = 0.0;
-        for (const TileCost &c : kTnCosts) {
-            if (sp > 1 && nk / sp < (c.tile == RingTile::none ? 16 : 8)) continue;
-            const double tc = tn_time(c, M, N, (double)nk, sp, n_cu);
-            if (t == 0.0 || tc < t) t = tc;
-        }
-        if (sp == 1 || (t > 0.0 && t < (best == 1 ? 0.985 : 0.99) * best_t)) {
+        const TileCost &c = choose_tile(kTnCosts, M, N, K, sp);   // what gemm_tn will take
+        const bool big = c.tile == RingTile::none;
+        if (sp > 1 ? nk / sp < (big ? 16 : 8) : big && sums > 1) continue;
+        const double t = tn_time(c, M, N, (double)nk, sp, n_cu);
+        if (best == 0 || t < (best == 1 ? 0.985 : 0.99) * best_t) {
             best_t = t;
             best = sp;
         }
     }
-    return best;
+    return std::max(best, 1);
+}
+
+template <int EPI>
+static hipError_t launch_tn_epi(const GemmArgs &g0, const TnRoute &route, hipStream_t s) {
+    GemmArgs g = g0;
+    if (group_m_override() > 0) g.group_m = group_m_override();
+    const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = (g.N + W4_BN - 1) / W4_BN, n_tail = tiles_m * tiles_n - route.n_whole;
+    hipLaunchKernelGGL(gemm_tn_w4e_kernel<EPI>, dim3((unsigned)(route.n_whole + n_tail * g.split_k)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n,
+                       route.n_whole, route.sums, route.sums_tail);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || n_tail == 0) return e;
+    hipLaunchKernelGGL(split_reduce_tiles_kernel, dim3((unsigned)n_tail * 8), dim3(256), 0, s, reinterpret_cast<float *>(g.C), g.ldc,
+                       g.split_ws, g.split_k - 1, g.M, g.N, route.n_whole, tiles_m, tiles_n, g.group_m);
+    return hipGetLastError();
+}
+
+static hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
+    const TnRoute route = tn_big_route(kTnCosts[0], g.M, g.N, g.K / BK, g.split_k, kComputeUnits);
+    if ((g.ldc & 3) || ((uintptr_t)g.C & 15)) return launch_tn_epi<EPI_GENERAL>(g, route, s);   // (unsplit then)
+    return g.N % W4_BN == 0 ? launch_tn_epi<EPI_FULL_F32>(g, route, s) : launch_tn_epi<EPI_QUADS_F32>(g, route, s);
 }
 
 hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
@@ -908,9 +1002,9 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
         return hipErrorInvalidValue;
     const int v = variant_override();
     const RingTile tile = v == 6 ? RingTile::none : v == 2 ? RingTile::t256x128 : v == 3 ? RingTile::t128x128
-                                                                                                   : choose_tile(kTnCosts, g).tile;
+                                                                                                   : choose_tile(kTnCosts, g.M, g.N, g.K, g.split_k).tile;
     if (tile == RingTile::none) return launch_tn(g, s);
-    const hipError_t e = gemm_tn_ring(g, tile, s);
+    const hipError_t e = gemm_tn_ring(g, tile, tn_partial_sums(g.M, g.N, g.K, kComputeUnits), s);
     if (e != hipSuccess || g.split_k == 1) return e;
     const int64_t quads = ((int64_t)g.M * g.N + 3) / 4;
     hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, reinterpret_cast<float *>(g.C),

@@ -128,6 +128,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
 // The walk over the stages, shared by the two kernels.  LOAD(J, T, SLOT) requests load J of stage T, READ(SET, KS, F, SLOT)
 // reads fragment F of slice KS into register set SET.  Stage T lives in slot T % S.  At the top of stage T: stage T + 1
 // has landed and every wave has read its fragments of stage T (one wait, one barrier), so slot T % S takes stage T + S.
+// RING_NEXT() follows the loads of a stage.  RING_SEAM(t) is the next stage, t at most, in front of which RING_AT_SEAM() runs.
 #define RING_STAGE(CS, NS, LOADS)                                                                       \
     {                                                                                                   \
         const int sn_ = slot + 1 == S ? 0 : slot + 1;                                                   \
@@ -143,6 +144,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
                 mfma16_acc(acc[i][j], fr[CS][ks][TM + j], fr[CS][ks][i]);                               \
                 __builtin_amdgcn_sched_barrier(0);                                                      \
             }                                                                                           \
+        if (LOADS) RING_NEXT();                                                                         \
         slot = sn_;                                                                                     \
     }
 #define RING_LAST_STAGE(CS, NS)                                                                         \
@@ -150,6 +152,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
         ring_wait_steps<LPS, S>(min(t + S - 1, nk - 1) - (t + 1));                                      \
         if (t + S < nk) {                                                                               \
             _Pragma("unroll") for (int j = 0; j < LPS; ++j) RING_LOAD(j, t + S, slot);                  \
+            RING_NEXT();                                                                                \
         }                                                                                               \
         RING_STAGE(CS, NS, false);                                                                      \
     }
@@ -159,13 +162,18 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
         _Pragma("unroll") for (int ks = 0; ks < 2; ++ks)                                                \
             _Pragma("unroll") for (int f = 0; f < TM + TN; ++f) RING_READ(0, ks, f, 0);                 \
         int t = 0, slot = 0;                                                                            \
-        for (; t + 1 + S < nk;) {                                                                       \
-            ring_wait<(S - 2) * LPS>();                                                                 \
-            RING_STAGE(0, 1, true);                                                                     \
-            ++t;                                                                                        \
-            ring_wait<(S - 2) * LPS>();                                                                 \
-            RING_STAGE(1, 0, true);                                                                     \
-            ++t;                                                                                        \
+        const int t_end = nk - 1 - S;                                                                   \
+        for (; t < t_end;) {                                                                            \
+            const int stop = RING_SEAM(t_end);                                                          \
+            for (; t < stop;) {                                                                         \
+                ring_wait<(S - 2) * LPS>();                                                             \
+                RING_STAGE(0, 1, true);                                                                 \
+                ++t;                                                                                    \
+                ring_wait<(S - 2) * LPS>();                                                             \
+                RING_STAGE(1, 0, true);                                                                 \
+                ++t;                                                                                    \
+            }                                                                                           \
+            RING_AT_SEAM();                                                                             \
         }                                                                                               \
         for (; t < nk;) {                                                                               \
             RING_LAST_STAGE(0, 1);                                                                      \
@@ -268,7 +276,13 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
         for (int j = 0; j < LPS; ++j)
             *reinterpret_cast<ru32x4 *>(ring + (j < LA ? fill_a + j * 1024 : fill_b + (j - LA) * 1024) + lane * 16) = tv[j];
     }
+#define RING_SEAM(T) (T)
+#define RING_AT_SEAM()
+#define RING_NEXT()
     RING_WALK();
+#undef RING_SEAM
+#undef RING_AT_SEAM
+#undef RING_NEXT
 #undef RING_LOAD
 #undef RING_READ
     ring_store<BM, BN, TM, TN, F32>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
@@ -281,8 +295,9 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
 template <int W>
 __device__ __forceinline__ int ring_swz(int r) { return ((W == 64 ? (r >> 1) & 1 : r & 3) << 1) | ((r >> 3) & 1); }
 
-template <int BM, int BN, int S>
-__global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+// CHAINS: at most `chain` stages (even) are added up in one go; the sums so far are kept in a second set of registers.
+template <int BM, int BN, int S, bool CHAINS>
+__global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, int tiles_n, int chain) {
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     typedef __attribute__((address_space(3))) s16x4 *trptr;
     constexpr int TM = BM / 32, TN = BN / 32, MPS = TM * TN;
@@ -307,7 +322,8 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
 
-    const bf16_t *abase = g.A + (int64_t)kb * RK * g.lda, *bbase = g.B + (int64_t)kb * RK * g.ldb;
+    const bf16_t *abase = g.A + (int64_t)kb * RK * g.lda, *bbase = g.B + (int64_t)kb * RK * g.ldb;   // of the next stage to load
+    const int64_t astep = (int64_t)RK * g.lda, bstep = (int64_t)RK * g.ldb;
     uint32_t off[LPS];
 #pragma unroll
     for (int j = 0; j < LPS; ++j) {
@@ -341,8 +357,13 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+#define RING_NEXT()                                                                                     \
+    {                                                                                                   \
+        abase += astep;                                                                                 \
+        bbase += bstep;                                                                                 \
+    }
 #define RING_LOAD(J, T, SLOT)                                                                           \
-    ring_load((J) < LA ? abase + (int64_t)(T) * RK * g.lda : bbase + (int64_t)(T) * RK * g.ldb, off[J], \
+    ring_load((J) < LA ? abase : bbase, off[J],                                                         \
               lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
     {                                                                                                   \
@@ -359,10 +380,42 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
         if (s < nk) {
 #pragma unroll
             for (int j = 0; j < LPS; ++j) RING_LOAD(j, s, s);
+            RING_NEXT();
         }
+    f32x4 sum[CHAINS ? TM : 1][TN];
+#define RING_ADD_CHAIN()                                                                                \
+    {                                                                                                   \
+        _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                  \
+            _Pragma("unroll") for (int j = 0; j < TN; ++j) sum[i][j] += acc[i][j];                      \
+    }
+#define RING_SEAM(T) (CHAINS ? min(seam, (T)) : (T))
+#define RING_AT_SEAM()                                                                                  \
+    if (CHAINS && t == seam) {                                                                          \
+        mfma16_settle(acc);                                                                             \
+        RING_ADD_CHAIN();                                                                               \
+        _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                  \
+            _Pragma("unroll") for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};       \
+        seam += chain;                                                                                  \
+    }
+    int seam = chain;
+    if constexpr (CHAINS) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     RING_WALK();
+#undef RING_SEAM
+#undef RING_AT_SEAM
+#undef RING_NEXT
 #undef RING_LOAD
 #undef RING_READ
+    if constexpr (CHAINS) {
+        RING_ADD_CHAIN();
+        ring_store<BM, BN, TM, TN, true>(g, sum, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
+        return;
+    }
+#undef RING_ADD_CHAIN
     ring_store<BM, BN, TM, TN, true>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
 }
 
@@ -391,15 +444,22 @@ hipError_t launch_nt(const GemmArgs &g, int first, hipStream_t s) {
     if (g.K % RK) return g.out_fp32 ? launch_nt_one<BM, BN, S, true, true>(g, first, s) : launch_nt_one<BM, BN, S, false, true>(g, first, s);
     return g.out_fp32 ? launch_nt_one<BM, BN, S, true, false>(g, first, s) : launch_nt_one<BM, BN, S, false, false>(g, first, s);
 }
-template <int BM, int BN, int S>
-hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
+template <int BM, int BN, int S, bool CHAINS>
+hipError_t launch_tn_one(const GemmArgs &g, int chain, hipStream_t s) {
     static bool attr = false;
     constexpr size_t lds = (size_t)S * (BM + BN) * 128;
-    const hipError_t e = ring_attr(ring_tn_kernel<BM, BN, S>, lds, &attr);
+    const hipError_t e = ring_attr(ring_tn_kernel<BM, BN, S, CHAINS>, lds, &attr);
     if (e != hipSuccess) return e;
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    hipLaunchKernelGGL((ring_tn_kernel<BM, BN, S>), dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g, tiles_m, tiles_n);
+    hipLaunchKernelGGL((ring_tn_kernel<BM, BN, S, CHAINS>), dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g,
+                       tiles_m, tiles_n, chain);
     return hipGetLastError();
+}
+// partial_sums: of every output, in all
+template <int BM, int BN, int S>
+hipError_t launch_tn(const GemmArgs &g, int partial_sums, hipStream_t s) {
+    const int chains = (partial_sums + g.split_k - 1) / g.split_k, stages = g.K / RK / g.split_k, chain = stages / chains & ~1;
+    return chains > 1 && chain > 0 ? launch_tn_one<BM, BN, S, true>(g, chain, s) : launch_tn_one<BM, BN, S, false>(g, 0, s);
 }
 
 }  // namespace
@@ -416,12 +476,12 @@ hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t
     }
 }
 
-hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, hipStream_t s) {
+hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s) {
     switch (tile) {
-        case RingTile::t256x128: return launch_tn<256, 128, 3>(g, s);
-        case RingTile::t128x128: return launch_tn<128, 128, 3>(g, s);
-        case RingTile::t128x64: return launch_tn<128, 64, 3>(g, s);
-        case RingTile::t64x64: return launch_tn<64, 64, 3>(g, s);
+        case RingTile::t256x128: return launch_tn<256, 128, 3>(g, partial_sums, s);
+        case RingTile::t128x128: return launch_tn<128, 128, 3>(g, partial_sums, s);
+        case RingTile::t128x64: return launch_tn<128, 64, 3>(g, partial_sums, s);
+        case RingTile::t64x64: return launch_tn<64, 64, 3>(g, partial_sums, s);
         default: return hipErrorInvalidValue;
     }
 }

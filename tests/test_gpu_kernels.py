@@ -221,8 +221,7 @@ def test_gemm_weight_gradient_with_split_reduction(orc64, n, out, inn, split):
 
 @pytest.mark.parametrize("n,out,inn,split", [(1024, 4352, 4360, 2), (1216, 4104, 4352, 5)])
 def test_gemm_weight_gradient_split_last_round(n, out, inn, split):
-    """More than 256 tiles of 256 x 256: only those of the last round are split, and only they may differ (by the order of fp32
-    sums) from the unsplit product; with and without accumulation."""
+    """More than 256 tiles of 256 x 256, split and unsplit, with and without accumulation."""
     g = torch.Generator(device="cuda").manual_seed(n)
     DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
     ref = DY.double().T @ X.double()
@@ -234,7 +233,58 @@ def test_gemm_weight_gradient_split_last_round(n, out, inn, split):
         for dw, sp in ((whole, 1), (cut, split)):
             ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, dw.data_ptr(), inn, out, inn, n, acc, sp, WS.data_ptr(), None))
             assert float((dw.double() - (1 + acc) * ref).abs().max()) <= 2 * tol
-    assert float((whole == cut).float().mean()) > 0.5   # 256 of at most 306 tiles are the same work
+
+
+@pytest.mark.parametrize("n,out,inn,split,sums", [(6016, 4352, 4360, 2, 2), (8192, 4104, 4352, 3, 3), (12288, 4352, 4360, 2, 4),
+                                                   (6528, 640, 4608, 3, 3), (11264, 448, 3272, 5, 5), (4224, 672, 3328, 2, 2),
+                                                   (10496, 2432, 272, 5, 5), (5440, 264, 296, 2, 2)])
+def test_gemm_weight_gradient_split_sums_every_tile_in_pieces(n, out, inn, split, sums):
+    """Every output is made of as many partial sums as its size asks for, whether they have a workgroup each or share one: bit
+    for bit the pieces' own products added in order."""
+    g = torch.Generator(device="cuda").manual_seed(n + split)
+    DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
+    WS = torch.full(((split - 1) * out * inn,), 9.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        got = torch.full((out, inn), 3.0, dtype=torch.float32, device="cuda")
+        want = got.clone()
+        ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, got.data_ptr(), inn, out, inn, n, acc, split, WS.data_ptr(), None))
+        for c in range(split):           # a chunk of the split: its pieces in order
+            part = want if c == 0 else torch.zeros_like(want)
+            for p in range(c * sums // split, (c + 1) * sums // split):
+                t0, t1 = p * (n // 64) // sums * 64, (p + 1) * (n // 64) // sums * 64
+                add = p > c * sums // split or (c == 0 and acc)
+                ok(L.mt_k_gemm_tn(DY[t0:].data_ptr(), out, X[t0:].data_ptr(), inn, part.data_ptr(), inn, out, inn, t1 - t0, add, None))
+            if c == 0 and split != sums:
+                whole = want.clone()     # tiles that are not split over workgroups: all pieces in order
+                for p in range(sums // split, sums):
+                    t0, t1 = p * (n // 64) // sums * 64, (p + 1) * (n // 64) // sums * 64
+                    ok(L.mt_k_gemm_tn(DY[t0:].data_ptr(), out, X[t0:].data_ptr(), inn, whole.data_ptr(), inn, out, inn, t1 - t0, 1, None))
+            if c > 0:
+                want += part
+        same = got == want if split == sums else (got == want) | (got == whole)
+        assert bool(same.all())
+
+
+@pytest.mark.parametrize("out,inn,n,sums", [(120, 640, 4288, 2), (4728, 792, 15232, 3), (2048, 1024, 16384, 6), (5632, 2048, 16384, 4),
+                                            (7168, 5120, 32768, 5)])
+def test_weight_gradient_is_as_exact_as_its_partial_sums(out, inn, n, sums):
+    """With the split that the training step takes, the error against 64 bits is that of `sums` partial sums, the number that keeps
+    256 x 256 tiles of these sizes busy, or smaller.  A chain of m additions rounds m times to a part of a growing sum: its
+    squared error grows with m^2, so `sums` chains of m / sums additions have 1 / sqrt(sums) of the error of one."""
+    g = torch.Generator(device="cuda").manual_seed(out)
+    DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
+    ref = torch.zeros((out, inn), dtype=torch.float64, device="cuda")
+    for t in range(0, n, 4096):
+        ref += DY[t:t + 4096].double().T.contiguous() @ X[t:t + 4096].double()
+    split = L.mt_k_gemm_tn_pick_split(out, inn, n, 256)
+    WS = torch.empty(max(1, split - 1) * out * inn, dtype=torch.float32, device="cuda")
+    got, one = (torch.zeros((out, inn), dtype=torch.float32, device="cuda") for _ in range(2))
+    ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, got.data_ptr(), inn, out, inn, n, 0, split, WS.data_ptr(), None))
+    DYT, XT = DY.T.contiguous(), X.T.contiguous()      # the general kernel: one chain
+    ok(L.mt_k_gemm_nt(DYT.data_ptr(), n, XT.data_ptr(), n, one.data_ptr(), inn, None, 0, out, inn, n, 1, 0, None))
+    err, err_one = (float((x.double() - ref).norm() / ref.norm()) for x in (got, one))
+    print(f"[wgrad] {out} x {inn} x {n}: split {split}, error {err:.3e}, one chain {err_one:.3e}", flush=True)
+    assert err <= 1.05 * err_one / sums ** 0.5
 
 
 def test_split_choice_for_the_benchmark_shapes():
