@@ -124,7 +124,10 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
 // One wave per row at every width, loads on demand and rows beyond 4096 read twice took (gain-gradient sum included)
 // 722 us for 65 536 x 5120, 479 for x 4096, 145 for x 1024; this kernel takes 518, 398 and 102 (5.2 and 5.4 TB/s at the
 // first two; a copy reaches 4.9).
-constexpr int kNormBwdBlocks = 512;
+// A row of its own per block also makes a thread's chain of additions four times as long: it is cut every 32 rows, so that the
+// gain gradient of many rows stays as exact as with a chain per wave (262 144 rows, d = 1032, relative error against 64 bits:
+// one chain 4.2e-7, a chain per wave 2.7e-7, cut 1.6e-7).
+constexpr int kNormBwdBlocks = 512, kNormChain = 32;
 
 template <int NCH, int WPR>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *partial, const bf16_t *dy, const bf16_t *x,
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
     static_assert(WPR == 1 || WPR == 4, "a row belongs to one wave or to the whole block");
     constexpr int TPR = 64 * WPR, RPB = 4 / WPR;   // threads per row, rows per block at a time
     __shared__ float red[2][2][4];                 // [parity of the row][sum x^2, dot][wave]
-    __shared__ float dgs[WPR == 1 ? 8 * TPR * NCH : 1];
+    __shared__ float dgs[8 * TPR * NCH];           // WPR == 1: one set for the four waves; 4: the sums of each thread's ended chains
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = threadIdx.x % TPR;
     const int nch = d >> 3;
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
@@ -157,8 +160,28 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
     };
     const int64_t row0 = (int64_t)blockIdx.x * RPB + (WPR == 1 ? wave : 0), stride = (int64_t)gridDim.x * RPB;
     if (row0 < n) fetch(row0);
-    int par = 0;
+    bool ended = false;
+    const auto end_chain = [&]() {   // dg += the chains before
+        if (!ended) return;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) dg[i][k] = dgs[(i * 8 + k) * TPR + tr] + dg[i][k];
+    };
+    int par = 0, chain = 0;
     for (int64_t row = row0; row < n; row += stride, par ^= 1) {   // WPR == 4: the same rows in every wave of the block
+        if (WPR == 4 && ++chain > kNormChain) {
+            end_chain();
+#pragma unroll
+            for (int i = 0; i < NCH; ++i)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    dgs[(i * 8 + k) * TPR + tr] = dg[i][k];
+                    dg[i][k] = 0.f;
+                }
+            ended = true;
+            chain = 1;
+        }
         uint4 xv[NCH], yv[NCH], rv[NCH];
         float ss = 0.f, dot = 0.f;
 #pragma unroll
@@ -206,6 +229,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
             if (c < nch) reinterpret_cast<uint4 *>(dx + row * d)[c] = pack8(of);
         }
     }
+    if constexpr (WPR == 4) end_chain();
     if constexpr (WPR == 1) {   // the four waves' sums, ((w0 + w1) + w2) + w3
         for (int w = 0; w < 4; ++w) {
             if (wave == w)

@@ -409,6 +409,37 @@ def test_rmsnorm_at_the_widths_where_the_kernels_change(orc64, n, d):
     assert np.all(host(DG)[d:] == 4.0)
 
 
+@pytest.mark.parametrize("d", [1032, 2056])
+def test_rmsnorm_gain_gradient_of_many_rows_is_as_exact_as_short_chains(d):
+    """The gain gradient of 262 144 rows against 64 bits: no further off than the same fp32 terms added as 2048 chains of 128 rows,
+    4 chains to a block, the blocks' sums in 8 chains of 64."""
+    n = 1 << 18
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X, DY = (torch.randn((n, d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    G = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    DX, DG = torch.empty_like(X), torch.empty(d, dtype=torch.float32, device="cuda")
+    ws = torch.empty(L.mt_k_rmsnorm_bwd_ws_bytes(d) // 4, dtype=torch.float32, device="cuda")
+    ok(L.mt_k_rmsnorm_bwd(DX.data_ptr(), DG.data_ptr(), DY.data_ptr(), X.data_ptr(), G.data_ptr(), None, ws.data_ptr(), n, d, 1e-5, None))
+    ref = torch.zeros(d, dtype=torch.float64, device="cuda")
+    chains = torch.zeros((2048, d), dtype=torch.float32, device="cuda")
+    for t in range(0, n, 2048):                       # rows t .. t + 2047: the next term of each chain
+        x, dy = X[t:t + 2048].double(), DY[t:t + 2048].double()
+        r = 1.0 / torch.sqrt((x * x).mean(dim=1, keepdim=True) + 1e-5)
+        ref += (dy * x * r).sum(dim=0)
+        chains += DY[t:t + 2048].float() * X[t:t + 2048].float() * r.float()
+
+    def add(parts):                                   # [chains, terms, d] -> [chains, d], one term after the other
+        s = parts[:, 0].clone()
+        for i in range(1, parts.shape[1]):
+            s += parts[:, i]
+        return s
+    blocks = add(chains.view(512, 4, d))
+    short = add(add(blocks.view(64, 8, d).transpose(0, 1)).view(1, 8, d))[0]
+    err, err_short = (float((v.double() - ref).norm() / ref.norm()) for v in (DG, short))
+    print(f"[norm] d {d}: error {err:.3e}, short chains {err_short:.3e}", flush=True)
+    assert err <= 1.1 * err_short                     # norms over 1032 values and more: spread about 2 %
+
+
 # ----------------------------------------------------------------------------- RoPE
 @pytest.mark.parametrize("hd,base", [(64, 10000.0), (128, 1.0e6)])
 def test_rope_forward_and_inverse(orc64, hd, base):
