@@ -128,7 +128,8 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
 // a row of any width fits the registers next to its gain gradient.  The next row is requested before this one is reduced.
 // One wave per row at every width, loads on demand and rows beyond 4096 read twice took (gain-gradient sum included)
 // 722 us for 65 536 x 5120, 479 for x 4096, 145 for x 1024; this kernel takes 518, 398 and 102 (5.2 and 5.4 TB/s at the
-// first two; a copy reaches 4.9).
+// first two; a copy reaches 4.9), and since its loads have no branches (selecting zeros for them put the zeros and the
+// selected address into scratch memory) 372, 288 and 74 on a box where it took 446, 305 and 79.
 // A row of its own per block also makes a thread's chain of additions four times as long: it is cut every 32 rows, so that the
 // gain gradient of many rows stays as exact as with a chain per wave (262 144 rows, d = 1032, relative error against 64 bits:
 // one chain 4.2e-7, a chain per wave 2.7e-7, cut 1.6e-7).
@@ -143,25 +144,26 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
     __shared__ float dgs[8 * TPR * NCH];           // WPR == 1: one set for the four waves; 4: the sums of each thread's ended chains
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tr = threadIdx.x % TPR;
     const int nch = d >> 3;
-    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
     float dg[NCH][8];
     uint4 gv[NCH], xn[NCH], yn[NCH], rn[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = tr + TPR * i;
-        gv[i] = c < nch ? reinterpret_cast<const uint4 *>(gain)[c] : zero;
+        gv[i] = reinterpret_cast<const uint4 *>(gain)[min(tr + TPR * i, nch - 1)];
+        rn[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
         for (int k = 0; k < 8; ++k) dg[i][k] = 0.f;
     }
+    // without branches (chunks past the row re-read its last one and are left out of the sums)
     auto fetch = [&](int64_t row) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int c = tr + TPR * i;
-            const bool ok = c < nch;
-            xn[i] = ok ? reinterpret_cast<const uint4 *>(x + row * d)[c] : zero;
-            yn[i] = ok ? reinterpret_cast<const uint4 *>(dy + row * d)[c] : zero;
-            rn[i] = ok && dres ? reinterpret_cast<const uint4 *>(dres + row * d)[c] : zero;
+            const int64_t c = row * nch + min(tr + TPR * i, nch - 1);
+            xn[i] = reinterpret_cast<const uint4 *>(x)[c];
+            yn[i] = reinterpret_cast<const uint4 *>(dy)[c];
         }
+        if (!dres) return;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) rn[i] = reinterpret_cast<const uint4 *>(dres)[row * nch + min(tr + TPR * i, nch - 1)];
     };
     const int64_t row0 = (int64_t)blockIdx.x * RPB + (WPR == 1 ? wave : 0), stride = (int64_t)gridDim.x * RPB;
     if (row0 < n) fetch(row0);
@@ -198,11 +200,15 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
             unpack8(xv[i], xf);
             unpack8(yv[i], yf);
             unpack8(gv[i], gf);
+            float s1 = 0.f, s2 = 0.f;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                ss += xf[k] * xf[k];
-                dot += gf[k] * yf[k] * xf[k];
+                s1 += xf[k] * xf[k];
+                s2 += gf[k] * yf[k] * xf[k];
             }
+            const bool in_row = tr + TPR * i < nch;
+            ss += in_row ? s1 : 0.f;
+            dot += in_row ? s2 : 0.f;
         }
         if (row + stride < n) fetch(row + stride);
         ss = wave_sum(ss);
@@ -261,23 +267,25 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
     }
 }
 
-// out[j] (+)= sum over rows of partial[r][j].  A block owns 32 columns, four per lane; its 128 row groups each add every
-// 128th row in order (at most 4 of the 512 rows that the callers produce: all of them in flight together) and the group
+// out[j] (+)= sum over rows of partial[r][j].  A block owns 32 columns, four per lane; its RG row groups each add every
+// RG-th row in order (at most 4 of the 512 rows that the callers produce: all of them in flight together) and the group
 // sums are added in a fixed tree, so the result does not depend on the launch.  Bound by latency, not by the 10 MB:
-// 512 x 5120 took 20.6 us with one float per lane and 8 row groups, 5.0 us so.
-__global__ __launch_bounds__(1024) void colsum_kernel(float *out, const float *partial, int nrows, int d, int accumulate) {
-    __shared__ f32x4 red[128][8];
+// 512 x 5120 took 20.6 us with one float per lane and 8 row groups, 5.0 us with 128.  Few rows take fewer groups (the same
+// sums: the others would add zeros): less of the chip and fewer barriers.
+template <int RG>
+__global__ __launch_bounds__(8 * RG) void colsum_kernel(float *out, const float *partial, int nrows, int d, int accumulate) {
+    __shared__ f32x4 red[RG][8];
     const int cl = threadIdx.x & 7, rg = threadIdx.x >> 3;
     const int j = blockIdx.x * 32 + cl * 4;   // d is a multiple of 8
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (j < d) {
 #pragma unroll 4
-        for (int r = rg; r < nrows; r += 128) s += *reinterpret_cast<const f32x4_a4 *>(partial + (int64_t)r * d + j);
+        for (int r = rg; r < nrows; r += RG) s += *reinterpret_cast<const f32x4_a4 *>(partial + (int64_t)r * d + j);
     }
     red[rg][cl] = s;
     __syncthreads();
 #pragma unroll
-    for (int h = 64; h > 0; h >>= 1) {
+    for (int h = RG / 2; h > 0; h >>= 1) {
         if (rg < h) red[rg][cl] += red[rg + h][cl];
         __syncthreads();
     }
@@ -285,6 +293,12 @@ __global__ __launch_bounds__(1024) void colsum_kernel(float *out, const float *p
         f32x4_a4 *o = reinterpret_cast<f32x4_a4 *>(out + j);
         *o = accumulate ? *o + red[0][cl] : red[0][cl];
     }
+}
+void launch_colsum(float *out, const float *partial, int nrows, int d, int accumulate, hipStream_t s) {
+    const dim3 grid((unsigned)((d + 31) / 32));
+    if (nrows <= 8) hipLaunchKernelGGL(colsum_kernel<8>, grid, dim3(64), 0, s, out, partial, nrows, d, accumulate);
+    else if (nrows <= 32) hipLaunchKernelGGL(colsum_kernel<32>, grid, dim3(256), 0, s, out, partial, nrows, d, accumulate);
+    else hipLaunchKernelGGL(colsum_kernel<128>, grid, dim3(1024), 0, s, out, partial, nrows, d, accumulate);
 }
 
 // ------------------------------------------------------------------ bias gradient (column sums of a bf16 matrix)
@@ -676,8 +690,7 @@ hipError_t rmsnorm_bwd(bf16_t *dx_out, float *dgain, const bf16_t *dy, const bf1
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, dx_out, partial, dy, x, gain, dres, n, d, eps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(d, 32)), dim3(1024), 0, s, dgain, partial, (int)grid, d,
-                       accumulate_dgain);
+    launch_colsum(dgain, partial, (int)grid, d, accumulate_dgain, s);
     return hipGetLastError();
 }
 
@@ -716,7 +729,7 @@ hipError_t bias_grad(float *db, const bf16_t *x, int64_t ld, int64_t n, int32_t 
                        ld, n, cols, rpb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(blocks_for(cols, 32)), dim3(1024), 0, s, db, ws, kBiasGradRowBlocks, cols, 0);
+    launch_colsum(db, ws, kBiasGradRowBlocks, cols, 0, s);
     return hipGetLastError();
 }
 
