@@ -69,7 +69,8 @@ int32_t mt_k_gemm_tn(const uint16_t *At, int64_t lda, const uint16_t *Bt, int64_
  * of workgroups badly.  The tiles of that round (of large outputs), or all tiles (of small ones), have a workgroup per chunk:
  * chunk 0 writes C, chunk s > 0 its tiles of a slice of ws (device, at least (split_k - 1) * M * N floats, 16-byte aligned),
  * and a second kernel adds them to C in order, so the result is deterministic.  Every output is made of at least as many
- * partial sums as keep the precision of a sum over K terms (1 to 6, by M, N and K), whichever tiles share a workgroup.
+ * partial sums as keep the precision of a sum over K terms (1 to 6, by M, N and K), and with any split other than the one
+ * that mt_k_gemm_tn_pick_split returns of at least split_k, whichever tiles share a workgroup.
  * 1 <= split_k <= K / 64; split_k > 1 needs N % 4 == 0, ldc % 4 == 0 and a 16-byte aligned C.
  * mt_k_gemm_tn_pick_split returns the split the training step would choose on n_cu compute units. */
 int32_t mt_k_gemm_tn_split(const uint16_t *At, int64_t lda, const uint16_t *Bt, int64_t ldb, float *C, int64_t ldc, int32_t M,

@@ -158,7 +158,8 @@ struct GemmArgs {
     // round (256 x 256 kernel) or for all tiles (smaller ones); chunk 0 stores to C, chunk s > 0 to split_ws + (s - 1) M N
     // (fp32, pitch N; where a tile is not split, left as it is), and a second kernel adds them to C in that order.  With
     // split_k > 1, and in the kernels with smaller tiles always, every output is made of as many partial sums as its size
-    // asks for (1 to 6), whether they have a workgroup each or share one.
+    // asks for (1 to 6), whether they have a workgroup each or share one; with a split that is not gemm_tn_pick_split's own of at
+    // least split_k.
     int32_t split_k = 1;
     float *split_ws = nullptr;
     // tile order of the large-grid kernels: tile rows per group (a group is walked column by column); 0 = kGroupMLarge

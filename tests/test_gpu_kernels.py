@@ -235,11 +235,11 @@ def test_gemm_weight_gradient_split_last_round(n, out, inn, split):
             assert float((dw.double() - (1 + acc) * ref).abs().max()) <= 2 * tol
 
 
-@pytest.mark.parametrize("n,out,inn,split,sums", [(6016, 4352, 4360, 2, 2), (8192, 4104, 4352, 3, 3), (12288, 4352, 4360, 2, 4),
+@pytest.mark.parametrize("n,out,inn,split,sums", [(6016, 4352, 4360, 2, 2), (3072, 4352, 4360, 3, 3), (8192, 4104, 4352, 3, 3), (12288, 4352, 4360, 2, 4),
                                                    (6528, 640, 4608, 3, 3), (11264, 448, 3272, 5, 5), (4224, 672, 3328, 2, 2),
                                                    (10496, 2432, 272, 5, 5), (5440, 264, 296, 2, 2)])
 def test_gemm_weight_gradient_split_sums_every_tile_in_pieces(n, out, inn, split, sums):
-    """Every output is made of as many partial sums as its size asks for, whether they have a workgroup each or share one: bit
+    """Every output is made of as many partial sums as its size asks for, or as its caller, whether they have a workgroup each or share one: bit
     for bit the pieces' own products added in order."""
     g = torch.Generator(device="cuda").manual_seed(n + split)
     DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
@@ -285,6 +285,26 @@ def test_weight_gradient_is_as_exact_as_its_partial_sums(out, inn, n, sums):
     err, err_one = (float((x.double() - ref).norm() / ref.norm()) for x in (got, one))
     print(f"[wgrad] {out} x {inn} x {n}: split {split}, error {err:.3e}, one chain {err_one:.3e}", flush=True)
     assert err <= 1.05 * err_one / sums ** 0.5
+
+
+@pytest.mark.parametrize("out,inn,n,split", [(22016, 4096, 16384, 4), (4352, 4360, 1024, 3)])
+def test_weight_gradient_split_of_the_callers_own(out, inn, n, split):
+    """A split that is not the training step's choice is taken at its word: that many partial sums of every output, also in the
+    tiles of full rounds (which made one chain: 1 / sqrt(split) of its error is then the bound, as above)."""
+    assert L.mt_k_gemm_tn_pick_split(out, inn, n, 256) != split
+    g = torch.Generator(device="cuda").manual_seed(out)
+    DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
+    ref = torch.zeros((out, inn), dtype=torch.float64, device="cuda")
+    for t in range(0, n, 4096):
+        ref += DY[t:t + 4096].double().T.contiguous() @ X[t:t + 4096].double()
+    WS = torch.empty((split - 1) * out * inn, dtype=torch.float32, device="cuda")
+    got, one = (torch.zeros((out, inn), dtype=torch.float32, device="cuda") for _ in range(2))
+    ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, got.data_ptr(), inn, out, inn, n, 0, split, WS.data_ptr(), None))
+    DYT, XT = DY.T.contiguous(), X.T.contiguous()
+    ok(L.mt_k_gemm_nt(DYT.data_ptr(), n, XT.data_ptr(), n, one.data_ptr(), inn, None, 0, out, inn, n, 1, 0, None))
+    err, err_one = (float((x.double() - ref).norm() / ref.norm()) for x in (got, one))
+    print(f"[wgrad] {out} x {inn} x {n}: own split {split}, error {err:.3e}, one chain {err_one:.3e}", flush=True)
+    assert err <= 1.05 * err_one / split ** 0.5
 
 
 def test_split_choice_for_the_benchmark_shapes():
