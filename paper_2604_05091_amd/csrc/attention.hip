@@ -750,20 +750,11 @@ bool rope_tables_ok(const AttnArgs &a) {
 
 }  // namespace
 
-template <typename K>
-static hipError_t ensure_lds(K kernel, size_t bytes, bool *done) {
-    if (*done || bytes <= 48 * 1024) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess) *done = true;
-    return e;
-}
-
 template <int HD, int QW, int KW>
 static hipError_t launch_fwd(const AttnArgs &a, hipStream_t s) {
     constexpr size_t lds = 2 * (2 * 64 * (HD + kFwdPad)) * sizeof(bf16_t);
     static_assert(KW == 1 || (size_t)QW * (HD / 32 * 16 + 2) * 64 * sizeof(float) <= lds, "room for the other half's sums");
-    static bool done = false;
+    static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW>, lds, &done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
@@ -775,7 +766,7 @@ template <int HD, int QW, int KW>
 static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
     constexpr size_t lds = 2 * (2 * 64 * (HD + kDqPad)) * sizeof(bf16_t);
     static_assert(KW == 1 || (size_t)QW * (HD / 32 * 16) * 64 * sizeof(float) <= lds, "room for the other half's sums");
-    static bool done = false;
+    static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW>, lds, &done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
@@ -820,7 +811,7 @@ static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     // V [KB][hd + 8] | two stages of Q, dO [64][hd + pad] + 64 lse + 64 delta
     constexpr size_t lds = (KB * (HD + 8) + 2 * (2 * 64 * (HD + kDkdvPad))) * sizeof(bf16_t) + 2 * 512;
     static_assert(QW == 1 || (size_t)KW * (HD / 32) * 16 * 64 * sizeof(float) <= lds, "room for the other half's sums");
-    static bool done = false;
+    static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW>, lds, &done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW>), dim3(grid_blocks((a.T + KB - 1) / KB, a.B * a.Hkv)),

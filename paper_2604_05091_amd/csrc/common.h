@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <atomic>
 
 namespace mt {
 
@@ -124,6 +125,16 @@ __device__ __forceinline__ int gemm_walk_start(int tm, int nk) {
 #endif  // __HIPCC__
 
 // ---------------------------------------------------------------- launchers (host side)
+// More than 48 KB of dynamic LDS have to be asked for once per kernel (done: that kernel's own flag; threads that launch
+// it for the first time at the same time may both ask).
+template <typename K>
+inline hipError_t ensure_lds(K kernel, size_t bytes, std::atomic<bool> *done) {
+    if (done->load(std::memory_order_relaxed) || bytes <= 48 * 1024) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) done->store(true, std::memory_order_relaxed);
+    return e;
+}
+
 // Every launcher validates nothing: callers (engine, C ABI wrappers) check shapes first.
 
 // C[M,N] = A[M,K] . B[N,K]^T (+ R) ; A, B bf16 with the reduction index contiguous.

@@ -419,19 +419,11 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
     ring_store<BM, BN, TM, TN, true>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
 }
 
-template <typename K>
-hipError_t ring_attr(K kernel, size_t lds, bool *attr_set) {
-    if (*attr_set) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    *attr_set = e == hipSuccess;
-    return e;
-}
-
 template <int BM, int BN, int S, bool F32, bool TAIL>
 hipError_t launch_nt_one(const GemmArgs &g, int first, hipStream_t s) {
-    static bool attr = false;
+    static std::atomic<bool> attr{false};
     constexpr size_t lds = (size_t)S * (BM + BN) * 128;
-    const hipError_t e = ring_attr(ring_nt_kernel<BM, BN, S, F32, TAIL>, lds, &attr);
+    const hipError_t e = ensure_lds(ring_nt_kernel<BM, BN, S, F32, TAIL>, lds, &attr);
     if (e != hipSuccess) return e;
     const int bm = first < 0 ? BM : 256, bn = first < 0 ? BN : 256;
     const int tiles_m = (g.M + bm - 1) / bm, tiles_n = (g.N + bn - 1) / bn;
@@ -446,9 +438,9 @@ hipError_t launch_nt(const GemmArgs &g, int first, hipStream_t s) {
 }
 template <int BM, int BN, int S, bool CHAINS>
 hipError_t launch_tn_one(const GemmArgs &g, int chain, hipStream_t s) {
-    static bool attr = false;
+    static std::atomic<bool> attr{false};
     constexpr size_t lds = (size_t)S * (BM + BN) * 128;
-    const hipError_t e = ring_attr(ring_tn_kernel<BM, BN, S, CHAINS>, lds, &attr);
+    const hipError_t e = ensure_lds(ring_tn_kernel<BM, BN, S, CHAINS>, lds, &attr);
     if (e != hipSuccess) return e;
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     hipLaunchKernelGGL((ring_tn_kernel<BM, BN, S, CHAINS>), dim3((unsigned)(tiles_m * tiles_n * g.split_k)), dim3(256), lds, s, g,
