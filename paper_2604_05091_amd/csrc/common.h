@@ -199,6 +199,11 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s);
 // Reduction split for gemm_tn that minimises the estimated time of an M x N x K weight-gradient product on n_cu
 // compute units without summing it in longer chains than its size allows, 1 = none; the workspace is (split - 1) * M * N floats.
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu);
+// What gemm_nt (without a fused store) and gemm_tn take for a product, for tests and tools (no launch; a diagnostic override is left
+// out).  nt: the first `whole` tiles of 256 x 256 go to that kernel, the others to tiles of tile_m x tile_n (0: there are none).
+// tn: tiles of tile_m x tile_n, `whole` of which a workgroup walks alone in the 256 x 256 kernel.
+void gemm_nt_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
+void gemm_tn_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
 
 // out[b][c][r] = in[b][r][c] for r < rows, c < cols (bf16); leading dimensions in elements.
 // Two batch levels (b0 < nb0, b1 < nb1) with independent strides on each side.

@@ -895,6 +895,37 @@ bool gemm_nt_fuses_glu_bwd(const GemmArgs &g) {
            !((uintptr_t)g.glu_bwd_gu & 15);
 }
 
+// What takes an NT product without a fused store: the first `whole` tiles of 256 x 256 in the tile order the kernel above, the others
+// that of `tile` (null: there are none).
+struct NtRoute { int whole; const TileCost *tile; };
+static NtRoute nt_route(const GemmArgs &g) {
+    TileCost costs[sizeof kNtCosts / sizeof kNtCosts[0]];
+    std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
+    if (!whole_line_store(g)) costs[0].fixed += kGuardedStore;
+    const TileCost &one = choose_tile(costs, g.M, g.N, g.K, 1);
+    // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
+    // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
+    // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
+    const double stages = (double)((g.K + BK - 1) / BK), tiles = tile_count(costs[0], g.M, g.N);
+    const int whole = (int)(std::floor(tiles / kRound) * kRound), rest = (int)tiles - whole;
+    if (g.K % BK == 0 && whole > 0 && rest > 0) {
+        double best_t = 0.97 * tn_time(one, g.M, g.N, stages, 1, kComputeUnits);
+        int small = 0;
+        for (int i = 1; i < (int)std::size(kNtCosts); ++i) {
+            const TileCost &c = kNtCosts[i];
+            const double t = tile_time(costs[0], whole, stages, kComputeUnits) + 3.0 +
+                             tile_time(c, (double)rest * (256 / c.bm) * (256 / c.bn), stages, kComputeUnits);
+            if (t < best_t) {
+                best_t = t;
+                small = i;
+            }
+        }
+        if (small) return {whole, &kNtCosts[small]};
+    }
+    if (one.tile == RingTile::none) return {(int)tiles, nullptr};
+    return {0, &kNtCosts[&one - costs]};
+}
+
 hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
     GemmArgs g = g0;
     if (group_m_override() > 0) g.group_m = group_m_override();
@@ -917,33 +948,17 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
         case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
         default: break;
     }
-    TileCost costs[sizeof kNtCosts / sizeof kNtCosts[0]];
-    std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
-    if (!whole_line_store(g)) costs[0].fixed += kGuardedStore;
-    const TileCost &one = choose_tile(costs, g.M, g.N, g.K, 1);
-    // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
-    // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
-    // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
-    const double stages = (double)((g.K + BK - 1) / BK), tiles = tile_count(costs[0], g.M, g.N);
-    const int whole = (int)(std::floor(tiles / kRound) * kRound), rest = (int)tiles - whole;
-    if (g.K % BK == 0 && whole > 0 && rest > 0) {
-        double best_t = 0.97 * tn_time(one, g.M, g.N, stages, 1, kComputeUnits);
-        const TileCost *small = nullptr;
-        for (const TileCost &c : costs) {
-            if (c.tile == RingTile::none) continue;
-            const double t = tile_time(costs[0], whole, stages, kComputeUnits) + 3.0 +
-                             tile_time(c, (double)rest * (256 / c.bm) * (256 / c.bn), stages, kComputeUnits);
-            if (t < best_t) {
-                best_t = t;
-                small = &c;
-            }
-        }
-        if (small) {
-            const hipError_t e = launch_w4e(g, s, whole);
-            return e == hipSuccess ? gemm_nt_ring(g, small->tile, whole, s) : e;
-        }
-    }
-    return one.tile == RingTile::none ? launch_w4e(g, s) : gemm_nt_ring(g, one.tile, -1, s);
+    const NtRoute r = nt_route(g);
+    if (r.whole == 0) return gemm_nt_ring(g, r.tile->tile, -1, s);
+    const hipError_t e = launch_w4e(g, s, r.whole);
+    return e == hipSuccess && r.tile ? gemm_nt_ring(g, r.tile->tile, r.whole, s) : e;
+}
+
+void gemm_nt_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n) {
+    const NtRoute r = nt_route(g);
+    *whole = r.whole;
+    *tile_m = r.tile ? r.tile->bm : 0;
+    *tile_n = r.tile ? r.tile->bn : 0;
 }
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
@@ -1020,6 +1035,13 @@ hipError_t gemm_tn(const GemmArgs &g, hipStream_t s) {
     hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, reinterpret_cast<float *>(g.C),
                        g.ldc, g.split_ws, g.split_k - 1, g.M, g.N);
     return hipGetLastError();
+}
+
+void gemm_tn_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n) {
+    const TileCost &c = choose_tile(kTnCosts, g.M, g.N, g.K, g.split_k);
+    *whole = c.tile == RingTile::none ? tn_big_route(c, g.M, g.N, g.K / BK, g.split_k, tn_sums_of_split(g), kComputeUnits).n_whole : 0;
+    *tile_m = c.bm;
+    *tile_n = c.bn;
 }
 
 }  // namespace mt

@@ -33,6 +33,13 @@ ROW1, ROW2, ROW_ATT_BWD, ROW_FLOOR = 2.0 ** -7, 2.0 ** -6, 2.0 ** -5, 2.0 ** -9
 
 
 # ----------------------------------------------------------------------------- GEMM
+def gemm_route(token_major, M, N, K, ldc=0, split=1):
+    """(256 x 256 tiles that a workgroup of the large-grid kernel takes alone, tile of the others)"""
+    r = (ctypes.c_int32 * 3)()
+    ok(L.mt_k_gemm_route(token_major, M, N, K, ldc or N, split, ctypes.addressof(r)))
+    return r[0], (r[1], r[2])
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 1376, 256), (256, 256, 688), (300, 200, 136), (72, 1024, 264),
                                    (4000, 3100, 200), (4096, 3072, 128)])
 def test_gemm_nt_bf16_out(orc64, M, N, K):
@@ -70,8 +77,9 @@ def test_gemm_nt_residual_strides_fp32_accumulate(orc64):
 
 @pytest.mark.parametrize("M,N,K", [(4100, 3080, 192), (3840, 3328, 64), (256 * 14, 256 * 14, 320)])
 def test_gemm_large_grid_kernel_all_epilogues(orc64, M, N, K):
-    """Problems with >= 192 tiles of 256 x 256 and K % 64 == 0 take the 4-wave pipelined kernel: ragged
+    """Grids of around 200 tiles of 256 x 256, the last in that kernel, the others in 64 x 64 tiles: ragged
     and exact edges, odd and even step counts, bf16 with residual and strides, fp32 with accumulate."""
+    assert gemm_route(0, M, N, K, N + 8) == ((196, (0, 0)) if K == 320 else (0, (64, 64)))
     rng = np.random.default_rng(M * 7 + N * 3 + K)
     lda, ldb, ldc, ldr = K + 8, K + 16, N + 8, N + 24
     a_full, b_full = bf16_round(rng.standard_normal((M, lda))), bf16_round(rng.standard_normal((N, ldb)))
@@ -95,7 +103,7 @@ def test_gemm_large_grid_kernel_all_epilogues(orc64, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(300, 200, 136), (4100, 3080, 128)])
 def test_gemm_bias_epilogue_and_bias_gradient(orc64, M, N, K):
-    """C = A B^T + bias in both GEMM kernels (small grid / large grid), and db = column sums."""
+    """C = A B^T + bias in small tiles (a small and a larger grid), and db = column sums."""
     rng = np.random.default_rng(M + N)
     a, b = bf16_round(rng.standard_normal((M, K))), bf16_round(rng.standard_normal((N, K)))
     bias = bf16_round(rng.standard_normal(N))
@@ -112,15 +120,52 @@ def test_gemm_bias_epilogue_and_bias_gradient(orc64, M, N, K):
     assert np.max(np.abs(host(DB) - want)) <= 1e-5 * np.sqrt(M) * np.max(np.abs(host(C)))
 
 
+@pytest.mark.parametrize("M,N,K,pad", [(2439, 5888, 64, 8), (2440, 5888, 128, 0), (2439, 5888, 192, 8),       # whole lines
+                                       (2445, 3272, 4160, 0), (2560, 3272, 4096, 8), (2445, 3306, 4096, 3),  # ragged columns
+                                       (2560, 3328, 4160, 1)])                                               # unaligned rows
+def test_gemm_256_tiles_every_store(M, N, K, pad):
+    """The kernel with 256 x 256 tiles: plain, residual, bias, fp32 and accumulating stores, whole lines and guarded ones, one step,
+    two, and odd and even numbers of them."""
+    ldc, ldr = N + pad, N + 2 * pad
+    assert gemm_route(0, M, N, K, ldc)[1] == (0, 0)
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B, R, BI = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, K), (N, K), (M, ldr), (1, N)))
+    ref = A.double() @ B.double().T.contiguous()
+    C = torch.zeros((M, ldc), dtype=torch.bfloat16, device="cuda")
+    for what, add in (("plain", 0), ("residual", R[:, :N].double()), ("bias", BI.double())):
+        if what == "bias":
+            ok(L.mt_k_gemm_nt_bias(A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), ldc, BI.data_ptr(), M, N, K, None))
+        else:
+            ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), ldc, R.data_ptr() if what == "residual" else None, ldr,
+                              M, N, K, 0, 0, None))
+        want = ref + add
+        # one rounding to bf16 (2^-9 of the value) after fp32 sums
+        assert bool(((C[:, :N].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * K ** 0.5).all()), what
+        assert bool((C[:, N:] == 0).all()), what
+    F = torch.full((M, ldc), 3.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, F.data_ptr(), ldc, None, 0, M, N, K, 1, acc, None))
+        # each of K additions rounds to 2^-24 of a partial sum of at most about 10 sqrt(K)
+        assert float((F[:, :N].double() - (1 + acc) * ref).abs().max()) <= K * 2.0 ** -24 * 10 * K ** 0.5
+    assert bool((F[:, N:] == 3).all())
+
+
 # Sizes around the edges of the smaller tiles (64 x 64, 128 x 64, 128 x 128, 256 x 128) and of the ring of three stages:
 # one stage and less, two, three, four and more, odd counts, partial last stages; columns and pitches that are whole
 # 16-byte chunks and that are not.
-@pytest.mark.parametrize("M,N,K,pad", [(8, 8, 8, 0), (64, 64, 64, 0), (65, 63, 72, 1), (130, 200, 128, 8), (333, 72, 184, 4),
-                                       (256, 512, 256, 8), (1000, 520, 328, 0), (1000, 1030, 1000, 2), (2050, 1544, 448, 8),
-                                       (3000, 1024, 136, 0), (2304, 2056, 200, 3)])
-def test_gemm_small_tiles_edges(orc64, M, N, K, pad):
+T64, T128X64, T128, T256X128 = (64, 64), (128, 64), (128, 128), (256, 128)
+@pytest.mark.parametrize("M,N,K,pad,tile", [(8, 8, 8, 0, T64), (64, 64, 64, 0, T64), (65, 63, 72, 1, T64), (130, 200, 128, 8, T64),
+                                            (333, 72, 184, 4, T64), (256, 512, 256, 8, T64), (1000, 520, 328, 0, T64),
+                                            (1000, 1030, 1000, 2, T64), (2050, 1544, 448, 8, T128), (3000, 1024, 136, 0, T64),
+                                            (2304, 2056, 200, 3, T64),
+                                            (641, 4520, 72, 8, T128X64), (5591, 518, 128, 1, T128X64), (514, 5632, 128, 0, T128X64),
+                                            (518, 5449, 328, 3, T128), (4867, 585, 320, 0, T128), (578, 5120, 328, 8, T128),
+                                            (1410, 4945, 72, 1, T256X128), (1223, 5714, 128, 2, T256X128), (1542, 4608, 128, 8, T256X128),
+                                            (1543, 4608, 72, 0, T256X128)])
+def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
     rng = np.random.default_rng(M * 5 + N * 3 + K)
     lda, ldb, ldc, ldr = K + 8, K + 16, N + pad, N + 3 * pad
+    assert gemm_route(0, M, N, K, ldc) == (0, tile)
     a, b = bf16_round(rng.standard_normal((M, lda))), bf16_round(rng.standard_normal((N, ldb)))
     r, bias = bf16_round(rng.standard_normal((M, ldr))), bf16_round(rng.standard_normal(N))
     ref = orc64.linear_fwd(np.ascontiguousarray(a[:, :K]), np.ascontiguousarray(b[:, :K]))
@@ -139,18 +184,28 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad):
     assert np.all(host(F)[:, N:] == 3)
 
 
-@pytest.mark.parametrize("M,N,K", [(4096, 5120, 128), (4360, 4352, 64), (4100, 4616, 192), (3000, 5632, 320)])
-def test_gemm_rest_of_the_rounds_in_smaller_tiles(M, N, K):
-    """A little more than 256 tiles of 256 x 256: the full round in those, the rest in smaller ones; complete and ragged edges."""
+@pytest.mark.parametrize("M,N,K,whole,tile", [(4096, 5120, 128, 0, T128X64), (4360, 4352, 64, 0, T64), (4100, 4616, 192, 0, T128X64),
+                                              (3000, 5632, 320, 256, T64), (3334, 5632, 256, 256, T128X64), (3340, 5632, 512, 256, T128),
+                                              (3377, 5888, 1024, 256, T256X128),
+                                              (2825, 5704, 2048, 256, T64), (5155, 3074, 3072, 256, T128X64), (2309, 7288, 3072, 256, T128),
+                                              (6668, 7818, 4096, 768, T256X128)])
+def test_gemm_rest_of_the_rounds_in_smaller_tiles(M, N, K, whole, tile):
+    """A little more than whole rounds of 256 tiles of 256 x 256: the full rounds in those, the rest in smaller ones, or all in smaller
+    ones where that is estimated faster; complete and ragged edges."""
+    assert gemm_route(0, M, N, K) == (whole, tile)
     g = torch.Generator(device="cuda").manual_seed(M + N)
     A, B, R = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, K), (N, K), (M, N)))
-    ref = A.double() @ B.double().T
+    ref = A.double() @ B.double().T.contiguous()
     C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
     for res in (None, R):
         ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), N, res.data_ptr() if res is not None else None, N, M, N, K, 0, 0, None))
         want = ref if res is None else ref + R.double()
         # one rounding to bf16 (2^-9 of the value) after fp32 sums
         assert bool(((C.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * K ** 0.5).all())
+    BI = R[0].contiguous()
+    ok(L.mt_k_gemm_nt_bias(A.data_ptr(), K, B.data_ptr(), K, C.data_ptr(), N, BI.data_ptr(), M, N, K, None))
+    want = ref + BI.double()
+    assert bool(((C.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * K ** 0.5).all())
     F = torch.full((M, N), 3.0, dtype=torch.float32, device="cuda")
     for acc in (0, 1):
         ok(L.mt_k_gemm_nt(A.data_ptr(), K, B.data_ptr(), K, F.data_ptr(), N, None, 0, M, N, K, 1, acc, None))
@@ -192,6 +247,24 @@ def test_gemm_token_major_weight_gradient_small_tiles(orc64, n, out, inn):
         for acc in (0, 1):
             ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, DW.data_ptr(), inn, out, inn, n, acc, split, WS.data_ptr(), None))
             assert_rows_close(host(DW), (1 + acc) * ref, 2e-5, what=f"split {split}")
+
+
+@pytest.mark.parametrize("n,out,inn,split,tile", [(1088, 8, 8, 1, T64), (192, 5456, 144, 3, T64), (512, 648, 5416, 1, T128X64),
+                                                  (576, 1920, 4896, 1, T128X64), (320, 584, 4872, 1, T128), (576, 8, 8, 2, T128),
+                                                  (192, 5192, 1352, 1, T256X128), (256, 5456, 136, 3, T256X128),
+                                                  (192, 3656, 3912, 1, (256, 256)), (128, 3088, 2080, 2, (256, 256))])
+def test_gemm_token_major_weight_gradient_every_tile(n, out, inn, split, tile):
+    """Each tile of the token-major kernels, unsplit and split where the estimate takes it so; ragged edges."""
+    assert gemm_route(1, out, inn, n, inn, split)[1] == tile
+    g = torch.Generator(device="cuda").manual_seed(n + out + inn)
+    DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
+    ref = DY.double().T.contiguous() @ X.double()
+    WS = torch.full((max(1, split - 1) * out * inn,), 9.0, dtype=torch.float32, device="cuda")
+    DW = torch.full((out, inn), 7.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        ok(L.mt_k_gemm_tn_split(DY.data_ptr(), out, X.data_ptr(), inn, DW.data_ptr(), inn, out, inn, n, acc, split, WS.data_ptr(), None))
+        # each of n additions rounds to 2^-24 of a partial sum of at most about 10 sqrt(n)
+        assert float((DW.double() - (1 + acc) * ref).abs().max()) <= n * 2.0 ** -24 * 10 * n ** 0.5
 
 
 @pytest.mark.parametrize("n,out,inn,split", [(2048, 520, 1032, 2), (4096, 264, 256, 5), (1024, 1280, 776, 3)])
