@@ -155,6 +155,10 @@ int32_t mt_k_flash_bwd(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t lddk, u
                        float *delta, int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, float scale,
                        void *stream);
 
+/* Which blocks the attention kernels take at this size (host only, launches nothing): queries of the forward, queries of dq (256, or
+ * 128 with the keys split over two sets of waves), keys of dk and dv (256, or 128 or 64 with the queries split). */
+int32_t mt_k_flash_route(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *route);
+
 /* The same with the backward of a rotary embedding folded into the stores: q and k are the rotated tensors the
  * forward attended with, and dq, dk come out as gradients of the unrotated ones (rotated back by the angle of
  * position t; pairs (j, j + hd/2)); tables cos/sin [T, hd/2] fp32, 16-byte aligned.  Equal to mt_k_flash_bwd

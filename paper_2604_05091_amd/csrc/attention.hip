@@ -205,18 +205,34 @@ __device__ __forceinline__ void mfma_tr_accumulate(f32x16 *acc, const bf16_t *ti
 // 2, 4 or 8 parts on different XCDs, every part an even share of light and heavy blocks: 8192 tokens, 4 query heads, 1 KV
 // head of 128: forward 512 -> 213 us, dQ 708 -> 287.  Up to 7 % of idle XCD time a set stays whole (sharing one L2).
 constexpr int kXcds = 8;
-__host__ __device__ __forceinline__ int set_parts(int n_sets) {
+inline int set_parts(int n_sets) {
     int p = 1;
     while (p < kXcds && (n_sets * p + kXcds - 1) / kXcds * kXcds * 100 > n_sets * p * 107) p *= 2;
     return p;
 }
-__device__ __forceinline__ bool decode_block(int per_set, int n_sets, int *set, int *inner) {
-    const int p = set_parts(n_sets), per_part = (per_set + p - 1) / p;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    const int part_id = (slot / per_part) * kXcds + xcd, i = slot % per_part, part = part_id % p;
-    *set = part_id / p;
+// An XCD hands its workgroups to its four shader engines (8 compute units each) in turn and in order.  Up to three workgroups per
+// compute unit (kByRank for an XCD's 32) the order is by rank: the heaviest block of every set, then the next one of every
+// set.  With set after set an engine can get nothing but heavy blocks, and two rounds of them where one and a light block would
+// do.  head_dim 128, set after set -> by rank, us: 1 x 2048, 18 heads in blocks of 128 queries (36 workgroups per XCD) forward 84.9 -> 45.5;
+// 1 x 1536, 64 heads in blocks of 256 (48) 79.3 -> 52.0; 1 x 4096, 9 heads, backward in blocks of 128 472 -> 251.  Beyond that set
+// after set, so that those who run together share an L2's worth of keys.  copies: blocks of one rank in a set.
+constexpr int kByRank = 96;
+struct BlockMap {   // worked out on the host: a workgroup of a short sequence lives for a few microseconds
+    int n_sets, per_set, n_parts, per_part, log_parts;
+    bool by_rank;
+};
+inline BlockMap block_map(int per_set, int n_sets, int copies) {
+    const int p = set_parts(n_sets);
+    BlockMap m = {n_sets, per_set, (n_sets * p + kXcds - 1) / kXcds, (per_set + p - 1) / p, __builtin_ctz(p), false};
+    m.by_rank = (int64_t)m.n_parts * m.per_part <= kByRank && m.n_parts * copies > 1;
+    return m;
+}
+__device__ __forceinline__ bool decode_block(const BlockMap &m, int *set, int *inner) {
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, by = m.by_rank ? m.n_parts : m.per_part, quot = slot / by, rest = slot - quot * by;
+    const int i = m.by_rank ? quot : rest, part_id = (m.by_rank ? rest : quot) * kXcds + xcd, p = 1 << m.log_parts, part = part_id & (p - 1);
+    *set = part_id >> m.log_parts;
     *inner = i * p + (i & 1 ? p - 1 - part : part);
-    return *set < n_sets && *inner < per_set;
+    return *set < m.n_sets && *inner < m.per_set;
 }
 // Causal work falls off linearly with the block index, and the workgroups of an XCD are handed to its shader
 // engines round-robin in dispatch order: with the plain order "heaviest first" one engine would always get the
@@ -230,10 +246,7 @@ __device__ __forceinline__ int snake8(int i, int n) {
     if (n > 128 || !(row & 1) || row * 8 + 7 >= n) return i;
     return row * 8 + 7 - (i & 7);
 }
-inline unsigned grid_blocks(int per_set, int n_sets) {
-    const int p = set_parts(n_sets);
-    return (unsigned)((n_sets * p + kXcds - 1) / kXcds * kXcds * ((per_set + p - 1) / p));
-}
+inline unsigned grid_blocks(const BlockMap &m) { return (unsigned)(m.n_parts * kXcds) * (unsigned)m.per_part; }
 
 // ------------------------------------------------------------------ forward
 // grid (q blocks of 32*QW rows, heaviest first; Hq; B); wave w owns 32 queries.  K and V tiles of 64
@@ -249,16 +262,16 @@ inline unsigned grid_blocks(int per_set, int n_sets) {
 #endif
 constexpr int kFwdPad = MT_FWD_PAD, kDqPad = MT_DQ_PAD;
 template <int HD, int QW, int KW>
-__global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, BlockMap map) {
     constexpr int LDK = HD + kFwdPad, NT = 64 * QW * KW, BQ = 32 * QW, NR = 2 / KW;
     constexpr int STAGE = 2 * 64 * LDK;
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
     int set, inner;
-    if (!decode_block(G * nqb, a.B * a.Hkv, &set, &inner)) return;
-    const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + inner / nqb;
-    const int qb = nqb - 1 - snake8(inner % nqb, nqb);  // heaviest query blocks first, in alternating rows of 8
+    if (!decode_block(map, &set, &inner)) return;
+    const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
+    const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));  // heaviest query blocks first (in alternating rows of 8)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
     const int qw = wave % QW, kw = wave / QW;
@@ -426,7 +439,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a) {
 // Same ownership as the forward: a lane owns one query, loops over key tiles <= q.
 // KW = 2 splits the tiles' keys over two sets of waves as in the forward; their sums are added at the end.
 template <int HD, int QW, int KW>
-__global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, BlockMap map) {
     constexpr int BQ = 32 * QW, NT = 64 * QW * KW;
     constexpr int LDK = HD + kDqPad;
     constexpr int STAGE = 2 * 64 * LDK;
@@ -434,9 +447,9 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a) 
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
     int set, inner;
-    if (!decode_block(G * nqb, a.B * a.Hkv, &set, &inner)) return;
-    const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + inner / nqb;
-    const int qb = nqb - 1 - snake8(inner % nqb, nqb);
+    if (!decode_block(map, &set, &inner)) return;
+    const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
+    const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
     const int qw = wave % QW, kw = wave / QW;
@@ -573,7 +586,7 @@ constexpr int kDkdvPad = 40;
 // LDS at the end (fixed order).  (8, 1) above is the cheapest per tile, (4, 2) and (2, 2) have shorter walks: see
 // choose_dkdv.
 template <int HD, int KW, int QW>
-__global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a, BlockMap map) {
     constexpr int LDK = HD + kDkdvPad, LDKV = HD + 8, HB = HD / 32, KB = 32 * KW, NT = 64 * KW * QW;
     constexpr int V_BF = KB * LDKV;
     constexpr int STAGE_BF = 2 * 64 * LDK, STAGE = STAGE_BF + 256;
@@ -582,8 +595,8 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
 
     const int T = a.T, G = a.Hq / a.Hkv, nkb = (T + KB - 1) / KB;
     int set, kvb;
-    if (!decode_block(nkb, a.B * a.Hkv, &set, &kvb)) return;
-    kvb = snake8(kvb, nkb);
+    if (!decode_block(map, &set, &kvb)) return;
+    if (!map.by_rank) kvb = snake8(kvb, nkb);
     const int b = set / a.Hkv, hk = set % a.Hkv;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
     const int tr_off = tr_lane_offset(lane, LDK);
@@ -757,8 +770,9 @@ static hipError_t launch_fwd(const AttnArgs &a, hipStream_t s) {
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW>, lds, &done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
-                       dim3(64 * QW * KW), lds, s, a);
+    const int G = a.Hq / a.Hkv;
+    const BlockMap map = block_map(G * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv, G);
+    hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
     return hipGetLastError();
 }
 
@@ -769,23 +783,63 @@ static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW>, lds, &done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW>), dim3(grid_blocks((a.Hq / a.Hkv) * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv)),
-                       dim3(64 * QW * KW), lds, s, a);
+    const int G = a.Hq / a.Hkv;
+    const BlockMap map = block_map(G * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv, G);
+    hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
     return hipGetLastError();
 }
 
+// Estimated time in us of a kernel that takes blocks of `block` queries (or keys): the walk of the heaviest block, or the work of
+// all blocks on 256 compute units, or, where the blocks come by rank, the r-th block of a compute unit behind r - 1 that are at
+// least as heavy (`share` < 1: two workgroups of the kernel share a compute unit).  `tile` and `full` are us per 64-row tile when
+// a walk decides and when the chip is full, `start` and `start_full` per block.  Fitted to 316 shapes (T 64 .. 4096, 24 .. 768 blocks of
+// 128 queries, 1 .. 8 query heads per KV head) on which the choice between the kernels comes out within 1 % of the best on average.
+struct AttnCost { int block; double start, tile, start_full, full, share; };
+static double attn_time(const AttnArgs &a, const AttnCost &c, bool keys) {
+    const int G = a.Hq / a.Hkv, nt = (a.T + 63) / 64, nb = (a.T + c.block - 1) / c.block, tpb = c.block / 64, n_sets = a.B * a.Hkv;
+    const int copies = keys ? 1 : G, per_set = copies * nb;
+    const BlockMap map = block_map(per_set, n_sets, copies);
+    const auto tiles = [&](int inner) -> double { return keys ? (double)G * (nt - inner * tpb) : (double)std::min(nt, (nb - inner / G) * tpb); };
+    const double mean = keys ? G * (nt - (nb - 1) * tpb * 0.5) : ((nb - 1) * 0.5 * nb * tpb + nt) / nb;
+    double t = std::max(c.start + tiles(0) * c.tile, (double)n_sets * per_set / 256.0 * (c.start_full + mean * c.full));
+    const int64_t slots = (int64_t)map.n_parts * map.per_part;
+    if (slots <= kByRank)
+        for (int r = 1; r * 32 < slots; ++r)
+            t = std::max(t, (1 + r * c.share) * (c.start + tiles(std::min(per_set - 1, (r * 32 / map.n_parts) << map.log_parts)) * c.tile));
+    return t;
+}
+// the first whose estimate no later one beats by 3 %
+template <int N>
+static int cheapest(const AttnArgs &a, const AttnCost (&costs)[N], bool keys) {
+    int best = 0;
+    double best_t = attn_time(a, costs[0], keys);
+    for (int i = 1; i < N; ++i) {
+        const double t = attn_time(a, costs[i], keys);
+        if (t < 0.97 * best_t) {
+            best = i;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
 // Forward and dQ: blocks of 128 queries with the keys split over two sets of waves, or blocks of 256?  The former walk
-// their keys in two thirds of the time (per 64-key tile 1.16 against 1.68 us at head_dim 128, 0.9 against 1.3 at 64) but fetch K and
-// V twice as often.  They are taken while about one round of them covers the problem (256 compute units).  Measured,
-// blocks of 256 -> 128, us (forward; dQ), head_dim 128 unless said:
-//   256 blocks: 1 x 8192 x 4 heads 212 -> 153; 288 -> 175       1 x 4096 x 8 110 -> 81; 149 -> 92      2 x 1024 x 16 33 -> 27; 44 -> 31
-//   288: 1 x 1536 x 24 47 -> 36; 62 -> 42     320: 1 x 1024 x 40 35 -> 41; 46 -> 48     384 (head_dim 64): 3 x 1000 x 16 24 -> 27; 28 -> 37
-//   4096: 4 x 4096 x 32 610 -> 733; 830 -> 910
-// With head_dim 64 the forward is bound by its vector arithmetic and four of the smaller workgroups' waves fit on a SIMD:
-// up to 4096 tokens and with several rounds they win again (8 x 2048 x 16 154 -> 119, 4 x 4096 x 16 214 -> 207; 1 x 8192 x 32 359 -> 377).
+// their keys in two thirds of the time but fetch K and V twice as often.  Measured, blocks of 256 -> 128, us (forward; backward with
+// dK/dV as below), head_dim 128 unless said:
+//   256 blocks of 128: 1 x 1024 x 32 heads 33 -> 27      1 x 2048 x 16 59 -> 45; 467 -> 443      1 x 4096 x 8 109 -> 81; 352 -> 299
+//   264 .. 320: 1 x 384 x 101 17 -> 21; 54 -> 57    1 x 768 x 48 27 -> 22; 85 -> 75    1 x 1536 x 25 46 -> 36; 148 -> 127
+//   512: 1 x 1024 x 64 35 -> 35; 113 -> 109    1 x 2048 x 32 61 -> 54; 199 -> 182      768: 1 x 1536 x 64 52 -> 69; 176 -> 188
+// In grids beyond kByRank the line is drawn by sizes: with head_dim 64 the forward is bound by its vector arithmetic, four of
+// the smaller workgroups' waves fit on a SIMD, and up to 4096 tokens they win (8 x 2048 x 16 156 -> 122, 4 x 4096 x 16 214 -> 207;
+// 1 x 8192 x 32 359 -> 377); head_dim 128 4 x 4096 x 32 610 -> 733; 830 -> 910.  (Some dQ would win there too: 8 x 2048 x 16, head_dim 64, 182 -> 168.)
 static bool split_keys(const AttnArgs &a, bool forward) {
-    const int64_t blocks = (int64_t)a.B * a.Hq * ((a.T + 127) / 128);
-    return blocks <= 288 || (forward && a.hd == 64 && a.T <= 4096 && blocks >= 1024);
+    static const AttnCost fwd64[] = {{256, 2.7, 1.15, 2.7, 1.5, 1.0}, {128, 3.2, 0.8, 1.76, 0.62, 0.55}};
+    static const AttnCost dq64[] = {{256, 3.4, 1.25, 3.4, 1.5, 1.0}, {128, 4.0, 0.85, 4.0, 0.95, 1.0}};
+    static const AttnCost hd128[] = {{256, 4.0, 1.62, 4.0, 1.9, 1.0}, {128, 5.2, 1.13, 5.2, 1.25, 1.0}};
+    const BlockMap map = block_map(a.Hq / a.Hkv * ((a.T + 255) / 256), a.B * a.Hkv, a.Hq / a.Hkv);
+    if ((int64_t)map.n_parts * map.per_part > kByRank)
+        return forward && a.hd == 64 && a.T <= 4096 && (int64_t)a.B * a.Hq * ((a.T + 127) / 128) >= 1024;
+    return cheapest(a, a.hd == 128 ? hd128 : forward ? fwd64 : dq64, false) == 1;
 }
 
 hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
@@ -814,38 +868,22 @@ static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW>, lds, &done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW>), dim3(grid_blocks((a.T + KB - 1) / KB, a.B * a.Hkv)),
-                       dim3(64 * KW * QW), lds, s, a);
+    const BlockMap map = block_map((a.T + KB - 1) / KB, a.B * a.Hkv, 1);
+    hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW>), dim3(grid_blocks(map)), dim3(64 * KW * QW), lds, s, a, map);
     return hipGetLastError();
 }
 
-// Estimated time of the dK/dV kernel in us for key blocks of kb keys: the walk of the first block (every query tile of
-// every head of the group), or the work of all blocks on 256 compute units, whichever is longer.  `tile` and `full` are us per
-// 64-query tile when a walk decides and when the chip is full, `start` and `start_full` per block; fitted to 27 shapes
-// (T 128 .. 32768, 1 .. 32 KV heads), which they meet within 15 %.  us for (8, 1) / (4, 2) / (2, 2), head_dim 128:
-//   1 x 4096, 40 heads on 8 KV heads 966 / 685 / 593     1 x 8192, 40 on 8 1996 / 1565 / 2153     1 x 8192, 4 on 1 1541 / 1083 / 838
-//   4 x 4096, 32 on 32 1131 / 1278 / 1983                2 x 1024, 16 on 16 56 / 42 / 55          8 x 512, 32 on 32 72 / 104 / 127
-// head_dim 64: 3 x 1000, 16 on 4 133 / 83 / 93; 8 x 2048, 16 on 16 243 / 223 / 269; 1 x 32768, 4 on 4 1208 / 1303 / 1730.
-struct DkdvCost { int kb; double start, tile, start_full, full; };
-static double dkdv_time(const AttnArgs &a, const DkdvCost &c) {
-    const double n_qt = (a.T + 63) / 64, nkb = (a.T + c.kb - 1) / c.kb, G = a.Hq / a.Hkv;
-    const double mean = G * (n_qt - (nkb - 1) * (c.kb / 64) * 0.5);   // tiles of a block, averaged over the blocks
-    return std::max(c.start + G * n_qt * c.tile, (double)a.B * a.Hkv * nkb / 256.0 * (c.start_full + mean * c.full));
-}
+// Which dK/dV kernel.  us of the backward (with dQ and the row sums) for (8, 1) / (4, 2) / (2, 2), head_dim 128:
+//   1 x 1024, 40 heads on 10 KV heads 232 / 186 / 150     1 x 4096, 9 on 9 298 / 251 / 246       1 x 2048, 48 on 12 497 / 399 / 328
+//   1 x 768, 85 on 85 101 / 110 / 140                     1 x 512, 72 on 72 60 / 55 / 65         1 x 1536, 64 on 64 188 / 208 / 263
+// head_dim 64, (8, 1) / (4, 2): 3 x 1000, 16 on 4 163 / 110; 7 x 600, 32 on 32 105 / 118; 8 x 2048, 16 on 16 427 / 405.
+// Up to 128 keys and without groups of query heads, a walk of two tiles, the halves' merge costs more than it saves: 264 heads, 128
+// tokens, head_dim 128 50 / 53 / 54.
 static int choose_dkdv(const AttnArgs &a) {
-    static const DkdvCost hd64[] = {{256, 2.0, 2.05, 14.0, 2.3}, {128, 2.5, 1.22, 7.0, 1.27}};
-    static const DkdvCost hd128[] = {{256, 6.0, 3.05, 10.0, 3.9}, {128, 5.0, 2.05, 6.0, 2.35}, {64, 5.0, 1.75, 5.0, 1.78}};
-    const DkdvCost *costs = a.hd == 64 ? hd64 : hd128;
-    int best = 0;
-    double best_t = dkdv_time(a, costs[0]);
-    for (int i = 1; i < (a.hd == 64 ? 2 : 3); ++i) {
-        const double t = dkdv_time(a, costs[i]);
-        if (t < 0.97 * best_t) {
-            best = i;
-            best_t = t;
-        }
-    }
-    return best;
+    static const AttnCost hd64[] = {{256, 2.0, 2.05, 14.0, 2.3, 1.0}, {128, 4.0, 1.22, 10.0, 1.27, 1.0}};
+    static const AttnCost hd128[] = {{256, 6.0, 3.05, 10.0, 3.9, 1.0}, {128, 9.0, 2.05, 10.0, 2.35, 1.0}, {64, 9.0, 1.75, 7.0, 1.78, 1.0}};
+    if (a.T <= 128 && a.Hq == a.Hkv) return 0;
+    return a.hd == 64 ? cheapest(a, hd64, true) : cheapest(a, hd128, true);
 }
 
 hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
@@ -861,6 +899,13 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
         case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);
         default: return launch_dkdv<128, 2, 2>(a, s);
     }
+}
+
+void flash_route(const AttnArgs &a, int *fwd, int *dq, int *dkdv) {
+    static const int keys[] = {256, 128, 64};
+    *fwd = split_keys(a, true) ? 128 : 256;
+    *dq = split_keys(a, false) ? 128 : 256;
+    *dkdv = keys[choose_dkdv(a)];
 }
 
 }  // namespace mt

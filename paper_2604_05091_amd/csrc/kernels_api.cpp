@@ -203,6 +203,16 @@ int32_t mt_k_reduce_sum(float *out, const float *in, int64_t n, float scale, int
     return to_status(reduce_sum(out, in, n, scale, accumulate, S(stream)));
 }
 
+int32_t mt_k_flash_route(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *route) {
+    if (B <= 0 || T <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || (hd != 64 && hd != 128) || !route) return MT_ERR_INVALID_ARG;
+    AttnArgs a{};
+    a.B = B; a.T = T; a.Hq = Hq; a.Hkv = Hkv; a.hd = hd;
+    int fwd, dq, dkdv;
+    flash_route(a, &fwd, &dq, &dkdv);
+    route[0] = fwd; route[1] = dq; route[2] = dkdv;
+    return MT_OK;
+}
+
 int32_t mt_k_flash_fwd(uint16_t *o, int64_t ldo, float *lse, const uint16_t *q, int64_t ldq, const uint16_t *k,
                        int64_t ldk, const uint16_t *v, int64_t ldv, int32_t B, int32_t T, int32_t Hq, int32_t Hkv,
                        int32_t hd, float scale, void *stream) {

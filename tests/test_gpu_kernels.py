@@ -836,12 +836,26 @@ def test_flash_attention_forward_backward(orc64, B, T, Hq, Hkv, hd):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + hd)
 
 
-# Both ways of sharing a block among waves (few blocks: keys or queries split over two sets of waves; many: not), edges of
-# 32-, 64-, 128- and 256-row blocks, and set counts (batch x KV heads) that do and do not fill the 8 XCDs evenly.
-@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 24, 8, 8, 128), (3, 40, 3, 1, 64), (1, 136, 9, 3, 128), (5, 264, 2, 1, 64), (1, 1032, 4, 1, 128),
-                                           (3, 104, 18, 6, 64), (10, 136, 20, 4, 64), (5, 152, 32, 4, 128), (2, 1024, 32, 32, 64),
-                                           (8, 256, 32, 32, 128), (1, 2056, 2, 2, 64)])
-def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd):
+def attention_route(B, T, Hq, Hkv, hd):
+    """(queries per block of the forward, of dq, keys per block of dk and dv): fewer than 256 share a block among two sets of waves"""
+    r = (ctypes.c_int32 * 3)()
+    ok(L.mt_k_flash_route(B, T, Hq, Hkv, hd, ctypes.addressof(r)))
+    return tuple(r)
+
+
+# Both ways of sharing a block among waves (keys or queries split over two sets of waves, or not), edges of 32-, 64-, 128- and 256-row
+# blocks, set counts (batch x KV heads) that do and do not fill the 8 XCDs evenly, and both orders of the blocks: by rank, in one round
+# and in several, and set after set (more than 96 blocks per XCD).
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd,route", [(1, 24, 8, 8, 128, (256, 256, 256)), (3, 40, 3, 1, 64, (256, 256, 128)), (1, 136, 9, 3, 128, (128, 128, 64)),
+                               (5, 264, 2, 1, 64, (128, 128, 128)), (1, 1032, 4, 1, 128, (128, 128, 64)), (3, 104, 18, 6, 64, (128, 128, 128)),
+                               (10, 136, 20, 4, 64, (256, 256, 128)), (5, 152, 32, 4, 128, (256, 256, 64)), (2, 1024, 32, 32, 64, (128, 256, 256)),
+                               (8, 256, 32, 32, 128, (256, 256, 256)), (1, 2056, 2, 2, 64, (128, 128, 128)), (13, 136, 15, 5, 64, (128, 128, 128)),
+                               (39, 136, 10, 5, 64, (128, 256, 256)), (28, 264, 9, 3, 64, (128, 128, 128)), (25, 264, 6, 2, 64, (128, 256, 128)),
+                               (26, 264, 15, 5, 64, (128, 256, 128)), (13, 264, 5, 5, 64, (128, 256, 128)), (22, 136, 9, 3, 128, (128, 128, 128)),
+                               (33, 264, 2, 1, 128, (256, 256, 64)), (26, 136, 15, 5, 128, (256, 256, 128)), (26, 264, 5, 5, 128, (128, 128, 256)),
+                               (10, 264, 15, 5, 128, (256, 256, 64)), (26, 264, 15, 5, 128, (256, 256, 256)), (11, 264, 3, 3, 128, (128, 128, 128))])
+def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd, route):
+    assert attention_route(B, T, Hq, Hkv, hd) == route
     # dq of the first few queries: delta = dO . O carries O's bf16 rounding, 2^-9 sqrt(hd) = 0.022 for unit normal data and
     # hd = 128; times scale (0.088), P <= 1 and the largest |k| (about 4) that is 0.008, whereas ROW_FLOOR allows 2^-9 of
     # the largest |dq| (about 3 in a short sequence): 0.006
@@ -851,6 +865,7 @@ def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd):
 def test_flash_attention_scores_of_minus_infinity(orc64):
     """Keys whose scores are -inf for a query (inf * -1) have no weight, also where a whole 32-key half is such."""
     B, T, H, hd = 1, 136, 2, 64
+    assert attention_route(B, T, H, H, hd)[0] == 128
     rng = np.random.default_rng(3)
     q, k, v = (bf16_round(rng.standard_normal((T, H * hd))) for _ in range(3))
     q[:, ::hd] = 1.0
@@ -875,6 +890,7 @@ def test_flash_attention_scores_of_minus_infinity_for_some_queries(orc64, first)
     """The scores of 32 keys (one half of the first 64-key tile) overflow to -inf for every other query of a wave only.
     Every query that also sees another key has a finite result, whatever its neighbours see."""
     B, T, H, hd = 1, 136, 2, 64
+    assert attention_route(B, T, H, H, hd)[0] == 128
     rng = np.random.default_rng(first + 5)
     q, k, v = (bf16_round(rng.standard_normal((T, H * hd))) for _ in range(3))
     masked = np.zeros(T, bool)
