@@ -84,9 +84,16 @@ __device__ __forceinline__ void mfma16_acc(f32x4 &acc, const bf16x8 &a, const bf
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 // every accumulator has been written (16 wait states, the slowest of these instructions needs 11) and may be read
+__device__ __forceinline__ void mfma16_drain() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+// The same, for the compiler too.  Where two paths with these instructions meet in front of it, the compiler may move accumulators at
+// the end of one of them: that path ends with a mfma16_drain of its own (tests/test_matrix_hazards.py looks for such moves).
 template <int I, int J>
 __device__ __forceinline__ void mfma16_settle(f32x4 (&acc)[I][J]) {
-    asm volatile("s_nop 15" ::: "memory");
+    mfma16_drain();
 #pragma unroll
     for (int i = 0; i < I; ++i)
 #pragma unroll
@@ -120,6 +127,38 @@ __device__ __forceinline__ int gemm_walk_start(int tm, int nk) {
     int h = tm >> 2;
     h ^= h >> 1; h ^= h >> 2; h ^= h >> 4;   // any eight groups in arithmetic progression by a power of two: distinct low bits
     return (h & 7) * (nk >> 3);
+}
+
+// Eight bf16 columns of a row that need not be complete or aligned.  Class of an access of the columns col .. + 7 of [.., n] with row
+// pitch ld at p: 16 (bytes at once), 8, or 2 (element by element, columns < n only).
+__device__ __forceinline__ int row_access(const void *p, int64_t ld, int col, int n) {
+    return col + 8 > n ? 2 : !(ld & 7) && !((uintptr_t)p & 15) ? 16 : !(ld & 3) && !((uintptr_t)p & 7) ? 8 : 2;
+}
+__device__ __forceinline__ void row_add8(float (&v)[8], const bf16_t *r, int access, int col, int n) {
+    if (access >= 8) {
+        const uint4 u = access == 16 ? *reinterpret_cast<const uint4 *>(r)
+                                     : uint4{reinterpret_cast<const uint2 *>(r)[0].x, reinterpret_cast<const uint2 *>(r)[0].y,
+                                             reinterpret_cast<const uint2 *>(r)[1].x, reinterpret_cast<const uint2 *>(r)[1].y};
+        v[0] += bflo(u.x); v[1] += bfhi(u.x); v[2] += bflo(u.y); v[3] += bfhi(u.y);
+        v[4] += bflo(u.z); v[5] += bfhi(u.z); v[6] += bflo(u.w); v[7] += bfhi(u.w);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (col + e < n) v[e] += bf2f(r[e]);
+    }
+}
+__device__ __forceinline__ void row_store8(bf16_t *c, const float (&v)[8], int access, int col, int n) {
+    const uint4 u = {pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])};
+    if (access == 16) {
+        *reinterpret_cast<uint4 *>(c) = u;
+    } else if (access == 8) {
+        reinterpret_cast<uint2 *>(c)[0] = uint2{u.x, u.y};
+        reinterpret_cast<uint2 *>(c)[1] = uint2{u.z, u.w};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (col + e < n) c[e] = f2bf(v[e]);
+    }
 }
 
 #endif  // __HIPCC__

@@ -58,14 +58,11 @@ __device__ __forceinline__ void w4_flush_rows(bf16_t *C, int64_t ldc, int M, int
 
 // Epilogue of the 4-wave kernels.  The MFMAs are issued with the operands swapped (B fragment first), so each
 // 16x16 block holds C transposed: the lane owns row l16 of the block and its four consecutive columns
-// 4 hq + (0..3): one 8-byte (bf16) or 16-byte (fp32) store each.
-__device__ __forceinline__ void w4_store(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn,
-                                         int l16, int hq) {
-    constexpr int BM = W4_BM, BN = W4_BN;
+// 4 hq + (0..3): one 16-byte store each in fp32.
+__device__ __forceinline__ void w4_store_guarded_f32(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn,
+                                                     int l16, int hq) {
     const int row_l = m0 + wm * 128 + l16, col_l = n0 + wn * 128 + hq * 4;
-    const bool full = (m0 + BM <= g.M) && (n0 + BN <= g.N);
-    const bool vec = full && !(g.ldc & 3) && !((uintptr_t)g.C & 15) && (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) &&
-                     !((uintptr_t)g.bias & 7);
+    const bool vec = m0 + W4_BM <= g.M && n0 + W4_BN <= g.N && !(g.ldc & 3) && !((uintptr_t)g.C & 15);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int row = row_l + i * 16;
@@ -73,36 +70,49 @@ __device__ __forceinline__ void w4_store(const GemmArgs &g, const f32x4 (&acc)[8
         for (int j = 0; j < 8; ++j) {
             const int col = col_l + j * 16;
             f32x4 v = acc[i][j];
-            if (g.out_fp32) {
-                float *cp = reinterpret_cast<float *>(g.C) + (int64_t)row * g.ldc + col;
-                if (vec) {
-                    if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp);
-                    *reinterpret_cast<f32x4 *>(cp) = v;
-                } else if (row < g.M) {
+            float *cp = reinterpret_cast<float *>(g.C) + (int64_t)row * g.ldc + col;
+            if (vec) {
+                if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(cp);
+                *reinterpret_cast<f32x4 *>(cp) = v;
+            } else if (row < g.M) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (col + e < g.N) cp[e] = v[e] + (g.accumulate ? cp[e] : 0.f);
-                }
-            } else {
-                bf16_t *cp = reinterpret_cast<bf16_t *>(g.C) + (int64_t)row * g.ldc + col;
-                const bf16_t *rp = g.R ? g.R + (int64_t)row * g.ldr + col : nullptr;
-                if (vec) {
-                    if (g.bias) {
-                        const uint2 bv = *reinterpret_cast<const uint2 *>(g.bias + col);
-                        v[0] += bflo(bv.x); v[1] += bfhi(bv.x); v[2] += bflo(bv.y); v[3] += bfhi(bv.y);
-                    }
-                    if (rp) {
-                        const uint2 rv = *reinterpret_cast<const uint2 *>(rp);
-                        v[0] += bflo(rv.x); v[1] += bfhi(rv.x); v[2] += bflo(rv.y); v[3] += bfhi(rv.y);
-                    }
-                    *reinterpret_cast<uint2 *>(cp) = uint2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
-                } else if (row < g.M) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (col + e < g.N)
-                            cp[e] = f2bf(v[e] + (g.bias ? bf2f(g.bias[col + e]) : 0.f) + (rp ? bf2f(rp[e]) : 0.f));
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < g.N) cp[e] = v[e] + (g.accumulate ? cp[e] : 0.f);
             }
+        }
+    }
+}
+
+// bf16 for any columns, pitches and alignment, bias and residual added in fp32 before the one rounding.  Blocks of 16 rows pass through
+// the wave's LDS region as fp32 (pitch 132: the 16-byte writes of consecutive rows fall on disjoint banks) and leave row-wise, 8 columns
+// per lane.  From the accumulator layout with a test per element -> here, us:
+// 16384 x 11000 x 4096 1176 -> 1055, 16384 x 11000 x 512 319 -> 222, 8192 x 4096 x 1024 with a pitch of 4100 110 -> 63 (with residual 170 -> 83).
+__device__ __forceinline__ void w4_store_guarded_bf16(const GemmArgs &g, const f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn,
+                                                      int l16, int hq, bf16_t *region) {
+    constexpr int P = 132;
+    static_assert(16 * P * 4 <= 128 * W4_EP_PITCH * 2, "room in the region");
+    float *st = reinterpret_cast<float *>(region);
+    const int lr = hq, lc = l16 * 8, col = n0 + wn * 128 + lc;
+    const int access = row_access(g.C, g.ldc, col, g.N), access_r = row_access(g.R, g.ldr, col, g.N);
+    float bias[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bias[e] = g.bias && col + e < g.N ? bf2f(g.bias[col + e]) : 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's reads of the block before
+#pragma unroll
+        for (int j = 0; j < 8; ++j) *reinterpret_cast<f32x4 *>(st + l16 * P + j * 16 + hq * 4) = acc[i][j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // its writes have landed
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const f32x4 lo = *reinterpret_cast<const f32x4 *>(st + (p * 4 + lr) * P + lc), hi = *reinterpret_cast<const f32x4 *>(st + (p * 4 + lr) * P + lc + 4);
+            const int64_t row = m0 + wm * 128 + i * 16 + p * 4 + lr;
+            if (row >= g.M || col >= g.N) continue;
+            float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += bias[e];
+            if (g.R) row_add8(v, g.R + row * g.ldr + col, access_r, col, g.N);
+            row_store8(reinterpret_cast<bf16_t *>(g.C) + row * g.ldc + col, v, access, col, g.N);
         }
     }
 }
@@ -311,7 +321,7 @@ __device__ __forceinline__ void w4_store_glu_bwd(const GemmArgs &g, const f32x4 
 
 // The epilogue is a template parameter: one kernel that carries all of them keeps so much guarded store code alive
 // that the compiler moves accumulators through scratch memory on the way out (measured: 13-16 us per tile).
-enum { EPI_GENERAL = 0, EPI_FULL_BF16 = 1, EPI_FULL_F32 = 2, EPI_ROPE = 3, EPI_GLU = 4, EPI_GLU_BWD = 5, EPI_FULL_BF16_RES = 6,
+enum { EPI_GUARDED_BF16 = 0, EPI_GUARDED_F32 = 10, EPI_FULL_BF16 = 1, EPI_FULL_F32 = 2, EPI_ROPE = 3, EPI_GLU = 4, EPI_GLU_BWD = 5, EPI_FULL_BF16_RES = 6,
        EPI_FULL_BF16_BIAS = 7, EPI_ROPE_BIAS = 8, EPI_QUADS_F32 = 9 };
 // region: the wave's private LDS staging block (128 rows of W4_EP_PITCH bf16), free once the k-loop's last barrier has passed
 template <int EPI>
@@ -325,7 +335,8 @@ __device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x4 (&acc
     else if constexpr (EPI == EPI_FULL_BF16_RES) w4_store_full_bf16<false, true>(g, acc, m0, n0, wm, wn, l16, hq, region);
     else if constexpr (EPI == EPI_FULL_BF16_BIAS) w4_store_full_bf16<true, false>(g, acc, m0, n0, wm, wn, l16, hq, region);
     else if constexpr (EPI == EPI_FULL_F32) w4_store_full_f32(g, acc, m0, n0, wm, wn, l16, hq);
-    else w4_store(g, acc, m0, n0, wm, wn, l16, hq);
+    else if constexpr (EPI == EPI_GUARDED_BF16) w4_store_guarded_bf16(g, acc, m0, n0, wm, wn, l16, hq, region);
+    else w4_store_guarded_f32(g, acc, m0, n0, wm, wn, l16, hq);
 }
 // ---------------------------------------------------------------------------------------------
 // The main loop.  Operands go from memory straight into LDS (no staging registers, no LDS store instructions): full
@@ -338,8 +349,8 @@ __device__ __forceinline__ void w4_epilogue(const GemmArgs &g, const f32x4 (&acc
 //            four waves share it), which leaves every load at least the 1024 clocks of the next slice 0 to land
 // What bounds it is power: the chip clocks down to what its matrix cores, registers and LDS draw.  The 16x16x32 MFMA
 // moves a fifth fewer register bytes per multiplication than 32x32x16 (each accumulator is read and written once per 32
-// reduction indices instead of 16), and the 2 x 2 zigzag below changes one operand per MFMA: 8192^3 759 us -> 689 (1450 ->
-// 1597 TFLOP/s), 4096^3 101 -> 91, 16384 x 11008 x 4096 1085 -> 1024.  The accumulators are updated in place by assembly (mfma16_acc):
+// reduction indices instead of 16), and the 2 x 2 zigzag below changes one operand per MFMA: 8192^3 743 us -> 691 (1480 ->
+// 1591 TFLOP/s), 4096^3 100 -> 91, 16384 x 11008 x 4096 1074 -> 1014 (boxes differ by 5 %).  The accumulators are updated in place by assembly (mfma16_acc):
 // given the builtin, the register allocator renames them, 500 moves per 256 MFMAs (8192^3: 916 us).
 constexpr int WE_HALF = 256 * 64 * 2, WE_SLOT = 2 * WE_HALF, WE_ARRAY = 2 * 128 * W4_EP_PITCH * 2;
 static_assert(WE_ARRAY >= WE_SLOT, "a slot must fit into two staging blocks");
@@ -466,7 +477,10 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
         WE_STEP(sl0, sl1, kt);
         WE_STEP(sl1, sl0, kt + 1);
     }
-    if (kt < nk) WE_STEP(sl0, sl1, kt);
+    if (kt < nk) {
+        WE_STEP(sl0, sl1, kt);
+        mfma16_drain();
+    }
     WE_WAIT(0);   // the loads requested past the end have landed before the store staging reuses the arrays
 #undef WE_LOAD1
 #undef WE_READ1
@@ -507,7 +521,7 @@ hipError_t launch_w4e(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
     if (g.glu_F > 0) return launch_w4e_epi<EPI_GLU>(g, s);
     if (g.rope_cos) return g.bias ? launch_w4e_epi<EPI_ROPE_BIAS>(g, s) : launch_w4e_epi<EPI_ROPE>(g, s);
     if (g.glu_bwd_gu) return launch_w4e_epi<EPI_GLU_BWD>(g, s);
-    if (!whole_line_store(g)) return launch_w4e_epi<EPI_GENERAL>(g, s, n_tiles);
+    if (!whole_line_store(g)) return g.out_fp32 ? launch_w4e_epi<EPI_GUARDED_F32>(g, s, n_tiles) : launch_w4e_epi<EPI_GUARDED_BF16>(g, s, n_tiles);
     if (g.out_fp32) return launch_w4e_epi<EPI_FULL_F32>(g, s, n_tiles);
     if (g.R) return launch_w4e_epi<EPI_FULL_BF16_RES>(g, s, n_tiles);
     return g.bias ? launch_w4e_epi<EPI_FULL_BF16_BIAS>(g, s, n_tiles) : launch_w4e_epi<EPI_FULL_BF16>(g, s, n_tiles);
@@ -702,12 +716,15 @@ __global__ __launch_bounds__(W4_NT) void gemm_tn_w4e_kernel(GemmArgs g, int tile
             WT_STEP(sl0, sl1, kt);
             WT_STEP(sl1, sl0, kt + 1);
         }
-        if (kt < nk) WT_STEP(sl0, sl1, kt);
+        if (kt < nk) {
+            WT_STEP(sl0, sl1, kt);
+            mfma16_drain();
+        }
         WT_WAIT(0);
         mfma16_settle(acc);
-        const bool more = EPI != EPI_GENERAL && ++piece < piece_end;   // (a split has aligned rows)
+        const bool more = EPI != EPI_GUARDED_F32 && ++piece < piece_end;   // (a split has aligned rows)
         if (more) WT_BEGIN();   // their flight covers the store
-        if constexpr (EPI == EPI_GENERAL) w4_store(g, acc, m0, n0, wm, wn, l16, hq);
+        if constexpr (EPI == EPI_GUARDED_F32) w4_store_guarded_f32(g, acc, m0, n0, wm, wn, l16, hq);
         else tn_store<EPI == EPI_FULL_F32>(g, acc, m0, n0, wm, wn, l16, hq);
         if (!more) break;
         g.accumulate = 1;
@@ -855,8 +872,13 @@ static double tn_time(const TileCost &c, int64_t M, int64_t N, double stages, in
     return t + 3.0 + (split + 1) * 4.0 * (double)M * (double)N / 3.5e6 + (c.per_cu > 1 ? stages * c.part + c.fixed : 0.0);
 }
 
-// The 256 x 256 kernel's guarded store (ragged columns, unaligned rows) writes partial lines: this much more per tile.
-constexpr double kGuardedStore = 14.0;
+// The 256 x 256 kernel's guarded stores (ragged columns, unaligned rows) cost this much more per tile: in fp32, and element by element,
+// they write partial lines.
+constexpr double kGuardedStore = 14.0, kGuardedRows = 2.0;
+static double guarded_store(const GemmArgs &g) {
+    const bool rows = !g.out_fp32 && !(g.ldc & 3) && !((uintptr_t)g.C & 7) && (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7)));
+    return whole_line_store(g) ? 0.0 : rows ? kGuardedRows : kGuardedStore;
+}
 
 template <int N_COSTS>
 static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], int64_t M, int64_t N, int64_t K, int split) {
@@ -901,7 +923,7 @@ struct NtRoute { int whole; const TileCost *tile; };
 static NtRoute nt_route(const GemmArgs &g) {
     TileCost costs[sizeof kNtCosts / sizeof kNtCosts[0]];
     std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
-    if (!whole_line_store(g)) costs[0].fixed += kGuardedStore;
+    costs[0].fixed += guarded_store(g);
     const TileCost &one = choose_tile(costs, g.M, g.N, g.K, 1);
     // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
     // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
@@ -1010,7 +1032,7 @@ static int tn_sums_of_split(const GemmArgs &g) {
 
 static hipError_t launch_tn(const GemmArgs &g, hipStream_t s) {
     const TnRoute route = tn_big_route(kTnCosts[0], g.M, g.N, g.K / BK, g.split_k, tn_sums_of_split(g), kComputeUnits);
-    if ((g.ldc & 3) || ((uintptr_t)g.C & 15)) return launch_tn_epi<EPI_GENERAL>(g, route, s);   // (unsplit then)
+    if ((g.ldc & 3) || ((uintptr_t)g.C & 15)) return launch_tn_epi<EPI_GUARDED_F32>(g, route, s);   // (unsplit then)
     return g.N % W4_BN == 0 ? launch_tn_epi<EPI_FULL_F32>(g, route, s) : launch_tn_epi<EPI_QUADS_F32>(g, route, s);
 }
 

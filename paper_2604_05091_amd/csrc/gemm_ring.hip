@@ -75,52 +75,78 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
     const int r0 = tid / LPR, col = n0 + (tid % LPR) * CPL;
     if (col >= g.N) return;
     const float *sp = st + r0 * P + (tid % LPR) * CPL;
+    // Passes in groups of U: their LDS reads, and the reads of what is added, are in flight together (a pass that ends at the last row
+    // by a branch would wait for its own read); rows past the end re-read the last one and are not stored.
+    constexpr int N_PASS = BM / RPI, U = N_PASS < 4 ? N_PASS : 4;
+    static_assert(N_PASS % U == 0, "whole groups");
     if constexpr (F32) {
         const bool vec = !(g.ldc & 3) && !((uintptr_t)g.C & 15) && col + 4 <= g.N;
-        float *cp = reinterpret_cast<float *>(g.C) + (int64_t)(m0 + r0) * g.ldc + col;
-#pragma unroll 4
-        for (int it = 0; it < BM / RPI; ++it) {
-            if (m0 + r0 + it * RPI >= g.M) break;
-            f32x4 v = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P);
-            float *c = cp + (int64_t)it * RPI * g.ldc;
+        float *cp = reinterpret_cast<float *>(g.C) + col;
+        for (int it = 0; it < N_PASS; it += U) {
+            if (m0 + it * RPI >= g.M) break;   // the same for the whole workgroup
+            f32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P);
             if (vec) {
-                if (g.accumulate) v += *reinterpret_cast<const f32x4 *>(c);
-                *reinterpret_cast<f32x4 *>(c) = v;
+                if (g.accumulate) {
+                    f32x4 c[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        c[u] = *reinterpret_cast<const f32x4 *>(cp + (int64_t)min(m0 + r0 + (it + u) * RPI, g.M - 1) * g.ldc);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] += c[u];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (m0 + r0 + (it + u) * RPI < g.M) *reinterpret_cast<f32x4 *>(cp + (int64_t)(m0 + r0 + (it + u) * RPI) * g.ldc) = v[u];
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (col + e < g.N) c[e] = v[e] + (g.accumulate ? c[e] : 0.f);
+                for (int u = 0; u < U; ++u) {
+                    if (m0 + r0 + (it + u) * RPI >= g.M) break;
+                    float *c = cp + (int64_t)(m0 + r0 + (it + u) * RPI) * g.ldc;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) c[e] = v[u][e] + (g.accumulate ? c[e] : 0.f);
+                }
             }
         }
     } else {
-        const bool vec = !(g.ldc & 7) && !((uintptr_t)g.C & 15) && col + 8 <= g.N &&
-                         (!g.R || (!(g.ldr & 7) && !((uintptr_t)g.R & 15)));
+        const int access = row_access(g.C, g.ldc, col, g.N), access_r = row_access(g.R, g.ldr, col, g.N);
         float bias[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) bias[e] = g.bias && col + e < g.N ? bf2f(g.bias[col + e]) : 0.f;
-        bf16_t *cp = reinterpret_cast<bf16_t *>(g.C) + (int64_t)(m0 + r0) * g.ldc + col;
-        const bf16_t *rp = g.R ? g.R + (int64_t)(m0 + r0) * g.ldr + col : nullptr;
-#pragma unroll 4
-        for (int it = 0; it < BM / RPI; ++it) {
-            if (m0 + r0 + it * RPI >= g.M) break;
-            const f32x4 lo = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P), hi = *reinterpret_cast<const f32x4 *>(sp + it * RPI * P + 4);
-            float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        bf16_t *cp = reinterpret_cast<bf16_t *>(g.C) + col;
+        const bf16_t *rp = g.R ? g.R + col : nullptr;
+        for (int it = 0; it < N_PASS; it += U) {
+            if (m0 + it * RPI >= g.M) break;   // the same for the whole workgroup
+            float v[U][8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += bias[e];
-            bf16_t *c = cp + (int64_t)it * RPI * g.ldc;
-            const bf16_t *r = rp ? rp + (int64_t)it * RPI * g.ldr : nullptr;
-            if (vec) {
-                if (r) {
-                    const uint4 rv = *reinterpret_cast<const uint4 *>(r);
-                    v[0] += bflo(rv.x); v[1] += bfhi(rv.x); v[2] += bflo(rv.y); v[3] += bfhi(rv.y);
-                    v[4] += bflo(rv.z); v[5] += bfhi(rv.z); v[6] += bflo(rv.w); v[7] += bfhi(rv.w);
+            for (int u = 0; u < U; ++u) {
+                const f32x4 lo = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P), hi = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[u][e] = lo[e] + bias[e];
+                    v[u][4 + e] = hi[e] + bias[4 + e];
                 }
-                *reinterpret_cast<uint4 *>(c) = uint4{pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (col + e < g.N) c[e] = f2bf(v[e] + (r ? bf2f(r[e]) : 0.f));
             }
+            if (rp && access_r == 16) {
+                uint4 rv[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    rv[u] = *reinterpret_cast<const uint4 *>(rp + (int64_t)min(m0 + r0 + (it + u) * RPI, g.M - 1) * g.ldr);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u][0] += bflo(rv[u].x); v[u][1] += bfhi(rv[u].x); v[u][2] += bflo(rv[u].y); v[u][3] += bfhi(rv[u].y);
+                    v[u][4] += bflo(rv[u].z); v[u][5] += bfhi(rv[u].z); v[u][6] += bflo(rv[u].w); v[u][7] += bfhi(rv[u].w);
+                }
+            } else if (rp) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    row_add8(v[u], rp + (int64_t)min(m0 + r0 + (it + u) * RPI, g.M - 1) * g.ldr, access_r, col, g.N);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (m0 + r0 + (it + u) * RPI < g.M) row_store8(cp + (int64_t)(m0 + r0 + (it + u) * RPI) * g.ldc, v[u], access, col, g.N);
         }
     }
 }
@@ -240,12 +266,15 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = (g.K + RK - 1) / RK;
-    // first reduction index of the stage walked as number t: with TAIL number 0 is the partial stage (below), otherwise the walk
-    // starts where the 256 x 256 kernel's does
-    const int start = TAIL ? -1 : gemm_walk_start(m0 >> 8, nk);
-    const auto k_of = [&](int t) { return (int64_t)(t + start - (t + start >= nk ? nk : 0)) * RK; };
+    // with TAIL the partial stage is walked first (below), otherwise the walk starts where the 256 x 256 kernel's does
+    int kn = TAIL ? 0 : gemm_walk_start(m0 >> 8, nk) * RK;   // reduction index of the next stage to load
+#define RING_NEXT()                                                                                     \
+    {                                                                                                   \
+        kn += RK;                                                                                       \
+        if (!TAIL && kn == g.K) kn = 0;                                                                 \
+    }
 #define RING_LOAD(J, T, SLOT)                                                                           \
-    ring_load(((J) < LA ? abase : bbase) + k_of(T), off[J],                                             \
+    ring_load(((J) < LA ? abase : bbase) + kn, off[J],                                                  \
               lds0 + (uint32_t)(SLOT) * STAGE + ((J) < LA ? fill_a + (J) * 1024u : fill_b + ((J) - LA) * 1024u))
 #define RING_READ(SET, KS, F, SLOT)                                                                     \
     fr[SET][KS][F] = *reinterpret_cast<const bf16x8 *>(ring + (SLOT) * STAGE + ((F) < TM ? rda[KS] + (F) * 2048 : rdb[KS] + ((F) - TM) * 2048))
@@ -264,12 +293,14 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     } else {
 #pragma unroll
         for (int j = 0; j < LPS; ++j) RING_LOAD(j, 0, 0);
+        RING_NEXT();
     }
 #pragma unroll
     for (int s = 1; s < S; ++s)
         if (s < nk) {
 #pragma unroll
             for (int j = 0; j < LPS; ++j) RING_LOAD(j, s, s);
+            RING_NEXT();
         }
     if constexpr (TAIL) {
 #pragma unroll
@@ -278,7 +309,6 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     }
 #define RING_SEAM(T) (T)
 #define RING_AT_SEAM()
-#define RING_NEXT()
     RING_WALK();
 #undef RING_SEAM
 #undef RING_AT_SEAM

@@ -121,6 +121,7 @@ def test_gemm_bias_epilogue_and_bias_gradient(orc64, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,pad", [(2439, 5888, 64, 8), (2440, 5888, 128, 0), (2439, 5888, 192, 8),       # whole lines
+                                       (2439, 5888, 192, 4),                                                # 8-byte aligned rows
                                        (2445, 3272, 4160, 0), (2560, 3272, 4096, 8), (2445, 3306, 4096, 3),  # ragged columns
                                        (2560, 3328, 4160, 1)])                                               # unaligned rows
 def test_gemm_256_tiles_every_store(M, N, K, pad):
@@ -159,7 +160,7 @@ T64, T128X64, T128, T256X128 = (64, 64), (128, 64), (128, 128), (256, 128)
                                             (1000, 1030, 1000, 2, T64), (2050, 1544, 448, 8, T128), (3000, 1024, 136, 0, T64),
                                             (2304, 2056, 200, 3, T64),
                                             (641, 4520, 72, 8, T128X64), (5591, 518, 128, 1, T128X64), (514, 5632, 128, 0, T128X64),
-                                            (518, 5449, 328, 3, T128), (4867, 585, 320, 0, T128), (578, 5120, 328, 8, T128),
+                                            (518, 5449, 328, 3, T128), (4867, 585, 320, 0, T128), (578, 5120, 328, 8, T128), (578, 5120, 328, 4, T128), (1000, 520, 328, 4, T64),
                                             (1410, 4945, 72, 1, T256X128), (1223, 5714, 128, 2, T256X128), (1542, 4608, 128, 8, T256X128),
                                             (1543, 4608, 72, 0, T256X128)])
 def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
