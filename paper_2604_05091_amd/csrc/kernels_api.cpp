@@ -102,15 +102,15 @@ int32_t mt_k_gemm_tn_split(const uint16_t *At, int64_t lda, const uint16_t *Bt, 
 }
 int32_t mt_k_gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int32_t n_cu) { return gemm_tn_pick_split(M, N, K, n_cu); }
 
-int32_t mt_k_gemm_route(int32_t token_major, int32_t M, int32_t N, int32_t K, int64_t ldc, int32_t split_k, int32_t *route) {
-    if (M <= 0 || N <= 0 || K <= 0 || ldc < N || !route) return MT_ERR_INVALID_ARG;
-    if (token_major ? K % 64 || split_k < 1 || split_k > K / 64 : split_k != 1) return MT_ERR_INVALID_ARG;
+int32_t mt_k_gemm_route(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc, int32_t split_k, int32_t *route) {
+    if (form < 0 || form > 2 || M <= 0 || N <= 0 || K <= 0 || ldc < N || !route) return MT_ERR_INVALID_ARG;
+    if (form == 2 ? K % 64 || split_k < 1 || split_k > K / 64 : split_k != 1) return MT_ERR_INVALID_ARG;
     GemmArgs g;
     g.A = g.B = g.R = nullptr; g.C = nullptr; g.lda = g.ldb = K; g.ldc = ldc; g.ldr = 0;
-    g.M = M; g.N = N; g.K = K; g.out_fp32 = 1; g.accumulate = 0;
+    g.M = M; g.N = N; g.K = K; g.out_fp32 = form > 0; g.accumulate = 0;
     g.split_k = split_k;
     int whole, tm, tn;
-    if (token_major) gemm_tn_route(g, &whole, &tm, &tn);
+    if (form == 2) gemm_tn_route(g, &whole, &tm, &tn);
     else gemm_nt_route(g, &whole, &tm, &tn);
     route[0] = whole; route[1] = tm; route[2] = tn;
     return MT_OK;

@@ -33,10 +33,13 @@ ROW1, ROW2, ROW_ATT_BWD, ROW_FLOOR = 2.0 ** -7, 2.0 ** -6, 2.0 ** -5, 2.0 ** -9
 
 
 # ----------------------------------------------------------------------------- GEMM
-def gemm_route(token_major, M, N, K, ldc=0, split=1):
+NT_BF16, NT_F32, TN = 0, 1, 2
+
+
+def gemm_route(form, M, N, K, ldc=0, split=1):
     """(256 x 256 tiles that a workgroup of the large-grid kernel takes alone, tile of the others)"""
     r = (ctypes.c_int32 * 3)()
-    ok(L.mt_k_gemm_route(token_major, M, N, K, ldc or N, split, ctypes.addressof(r)))
+    ok(L.mt_k_gemm_route(form, M, N, K, ldc or N, split, ctypes.addressof(r)))
     return r[0], (r[1], r[2])
 
 
@@ -79,7 +82,7 @@ def test_gemm_nt_residual_strides_fp32_accumulate(orc64):
 def test_gemm_large_grid_kernel_all_epilogues(orc64, M, N, K):
     """Grids of around 200 tiles of 256 x 256, the last in that kernel, the others in 64 x 64 tiles: ragged
     and exact edges, odd and even step counts, bf16 with residual and strides, fp32 with accumulate."""
-    assert gemm_route(0, M, N, K, N + 8) == ((196, (0, 0)) if K == 320 else (0, (64, 64)))
+    assert gemm_route(NT_BF16, M, N, K, N + 8) == ((196, (0, 0)) if K == 320 else (0, (64, 64)))
     rng = np.random.default_rng(M * 7 + N * 3 + K)
     lda, ldb, ldc, ldr = K + 8, K + 16, N + 8, N + 24
     a_full, b_full = bf16_round(rng.standard_normal((M, lda))), bf16_round(rng.standard_normal((N, ldb)))
@@ -128,7 +131,7 @@ def test_gemm_256_tiles_every_store(M, N, K, pad):
     """The kernel with 256 x 256 tiles: plain, residual, bias, fp32 and accumulating stores, whole lines and guarded ones, one step,
     two, and odd and even numbers of them."""
     ldc, ldr = N + pad, N + 2 * pad
-    assert gemm_route(0, M, N, K, ldc)[1] == (0, 0)
+    assert gemm_route(NT_BF16, M, N, K, ldc)[1] == (0, 0) and (gemm_route(NT_F32, M, N, K, ldc)[1] == (0, 0) or pad == 4)
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, B, R, BI = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, K), (N, K), (M, ldr), (1, N)))
     ref = A.double() @ B.double().T.contiguous()
@@ -166,7 +169,7 @@ T64, T128X64, T128, T256X128 = (64, 64), (128, 64), (128, 128), (256, 128)
 def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
     rng = np.random.default_rng(M * 5 + N * 3 + K)
     lda, ldb, ldc, ldr = K + 8, K + 16, N + pad, N + 3 * pad
-    assert gemm_route(0, M, N, K, ldc) == (0, tile)
+    assert gemm_route(NT_BF16, M, N, K, ldc) == gemm_route(NT_F32, M, N, K, ldc) == (0, tile)
     a, b = bf16_round(rng.standard_normal((M, lda))), bf16_round(rng.standard_normal((N, ldb)))
     r, bias = bf16_round(rng.standard_normal((M, ldr))), bf16_round(rng.standard_normal(N))
     ref = orc64.linear_fwd(np.ascontiguousarray(a[:, :K]), np.ascontiguousarray(b[:, :K]))
@@ -193,7 +196,7 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
 def test_gemm_rest_of_the_rounds_in_smaller_tiles(M, N, K, whole, tile):
     """A little more than whole rounds of 256 tiles of 256 x 256: the full rounds in those, the rest in smaller ones, or all in smaller
     ones where that is estimated faster; complete and ragged edges."""
-    assert gemm_route(0, M, N, K) == (whole, tile)
+    assert gemm_route(NT_BF16, M, N, K) == gemm_route(NT_F32, M, N, K) == (whole, tile)
     g = torch.Generator(device="cuda").manual_seed(M + N)
     A, B, R = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, K), (N, K), (M, N)))
     ref = A.double() @ B.double().T.contiguous()
@@ -256,7 +259,7 @@ def test_gemm_token_major_weight_gradient_small_tiles(orc64, n, out, inn):
                                                   (192, 3656, 3912, 1, (256, 256)), (128, 3088, 2080, 2, (256, 256))])
 def test_gemm_token_major_weight_gradient_every_tile(n, out, inn, split, tile):
     """Each tile of the token-major kernels, unsplit and split where the estimate takes it so; ragged edges."""
-    assert gemm_route(1, out, inn, n, inn, split)[1] == tile
+    assert gemm_route(TN, out, inn, n, inn, split)[1] == tile
     g = torch.Generator(device="cuda").manual_seed(n + out + inn)
     DY, X = (torch.randn((n, w), device="cuda", generator=g).to(torch.bfloat16) for w in (out, inn))
     ref = DY.double().T.contiguous() @ X.double()
