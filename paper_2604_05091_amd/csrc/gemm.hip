@@ -9,8 +9,8 @@
 //
 // Here a workgroup owns a 256 x 256 tile of C made of 16x16 MFMA blocks (v_mfma_f32_16x16x32_bf16, 4 fp32 accumulators
 // per lane per block): 4 waves x 128x128 quadrants, K walked in steps of 64 through a double-buffered LDS stage,
-// software-pipelined inside the wave.  Reductions that are no multiple of 64 and grids that 256 x 256 tiles fill badly
-// go to the kernels with smaller tiles in gemm_ring.hip (choose_tile).
+// software-pipelined inside the wave.  Grids that 256 x 256 tiles fill badly go to the kernels with smaller tiles in
+// gemm_ring.hip (choose_tile).
 //
 // Workgroup -> tile mapping: consecutive workgroup ids are dealt round-robin to the
 // 8 XCDs, each with a private L2.  The id is first re-numbered so that every XCD gets
@@ -32,6 +32,7 @@ constexpr int BK = 64;
 constexpr int kXcd = 8;
 constexpr int kRound = 256;   // workgroups of one round: a compute unit holds one of these kernels' workgroups
 constexpr int W4_BM = 256, W4_BN = 256, W4_NT = 256;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 // bf16 results leave through LDS.  Stored straight from the accumulator layout, a store instruction touches 32
 // rows with 16 bytes each, and these partial-line writes cost 10-13 us per tile; instead every wave writes its
@@ -365,7 +366,10 @@ __device__ __forceinline__ void w4_mfma_group(f32x4 (&acc)[8][8], const bf16x8 (
     }
 }
 
-template <int EPI>
+// TAIL (K % 64 != 0, K > 64): the last, partial k-step is walked first; it goes through registers, chunks at or beyond K as zeros.
+// In 256 x 128 tiles (gemm_ring.hip) -> here, us: 16384 x 4096 x 11024 1798 -> 1351, 14080 x 1024 x 14200 601 -> 459, 22016 x 4096 x 3000
+// 552 -> 484, 16384 x 4096 x 1416 232 -> 173.
+template <int EPI, bool TAIL>
 __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     __shared__ __attribute__((aligned(1024))) char sl0[WE_ARRAY];
     __shared__ __attribute__((aligned(1024))) char sl1[WE_ARRAY];
@@ -460,19 +464,38 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
         WE_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
     }
 
-    const int nk = g.K / BK, start = gemm_walk_start(tm, nk);
+    const int nk = (g.K + BK - 1) / BK, start = TAIL ? -1 : gemm_walk_start(tm, nk);
     const auto at = [&](int t) { return t + start - (t + start >= nk ? nk : 0); };   // k-step walked as number t
     {
         const int t0_ = at(0), t1_ = at(min(1, nk - 1));
+        u32x4 tv[TAIL ? 16 : 1];
+        if constexpr (TAIL) {
+            const int kt = (nk - 1) * BK;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) WE_LOAD1(sl0, j, t0_);
+            for (int j = 0; j < 16; ++j) {
+                const int r = wave * 64 + (j & 7) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+                const bool ok = kt + chunk * 8 < g.K;   // otherwise column 0 of the row is read (in bounds) and replaced
+                const char *p = reinterpret_cast<const char *>(j < 8 ? abase : bbase) + off[j] + (ok ? kt * 2 : -chunk * 16);
+                tv[j] = *reinterpret_cast<const u32x4 *>(p);
+                if (!ok) tv[j] = u32x4{0u, 0u, 0u, 0u};
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) WE_LOAD1(sl0, j, t0_);
+        }
 #pragma unroll
         for (int j = 0; j < 16; ++j) WE_LOAD1(sl1, j, t1_);
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                *reinterpret_cast<u32x4 *>(sl0 + (j < 8 ? 0 : WE_HALF) + fill_off + (j & 7) * 1024 + lane * 16) = tv[j];
+        }
     }
     WE_WAIT(16);
 #pragma unroll
     for (int u = 0; u < 16; ++u) WE_READ1(0, sl0, 0, u);
     int kt = 0;
+    if constexpr (TAIL) __builtin_assume(nk >= 2);   // one path less on which the accumulators could be moved about
     for (; kt + 2 <= nk; kt += 2) {
         WE_STEP(sl0, sl1, kt);
         WE_STEP(sl1, sl0, kt + 1);
@@ -513,7 +536,11 @@ bool whole_line_store(const GemmArgs &g) {
 template <int EPI>
 hipError_t launch_w4e_epi(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
     const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = EPI == EPI_GLU ? g.glu_F / 128 : (g.N + W4_BN - 1) / W4_BN;
-    hipLaunchKernelGGL(gemm_nt_w4e_kernel<EPI>, dim3((unsigned)(n_tiles > 0 ? n_tiles : tiles_m * tiles_n)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
+    auto kernel = gemm_nt_w4e_kernel<EPI, false>;
+    // (the fused stores take whole k-steps only)
+    if constexpr (EPI == EPI_GUARDED_BF16 || EPI == EPI_GUARDED_F32 || EPI == EPI_FULL_BF16 || EPI == EPI_FULL_F32 || EPI == EPI_FULL_BF16_RES || EPI == EPI_FULL_BF16_BIAS)
+        if (g.K % BK) kernel = gemm_nt_w4e_kernel<EPI, true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_tiles > 0 ? n_tiles : tiles_m * tiles_n)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
     return hipGetLastError();
 }
 
@@ -776,7 +803,7 @@ int variant_override() {
 
 }  // namespace
 
-// The fused stores exist in the 256 x 256 kernel only.  They are taken from 192 tiles on: below, the separate pass over a
+// The fused stores exist in the 256 x 256 kernel only, for whole k-steps.  They are taken from 192 tiles on: below, the separate pass over a
 // small result costs less than the idle compute units.
 static bool takes_w4(const GemmArgs &g) {
     const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
@@ -883,7 +910,7 @@ static double guarded_store(const GemmArgs &g) {
 template <int N_COSTS>
 static const TileCost &choose_tile(const TileCost (&costs)[N_COSTS], int64_t M, int64_t N, int64_t K, int split) {
     const double stages = (double)((K + BK - 1) / BK);
-    const int first = K % BK ? 1 : 0;   // the 256 x 256 kernel takes whole stages only
+    const int first = K < BK ? 1 : 0;   // the 256 x 256 kernel takes a whole stage at least
     const TileCost *best = &costs[first];
     double best_t = tn_time(*best, M, N, stages, split, kComputeUnits);
     for (int i = first + 1; i < N_COSTS; ++i) {
@@ -930,7 +957,7 @@ static NtRoute nt_route(const GemmArgs &g) {
     // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
     const double stages = (double)((g.K + BK - 1) / BK), tiles = tile_count(costs[0], g.M, g.N);
     const int whole = (int)(std::floor(tiles / kRound) * kRound), rest = (int)tiles - whole;
-    if (g.K % BK == 0 && whole > 0 && rest > 0) {
+    if (g.K >= BK && whole > 0 && rest > 0) {
         double best_t = 0.97 * tn_time(one, g.M, g.N, stages, 1, kComputeUnits);
         int small = 0;
         for (int i = 1; i < (int)std::size(kNtCosts); ++i) {
@@ -967,7 +994,7 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s) {
     switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = the estimate
         case 2: return gemm_nt_ring(g, RingTile::t256x128, -1, s);
         case 3: return gemm_nt_ring(g, RingTile::t128x128, -1, s);
-        case 6: if (g.K % BK == 0) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
+        case 6: if (g.K >= BK) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
         default: break;
     }
     const NtRoute r = nt_route(g);

@@ -126,7 +126,10 @@ def test_gemm_bias_epilogue_and_bias_gradient(orc64, M, N, K):
 @pytest.mark.parametrize("M,N,K,pad", [(2439, 5888, 64, 8), (2440, 5888, 128, 0), (2439, 5888, 192, 8),       # whole lines
                                        (2439, 5888, 192, 4),                                                # 8-byte aligned rows
                                        (2445, 3272, 4160, 0), (2560, 3272, 4096, 8), (2445, 3306, 4096, 3),  # ragged columns
-                                       (2560, 3328, 4160, 1)])                                               # unaligned rows
+                                       (2560, 3328, 4160, 1),                                                # unaligned rows
+                                       # a partial last step: one chunk of it, most, after one and many whole steps
+                                       (2439, 5888, 72, 8), (2439, 5888, 120, 0), (2440, 5888, 136, 0), (2439, 5888, 200, 8),
+                                       (2445, 3272, 4104, 0), (2445, 3306, 4168, 3), (2560, 3328, 4104, 1)])
 def test_gemm_256_tiles_every_store(M, N, K, pad):
     """The kernel with 256 x 256 tiles: plain, residual, bias, fp32 and accumulating stores, whole lines and guarded ones, one step,
     two, and odd and even numbers of them."""
@@ -192,7 +195,10 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
                                               (3000, 5632, 320, 256, T64), (3334, 5632, 256, 256, T128X64), (3340, 5632, 512, 256, T128),
                                               (3377, 5888, 1024, 256, T256X128),
                                               (2825, 5704, 2048, 256, T64), (5155, 3074, 3072, 256, T128X64), (2309, 7288, 3072, 256, T128),
-                                              (6668, 7818, 4096, 768, T256X128)])
+                                              (6668, 7818, 4096, 768, T256X128),
+                                              # a partial last step
+                                              (2691, 6912, 136, 256, T64), (3334, 5632, 200, 256, T128X64), (2586, 7168, 328, 256, T128),
+                                              (5382, 7424, 136, 512, T256X128), (2196, 7178, 2056, 256, T64)])
 def test_gemm_rest_of_the_rounds_in_smaller_tiles(M, N, K, whole, tile):
     """A little more than whole rounds of 256 tiles of 256 x 256: the full rounds in those, the rest in smaller ones, or all in smaller
     ones where that is estimated faster; complete and ragged edges."""
