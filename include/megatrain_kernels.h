@@ -128,7 +128,8 @@ int32_t mt_k_swiglu_bwd(uint16_t *dgu, const uint16_t *ds, const uint16_t *gu, i
 int32_t mt_k_embed_gather(uint16_t *h, const uint16_t *table, const int32_t *tokens, int64_t n, int32_t d,
                           void *stream);
 /* dtable [V,d] fp32, every row written: row v = sum of dh[order[i],:] for i in [row_start[v], row_start[v+1]),
- * added in that order (deterministic).  row_start has V+1 entries. */
+ * in a fixed order (deterministic): up to 32 terms as listed, more as eighths of the list whose sums are added in turn.
+ * row_start has V+1 entries. */
 int32_t mt_k_embed_scatter(float *dtable, const uint16_t *dh, const int32_t *row_start, const int32_t *order,
                            int32_t V, int32_t d, void *stream);
 

@@ -513,7 +513,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
 // One block per row: maximum and sum of exponentials, then the gradient.  HBM-bound at 6 V bytes per row if the logits are
 // read once: up to 4 NR NT of them (32 768) stay in the registers of the block's NT threads between the two passes; wider
 // rows (NR = 0) are read twice, the first time with a running maximum.  8192 rows, before (256 threads, two reads) and
-// after: V = 32 000 470 -> 312 us (5.05 TB/s), 16 384 208 -> 157, 8000 100 -> 75, 1024 13.1 -> @V1024@.
+// after: V = 32 000 468 -> 282 us (5.6 TB/s), 16 384 208 -> 156, 8000 99 -> 75, 1024 14.1 -> 12.5.
 
 template <int NT>
 __device__ __forceinline__ float block_reduce(float v, float *buf, bool is_max) {
@@ -764,7 +764,12 @@ hipError_t embed_gather(bf16_t *h, const bf16_t *table, const int32_t *tokens, i
 hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
                          int32_t d, hipStream_t s) {
     if (V <= 0 || d <= 0 || (d & 7)) return hipErrorInvalidValue;
-    const int nc = d <= 512 ? 1 : d <= 1024 ? 2 : 4;
+    // wide shares for big tables; smaller ones where the blocks would be too few for the chip (NC = 1 / 2 / 4 / a block per row, us):
+    // 4848 uniform tokens, V = 1096, d = 1280 5.4 / 5.4 / 6.3 / 5.6; 4096 tokens, V = 1024, d = 1024 4.5 / 5.4 / 6.0 / 5.1; 65 536, 2000, 5120
+    // 173 / 167 / 188 / 207; 4096, 4000, 4096 16.5 / 16.1 / 16.5 / 18.9; 800, 11 704, 1600 17.8 / 16.0 / 15.6 / 15.2; 65 536, 32 000, 4096
+    // 297 / 260 / 213 / 217
+    const auto blocks = [&](int nc) { return (int64_t)((V + 7) / 8) * ((d + 512 * nc - 1) / (512 * nc)); };
+    const int nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
     const dim3 grid(nc * blocks_for(V, kScatterWaves * nc), blocks_for(d, 512 * nc)), block(64 * kScatterWaves);
     if (nc == 1) hipLaunchKernelGGL(embed_scatter_kernel<1>, grid, block, 0, s, dtable, dh, row_start, order, V, d);
     else if (nc == 2) hipLaunchKernelGGL(embed_scatter_kernel<2>, grid, block, 0, s, dtable, dh, row_start, order, V, d);
