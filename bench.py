@@ -89,7 +89,8 @@ def cpu_baseline(name: str) -> dict:
 
 def gemm_source_hash() -> str:
     import hashlib
-    return hashlib.sha256(open(os.path.join(ROOT, "paper_2604_05091_amd", "csrc", "gemm.hip"), "rb").read()).hexdigest()[:16]
+    src = b"".join(open(os.path.join(ROOT, "paper_2604_05091_amd", "csrc", f), "rb").read() for f in ("gemm.hip", "gemm_ring.hip"))
+    return hashlib.sha256(src).hexdigest()[:16]
 
 
 def measured_traffic(name: str, dom: int):
@@ -178,7 +179,7 @@ def run_workload(name: str, steps: int, warmup: int, args, flags: int = 0, adam:
     cls_fl = np.sum([s["class_flops"] for s in per_step], axis=0)
     cls_n = np.sum([s["class_launches"] for s in per_step], axis=0)
     cls_by = np.sum([s["class_bytes"] for s in per_step], axis=0)
-    names = ["gemm_nt_w4e_kernel<*> + gemm_tn_w4e_kernel<*> (bf16 MFMA GEMM)", "flash_fwd_kernel", "flash_bwd_dkdv_kernel + flash_bwd_dq_kernel"]
+    names = ["gemm_nt_w4e_kernel<*> + gemm_tn_w4e_kernel<*> + ring_nt_kernel<*> + ring_tn_kernel<*> (bf16 MFMA GEMM)", "flash_fwd_kernel", "flash_bwd_dkdv_kernel + flash_bwd_dq_kernel"]
     dom = int(np.argmax(cls_ms))
     achieved = cls_fl[dom] / (cls_ms[dom] * 1e-3) / 1e12 if cls_ms[dom] > 0 else 0.0
     traffic, traffic_note = measured_traffic(name, dom)
