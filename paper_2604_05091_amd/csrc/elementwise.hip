@@ -73,9 +73,10 @@ __global__ __launch_bounds__(256) void transpose_kernel(TransposeArgs t) {
 }
 
 // ------------------------------------------------------------------ RMSNorm forward
-// One wave per row; the row is held in registers (NCH chunks of 8 per lane), four waves on a SIMD at every width
-// (4026 x 7368 with three 22.1 us, with four 18.3).
-template <int NCH>
+// One wave per row; the row is held in registers (NCH chunks of 8 per lane).  PACKED: as it was loaded; otherwise the compiler keeps
+// the unpacked row, and fewer waves fit on a SIMD (NCH = 8: five instead of eight).  A launch of few rounds is the faster for more
+// waves, one of many for fewer (see rmsnorm_fwd).
+template <int NCH, bool PACKED>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n,
                                                           int d, float eps) {
     const int lane = threadIdx.x & 63;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
         }
     }
     ss = wave_sum(ss);
-    if constexpr (NCH > 12) {   // kept as loaded: the compiler would keep the unpacked row, and three waves on a SIMD instead of four
+    if constexpr (PACKED) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) asm volatile("" : "+v"(xv[i].x), "+v"(xv[i].y), "+v"(xv[i].z), "+v"(xv[i].w));
     }
@@ -668,11 +669,14 @@ hipError_t rmsnorm_fwd(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n
                        hipStream_t s) {
     if (n <= 0 || d <= 0 || (d & 7) || d > 8192) return hipErrorInvalidValue;
     const unsigned grid = blocks_for(n, 4);
-    // by the next multiple of 1024 columns: a kernel for wider rows would load past the end of this one for nothing
-    // (3117 x 6144 with 16 chunks per lane 16.6 us, with 12 13.7)
-    decltype(&rmsnorm_fwd_kernel<2>) const kernels[8] = {rmsnorm_fwd_kernel<2>, rmsnorm_fwd_kernel<4>, rmsnorm_fwd_kernel<6>, rmsnorm_fwd_kernel<8>,
-                                                         rmsnorm_fwd_kernel<10>, rmsnorm_fwd_kernel<12>, rmsnorm_fwd_kernel<14>, rmsnorm_fwd_kernel<16>};
-    const auto kernel = kernels[(d - 1) / 1024];
+    // Few rows: by the next multiple of 1024 columns (a kernel for wider rows would load past the end of this one for nothing), rows
+    // packed: 5136 x 3904 14.7 -> 13.4 us, 8192 x 5120 25.9 -> 24.1, 3117 x 6144 16.7 -> 13.8, 4026 x 7368 22.0 -> 18.4.  Many: with fewer waves,
+    // 24 576 x 5120 98 -> 94, 65 536 x 3072 146 -> 141, x 5120 248 -> 241, x 6144 298 -> 288; 16 384 x 4096 39.5 -> 40.6.
+    const int k = (d - 1) / 1024;
+    decltype(&rmsnorm_fwd_kernel<2, false>) const few[8] = {rmsnorm_fwd_kernel<2, false>, rmsnorm_fwd_kernel<4, false>, rmsnorm_fwd_kernel<6, true>, rmsnorm_fwd_kernel<8, true>,
+                                                            rmsnorm_fwd_kernel<10, true>, rmsnorm_fwd_kernel<12, true>, rmsnorm_fwd_kernel<14, true>, rmsnorm_fwd_kernel<16, true>};
+    const auto many = k <= 1 ? rmsnorm_fwd_kernel<4, false> : k <= 3 ? rmsnorm_fwd_kernel<8, false> : k == 4 ? rmsnorm_fwd_kernel<10, false> : rmsnorm_fwd_kernel<16, false>;
+    const auto kernel = n < 20480 ? few[k] : many;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
     return hipGetLastError();
 }
