@@ -107,8 +107,8 @@ def measured_traffic(name: str, dom: int):
         return None, "no counter summary for this workload"
     hm = re.search(r"gemm_source_sha256_16 = ([0-9a-f]+)", text)
     if not hm or hm.group(1) != gemm_source_hash():
-        return None, "profiles/gemm_kernels_7B_hbm_traffic.md was measured on an older csrc/gemm.hip"
-    return float(m.group(1)), "profiles/gemm_kernels_7B_hbm_traffic.md (same csrc/gemm.hip)"
+        return None, "profiles/gemm_kernels_7B_hbm_traffic.md was measured on older csrc/gemm.hip and gemm_ring.hip"
+    return float(m.group(1)), "profiles/gemm_kernels_7B_hbm_traffic.md (same csrc/gemm.hip and gemm_ring.hip)"
 
 
 def run_workload(name: str, steps: int, warmup: int, args, flags: int = 0, adam: bool = True, quiet: bool = False) -> dict:
