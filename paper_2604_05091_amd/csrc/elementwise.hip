@@ -675,7 +675,7 @@ hipError_t rmsnorm_fwd(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n
     const int k = (d - 1) / 1024;
     decltype(&rmsnorm_fwd_kernel<2, false>) const few[8] = {rmsnorm_fwd_kernel<2, false>, rmsnorm_fwd_kernel<4, false>, rmsnorm_fwd_kernel<6, true>, rmsnorm_fwd_kernel<8, true>,
                                                             rmsnorm_fwd_kernel<10, true>, rmsnorm_fwd_kernel<12, true>, rmsnorm_fwd_kernel<14, true>, rmsnorm_fwd_kernel<16, true>};
-    const auto many = k <= 1 ? rmsnorm_fwd_kernel<4, false> : k <= 3 ? rmsnorm_fwd_kernel<8, false> : k == 4 ? rmsnorm_fwd_kernel<10, false> : rmsnorm_fwd_kernel<16, false>;
+    const auto many = k <= 1 ? few[k] : k <= 3 ? rmsnorm_fwd_kernel<8, false> : k == 4 ? rmsnorm_fwd_kernel<10, false> : rmsnorm_fwd_kernel<16, false>;
     const auto kernel = n < 20480 ? few[k] : many;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
     return hipGetLastError();
