@@ -872,6 +872,41 @@ def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd, route):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 264 else 0, dq_floor=2 * ROW_FLOOR)
 
 
+# A workgroup that goes through a list of blocks: one to four of them, odd numbers of tiles, lists of different lengths, padding between
+# the sets of an XCD (sets no multiple of 8), blocks with fewer rows than a wave owns.
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(64, 72, 12, 12, 128), (17, 328, 24, 8, 128), (41, 264, 8, 4, 128), (4, 840, 33, 33, 128)])
+def test_flash_attention_lists_of_blocks(orc64, B, T, Hq, Hkv, hd):
+    assert attention_route(B, T, Hq, Hkv, hd)[0] == 256
+    _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 264 else 0, dq_floor=2 * ROW_FLOOR)
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 72, 2, 1, 64), (1, 136, 2, 1, 128), (64, 136, 8, 8, 128)])
+def test_flash_attention_rows_in_reverse_order(B, T, Hq, Hkv, hd):
+    """Rows may lie anywhere a 64-bit pitch reaches: stored last row first (negative pitches) they give the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    nq, nkv = Hq * hd, Hkv * hd
+    ld, n, scale = nq + 2 * nkv, B * T, 1.0 / np.sqrt(hd)
+    x = torch.randn((n, ld), device="cuda", generator=g).to(torch.bfloat16)
+    dout = torch.randn((n, nq), device="cuda", generator=g).to(torch.bfloat16)
+    got = []
+    for sign in (1, -1):
+        # (the batch's sequences follow each other in the same order as the rows)
+        X, DO = (x, dout) if sign > 0 else (x.flip(0).contiguous(), dout.flip(0).contiguous())
+        p, do = (X.data_ptr(), DO.data_ptr()) if sign > 0 else (X.data_ptr() + 2 * (n - 1) * ld, DO.data_ptr() + 2 * (n - 1) * nq)
+        O, LSE = torch.zeros((n, nq), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, Hq, T), device="cuda")
+        DELTA, D = torch.zeros((B, Hq, T), device="cuda"), torch.zeros((n, ld), dtype=torch.bfloat16, device="cuda")
+        a = (p, sign * ld, p + 2 * nq, sign * ld, p + 2 * (nq + nkv), sign * ld)
+        ok(L.mt_k_flash_fwd(O.data_ptr(), nq, LSE.data_ptr(), *a, B, T, Hq, Hkv, hd, scale, None))
+        d = D.data_ptr()
+        ODO = O if sign > 0 else O.flip(0).contiguous()
+        po = O.data_ptr() if sign > 0 else ODO.data_ptr() + 2 * (n - 1) * nq
+        ok(L.mt_k_flash_bwd(d, ld, d + 2 * nq, ld, d + 2 * (nq + nkv), ld, do, sign * nq, *a, po, sign * nq, LSE.data_ptr(), DELTA.data_ptr(),
+                            B, T, Hq, Hkv, hd, scale, None))
+        got.append((O, LSE, D))
+    for one, other in zip(*got):
+        assert torch.equal(one, other)
+
+
 def test_flash_attention_scores_of_minus_infinity(orc64):
     """Keys whose scores are -inf for a query (inf * -1) have no weight, also where a whole 32-key half is such."""
     B, T, H, hd = 1, 136, 2, 64
