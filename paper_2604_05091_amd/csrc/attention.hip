@@ -23,11 +23,9 @@
 // reads give exactly the eight reduction indices of the accumulator permutation.
 // dQ and dK/dV are separate kernels: no atomics, results are bit-reproducible.
 //
-// LDS rows have a pitch of head_dim + 40 elements: consecutive rows then start 20 banks apart, which keeps
-// the 16-byte row reads conflict-free and lets the four rows touched by one transposing read overlap in 12
-// of the 64 banks only (a pitch of head_dim + 8 piles them onto the same 28 banks and halves the LDS rate).
-#include <stdlib.h>
-
+// Tiles go from memory to LDS without passing through registers (DirectTile); where their 16-byte chunks lie is chosen so that
+// row-wise and transposing reads are free of bank conflicts.  Against tiles that were fetched into registers and written to LDS
+// (rows padded by 80 bytes): forward 2-15 %, backward 4-19 % faster, most on short walks.
 #include <algorithm>
 
 #include "common.h"
@@ -42,54 +40,6 @@ constexpr float kLazyMax = 8.0f;  // forward: the running maximum may lag the tr
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-// Register-staged cooperative copy of a [ROWS x COLS] bf16 tile (row-major source, leading dimension ld)
-// into LDS with pitch LDP, by NT threads.  fetch() issues all global loads back to back (out-of-range
-// chunks are redirected to the tile origin, which is always readable, and remembered in a bit mask);
-// commit() writes the registers to LDS, zeros for the out-of-range chunks.  Splitting the two lets the
-// loads of tile t+1 fly while tile t is being multiplied.
-template <int ROWS, int COLS, int LDP, int NT>
-struct TileStage {
-    static constexpr int CPR = COLS / 8, CHUNKS = ROWS * CPR, N = CHUNKS / NT;
-    static_assert(CHUNKS % NT == 0, "tile must split evenly over the threads");
-    u32x4 v[N];
-    uint32_t okmask;
-    __device__ __forceinline__ void fetch(const bf16_t *src, int64_t ld, int rows_valid, int cols_valid) {
-        okmask = 0;
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int chunk = threadIdx.x + NT * j, r = chunk / CPR, c = (chunk % CPR) * 8;
-            const bool ok = r < rows_valid && c < cols_valid;
-            const bf16_t *p = src + (ok ? (int64_t)r * ld + c : 0);
-            v[j] = *reinterpret_cast<const u32x4 *>(p);
-            okmask |= (ok ? 1u : 0u) << j;
-        }
-    }
-    // Rows past rows_valid re-read the last valid row instead of becoming zeros (callers that mask those
-    // rows anyway); no select on the way to LDS, so the values never have to pass through the VALU.
-    __device__ __forceinline__ void fetch_clamped(const bf16_t *src, int64_t ld, int rows_valid) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int chunk = threadIdx.x + NT * j, r = min(chunk / CPR, rows_valid - 1), c = (chunk % CPR) * 8;
-            v[j] = *reinterpret_cast<const u32x4 *>(src + (int64_t)r * ld + c);
-        }
-    }
-    __device__ __forceinline__ void commit_plain(bf16_t *dst) const {
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int chunk = threadIdx.x + NT * j, r = chunk / CPR, c = (chunk % CPR) * 8;
-            *reinterpret_cast<u32x4 *>(dst + r * LDP + c) = v[j];
-        }
-    }
-    __device__ __forceinline__ void commit(bf16_t *dst) const {
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int chunk = threadIdx.x + NT * j, r = chunk / CPR, c = (chunk % CPR) * 8;
-            *reinterpret_cast<u32x4 *>(dst + r * LDP + c) = ((okmask >> j) & 1u) ? v[j] : zero;
-        }
-    }
-};
-
 // Unpadded LDS tiles, filled by loads that write LDS directly (a wave's 64 lanes x 16 bytes land one after the other, so padding is
 // not possible): the 16-byte chunk c of row r lies at position c ^ swz(r) of its row, and every lane fetches the chunk that belongs at its
 // position.  swz takes different values for the rows that one pass of a 16-byte row read covers (16 rows of 256 bytes, 8 pairs of rows
@@ -101,7 +51,11 @@ __device__ __forceinline__ int swz(int r) {
 // byte offset of the lane's part of a row-wise fragment (row l32, 8 columns from 8 hl): k-step ks lies at row_off ^ (32 ks), rows + 32 n at + n 64 HD
 template <int HD>
 __device__ __forceinline__ uint32_t row_off(int l32, int hl) { return l32 * (2 * HD) + ((hl ^ swz<HD>(l32)) << 4); }
-// The same for a transposing fragment read (lane layout as in read_tr_frag): columns + 32 hb at off ^ (64 hb), rows + 8 at + 16 HD and ^ 32.
+// The same for a transposing fragment read: columns + 32 hb at off ^ (64 hb), rows + 8 at + 16 HD and ^ 32.  Its result is the A operand
+// of an MFMA whose output rows are the tile's columns 32 hb .. + 31 (lane l % 32 <-> column) and whose eight reduction slots of lane
+// half hl are the rows row0 + 4 hl + {0..3} and row0 + 8 + 4 hl + {0..3}: the order in which a lane holds the matching accumulator
+// registers of a 32x32 block.  ds_read_b64_tr_b16 works on groups of 16 lanes: lane i of a group supplies the address of 4
+// consecutive columns of one row (i / 4); it receives column i of the 4 x 16 block so formed, rows 0..3.
 template <int HD>
 __device__ __forceinline__ uint32_t tr_off_swz(int lane) {
     const int g = lane >> 4, i = lane & 15, r = (g >> 1) * 4 + (i >> 2);
@@ -120,32 +74,30 @@ __host__ __device__ inline bool near_pitch(int64_t ld) { return ld >= 0 && ld < 
 // Fills such a tile of ROWS rows with the rows row0 .. of src (pitch ld), NW waves.  The loads are assembly and the waits for them are
 // written by hand: in front of every LDS read that might alias a builtin load-to-LDS the compiler waits for all of them.  A load covers
 // 4 or 8 whole rows, rows come in multiples of 8, so rows past the end (row_end) are replaced by the last ones for a whole load at a
-// time, in scalar registers.  (The lane's offset from the first row of a load has 32 bits; row pitches beyond that, or negative, take
-// a 64-bit address per lane.)
-template <int ROWS, int HD, int NW, bool FAR = true>
+// time, in scalar registers.  The lane's offset from the first row of a load has 32 bits; FAR: row pitches beyond that, or negative, a
+// 64-bit address per lane.
+template <int ROWS, int HD, int NW, bool FAR, int GS = 1024>
 struct DirectTile {
-    static constexpr int LPR = HD / 8, RPL = 64 / LPR, N = ROWS / (RPL * NW);
+    static constexpr int LPR = HD / 8, RPL = 64 / LPR, N = ROWS / (RPL * NW);   // lanes per row, rows per load, loads of a wave
     static_assert(N * RPL * NW == ROWS, "tile must split evenly over the waves");
     uint32_t row_bytes, chunk, lds_wave;
     int r, wave;
-    bool near;
     __device__ __forceinline__ void init(const void *smem, int64_t ld, int lane, int wave_) {
         typedef __attribute__((address_space(3))) const void *lptr;
-        wave = __builtin_amdgcn_readfirstlane(wave_);
+        wave = wave_;
         r = lane / LPR;
-        near = near_pitch(ld);
         row_bytes = r * (uint32_t)ld * 2;
-        chunk = ((lane % LPR) ^ swz<HD>(RPL * wave_ + r)) << 4;
-        lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr)smem + (uint32_t)wave_ * 1024u);
+        chunk = ((lane % LPR) ^ (GS == 1024 ? swz<HD>(RPL * wave_ + r) : r << 2)) << 4;
+        lds_wave = (uint32_t)(uintptr_t)(lptr)smem + (uint32_t)wave_ * GS;
     }
     __device__ __forceinline__ void load(uint32_t lds_off, const bf16_t *src, int64_t ld, int row0, int row_end) const {
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             const int row = min(row0 + RPL * (wave + NW * j), row_end - RPL);
             const bf16_t *p = src + (int64_t)row * ld;
-            const uint32_t m0 = lds_wave + lds_off + j * (NW * 1024);
-            const uint32_t c = RPL * NW % 16 ? chunk ^ (swz<HD>(RPL * NW * j) << 4) : chunk;   // (the rows of a load differ from those of the first)
-            if (!FAR || near) {
+            const uint32_t m0 = lds_wave + lds_off + j * (NW * GS);
+            const uint32_t c = GS == 1024 && RPL * NW % 16 ? chunk ^ (swz<HD>(RPL * NW * j) << 4) : chunk;   // (the rows of a load differ from those of the first)
+            if (!FAR) {
                 asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(row_bytes + c), "s"(p), "s"(m0) : "memory");
             } else {
                 const char *q = reinterpret_cast<const char *>(p + (int64_t)r * ld) + c;
@@ -154,8 +106,63 @@ struct DirectTile {
         }
     }
 };
+// (in a scalar register: what depends on it is a scalar branch)
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 // all tiles that this wave asked for have landed and its LDS reads are done, and so have those of the other waves
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__device__ __forceinline__ uint32_t lds_address(const void *smem) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)smem; }
+// Tiles of the backward.  It reads most of them row-wise and transposed and has fewer registers for addresses, so with head_dim 128 the
+// four rows of a load are followed by 16 bytes of padding and only a chunk's 64-byte group is swizzled (by the row's place in its load:
+// the rows of a load then differ in the group, the loads in the place within it): the other column bits, and all row steps, are constants of
+// the instruction.  head_dim 64: as above.
+template <int HD>
+struct BwdTile {
+    static constexpr int GS = HD == 128 ? 1040 : 1024, RPL = 512 / HD, ROW = 2 * HD;
+    static constexpr uint32_t BYTES = 64 / RPL * GS;   // of 64 rows
+    static __device__ __forceinline__ uint32_t rows(int n) { return n / RPL * GS; }   // offset of row n (a multiple of 8)
+    uint32_t ra[4], ta[HD / 32];   // (LDS addresses as numbers: through a pointer to the dynamic LDS the compiler adds its base, 0, over and over)
+    __device__ __forceinline__ void init(const void *smem, int lane) {
+        const uint32_t base = lds_address(smem);
+        const int l32 = lane & 31, hl = lane >> 5, g = lane >> 4, i = lane & 15;
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+            ra[n] = base + (HD == 128 ? l32 / 4 * GS + (l32 & 3) * ROW + ((n ^ (l32 & 3)) << 6) + hl * 16 : l32 * ROW + (((2 * n + hl) ^ swz<HD>(l32)) << 4));
+        const int r = (g >> 1) * 4 + (i >> 2);
+#pragma unroll
+        for (int hb = 0; hb < HD / 32; ++hb)
+            ta[hb] = base + (HD == 128 ? (g >> 1) * GS + (i >> 2) * ROW + ((hb ^ (i >> 2)) << 6) + (g & 1) * 32 + (i & 3) * 8
+                               : r * ROW + (((hb * 4 + (g & 1) * 2 + ((i & 3) >> 1)) ^ swz<HD>(r)) << 4) + (i & 1) * 8);
+        // (one register each: known too well they are taken apart, and every combination with a constant is kept)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) asm volatile("" : "+v"(ra[n]));
+#pragma unroll
+        for (int hb = 0; hb < HD / 32; ++hb) asm volatile("" : "+v"(ta[hb]));
+    }
+    // 8 columns from 16 ks + 8 hl on of the lane's row (l32; add rows(n) to the tile's address for row n + l32)
+    __device__ __forceinline__ bf16x8 row_frag(uint32_t tile, int ks) const {
+        typedef __attribute__((address_space(3))) const bf16x8 *lds_ptr;
+        return *(lds_ptr)(tile + (HD == 128 ? ra[ks >> 1] + (ks & 1) * 32 : ra[ks]));
+    }
+    // transposing read (read_tr_swz) of the rows from row0 on (a multiple of 16), columns from 32 hb on
+    __device__ __forceinline__ bf16x8 tr_frag(uint32_t tile, int row0, int hb) const {
+        typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
+        const uint32_t p = tile + rows(row0);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + ta[hb]));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + rows(8) + (HD == 128 ? ta[hb] : ta[hb] ^ 32)));
+        typedef __attribute__((ext_vector_type(8))) short s16x8;
+        const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, v);
+    }
+    // acc[hb] += X^T (columns hb*32.. of the tile X, reduction rows row0 ..) * frag, for all hb
+    __device__ __forceinline__ void accumulate(f32x16 *acc, uint32_t tile, int row0, const bf16x8 &frag) const {
+        bf16x8 a[HD / 32];
+#pragma unroll
+        for (int hb = 0; hb < HD / 32; ++hb) a[hb] = tr_frag(tile, row0, hb);
+#pragma unroll
+        for (int hb = 0; hb < HD / 32; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[hb], frag, acc[hb], 0, 0, 0);
+    }
+};
 
 // the other half wave's value and the lane's own: their maximum, sum
 __device__ __forceinline__ float half_max(float v) {
@@ -263,17 +270,6 @@ __device__ __forceinline__ void write_owned_rows(bf16_t *out_row0, int64_t ld, c
     if (wide) flush_owned_rows<HD>(out_row0, ld, region, hl * 32 + l32, n_valid);
 }
 
-// acc[hb] += X^T (columns hb*32.. of the natural tile X, reduction rows rb*32 + cch*16 ..) * frag, for all hb
-template <int HD, int LDP>
-__device__ __forceinline__ void mfma_tr_accumulate(f32x16 *acc, const bf16_t *tile, int tr_off, int rb, int cch,
-                                                   const bf16x8 &frag) {
-    bf16x8 a[HD / 32];
-#pragma unroll
-    for (int hb = 0; hb < HD / 32; ++hb) a[hb] = read_tr_frag(tile, tr_off, LDP, rb * 32 + cch * 16, hb * 32);
-#pragma unroll
-    for (int hb = 0; hb < HD / 32; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[hb], frag, acc[hb], 0, 0, 0);
-}
-
 // Workgroup -> (batch, KV head, item) mapping shared by the three kernels.  Consecutive workgroup ids are
 // dealt round-robin to the 8 XCDs; all workgroups that read the same K/V (or Q/dO) stream are given ids
 // congruent modulo 8 and adjacent in dispatch order, so they run together on one XCD and the stream is
@@ -366,10 +362,6 @@ inline unsigned grid_blocks(const BlockMap &m) { return (unsigned)(m.n_parts * k
 // queries, one per 32-key half of every tile, and are merged through LDS at the end: half the walk per tile for problems whose
 // few blocks would otherwise walk their keys while the chip idles (split_keys).  A 32-key half is either wholly
 // visible to a wave's 32 queries, or the diagonal one (every query sees at least its first key), or skipped.
-#ifndef MT_DQ_PAD
-#define MT_DQ_PAD 40
-#endif
-constexpr int kDqPad = MT_DQ_PAD;
 // One tile of 64 keys (NR = 2) or one of its halves (NR = 1, keys key0 .. + 31 of it): scores of the wave's 32 queries, their softmax, O.
 // kv0: the tile's first key; q0: the wave's first query, qm: the lane's.
 template <int HD, int NR>
@@ -459,7 +451,7 @@ __device__ __forceinline__ void fwd_tile(f32x16 (&oacc)[HD / 32], float &m, floa
     }
 }
 
-template <int HD, int QW, int KW>
+template <int HD, int QW, int KW, bool FAR>
 __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, BlockMap map) {
     constexpr int BQ = 32 * QW, NR = 2 / KW;
     constexpr uint32_t TILE = 64 * HD * 2, STAGE = 2 * TILE;   // bytes; a stage is K, V
@@ -470,7 +462,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
     if (!decode_block(map, &set, &inner)) return;
     const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
     const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));  // heaviest query blocks first (in alternating rows of 8)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
     const uint32_t roff = row_off<HD>(l32, hl), toff = tr_off_swz<HD>(lane);
     const int qw = wave % QW, kw = wave / QW;
     const int q0 = qb * BQ + qw * 32, q = q0 + l32;
@@ -481,7 +473,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
     const bf16_t *vbase = a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD;
     const int kv_end = min(T, qb * BQ + BQ);
     const int ntiles = (kv_end + 63) / 64;
-    DirectTile<64, HD, QW * KW> dk, dv;
+    DirectTile<64, HD, QW * KW, FAR> dk, dv;
     dk.init(smem, a.ldk, lane, wave);
     dv.init(smem, a.ldv, lane, wave);
     dk.load(0, kbase, a.ldk, 0, T);
@@ -588,7 +580,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
     extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
     char *lds = reinterpret_cast<char *>(smem);
     const int T = a.T;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
     const uint32_t roff = row_off<HD>(l32, hl), toff = tr_off_swz<HD>(lane);
     const float c = a.scale * kLog2e, tau = kLazyMax / c;
     const int rounds = (map.n_slots + map.n_workers - 1) / map.n_workers;
@@ -598,7 +590,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
     dk.init(smem, a.ldk, lane, wave);
     dv.init(smem, a.ldv, lane, wave);
     dq.init(smem, a.ldq, lane, 0);
-    const uint32_t q_lds = Q_OFF + __builtin_amdgcn_readfirstlane(wave) * (32 * HD * 2);
+    const uint32_t q_lds = Q_OFF + wave * (32 * HD * 2);
 
     int k = 0;
     Block cur, nxt;
@@ -615,7 +607,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
         dv.load(stage + TILE, a.v + (int64_t)blk.b * T * a.ldv + (int64_t)blk.hk * HD, a.ldv, kt * 64, T);
     };
     const auto request_queries = [&](const Block &blk) {
-        dq.load(q_lds, a.q + (int64_t)blk.b * T * a.ldq + (int64_t)blk.h * HD, a.ldq, blk.qb * BQ + __builtin_amdgcn_readfirstlane(wave) * 32, T);
+        dq.load(q_lds, a.q + (int64_t)blk.b * T * a.ldq + (int64_t)blk.h * HD, a.ldq, blk.qb * BQ + wave * 32, T);
     };
     if (!find(&cur)) return;
     request_queries(cur);
@@ -659,24 +651,78 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 // ------------------------------------------------------------------ backward: dQ
 // Same ownership as the forward: a lane owns one query, loops over key tiles <= q.
 // KW = 2 splits the tiles' keys over two sets of waves as in the forward; their sums are added at the end.
-template <int HD, int QW, int KW>
+
+// the keys 32 rb .. + 31 (rb0 <= rb < rb0 + NR) of the tile that starts at key kv0
+template <int HD, int NR>
+__device__ __forceinline__ void dq_tile(f32x16 (&dqacc)[HD / 32], const bf16x8 (&qf)[HD / 16], const bf16x8 (&dof)[HD / 16], uint32_t Ks, uint32_t Vs,
+                                        const BwdTile<HD> &t, int rb0, int kv0, int q0, int qm, int hl, float c, float lse2, float dlt) {
+    const bool diag = kv0 + 63 > q0;
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        const int rb = NR == 1 ? rb0 : u;
+        const uint32_t Kr = Ks + BwdTile<HD>::rows(rb * 32), Vr = Vs + BwdTile<HD>::rows(rb * 32);
+        f32x16 sacc = zero16(), dpacc = zero16();
+#pragma unroll
+        for (int half = 0; half < HD / 64; ++half) {
+            bf16x8 kk[4], vv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                kk[j] = t.row_frag(Kr, half * 4 + j);
+                vv[j] = t.row_frag(Vr, half * 4 + j);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[j], qf[half * 4 + j], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv[j], dof[half * 4 + j], dpacc, 0, 0, 0);
+            }
+        }
+        if (diag) {  // wave-uniform: only tiles that touch the diagonal pay for the mask
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int kv = kv0 + rb * 32 + (r >> 2) * 8 + hl * 4 + (r & 3);
+                const float p = kv > qm ? 0.f : __builtin_amdgcn_exp2f(sacc[r] * c - lse2);
+                sacc[r] = p * (dpacc[r] - dlt);  // dS^T
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                sacc[r] = __builtin_amdgcn_exp2f(sacc[r] * c - lse2) * (dpacc[r] - dlt);
+        }
+        // dQ^T += K^T dS^T
+#pragma unroll
+        for (int cch = 0; cch < 2; ++cch) t.accumulate(dqacc, Kr, cch * 16, pack_frag(sacc, cch));
+    }
+}
+
+template <int HD, int QW, int KW, bool FAR>
 __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, BlockMap map) {
-    constexpr int BQ = 32 * QW, NT = 64 * QW * KW;
-    constexpr int LDK = HD + kDqPad;
-    constexpr int STAGE = 2 * 64 * LDK;
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+    constexpr int BQ = 32 * QW;
+    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE;   // a stage is K, V
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
     int set, inner;
     if (!decode_block(map, &set, &inner)) return;
     const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
     const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
-    const int tr_off = tr_lane_offset(lane, LDK);
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
+    BwdTile<HD> t;
+    t.init(smem, lane);
     const int qw = wave % QW, kw = wave / QW;
     const int q0 = qb * BQ + qw * 32, q = q0 + l32;
     const bool qok = q < T;
     const int qm = qok ? q : T - 1;
+
+    const bf16_t *kbase = a.k + (int64_t)b * T * a.ldk + (int64_t)hk * HD;
+    const bf16_t *vbase = a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD;
+    const int kv_end = min(T, qb * BQ + BQ);
+    const int ntiles = (kv_end + 63) / 64;
+    DirectTile<64, HD, QW * KW, FAR, BwdTile<HD>::GS> tk, tv;
+    tk.init(smem, a.ldk, lane, wave);
+    tv.init(smem, a.ldv, lane, wave);
+    tk.load(0, kbase, a.ldk, 0, T);
+    tv.load(TILE, vbase, a.ldv, 0, T);
 
     bf16x8 qf[HD / 16], dof[HD / 16];
     {
@@ -694,74 +740,22 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
     f32x16 dqacc[HD / 32];
 #pragma unroll
     for (int hb = 0; hb < HD / 32; ++hb) dqacc[hb] = zero16();
+    tile_barrier();
 
-    const bf16_t *kbase = a.k + (int64_t)b * T * a.ldk + (int64_t)hk * HD;
-    const bf16_t *vbase = a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD;
-    const int kv_end = min(T, qb * BQ + BQ);
-    const int ntiles = (kv_end + 63) / 64;
-
-    TileStage<64, HD, LDK, NT> stK, stV;
-    stK.fetch(kbase, a.ldk, T, HD);
-    stV.fetch(vbase, a.ldv, T, HD);
-    stK.commit(smem);
-    stV.commit(smem + 64 * LDK);
-    __syncthreads();
-
-    for (int kt = 0; kt < ntiles; ++kt) {
+    const auto step = [&](int kt, uint32_t stage) {
         const int kv0 = kt * 64;
-        const bool more = kt + 1 < ntiles;
-        const bf16_t *Ks = smem + (kt & 1) * STAGE, *Vs = Ks + 64 * LDK;
-        if (more) {
-            stK.fetch(kbase + (int64_t)(kv0 + 64) * a.ldk, a.ldk, T - kv0 - 64, HD);
-            stV.fetch(vbase + (int64_t)(kv0 + 64) * a.ldv, a.ldv, T - kv0 - 64, HD);
+        if (kt + 1 < ntiles) {
+            tk.load(STAGE - stage, kbase, a.ldk, kv0 + 64, T);
+            tv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + 64, T);
         }
         if (kv0 + (KW == 2 ? kw * 32 : 0) <= q0 + 31) {
-            const bool diag = kv0 + 63 > q0;
-#pragma unroll
-            for (int u = 0; u < 2 / KW; ++u) {
-                const int rb = KW == 2 ? kw : u;
-                f32x16 sacc = zero16(), dpacc = zero16();
-                const bf16_t *kr = Ks + (rb * 32 + l32) * LDK + hl * 8;
-                const bf16_t *vr = Vs + (rb * 32 + l32) * LDK + hl * 8;
-#pragma unroll
-                for (int half = 0; half < HD / 64; ++half) {
-                    bf16x8 kk[4], vv[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        kk[j] = *reinterpret_cast<const bf16x8 *>(kr + (half * 4 + j) * 16);
-                        vv[j] = *reinterpret_cast<const bf16x8 *>(vr + (half * 4 + j) * 16);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[j], qf[half * 4 + j], sacc, 0, 0, 0);
-                        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv[j], dof[half * 4 + j], dpacc, 0, 0, 0);
-                    }
-                }
-                if (diag) {  // wave-uniform: only tiles that touch the diagonal pay for the mask
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int kv = kv0 + rb * 32 + (r >> 2) * 8 + hl * 4 + (r & 3);
-                        const float p = kv > qm ? 0.f : __builtin_amdgcn_exp2f(sacc[r] * c - lse2);
-                        sacc[r] = p * (dpacc[r] - dlt);  // dS^T
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        sacc[r] = __builtin_amdgcn_exp2f(sacc[r] * c - lse2) * (dpacc[r] - dlt);
-                }
-                // dQ^T += K^T dS^T
-#pragma unroll
-                for (int cch = 0; cch < 2; ++cch)
-                    mfma_tr_accumulate<HD, LDK>(dqacc, Ks, tr_off, rb, cch, pack_frag(sacc, cch));
-            }
+            dq_tile<HD, 2 / KW>(dqacc, qf, dof, stage, stage + TILE, t, kw, kv0, q0, qm, hl, c, lse2, dlt);
         }
-        if (more) {
-            bf16_t *nx = smem + ((kt + 1) & 1) * STAGE;
-            stK.commit(nx);
-            stV.commit(nx + 64 * LDK);
-        }
-        __syncthreads();
+        tile_barrier();
+    };
+    for (int kt = 0; kt < ntiles; kt += 2) {   // by twos: the LDS addresses are then constants
+        step(kt, 0);
+        if (kt + 1 < ntiles) step(kt + 1, STAGE);
     }
     if constexpr (KW == 2) {
         constexpr int NV = HD / 32 * 16;
@@ -793,34 +787,112 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
 // cover the exponentials.  The lane's K fragments live in registers, its V fragments are re-read from LDS for
 // every half: with both in registers only one wave fits on a SIMD (that version, with a three-stage software
 // pipeline inside the wave to make up for it, measured 25 % slower at 128k tokens).  A block of 256 keys rather
-// than 128 halves the Q / dO bytes fetched and written to LDS per MFMA: LDS takes writes at ~70 bytes per clock,
-// and with 128-key blocks the tile commits alone were 15 % of the kernel's time.
-// LDS: V [256][HD + 8] | two stages of { Q, dO [64][HD + 40], lse * log2e [64], delta [64] }.
-// Row pitch HD + 40 elements: consecutive rows are 20 banks apart, which keeps the 16-byte row reads
-// conflict-free (odd multiple of 4 banks) and lets the four rows of a transposing read overlap in only
-// 12 of 64 banks (with HD + 8 they pile up on the same 28 banks).
-constexpr int kDkdvPad = 40;
+// than 128 halves the Q / dO bytes fetched and written to LDS per MFMA.
+// LDS: two stages of Q, dO (first: their addresses are then constants of the instructions) | V | their lse * log2e [64], delta [64].
 //
 // The work of a key block is one serial walk over G T / 64 tiles, so a short or narrow problem leaves most of the chip
 // idle while its few blocks walk.  KW, QW: KW waves own 32 keys each (blocks of 32 KW keys); with QW = 2 two such sets
 // share a block, one per 32-query half of every tile, and the second set's sums are added to the first's through
 // LDS at the end (fixed order).  (8, 1) above is the cheapest per tile, (4, 2) and (2, 2) have shorter walks: see
 // choose_dkdv.
-template <int HD, int KW, int QW>
+
+// the queries 32 rb .. + 31 (rb0 <= rb < rb0 + NR) of the tile that starts at query q0t; kv0w: the wave's first key, kv: the lane's;
+// stats: lse * log2e [64], delta [64] from the lane half's first query on; Vw: the wave's rows of V
+template <int HD, int NR, bool TIGHT>
+__device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dkacc)[HD / 32], const bf16x8 (&kf)[HD / 16], uint32_t Qs, uint32_t dOs,
+                                          uint32_t stats, uint32_t Vw, const BwdTile<HD> &t, int rb0, int q0t, int kv0w, int kv, int hl, float c) {
+    typedef __attribute__((address_space(3))) const f32x4 *lds_f4;
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        const int rb = NR == 1 ? rb0 : u, q0u = q0t + rb * 32;
+        if (q0u + 31 < kv0w) continue;  // wave-uniform: no query of the half sees a key of the wave
+        f32x16 s_ = zero16(), p_ = zero16();
+        const uint32_t qr = Qs + BwdTile<HD>::rows(rb * 32), dor = dOs + BwdTile<HD>::rows(rb * 32);
+#pragma unroll
+        for (int half = 0; half < HD / 64; ++half) {
+            bf16x8 qq[4], dd[4], vv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qq[i] = t.row_frag(qr, half * 4 + i);
+            // TIGHT: in two batches, for with all fragments on their way the registers do not suffice, and values that are brought back
+            // from scratch memory wait for the tile loads in front of them (4 x 4096, 32 heads: backward 2336 us, without 1996)
+            if constexpr (TIGHT) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qq[i], kf[half * 4 + i], s_, 0, 0, 0);
+                asm volatile("" : "+v"(s_) : : "memory");
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                dd[i] = t.row_frag(dor, half * 4 + i);
+                vv[i] = t.row_frag(Vw, half * 4 + i);
+            }
+            if constexpr (!TIGHT) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qq[i], kf[half * 4 + i], s_, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dd[i], vv[i], p_, 0, 0, 0);
+            if constexpr (TIGHT) asm volatile("" : "+v"(p_) : : "memory");
+        }
+        // P = exp2(S c - lse), dS = P (dP - delta); element r of the lane belongs to query
+        // q0u + (r >> 2) * 8 + hl * 4 + (r & 3), visible to the lane's key only if kv <= query
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const f32x4 lv = *(lds_f4)(stats + (rb * 32 + r4 * 8) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s_[r4 * 4 + e] = __builtin_amdgcn_exp2f(s_[r4 * 4 + e] * c - lv[e]);
+        }
+        if (q0u < kv0w + 31) {   // (scalar: only tiles at the diagonal pay for the mask)
+            const int lim = kv - (q0u + hl * 4);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s_[r] = (r >> 2) * 8 + (r & 3) < lim ? 0.f : s_[r];
+        }
+        f32x16 dsacc;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const f32x4 dv4 = *(lds_f4)(stats + (64 + rb * 32 + r4 * 8) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dsacc[r4 * 4 + e] = s_[r4 * 4 + e] * (p_[r4 * 4 + e] - dv4[e]);
+        }
+        // dV^T += dO^T P, dK^T += Q^T dS
+#pragma unroll
+        for (int cch = 0; cch < 2; ++cch) {
+            t.accumulate(dvacc, dor, cch * 16, pack_frag(s_, cch));
+            t.accumulate(dkacc, qr, cch * 16, pack_frag(dsacc, cch));
+            if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+// The softmax statistics of a tile's queries, fetched by the first two waves (one lane a query): a plain load with nothing computed
+// from it until it is put into LDS (arithmetic on the value would make these waves wait for it, and for the tile loads in front of it).
+struct TileStats {
+    float v;
+    __device__ __forceinline__ void fetch(const AttnArgs &a, int b, int h, int q0t, int wave, int lane) {
+        if (wave < 2) v = ((wave ? a.delta : a.lse) + ((int64_t)b * a.Hq + h) * a.T + q0t)[(uint32_t)min(lane, a.T - 1 - q0t)];
+    }
+    // queries past T: lse = +inf makes their P (and with it dS) exactly zero
+    __device__ __forceinline__ void commit(float *lds, int n_valid, int wave, int lane) const {
+        if (wave == 0) lds[lane] = lane < n_valid ? v * kLog2e : INFINITY;
+        if (wave == 1) lds[64 + lane] = v;
+    }
+};
+__device__ __forceinline__ float scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
+template <int HD, int KW, int QW, bool FAR>
 __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a, BlockMap map) {
-    constexpr int LDK = HD + kDkdvPad, LDKV = HD + 8, HB = HD / 32, KB = 32 * KW, NT = 64 * KW * QW;
-    constexpr int V_BF = KB * LDKV;
-    constexpr int STAGE_BF = 2 * 64 * LDK, STAGE = STAGE_BF + 256;
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    bf16_t *Vt = smem, *stages = smem + V_BF;
+    constexpr int HB = HD / 32, KB = 32 * KW, NW = KW * QW, GS = BwdTile<HD>::GS;
+    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE, V_OFF = 2 * STAGE, STAT_OFF = V_OFF + KB / 64 * TILE;
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    char *lds = reinterpret_cast<char *>(smem);
 
     const int T = a.T, G = a.Hq / a.Hkv, nkb = (T + KB - 1) / KB;
     int set, kvb;
     if (!decode_block(map, &set, &kvb)) return;
     if (!map.by_rank) kvb = snake8(kvb, nkb);
     const int b = set / a.Hkv, hk = set % a.Hkv;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hl = lane >> 5;
-    const int tr_off = tr_lane_offset(lane, LDK);
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
+    BwdTile<HD> t;
+    t.init(smem, lane);
     const int kw = wave % KW, qw = wave / KW;
     const int kv0w = kvb * KB + kw * 32, kv = kv0w + l32;
 
@@ -830,115 +902,58 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
         dvacc[hb] = zero16();
         dkacc[hb] = zero16();
     }
-    const float c = a.scale * kLog2e;
+    const float c = scalar(a.scale * kLog2e);
     const int qt_first = (kvb * KB) / 64, n_qt = (T + 63) / 64 - qt_first;
     const int total = G * n_qt;
 
-    using Stage = TileStage<64, HD, LDK, NT>;
-    Stage stQ, stDO;
-    float stat = 0.f;
-    bool stat_pad = false;
-    int f_head = 0, f_tile = 0;
-    auto fetch_next = [&]() {
+    DirectTile<64, HD, NW, FAR, GS> tq, tdo;
+    tq.init(smem, a.ldq, lane, wave);
+    tdo.init(smem, a.lddo, lane, wave);
+    TileStats stats;
+    int f_head = 0, f_tile = 0, n_valid = 0;
+    const auto request_next = [&](uint32_t stage) {
         const int h = hk * G + f_head, q0t = (qt_first + f_tile) * 64;
         if (++f_tile == n_qt) {
             f_tile = 0;
             ++f_head;
         }
-        stQ.fetch_clamped(a.q + ((int64_t)b * T + q0t) * a.ldq + (int64_t)h * HD, a.ldq, T - q0t);
-        stDO.fetch_clamped(a.dout + ((int64_t)b * T + q0t) * a.lddo + (int64_t)h * HD, a.lddo, T - q0t);
-        if (threadIdx.x < 128) {
-            // one plain load, nothing computed from it here: arithmetic on the value would make these two waves
-            // wait for it (and for the tile loads just issued) before they start on the current tile
-            const int qq = q0t + (threadIdx.x & 63);
-            const int64_t si = ((int64_t)b * a.Hq + h) * T + (qq < T ? qq : T - 1);
-            stat = *(threadIdx.x < 64 ? a.lse + si : a.delta + si);
-            stat_pad = qq >= T;
-        }
+        tq.load(stage, a.q + (int64_t)b * T * a.ldq + (int64_t)h * HD, a.ldq, q0t, T);
+        tdo.load(stage + TILE, a.dout + (int64_t)b * T * a.lddo + (int64_t)h * HD, a.lddo, q0t, T);
+        stats.fetch(a, b, h, q0t, wave, lane);
+        n_valid = T - q0t;
     };
-    auto commit = [&](int stage) {
-        bf16_t *sp = stages + stage * STAGE;
-        stQ.commit_plain(sp);
-        stDO.commit_plain(sp + 64 * LDK);
-        // queries past T: lse = +inf makes their P (and with it dS) exactly zero
-        if (threadIdx.x < 128)
-            reinterpret_cast<float *>(sp + STAGE_BF)[threadIdx.x] =
-                threadIdx.x < 64 ? (stat_pad ? INFINITY : stat * kLog2e) : stat;
+    const auto commit = [&](uint32_t stage) {
+        stats.commit(reinterpret_cast<float *>(lds + STAT_OFF + (stage ? 512 : 0)), n_valid, wave, lane);
     };
     bf16x8 kf[HD / 16];
     {
-        TileStage<KB, HD, LDKV, NT> stV;
-        stV.fetch(a.v + ((int64_t)b * T + kvb * KB) * a.ldv + (int64_t)hk * HD, a.ldv, T - kvb * KB, HD);
-        fetch_next();
+        DirectTile<KB, HD, NW, FAR, GS> tv;
+        tv.init(smem, a.ldv, lane, wave);
+        tv.load(V_OFF, a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD, a.ldv, kvb * KB, T);
+        request_next(0);
         const bf16_t *kp = a.k + ((int64_t)b * T + min(kv, T - 1)) * a.ldk + (int64_t)hk * HD + hl * 8;
 #pragma unroll
         for (int i = 0; i < HD / 16; ++i) kf[i] = load_frag_global(kp + i * 16);
-        stV.commit(Vt);
         commit(0);
     }
-    __syncthreads();
+    tile_barrier();
 
-    const bf16_t *vr = Vt + (kw * 32 + l32) * LDKV + hl * 8;
-    int tq = 0;  // query tile inside the head
-    for (int j = 0; j < total; ++j) {
-        const bf16_t *Qs = stages + (j & 1) * STAGE, *dOs = Qs + 64 * LDK;
-        const float *lses = reinterpret_cast<const float *>(Qs + STAGE_BF), *dlts = lses + 64;
-        const int q0t = (qt_first + tq) * 64;
+    const uint32_t Vw = V_OFF + BwdTile<HD>::rows(kw * 32);
+    uint32_t stat_base = lds_address(smem) + STAT_OFF + hl * 16;
+    asm volatile("" : "+v"(stat_base));   // (one register, see BwdTile)
+    int tq_ = 0;  // query tile inside the head
+    const auto step = [&](int j, uint32_t stage) {
         const bool more = j + 1 < total;
-        if (more) fetch_next();
-#pragma unroll
-        for (int u = 0; u < 2 / QW; ++u) {
-            const int rb = QW == 2 ? qw : u, q0u = q0t + rb * 32;
-            if (q0u + 31 < kv0w) continue;  // wave-uniform: no query of the half sees a key of the wave
-            f32x16 s_ = zero16(), p_ = zero16();
-            const bf16_t *qr = Qs + (rb * 32 + l32) * LDK + hl * 8;
-            const bf16_t *dor = dOs + (rb * 32 + l32) * LDK + hl * 8;
-#pragma unroll
-            for (int half = 0; half < HD / 64; ++half) {
-                bf16x8 qq[4], dd[4], vv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) qq[i] = *reinterpret_cast<const bf16x8 *>(qr + (half * 4 + i) * 16);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    dd[i] = *reinterpret_cast<const bf16x8 *>(dor + (half * 4 + i) * 16);
-                    vv[i] = *reinterpret_cast<const bf16x8 *>(vr + (half * 4 + i) * 16);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    s_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qq[i], kf[half * 4 + i], s_, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) p_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dd[i], vv[i], p_, 0, 0, 0);
-            }
-            // P = exp2(S c - lse), dS = P (dP - delta); element r of the lane belongs to query
-            // q0u + (r >> 2) * 8 + hl * 4 + (r & 3), visible to the lane's key only if kv <= query
-            const int lim = kv - (q0u + hl * 4);
-            const bool diag = q0u < kv0w + 31;
-            f32x16 dsacc;
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int qi = rb * 32 + r4 * 8 + hl * 4;
-                const float4 l4 = *reinterpret_cast<const float4 *>(lses + qi);
-                const float4 d4 = *reinterpret_cast<const float4 *>(dlts + qi);
-                const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = r4 * 4 + e;
-                    float p = __builtin_amdgcn_exp2f(s_[r] * c - lv[e]);
-                    if (diag) p = (r4 * 8 + e < lim) ? 0.f : p;
-                    s_[r] = p;
-                    dsacc[r] = p * (p_[r] - dv4[e]);
-                }
-            }
-            // dV^T += dO^T P, dK^T += Q^T dS
-#pragma unroll
-            for (int cch = 0; cch < 2; ++cch) {
-                mfma_tr_accumulate<HD, LDK>(dvacc, dOs, tr_off, rb, cch, pack_frag(s_, cch));
-                mfma_tr_accumulate<HD, LDK>(dkacc, Qs, tr_off, rb, cch, pack_frag(dsacc, cch));
-            }
-        }
-        if (more) commit((j + 1) & 1);
-        __syncthreads();
-        tq = tq + 1 == n_qt ? 0 : tq + 1;
+        if (more) request_next(STAGE - stage);
+        dkdv_tile<HD, 2 / QW, HD == 128 && NW == 8>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? 512 : 0), Vw, t, qw,
+                              (qt_first + tq_) * 64, kv0w, kv, hl, c);
+        if (more) commit(STAGE - stage);
+        tile_barrier();
+        tq_ = tq_ + 1 == n_qt ? 0 : tq_ + 1;
+    };
+    for (int j = 0; j < total; j += 2) {
+        step(j, 0);
+        if (j + 1 < total) step(j + 1, STAGE);
     }
     if constexpr (QW == 2) {
         float *red = reinterpret_cast<float *>(smem) + kw * (HB * 16 * 64) + lane;
@@ -984,17 +999,17 @@ bool rope_tables_ok(const AttnArgs &a) {
 
 }  // namespace
 
-template <int HD, int QW, int KW>
+template <int HD, int QW, int KW, bool FAR = false>
 static hipError_t launch_fwd(const AttnArgs &a, hipStream_t s) {
     // two stages of K and V, or what the results need on their way out (out_region, the other half's sums)
     constexpr size_t lds = std::max({(size_t)2 * 2 * 64 * HD * sizeof(bf16_t), (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
                                      KW == 1 ? 0 : (size_t)QW * (HD / 32 * 16 + 2) * 64 * sizeof(float)});
     static std::atomic<bool> done{false};
-    const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW>, lds, &done);
+    const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
     const int G = a.Hq / a.Hkv;
     const BlockMap map = block_map(G * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv, G);
-    hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
+    hipLaunchKernelGGL((flash_fwd_kernel<HD, QW, KW, FAR>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
     return hipGetLastError();
 }
 
@@ -1050,16 +1065,16 @@ static hipError_t launch_fwd_chain(const AttnArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int HD, int QW, int KW>
+template <int HD, int QW, int KW, bool FAR = false>
 static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
-    constexpr size_t lds = 2 * (2 * 64 * (HD + kDqPad)) * sizeof(bf16_t);
-    static_assert(KW == 1 || (size_t)QW * (HD / 32 * 16) * 64 * sizeof(float) <= lds, "room for the other half's sums");
+    constexpr size_t lds = std::max({(size_t)2 * 2 * BwdTile<HD>::BYTES, (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
+                                     KW == 1 ? 0 : (size_t)QW * (HD / 32 * 16) * 64 * sizeof(float)});
     static std::atomic<bool> done{false};
-    const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW>, lds, &done);
+    const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
     const int G = a.Hq / a.Hkv;
     const BlockMap map = block_map(G * ((a.T + 32 * QW - 1) / (32 * QW)), a.B * a.Hkv, G);
-    hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
+    hipLaunchKernelGGL((flash_bwd_dq_kernel<HD, QW, KW, FAR>), dim3(grid_blocks(map)), dim3(64 * QW * KW), lds, s, a, map);
     return hipGetLastError();
 }
 
@@ -1119,9 +1134,10 @@ static bool split_keys(const AttnArgs &a, bool forward) {
 hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
     if (!attn_shape_ok(a) || (a.ldq & 7) || (a.ldk & 7) || (a.ldv & 7) || (a.ldo & 3)) return hipErrorInvalidValue;
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || ((uintptr_t)a.o & 7)) return hipErrorInvalidValue;
+    if (!near_pitch(a.ldk) || !near_pitch(a.ldv)) return a.hd == 128 ? launch_fwd<128, 8, 1, true>(a, s) : launch_fwd<64, 8, 1, true>(a, s);
     if (split_keys(a, true)) return a.hd == 128 ? launch_fwd<128, 4, 2>(a, s) : launch_fwd<64, 4, 2>(a, s);
-    // (one tile of keys: nothing to fetch ahead, 5.4 us against 5.9; pitches beyond 32 bits: see DirectTile)
-    if (a.hd == 128 && a.T > 64 && near_pitch(a.ldq) && near_pitch(a.ldk) && near_pitch(a.ldv) && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256)))
+    // (one tile of keys: nothing to fetch ahead, 5.4 us against 5.9)
+    if (a.hd == 128 && a.T > 64 && near_pitch(a.ldq) && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256)))
         return launch_fwd_chain<128>(a, s);
     return a.hd == 128 ? launch_fwd<128, 8, 1>(a, s) : launch_fwd<64, 8, 1>(a, s);
 }
@@ -1132,21 +1148,22 @@ hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.dout) || ((uintptr_t)a.dq & 7))
         return hipErrorInvalidValue;
+    if (!near_pitch(a.ldk) || !near_pitch(a.ldv)) return a.hd == 128 ? launch_dq<128, 8, 1, true>(a, s) : launch_dq<64, 8, 1, true>(a, s);
     if (split_keys(a, false)) return a.hd == 128 ? launch_dq<128, 4, 2>(a, s) : launch_dq<64, 4, 2>(a, s);
     return a.hd == 128 ? launch_dq<128, 8, 1>(a, s) : launch_dq<64, 8, 1>(a, s);
 }
 
-template <int HD, int KW, int QW>
+template <int HD, int KW, int QW, bool FAR = false>
 static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     constexpr int KB = 32 * KW;
-    // V [KB][hd + 8] | two stages of Q, dO [64][hd + pad] + 64 lse + 64 delta
-    constexpr size_t lds = (KB * (HD + 8) + 2 * (2 * 64 * (HD + kDkdvPad))) * sizeof(bf16_t) + 2 * 512;
+    constexpr size_t lds = KB / 64 * BwdTile<HD>::BYTES + 2 * (2 * BwdTile<HD>::BYTES + 512);
+    static_assert((size_t)KW * 32 * (HD + 8) * sizeof(bf16_t) <= lds, "room for the results on their way out");
     static_assert(QW == 1 || (size_t)KW * (HD / 32) * 16 * 64 * sizeof(float) <= lds, "room for the other half's sums");
     static std::atomic<bool> done{false};
-    const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW>, lds, &done);
+    const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
     const BlockMap map = block_map((a.T + KB - 1) / KB, a.B * a.Hkv, 1);
-    hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW>), dim3(grid_blocks(map)), dim3(64 * KW * QW), lds, s, a, map);
+    hipLaunchKernelGGL((flash_bwd_dkdv_kernel<HD, KW, QW, FAR>), dim3(grid_blocks(map)), dim3(64 * KW * QW), lds, s, a, map);
     return hipGetLastError();
 }
 
@@ -1171,6 +1188,8 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.dout) || ((uintptr_t)a.dk & 7) ||
         ((uintptr_t)a.dv & 7))
         return hipErrorInvalidValue;
+    if (!near_pitch(a.ldq) || !near_pitch(a.ldv) || !near_pitch(a.lddo))
+        return a.hd == 128 ? launch_dkdv<128, 8, 1, true>(a, s) : launch_dkdv<64, 8, 1, true>(a, s);
     switch (choose_dkdv(a)) {
         case 0: return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
         case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);

@@ -882,7 +882,8 @@ def test_flash_attention_lists_of_blocks(orc64, B, T, Hq, Hkv, hd):
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 72, 2, 1, 64), (1, 136, 2, 1, 128), (64, 136, 8, 8, 128)])
 def test_flash_attention_rows_in_reverse_order(B, T, Hq, Hkv, hd):
-    """Rows may lie anywhere a 64-bit pitch reaches: stored last row first (negative pitches) they give the same bits."""
+    """Rows may lie anywhere a 64-bit pitch reaches: stored last row first (negative pitches) they give the same results.  (Up to the
+    rounding of sums in another order: such rows always take blocks of 256.  Held to what the oracle's tests allow for each.)"""
     g = torch.Generator(device="cuda").manual_seed(T)
     nq, nkv = Hq * hd, Hkv * hd
     ld, n, scale = nq + 2 * nkv, B * T, 1.0 / np.sqrt(hd)
@@ -903,8 +904,10 @@ def test_flash_attention_rows_in_reverse_order(B, T, Hq, Hkv, hd):
         ok(L.mt_k_flash_bwd(d, ld, d + 2 * nq, ld, d + 2 * (nq + nkv), ld, do, sign * nq, *a, po, sign * nq, LSE.data_ptr(), DELTA.data_ptr(),
                             B, T, Hq, Hkv, hd, scale, None))
         got.append((O, LSE, D))
-    for one, other in zip(*got):
-        assert torch.equal(one, other)
+    (o0, lse0, d0), (o1, lse1, d1) = ([host(t) for t in ts] for ts in got)
+    assert rel_l2(o1, o0) < BF16_TOL and rel_l2(lse1, lse0) < 1e-6 and rel_l2(d1, d0) < 2e-2
+    assert_rows_close(o1, o0, ROW2, width=hd, what="attention forward, rows in reverse order")
+    assert_rows_close(d1, d0, ROW_ATT_BWD, 2 * ROW_FLOOR, width=hd, what="attention backward, rows in reverse order")
 
 
 def test_flash_attention_scores_of_minus_infinity(orc64):
