@@ -108,8 +108,14 @@ struct DirectTile {
 };
 // (in a scalar register: what depends on it is a scalar branch)
 __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+__device__ __forceinline__ float scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 // all tiles that this wave asked for have landed and its LDS reads are done, and so have those of the other waves
-__device__ __forceinline__ void tile_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// The first wait is one that the compiler understands: otherwise it waits inside the loop for the loads of the fragments in front of it,
+// over and over, and with them for the tile that has just been asked for.
+__device__ __forceinline__ void tile_barrier() {
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 
 __device__ __forceinline__ uint32_t lds_address(const void *smem) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)smem; }
 // Tiles of the backward.  It reads most of them row-wise and transposed and has fewer registers for addresses, so with head_dim 128 the
@@ -163,6 +169,14 @@ struct BwdTile {
         for (int hb = 0; hb < HD / 32; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[hb], frag, acc[hb], 0, 0, 0);
     }
 };
+
+// what this wave asked for has landed, and these fragments are in their registers (here, not where a loop uses them first)
+template <int N>
+__device__ __forceinline__ void wave_barrier(bf16x8 (&f)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 
 // the other half wave's value and the lane's own: their maximum, sum
 __device__ __forceinline__ float half_max(float v) {
@@ -326,7 +340,7 @@ struct ChainMap {
 struct Block {
     int b, hk, h, qb;
 };
-// k-th block of this workgroup's list; false: padding (nothing to do), k >= rounds: the end
+// k-th entry of this workgroup's list; false: padding (nothing to do), k >= rounds: the end
 __device__ __forceinline__ bool chain_block(const ChainMap &c, int k, Block *out) {
     const int xcd = blockIdx.x % kXcds, w = blockIdx.x / kXcds, slot = k * c.n_workers + (k & 1 ? c.n_workers - 1 - w : w);
     if (slot >= c.n_slots) return false;
@@ -342,6 +356,15 @@ __device__ __forceinline__ bool chain_block(const ChainMap &c, int k, Block *out
     out->qb = c.n_blocks - 1 - rank;
     return true;
 }
+struct BlockList {
+    int k = 0;
+    __device__ __forceinline__ bool next(const ChainMap &c, Block *out) {
+        const int rounds = (c.n_slots + c.n_workers - 1) / c.n_workers;
+        while (k < rounds)
+            if (chain_block(c, k++, out)) return true;
+        return false;
+    }
+};
 // Causal work falls off linearly with the block index, and the workgroups of an XCD are handed to its shader
 // engines round-robin in dispatch order: with the plain order "heaviest first" one engine would always get the
 // heavier blocks of every set (measured: 15 us of idle time per block on the other engines' CUs at T = 4096).
@@ -537,32 +560,51 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
     if (qok && hl == 0) a.lse[((int64_t)b * a.Hq + h) * T + q] = (m * c + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
-// The wave's 32 x HD results through 4 KB of its own, 64 columns at a time (see write_owned_rows).
-template <int HD>
-__device__ __forceinline__ void write_rows_by_halves(bf16_t *out_row0, int64_t ld, const f32x16 *acc, float mul, int l32, int hl, int n_valid, char *region) {
+// The wave's 32 x HD results through 64 COLS bytes of its own, COLS columns at a time (see write_owned_rows).
+template <int HD, int COLS>
+__device__ __forceinline__ void write_rows_by_parts(bf16_t *out_row0, int64_t ld, const f32x16 *acc, float mul, int l32, int hl, int n_valid, char *region) {
     if ((ld & 7) || ((uintptr_t)out_row0 & 15)) {
         if (l32 < n_valid) store_owned_rows<HD>(out_row0 + l32 * ld, acc, mul, hl);
         return;
     }
-    const int lane = hl * 32 + l32, lr = lane >> 3;
+    constexpr int CH = COLS / 8, RPI = 64 / CH;   // chunks of 16 bytes per row, rows per store
+    const int lane = hl * 32 + l32, lr = lane / CH, lc = lane % CH;
 #pragma unroll
-    for (int half = 0; half < HD / 64; ++half) {
+    for (int part = 0; part < HD / COLS; ++part) {
 #pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2)
+        for (int h = 0; h < COLS / 32; ++h)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const f32x16 &v = acc[half * 2 + h2];
+                const f32x16 &v = acc[part * (COLS / 32) + h];
                 const uint2 u = {pack2bf(v[r4 * 4 + 0] * mul, v[r4 * 4 + 1] * mul), pack2bf(v[r4 * 4 + 2] * mul, v[r4 * 4 + 3] * mul)};
-                *reinterpret_cast<uint2 *>(region + l32 * 128 + (((h2 * 4 + r4) ^ (l32 & 7)) << 4) + hl * 8) = u;
+                *reinterpret_cast<uint2 *>(region + l32 * (2 * COLS) + (((h * 4 + r4) ^ (l32 & (CH - 1))) << 4) + hl * 8) = u;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int r = it * 8 + lr;
-            const uint4 u = *reinterpret_cast<const uint4 *>(region + r * 128 + (((lane & 7) ^ (r & 7)) << 4));
-            if (r < n_valid) *reinterpret_cast<uint4 *>(out_row0 + r * ld + half * 64 + (lane & 7) * 8) = u;
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int r = it * RPI + lr;
+            const uint4 u = *reinterpret_cast<const uint4 *>(region + r * (2 * COLS) + ((lc ^ (r & (CH - 1))) << 4));
+            if (r < n_valid) *reinterpret_cast<uint4 *>(out_row0 + r * ld + part * COLS + lc * 8) = u;
         }
     }
+}
+// The backward of the rotary embedding on the lane's row (see store_owned_rows_unrotated), times mul
+template <int HD>
+__device__ __forceinline__ void rotate_back(f32x16 *acc, float mul, int hl, const float *cs, const float *sn) {
+#pragma unroll
+    for (int hb = 0; hb < HD / 64; ++hb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int j = hb * 32 + r4 * 8 + hl * 4;
+            const float4 c4 = *reinterpret_cast<const float4 *>(cs + j), s4 = *reinterpret_cast<const float4 *>(sn + j);
+            const float c[4] = {c4.x, c4.y, c4.z, c4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float ya = acc[hb][r4 * 4 + e] * mul, yb = acc[hb + HD / 64][r4 * 4 + e] * mul;
+                acc[hb][r4 * 4 + e] = ya * c[e] + yb * sv[e];
+                acc[hb + HD / 64][r4 * 4 + e] = yb * c[e] - ya * sv[e];
+            }
+        }
 }
 
 // The same forward in blocks of 256 queries with one workgroup per compute unit that goes through a list of them.  A block of its own
@@ -583,7 +625,6 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
     const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
     const uint32_t roff = row_off<HD>(l32, hl), toff = tr_off_swz<HD>(lane);
     const float c = a.scale * kLog2e, tau = kLazyMax / c;
-    const int rounds = (map.n_slots + map.n_workers - 1) / map.n_workers;
 
     DirectTile<64, HD, 8, false> dk, dv;
     DirectTile<32, HD, 1, false> dq;   // a wave fetches its own queries
@@ -592,16 +633,8 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
     dq.init(smem, a.ldq, lane, 0);
     const uint32_t q_lds = Q_OFF + wave * (32 * HD * 2);
 
-    int k = 0;
+    BlockList list;
     Block cur, nxt;
-    const auto find = [&](Block *blk) {
-        for (; k < rounds; ++k)
-            if (chain_block(map, k, blk)) {
-                ++k;
-                return true;
-            }
-        return false;
-    };
     const auto request_tile = [&](const Block &blk, int kt, uint32_t stage) {
         dk.load(stage, a.k + (int64_t)blk.b * T * a.ldk + (int64_t)blk.hk * HD, a.ldk, kt * 64, T);
         dv.load(stage + TILE, a.v + (int64_t)blk.b * T * a.ldv + (int64_t)blk.hk * HD, a.ldv, kt * 64, T);
@@ -609,7 +642,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
     const auto request_queries = [&](const Block &blk) {
         dq.load(q_lds, a.q + (int64_t)blk.b * T * a.ldq + (int64_t)blk.h * HD, a.ldq, blk.qb * BQ + wave * 32, T);
     };
-    if (!find(&cur)) return;
+    if (!list.next(map, &cur)) return;
     request_queries(cur);
     request_tile(cur, 0, 0);
     tile_barrier();
@@ -618,7 +651,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 #pragma unroll
         for (int ks = 0; ks < HD / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(lds + q_lds + (roff ^ (ks * 32)));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const bool more = find(&nxt);
+        const bool more = list.next(map, &nxt);
         if (more) request_queries(nxt);
         const int q0 = cur.qb * BQ + wave * 32, q = q0 + l32, qm = min(q, T - 1);  // padded queries behave like the last row; never stored
         const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = min(ntiles, (q0 + 31) / 64 + 1) - 1;
@@ -626,22 +659,30 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 #pragma unroll
         for (int hb = 0; hb < HD / 32; ++hb) oacc[hb] = zero16();
         float m = -INFINITY, lsum = 0.f;
-        const auto step = [&](int kt, uint32_t stage) {
+        const auto request_after = [&](int kt, uint32_t stage) {
             if (kt + 1 < ntiles) request_tile(cur, kt + 1, STAGE - stage);
             else if (more && (kt & 1)) request_tile(nxt, 0, STAGE - stage);
+        };
+        const auto step = [&](int kt, uint32_t stage) {
+            request_after(kt, stage);
             if (kt <= last) fwd_tile<HD, 2>(oacc, m, lsum, qf, lds + stage, lds + stage + TILE, roff, toff, 0, kt * 64, q0, qm, hl, c, tau);
             tile_barrier();
         };
-        for (int kt = 0; kt < ntiles; kt += 2) {   // by twos: the LDS addresses are then constants, and every block starts in stage 0
+        int kt = 0;
+        for (; kt <= last; kt += 2) {   // by twos: the LDS addresses are then constants, and every block starts in stage 0
             step(kt, 0);
             step(kt + 1, STAGE);
-            if ((kt | 1) == (last | 1)) {
-                const float sum = half_sum(lsum);
-                if (q0 < T)
-                    write_rows_by_halves<HD>(a.o + ((int64_t)cur.b * T + q0) * a.ldo + (int64_t)cur.h * HD, a.ldo, oacc, 1.0f / sum, l32, hl,
-                                             min(32, T - q0), lds + O_OFF + wave * 4096);
-                if (q < T && hl == 0) a.lse[((int64_t)cur.b * a.Hq + cur.h) * T + q] = (m * c + __builtin_amdgcn_logf(sum)) * kLn2;
-            }
+        }
+        const float sum = half_sum(lsum);
+        if (q0 < T)
+            write_rows_by_parts<HD, 64>(a.o + ((int64_t)cur.b * T + q0) * a.ldo + (int64_t)cur.h * HD, a.ldo, oacc, 1.0f / sum, l32, hl,
+                                        min(32, T - q0), lds + O_OFF + wave * 4096);
+        if (q < T && hl == 0) a.lse[((int64_t)cur.b * a.Hq + cur.h) * T + q] = (m * c + __builtin_amdgcn_logf(sum)) * kLn2;
+        for (; kt < ntiles; kt += 2) {   // the other waves' tiles
+            request_after(kt, 0);
+            tile_barrier();
+            request_after(kt + 1, STAGE);
+            tile_barrier();
         }
         if (!more) break;
         cur = nxt;
@@ -778,6 +819,92 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
                              a.rope_cos ? a.rope_sin + (int64_t)q0 * (HD / 2) : nullptr, out_region<HD>(smem, qw));
 }
 
+// The same in blocks of 256 queries with one workgroup per compute unit that goes through a list of them (see flash_fwd_chain_kernel).  The
+// queries and output gradients of the next block come straight into their registers as soon as the wave is done with the present one.
+// us, backward, a workgroup per block -> lists (dK/dV too): 4 x 4096, 32 heads 1952 -> 1890; 8 x 2048, 16 heads 651 -> 547; 8 x 1024, 32 heads
+// 458 -> 353; 1 x 32768, 40 heads on 8 32 890 -> 32 600.  Bound like the forward; short lists are no slower (1 x 1536, 64 heads 165.5 both).
+template <int HD>
+__global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, ChainMap map) {
+    constexpr int BQ = 256;
+    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE, O_OFF = 2 * STAGE;
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    const int T = a.T;
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
+    BwdTile<HD> t;
+    t.init(smem, lane);
+    const float c = scalar(a.scale * kLog2e);
+    DirectTile<64, HD, 8, false, BwdTile<HD>::GS> tk, tv;
+    tk.init(smem, a.ldk, lane, wave);
+    tv.init(smem, a.ldv, lane, wave);
+
+    bf16x8 qf[HD / 16], dof[HD / 16];
+    float lse, dlt;
+    const auto request_tile = [&](const Block &blk, int kt, uint32_t stage) {
+        tk.load(stage, a.k + (int64_t)blk.b * T * a.ldk + (int64_t)blk.hk * HD, a.ldk, kt * 64, T);
+        tv.load(stage + TILE, a.v + (int64_t)blk.b * T * a.ldv + (int64_t)blk.hk * HD, a.ldv, kt * 64, T);
+    };
+    const auto request_queries = [&](const Block &blk) {
+        const int qm = min(blk.qb * BQ + wave * 32 + l32, T - 1);
+        const bf16_t *qp = a.q + ((int64_t)blk.b * T + qm) * a.ldq + (int64_t)blk.h * HD + hl * 8;
+        const bf16_t *dp = a.dout + ((int64_t)blk.b * T + qm) * a.lddo + (int64_t)blk.h * HD + hl * 8;
+#pragma unroll
+        for (int ks = 0; ks < HD / 16; ++ks) {
+            qf[ks] = load_frag_global(qp + ks * 16);
+            dof[ks] = load_frag_global(dp + ks * 16);
+        }
+        const int64_t stat = ((int64_t)blk.b * a.Hq + blk.h) * T + qm;
+        lse = a.lse[stat];
+        dlt = a.delta[stat];
+    };
+    BlockList list;
+    Block cur, nxt;
+    if (!list.next(map, &cur)) return;
+    request_tile(cur, 0, 0);
+    request_queries(cur);
+    tile_barrier();
+    while (true) {
+        asm volatile("" : "+v"(lse), "+v"(dlt));
+        wave_barrier(qf);
+        wave_barrier(dof);
+        const bool more = list.next(map, &nxt);
+        const int q0 = cur.qb * BQ + wave * 32, q = q0 + l32, qm = min(q, T - 1);
+        const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = min(ntiles, (q0 + 31) / 64 + 1) - 1;
+        const float lse2 = lse * kLog2e, delta = dlt;
+        f32x16 dqacc[HD / 32];
+#pragma unroll
+        for (int hb = 0; hb < HD / 32; ++hb) dqacc[hb] = zero16();
+        const auto request_after = [&](int kt, uint32_t stage) {
+            if (kt + 1 < ntiles) request_tile(cur, kt + 1, STAGE - stage);
+            else if (more && (kt & 1)) request_tile(nxt, 0, STAGE - stage);
+        };
+        const auto step = [&](int kt, uint32_t stage) {
+            request_after(kt, stage);
+            if (kt <= last) dq_tile<HD, 2>(dqacc, qf, dof, stage, stage + TILE, t, 0, kt * 64, q0, qm, hl, c, lse2, delta);
+            tile_barrier();
+        };
+        int kt = 0;
+        for (; kt <= last; kt += 2) {
+            step(kt, 0);
+            step(kt + 1, STAGE);
+        }
+        if (more) request_queries(nxt);
+        if (q0 < T) {
+            const bool rope = a.rope_cos != nullptr;
+            if (rope) rotate_back<HD>(dqacc, a.scale, hl, a.rope_cos + (int64_t)qm * (HD / 2), a.rope_sin + (int64_t)qm * (HD / 2));
+            write_rows_by_parts<HD, 64>(a.dq + ((int64_t)cur.b * T + q0) * a.lddq + (int64_t)cur.h * HD, a.lddq, dqacc, rope ? 1.0f : a.scale, l32, hl,
+                                        min(32, T - q0), reinterpret_cast<char *>(smem) + O_OFF + wave * 4096);
+        }
+        for (; kt < ntiles; kt += 2) {
+            request_after(kt, 0);
+            tile_barrier();
+            request_after(kt + 1, STAGE);
+            tile_barrier();
+        }
+        if (!more) break;
+        cur = nxt;
+    }
+}
+
 // ------------------------------------------------------------------ backward: dK, dV
 // grid: key blocks of 256 (heaviest first = block 0) x (batch, KV head); the query heads of the group and their
 // 64-query tiles >= the key block are walked as one sequence through a double-buffered LDS stage, one barrier
@@ -876,8 +1003,6 @@ struct TileStats {
         if (wave == 1) lds[64 + lane] = v;
     }
 };
-__device__ __forceinline__ float scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
-
 template <int HD, int KW, int QW, bool FAR>
 __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a, BlockMap map) {
     constexpr int HB = HD / 32, KB = 32 * KW, NW = KW * QW, GS = BwdTile<HD>::GS;
@@ -983,6 +1108,101 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
     }
 }
 
+// The same in blocks of 256 keys with one workgroup per compute unit that goes through a list of them (see flash_fwd_chain_kernel).  A
+// wave's keys and values are its own: those of the next block are requested as soon as it is done with the present one, and come in
+// while it stores its results.
+// LDS: two stages of Q, dO | V | statistics | the waves' results on their way out
+template <int HD>
+__global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, ChainMap map) {
+    constexpr int HB = HD / 32, KB = 256, GS = BwdTile<HD>::GS;
+    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE, V_OFF = 2 * STAGE, STAT_OFF = V_OFF + KB / 64 * TILE, O_OFF = STAT_OFF + 1024;
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    char *lds = reinterpret_cast<char *>(smem);
+    const int T = a.T, G = (int)(a.Hq / a.Hkv), nt = (T + 63) / 64;
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
+    BwdTile<HD> t;
+    t.init(smem, lane);
+    const float c = scalar(a.scale * kLog2e);
+    DirectTile<64, HD, 8, false, GS> tq, tdo;
+    DirectTile<32, HD, 1, false, GS> tv;
+    tq.init(smem, a.ldq, lane, wave);
+    tdo.init(smem, a.lddo, lane, wave);
+    tv.init(smem, a.ldv, lane, 0);
+    const uint32_t Vw = V_OFF + BwdTile<HD>::rows(32) * wave;
+    uint32_t stat_base = lds_address(smem) + STAT_OFF + hl * 16;
+    asm volatile("" : "+v"(stat_base));   // (one register, see BwdTile)
+
+    bf16x8 kf[HD / 16];
+    TileStats stats;
+    int n_valid = 0;
+    const auto block_of = [&](const Block &blk) { return map.n_blocks - 1 - blk.qb; };   // the heaviest block is the first
+    const auto request_keys = [&](const Block &blk) {
+        const int k0 = block_of(blk) * KB + wave * 32;
+        tv.load(Vw, a.v + (int64_t)blk.b * T * a.ldv + (int64_t)blk.h * HD, a.ldv, k0, T);
+        const bf16_t *kp = a.k + ((int64_t)blk.b * T + min(k0 + l32, T - 1)) * a.ldk + (int64_t)blk.h * HD + hl * 8;
+#pragma unroll
+        for (int i = 0; i < HD / 16; ++i) kf[i] = load_frag_global(kp + i * 16);
+    };
+    const auto request_tile = [&](const Block &blk, int head, int tile, uint32_t stage) {
+        const int h = blk.h * G + head, q0t = tile * 64;
+        tq.load(stage, a.q + (int64_t)blk.b * T * a.ldq + (int64_t)h * HD, a.ldq, q0t, T);
+        tdo.load(stage + TILE, a.dout + (int64_t)blk.b * T * a.lddo + (int64_t)h * HD, a.lddo, q0t, T);
+        stats.fetch(a, blk.b, h, q0t, wave, lane);
+        n_valid = T - q0t;
+    };
+    const auto commit = [&](uint32_t stage) { stats.commit(reinterpret_cast<float *>(lds + STAT_OFF + (stage ? 512 : 0)), n_valid, wave, lane); };
+
+    BlockList list;
+    Block cur, nxt;
+    if (!list.next(map, &cur)) return;
+    request_keys(cur);
+    request_tile(cur, 0, block_of(cur) * (KB / 64), 0);
+    commit(0);
+    wave_barrier(kf);
+    tile_barrier();
+    while (true) {
+        const bool more = list.next(map, &nxt);
+        const int kvb = block_of(cur), kv0w = kvb * KB + wave * 32, kv = kv0w + l32;
+        const int qt_first = kvb * (KB / 64), total = G * (nt - qt_first);
+        f32x16 dvacc[HB], dkacc[HB];
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) {
+            dvacc[hb] = zero16();
+            dkacc[hb] = zero16();
+        }
+        int head = 0, tile = qt_first;   // of the tile at work
+        const auto step = [&](int j, uint32_t stage) {
+            const int tile_ = tile;
+            if (++tile == nt) {
+                tile = qt_first;
+                ++head;
+            }
+            const bool here = j + 1 < total, there = !here && more && (j & 1);
+            if (here) request_tile(cur, head, tile, STAGE - stage);
+            if (there) request_tile(nxt, 0, block_of(nxt) * (KB / 64), STAGE - stage);
+            if (j < total) dkdv_tile<HD, 2, HD == 128>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? 512 : 0), Vw, t, 0, tile_ * 64, kv0w, kv, hl, c);
+            if (here || there) commit(STAGE - stage);
+            tile_barrier();
+        };
+        for (int j = 0; j < total; j += 2) {   // by twos, so that every block starts in stage 0
+            step(j, 0);
+            step(j + 1, STAGE);
+        }
+        if (more) request_keys(nxt);
+        if (kv0w < T) {
+            const int rows = min(32, T - kv0w), pos = min(kv, T - 1);
+            const bool rope = a.rope_cos != nullptr;
+            char *region = lds + O_OFF + wave * 2048;
+            if (rope) rotate_back<HD>(dkacc, a.scale, hl, a.rope_cos + (int64_t)pos * (HD / 2), a.rope_sin + (int64_t)pos * (HD / 2));
+            write_rows_by_parts<HD, 32>(a.dk + ((int64_t)cur.b * T + kv0w) * a.lddk + (int64_t)cur.h * HD, a.lddk, dkacc, rope ? 1.0f : a.scale, l32, hl, rows, region);
+            write_rows_by_parts<HD, 32>(a.dv + ((int64_t)cur.b * T + kv0w) * a.lddv + (int64_t)cur.h * HD, a.lddv, dvacc, 1.0f, l32, hl, rows, region);
+        }
+        wave_barrier(kf);   // no other wave waits for these keys and values
+        if (!more) break;
+        cur = nxt;
+    }
+}
+
 bool attn_shape_ok(const AttnArgs &a) {
     if (a.B <= 0 || a.T <= 0 || a.Hq <= 0 || a.Hkv <= 0 || a.Hq % a.Hkv) return false;
     if (a.hd != 64 && a.hd != 128) return false;
@@ -1078,6 +1298,18 @@ static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int HD>
+static hipError_t launch_dq_chain(const AttnArgs &a, hipStream_t s) {
+    constexpr size_t lds = 2 * 2 * BwdTile<HD>::BYTES + 8 * 4096;
+    static std::atomic<bool> done{false};
+    const hipError_t e = ensure_lds(&flash_bwd_dq_chain_kernel<HD>, lds, &done);
+    if (e != hipSuccess) return e;
+    const int G = a.Hq / a.Hkv, nqb = (a.T + 255) / 256;
+    const ChainMap c = chain_map(G * nqb, a.B * a.Hkv, a.Hkv, G, nqb, 1.0, [&](int r) { return std::min((a.T + 63) / 64, (nqb - r) * 4); });
+    hipLaunchKernelGGL((flash_bwd_dq_chain_kernel<HD>), dim3(kXcds * c.n_workers), dim3(512), lds, s, a, c);
+    return hipGetLastError();
+}
+
 // Estimated time in us of a kernel that takes blocks of `block` queries (or keys): the walk of the heaviest block, or the work of
 // all blocks on 256 compute units, or, where the blocks come by rank, the r-th block of a compute unit behind r - 1 that are at
 // least as heavy (`share` < 1: two workgroups of the kernel share a compute unit).  `tile` and `full` are us per 64-row tile when
@@ -1115,14 +1347,14 @@ static int cheapest(const AttnArgs &a, const AttnCost (&costs)[N], bool keys) {
 // Forward and dQ: blocks of 128 queries with the keys split over two sets of waves, or blocks of 256?  The former walk
 // their keys in two thirds of the time but fetch K and V twice as often.  Measured, blocks of 256 -> 128, us (forward; backward with
 // dK/dV as below), head_dim 128 unless said:
-//   256 blocks of 128: 1 x 1024 x 32 heads 33 -> 27      1 x 2048 x 16 59 -> 45; 467 -> 443      1 x 4096 x 8 109 -> 81; 352 -> 299
-//   264 .. 320: 1 x 384 x 101 17 -> 21; 54 -> 57    1 x 768 x 48 27 -> 22; 85 -> 75    1 x 1536 x 25 46 -> 36; 148 -> 127
-//   512: 1 x 1024 x 64 35 -> 35; 113 -> 109    1 x 2048 x 32 61 -> 54; 199 -> 182      768: 1 x 1536 x 64 52 -> 69; 176 -> 188
+//   256 blocks of 128: 1 x 1024 x 32 heads 30 -> 23; 81 -> 69     1 x 2048 x 16 51 -> 37; 133 -> 108     1 x 4096 x 8 95 -> 65; 238 -> 186
+//   264 .. 320: 1 x 384 x 101 15 -> 19; 52 -> 56    1 x 768 x 48 23 -> 19; 67 -> 60    1 x 1536 x 25 40 -> 30; 108 -> 93
+//   512: 1 x 1024 x 64 32 -> 32; 107 -> 104    1 x 2048 x 32 55 -> 47; 159 -> 146      768: 1 x 1536 x 64 49 -> 61; 166 -> 177
 // In grids beyond kByRank the line is drawn by sizes: with head_dim 64 the forward is bound by its vector arithmetic, four of
 // the smaller workgroups' waves fit on a SIMD, and up to 4096 tokens they win (8 x 2048 x 16 156 -> 122, 4 x 4096 x 16 214 -> 207;
 // 1 x 8192 x 32 359 -> 377); head_dim 128 4 x 4096 x 32 610 -> 733; 830 -> 910.  (Some dQ would win there too: 8 x 2048 x 16, head_dim 64, 182 -> 168.)
 static bool split_keys(const AttnArgs &a, bool forward) {
-    static const AttnCost fwd64[] = {{256, 2.7, 1.15, 2.7, 1.5, 1.0}, {128, 3.2, 0.8, 1.76, 0.62, 0.55}};
+    static const AttnCost fwd64[] = {{256, 2.89, 1.15, 2.7, 1.13, 1.0}, {128, 3.18, 0.92, 1.96, 0.65, 0.55}};
     static const AttnCost dq64[] = {{256, 3.4, 1.25, 3.4, 1.5, 1.0}, {128, 4.0, 0.85, 4.0, 0.95, 1.0}};
     static const AttnCost hd128[] = {{256, 4.0, 1.62, 4.0, 1.9, 1.0}, {128, 5.2, 1.13, 5.2, 1.25, 1.0}};
     const BlockMap map = block_map(a.Hq / a.Hkv * ((a.T + 255) / 256), a.B * a.Hkv, a.Hq / a.Hkv);
@@ -1150,6 +1382,7 @@ hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     if (!near_pitch(a.ldk) || !near_pitch(a.ldv)) return a.hd == 128 ? launch_dq<128, 8, 1, true>(a, s) : launch_dq<64, 8, 1, true>(a, s);
     if (split_keys(a, false)) return a.hd == 128 ? launch_dq<128, 4, 2>(a, s) : launch_dq<64, 4, 2>(a, s);
+    if (a.hd == 128 && a.T > 64 && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256))) return launch_dq_chain<128>(a, s);   // (T: as for the forward)
     return a.hd == 128 ? launch_dq<128, 8, 1>(a, s) : launch_dq<64, 8, 1>(a, s);
 }
 
@@ -1167,15 +1400,27 @@ static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int HD>
+static hipError_t launch_dkdv_chain(const AttnArgs &a, hipStream_t s) {
+    constexpr size_t lds = 4 * BwdTile<HD>::BYTES + 2 * 2 * BwdTile<HD>::BYTES + 1024 + 8 * 2048;
+    static std::atomic<bool> done{false};
+    const hipError_t e = ensure_lds(&flash_bwd_dkdv_chain_kernel<HD>, lds, &done);
+    if (e != hipSuccess) return e;
+    const int G = a.Hq / a.Hkv, nt = (a.T + 63) / 64, nkb = (a.T + 255) / 256;
+    const ChainMap c = chain_map(nkb, a.B * a.Hkv, a.Hkv, 1, nkb, 1.0, [&](int r) { return G * (nt - r * 4); });
+    hipLaunchKernelGGL((flash_bwd_dkdv_chain_kernel<HD>), dim3(kXcds * c.n_workers), dim3(512), lds, s, a, c);
+    return hipGetLastError();
+}
+
 // Which dK/dV kernel.  us of the backward (with dQ and the row sums) for (8, 1) / (4, 2) / (2, 2), head_dim 128:
-//   1 x 1024, 40 heads on 10 KV heads 232 / 186 / 150     1 x 4096, 9 on 9 298 / 251 / 246       1 x 2048, 48 on 12 497 / 399 / 328
-//   1 x 768, 85 on 85 101 / 110 / 140                     1 x 512, 72 on 72 60 / 55 / 65         1 x 1536, 64 on 64 188 / 208 / 263
-// head_dim 64, (8, 1) / (4, 2): 3 x 1000, 16 on 4 163 / 110; 7 x 600, 32 on 32 105 / 118; 8 x 2048, 16 on 16 427 / 405.
+//   1 x 1024, 40 heads on 10 KV heads 210 / 138 / 120     1 x 4096, 9 on 9 268 / 196 / 204       1 x 2048, 48 on 12 442 / 293 / 261
+//   1 x 1536, 25 on 25 117 / 93 / 108                     1 x 384, 101 on 101 50 / 52 / 58       1 x 1536, 64 on 64 163 / 175 / 218
+// head_dim 64, (8, 1) / (4, 2): 3 x 1000, 16 on 4 139 / 93.
 // Up to 128 keys and without groups of query heads, a walk of two tiles, the halves' merge costs more than it saves: 264 heads, 128
 // tokens, head_dim 128 50 / 53 / 54.
 static int choose_dkdv(const AttnArgs &a) {
     static const AttnCost hd64[] = {{256, 2.0, 2.05, 14.0, 2.3, 1.0}, {128, 4.0, 1.22, 10.0, 1.27, 1.0}};
-    static const AttnCost hd128[] = {{256, 6.0, 3.05, 10.0, 3.9, 1.0}, {128, 9.0, 2.05, 10.0, 2.35, 1.0}, {64, 9.0, 1.75, 7.0, 1.78, 1.0}};
+    static const AttnCost hd128[] = {{256, 6.0, 3.32, 12.59, 3.68, 1.0}, {128, 9.0, 2.05, 8.33, 1.98, 1.0}, {64, 9.0, 1.57, 7.0, 1.69, 1.0}};
     if (a.T <= 128 && a.Hq == a.Hkv) return 0;
     return a.hd == 64 ? cheapest(a, hd64, true) : cheapest(a, hd128, true);
 }
@@ -1191,7 +1436,14 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     if (!near_pitch(a.ldq) || !near_pitch(a.ldv) || !near_pitch(a.lddo))
         return a.hd == 128 ? launch_dkdv<128, 8, 1, true>(a, s) : launch_dkdv<64, 8, 1, true>(a, s);
     switch (choose_dkdv(a)) {
-        case 0: return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
+        case 0:
+            // (lists of less than three blocks save less than they cost: 1 x 1536, 64 heads, 3 blocks 163 -> 165 us; 3.8 blocks 3 % faster,
+            // 8 x 2048, 16 heads, 4 blocks 651 -> 547 together with dQ)
+            if (a.hd == 128 && chain_fits(a, (a.T + 255) / 256)) {
+                const BlockMap m = block_map((a.T + 255) / 256, a.B * a.Hkv, 1);
+                if (m.n_parts * m.per_part > 3 * kWorkers) return launch_dkdv_chain<128>(a, s);
+            }
+            return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
         case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);
         default: return launch_dkdv<128, 2, 2>(a, s);
     }
