@@ -157,8 +157,11 @@ int32_t mt_k_flash_bwd(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t lddk, u
                        void *stream);
 
 /* Which blocks the attention kernels take at this size (host only, launches nothing): queries of the forward, queries of dq (256, or
- * 128 with the keys split over two sets of waves), keys of dk and dv (256, or 128 or 64 with the queries split). */
+ * 128 with the keys split over two sets of waves), keys of dk and dv (256, or 128 or 64 with the queries split).  Problems that would
+ * leave most of the chip idle cut these blocks further: mt_k_flash_sets gives, for the three in turn, the rows of a block as it is taken and
+ * the number of sets of waves that share it (six values). */
 int32_t mt_k_flash_route(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *route);
+int32_t mt_k_flash_sets(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *sets);
 
 /* The same with the backward of a rotary embedding folded into the stores: q and k are the rotated tensors the
  * forward attended with, and dq, dk come out as gradients of the unrotated ones (rotated back by the angle of

@@ -126,7 +126,7 @@ template <int HD>
 struct BwdTile {
     static constexpr int GS = HD == 128 ? 1040 : 1024, RPL = 512 / HD, ROW = 2 * HD;
     static constexpr uint32_t BYTES = 64 / RPL * GS;   // of 64 rows
-    static __device__ __forceinline__ uint32_t rows(int n) { return n / RPL * GS; }   // offset of row n (a multiple of 8)
+    static __host__ __device__ constexpr uint32_t rows(int n) { return n / RPL * GS; }   // offset of row n (a multiple of 8)
     uint32_t ra[4], ta[HD / 32];   // (LDS addresses as numbers: through a pointer to the dynamic LDS the compiler adds its base, 0, over and over)
     __device__ __forceinline__ void init(const void *smem, int lane) {
         const uint32_t base = lds_address(smem);
@@ -474,10 +474,12 @@ __device__ __forceinline__ void fwd_tile(f32x16 (&oacc)[HD / 32], float &m, floa
     }
 }
 
+// rows of a tile that n sets of waves share, 32 of them each (a lone set takes both halves of 64)
+__host__ __device__ constexpr int walk_rows(int n) { return std::max(64, 32 * n); }
 template <int HD, int QW, int KW, bool FAR>
 __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, BlockMap map) {
-    constexpr int BQ = 32 * QW, NR = 2 / KW;
-    constexpr uint32_t TILE = 64 * HD * 2, STAGE = 2 * TILE;   // bytes; a stage is K, V
+    constexpr int BQ = 32 * QW, TK = walk_rows(KW), NR = TK / 32 / KW;
+    constexpr uint32_t TILE = TK * HD * 2, STAGE = 2 * TILE;   // bytes; a stage is K, V
     extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
@@ -495,8 +497,8 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
     const bf16_t *kbase = a.k + (int64_t)b * T * a.ldk + (int64_t)hk * HD;
     const bf16_t *vbase = a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD;
     const int kv_end = min(T, qb * BQ + BQ);
-    const int ntiles = (kv_end + 63) / 64;
-    DirectTile<64, HD, QW * KW, FAR> dk, dv;
+    const int ntiles = (kv_end + TK - 1) / TK;
+    DirectTile<TK, HD, QW * KW, FAR> dk, dv;
     dk.init(smem, a.ldk, lane, wave);
     dv.init(smem, a.ldv, lane, wave);
     dk.load(0, kbase, a.ldk, 0, T);
@@ -513,14 +515,14 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
     for (int hb = 0; hb < HD / 32; ++hb) oacc[hb] = zero16();
     float m = -INFINITY, lsum = 0.f;  // m: running maximum of the raw (unscaled) scores
     const float c = a.scale * kLog2e, tau = kLazyMax / c;
-    const int key0 = KW == 2 ? kw * 32 : 0;  // first key of this wave inside a tile
+    const int key0 = KW > 1 ? kw * 32 : 0;  // first key of this wave inside a tile
     tile_barrier();
 
     const auto step = [&](int kt, uint32_t stage) {
-        const int kv0 = kt * 64;
+        const int kv0 = kt * TK;
         if (kt + 1 < ntiles) {
-            dk.load(STAGE - stage, kbase, a.ldk, kv0 + 64, T);
-            dv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + 64, T);
+            dk.load(STAGE - stage, kbase, a.ldk, kv0 + TK, T);
+            dv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + TK, T);
         }
         if (kv0 + key0 <= q0 + 31) {  // otherwise the wave's keys lie after every one of its queries
             const char *Ks = reinterpret_cast<const char *>(smem) + stage;
@@ -553,6 +555,39 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
         }
         __syncthreads();
         if (kw == 1) return;
+    }
+    if constexpr (KW > 2) {   // as above, but all waves add: each a share of the columns of its QW neighbours' 32 queries
+        constexpr int QUADS = HD / 32 * 4;
+        f32x4 *sums = reinterpret_cast<f32x4 *>(smem);
+        float *stat = reinterpret_cast<float *>(smem) + QW * KW * (QUADS * 256);
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i)
+            sums[(wave * QUADS + i) * 64 + lane] = f32x4{oacc[i >> 2][(i & 3) * 4], oacc[i >> 2][(i & 3) * 4 + 1], oacc[i >> 2][(i & 3) * 4 + 2], oacc[i >> 2][(i & 3) * 4 + 3]};
+        stat[wave * 128 + lane] = m;   // -inf where this share saw no key: its weight below is zero
+        stat[wave * 128 + 64 + lane] = lsum;
+        __syncthreads();
+        float w[KW], mn = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+            w[i] = stat[(i * QW + qw) * 128 + lane];
+            mn = fmaxf(mn, w[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+            w[i] = __builtin_amdgcn_exp2f((w[i] - mn) * c);
+            sum += stat[(i * QW + qw) * 128 + 64 + lane] * w[i];
+        }
+        if (!qok) return;
+        bf16_t *out = a.o + ((int64_t)b * T + q) * a.ldo + (int64_t)h * HD;
+        const float mul = 1.0f / sum;
+        for (int p = kw; p < QUADS; p += KW) {
+            f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < KW; ++i) x += sums[((i * QW + qw) * QUADS + p) * 64 + lane] * w[i];
+            *reinterpret_cast<uint2 *>(out + (p >> 2) * 32 + (p & 3) * 8 + hl * 4) = uint2{pack2bf(x[0] * mul, x[1] * mul), pack2bf(x[2] * mul, x[3] * mul)};
+        }
+        if (kw == 0 && hl == 0) a.lse[((int64_t)b * a.Hq + h) * T + q] = (mn * c + __builtin_amdgcn_logf(sum)) * kLn2;
+        return;
     }
     if (q0 < T)
         write_owned_rows<HD>(a.o + ((int64_t)b * T + q0) * a.ldo + (int64_t)h * HD, a.ldo, oacc, 1.0f / lsum, l32, hl,
@@ -697,7 +732,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 template <int HD, int NR>
 __device__ __forceinline__ void dq_tile(f32x16 (&dqacc)[HD / 32], const bf16x8 (&qf)[HD / 16], const bf16x8 (&dof)[HD / 16], uint32_t Ks, uint32_t Vs,
                                         const BwdTile<HD> &t, int rb0, int kv0, int q0, int qm, int hl, float c, float lse2, float dlt) {
-    const bool diag = kv0 + 63 > q0;
+    const bool diag = kv0 + (NR == 1 ? rb0 * 32 + 31 : 63) > q0;
 #pragma unroll
     for (int u = 0; u < NR; ++u) {
         const int rb = NR == 1 ? rb0 : u;
@@ -736,10 +771,44 @@ __device__ __forceinline__ void dq_tile(f32x16 (&dqacc)[HD / 32], const bf16x8 (
     }
 }
 
+// The sums of N sets of W waves that shared a block, added up in the order of the sets and stored.  Wave w of every set owns the same 32 rows
+// (a lane one of them, at out); each adds and stores a share of their columns, so all of them work on it.  cs, sn: rotary tables at the row, or NULL.
+template <int HD, int W, int N>
+__device__ __forceinline__ void store_summed(bf16_t *out, const f32x16 *acc, float mul, int w, int set, int lane, bool valid,
+                                             const float *cs, const float *sn, char *smem) {
+    constexpr int HB = HD / 32, QUADS = HB * 4, PAIRS = HD / 64 * 4;   // quads of columns of a lane; pairs of them that rotate together
+    f32x4 *mine = reinterpret_cast<f32x4 *>(smem) + (set * W + w) * (QUADS * 64) + lane;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < QUADS; ++i)
+        mine[i * 64] = f32x4{acc[i >> 2][(i & 3) * 4], acc[i >> 2][(i & 3) * 4 + 1], acc[i >> 2][(i & 3) * 4 + 2], acc[i >> 2][(i & 3) * 4 + 3]};
+    __syncthreads();
+    if (!valid) return;
+    const f32x4 *first = reinterpret_cast<const f32x4 *>(smem) + w * (QUADS * 64) + lane;
+    for (int p = set; p < PAIRS; p += N) {
+        f32x4 x = first[p * 64], y = first[(p + PAIRS) * 64];
+#pragma unroll
+        for (int s = 1; s < N; ++s) {
+            x += first[(s * W * QUADS + p) * 64];
+            y += first[(s * W * QUADS + p + PAIRS) * 64];
+        }
+        const int j = (p >> 2) * 32 + (p & 3) * 8 + (lane >> 5) * 4;
+        x *= mul;
+        y *= mul;
+        if (cs) {
+            const f32x4 c = *reinterpret_cast<const f32x4 *>(cs + j), v = *reinterpret_cast<const f32x4 *>(sn + j);
+            const f32x4 r = x * c + y * v;
+            y = y * c - x * v;
+            x = r;
+        }
+        *reinterpret_cast<uint2 *>(out + j) = uint2{pack2bf(x[0], x[1]), pack2bf(x[2], x[3])};
+        *reinterpret_cast<uint2 *>(out + j + HD / 2) = uint2{pack2bf(y[0], y[1]), pack2bf(y[2], y[3])};
+    }
+}
 template <int HD, int QW, int KW, bool FAR>
 __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, BlockMap map) {
-    constexpr int BQ = 32 * QW;
-    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE;   // a stage is K, V
+    constexpr int BQ = 32 * QW, TK = walk_rows(KW);
+    constexpr uint32_t TILE = BwdTile<HD>::rows(TK), STAGE = 2 * TILE;   // a stage is K, V
     extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
@@ -758,8 +827,8 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
     const bf16_t *kbase = a.k + (int64_t)b * T * a.ldk + (int64_t)hk * HD;
     const bf16_t *vbase = a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD;
     const int kv_end = min(T, qb * BQ + BQ);
-    const int ntiles = (kv_end + 63) / 64;
-    DirectTile<64, HD, QW * KW, FAR, BwdTile<HD>::GS> tk, tv;
+    const int ntiles = (kv_end + TK - 1) / TK;
+    DirectTile<TK, HD, QW * KW, FAR, BwdTile<HD>::GS> tk, tv;
     tk.init(smem, a.ldk, lane, wave);
     tv.init(smem, a.ldv, lane, wave);
     tk.load(0, kbase, a.ldk, 0, T);
@@ -784,13 +853,13 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
     tile_barrier();
 
     const auto step = [&](int kt, uint32_t stage) {
-        const int kv0 = kt * 64;
+        const int kv0 = kt * TK;
         if (kt + 1 < ntiles) {
-            tk.load(STAGE - stage, kbase, a.ldk, kv0 + 64, T);
-            tv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + 64, T);
+            tk.load(STAGE - stage, kbase, a.ldk, kv0 + TK, T);
+            tv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + TK, T);
         }
-        if (kv0 + (KW == 2 ? kw * 32 : 0) <= q0 + 31) {
-            dq_tile<HD, 2 / KW>(dqacc, qf, dof, stage, stage + TILE, t, kw, kv0, q0, qm, hl, c, lse2, dlt);
+        if (kv0 + (KW > 1 ? kw * 32 : 0) <= q0 + 31) {
+            dq_tile<HD, TK / 32 / KW>(dqacc, qf, dof, stage, stage + TILE, t, kw, kv0, q0, qm, hl, c, lse2, dlt);
         }
         tile_barrier();
     };
@@ -812,6 +881,12 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
         }
         __syncthreads();
         if (kw == 1) return;
+    }
+    if constexpr (KW > 2) {
+        store_summed<HD, QW, KW>(a.dq + ((int64_t)b * T + q) * a.lddq + (int64_t)h * HD, dqacc, a.scale, qw, kw, lane, qok,
+                                 a.rope_cos ? a.rope_cos + (int64_t)qm * (HD / 2) : nullptr, a.rope_cos ? a.rope_sin + (int64_t)qm * (HD / 2) : nullptr,
+                                 reinterpret_cast<char *>(smem));
+        return;
     }
     if (q0 < T)
         write_owned_rows<HD>(a.dq + ((int64_t)b * T + q0) * a.lddq + (int64_t)h * HD, a.lddq, dqacc, a.scale, l32, hl,
@@ -924,8 +999,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
 // choose_dkdv.
 
 // the queries 32 rb .. + 31 (rb0 <= rb < rb0 + NR) of the tile that starts at query q0t; kv0w: the wave's first key, kv: the lane's;
-// stats: lse * log2e [64], delta [64] from the lane half's first query on; Vw: the wave's rows of V
-template <int HD, int NR, bool TIGHT>
+// stats: lse * log2e [TQ], delta [TQ] from the lane half's first query on; Vw: the wave's rows of V
+template <int HD, int NR, bool TIGHT, int TQ = 64>
 __device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dkacc)[HD / 32], const bf16x8 (&kf)[HD / 16], uint32_t Qs, uint32_t dOs,
                                           uint32_t stats, uint32_t Vw, const BwdTile<HD> &t, int rb0, int q0t, int kv0w, int kv, int hl, float c) {
     typedef __attribute__((address_space(3))) const f32x4 *lds_f4;
@@ -977,7 +1052,7 @@ __device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dka
         f32x16 dsacc;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            const f32x4 dv4 = *(lds_f4)(stats + (64 + rb * 32 + r4 * 8) * 4);
+            const f32x4 dv4 = *(lds_f4)(stats + (TQ + rb * 32 + r4 * 8) * 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) dsacc[r4 * 4 + e] = s_[r4 * 4 + e] * (p_[r4 * 4 + e] - dv4[e]);
         }
@@ -990,23 +1065,32 @@ __device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dka
         }
     }
 }
-// The softmax statistics of a tile's queries, fetched by the first two waves (one lane a query): a plain load with nothing computed
+// The softmax statistics of a tile's queries, fetched by its first waves (one lane a query): a plain load with nothing computed
 // from it until it is put into LDS (arithmetic on the value would make these waves wait for it, and for the tile loads in front of it).
+template <int TQ = 64>
 struct TileStats {
+    static constexpr int W = TQ / 64;   // waves for each of the two
     float v;
     __device__ __forceinline__ void fetch(const AttnArgs &a, int b, int h, int q0t, int wave, int lane) {
-        if (wave < 2) v = ((wave ? a.delta : a.lse) + ((int64_t)b * a.Hq + h) * a.T + q0t)[(uint32_t)min(lane, a.T - 1 - q0t)];
+        if (wave < 2 * W)
+            v = ((wave < W ? a.lse : a.delta) + ((int64_t)b * a.Hq + h) * a.T + q0t)[(uint32_t)min(wave % W * 64 + lane, a.T - 1 - q0t)];
     }
     // queries past T: lse = +inf makes their P (and with it dS) exactly zero
     __device__ __forceinline__ void commit(float *lds, int n_valid, int wave, int lane) const {
-        if (wave == 0) lds[lane] = lane < n_valid ? v * kLog2e : INFINITY;
-        if (wave == 1) lds[64 + lane] = v;
+        if (wave < W) lds[wave * 64 + lane] = wave * 64 + lane < n_valid ? v * kLog2e : INFINITY;
+        else if (wave < 2 * W) lds[wave * 64 + lane] = v;
     }
+};
+template <int HD, int KW, int QW>
+struct DkdvLds {
+    static constexpr uint32_t TILE = BwdTile<HD>::rows(walk_rows(QW)), V_BYTES = BwdTile<HD>::rows(32 * KW);
+    static constexpr uint32_t STATS = 8 * walk_rows(QW), STAT_OFF = 4 * TILE + V_BYTES, BYTES = STAT_OFF + 2 * STATS;
 };
 template <int HD, int KW, int QW, bool FAR>
 __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a, BlockMap map) {
-    constexpr int HB = HD / 32, KB = 32 * KW, NW = KW * QW, GS = BwdTile<HD>::GS;
-    constexpr uint32_t TILE = BwdTile<HD>::BYTES, STAGE = 2 * TILE, V_OFF = 2 * STAGE, STAT_OFF = V_OFF + KB / 64 * TILE;
+    constexpr int HB = HD / 32, KB = 32 * KW, NW = KW * QW, GS = BwdTile<HD>::GS, TQ = walk_rows(QW);
+    using Lds = DkdvLds<HD, KW, QW>;
+    constexpr uint32_t TILE = Lds::TILE, STAGE = 2 * TILE, V_OFF = 2 * STAGE, STAT_OFF = Lds::STAT_OFF;
     extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
     char *lds = reinterpret_cast<char *>(smem);
 
@@ -1028,16 +1112,16 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
         dkacc[hb] = zero16();
     }
     const float c = scalar(a.scale * kLog2e);
-    const int qt_first = (kvb * KB) / 64, n_qt = (T + 63) / 64 - qt_first;
+    const int qt_first = (kvb * KB) / TQ, n_qt = (T + TQ - 1) / TQ - qt_first;
     const int total = G * n_qt;
 
-    DirectTile<64, HD, NW, FAR, GS> tq, tdo;
+    DirectTile<TQ, HD, NW, FAR, GS> tq, tdo;
     tq.init(smem, a.ldq, lane, wave);
     tdo.init(smem, a.lddo, lane, wave);
-    TileStats stats;
+    TileStats<TQ> stats;
     int f_head = 0, f_tile = 0, n_valid = 0;
     const auto request_next = [&](uint32_t stage) {
-        const int h = hk * G + f_head, q0t = (qt_first + f_tile) * 64;
+        const int h = hk * G + f_head, q0t = (qt_first + f_tile) * TQ;
         if (++f_tile == n_qt) {
             f_tile = 0;
             ++f_head;
@@ -1048,13 +1132,14 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
         n_valid = T - q0t;
     };
     const auto commit = [&](uint32_t stage) {
-        stats.commit(reinterpret_cast<float *>(lds + STAT_OFF + (stage ? 512 : 0)), n_valid, wave, lane);
+        stats.commit(reinterpret_cast<float *>(lds + STAT_OFF + (stage ? Lds::STATS : 0)), n_valid, wave, lane);
     };
     bf16x8 kf[HD / 16];
     {
-        DirectTile<KB, HD, NW, FAR, GS> tv;
+        constexpr int VW = std::min(NW, KB / BwdTile<HD>::RPL);   // waves that fetch the values
+        DirectTile<KB, HD, VW, FAR, GS> tv;
         tv.init(smem, a.ldv, lane, wave);
-        tv.load(V_OFF, a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD, a.ldv, kvb * KB, T);
+        if (wave < VW) tv.load(V_OFF, a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD, a.ldv, kvb * KB, T);
         request_next(0);
         const bf16_t *kp = a.k + ((int64_t)b * T + min(kv, T - 1)) * a.ldk + (int64_t)hk * HD + hl * 8;
 #pragma unroll
@@ -1070,8 +1155,10 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
     const auto step = [&](int j, uint32_t stage) {
         const bool more = j + 1 < total;
         if (more) request_next(STAGE - stage);
-        dkdv_tile<HD, 2 / QW, HD == 128 && NW == 8>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? 512 : 0), Vw, t, qw,
-                              (qt_first + tq_) * 64, kv0w, kv, hl, c);
+        const int q0t = (qt_first + tq_) * TQ;
+        if (QW <= 2 || q0t + qw * 32 < T)
+            dkdv_tile<HD, TQ / 32 / QW, HD == 128 && NW == 8, TQ>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? Lds::STATS : 0), Vw, t, qw,
+                              q0t, kv0w, kv, hl, c);
         if (more) commit(STAGE - stage);
         tile_barrier();
         tq_ = tq_ + 1 == n_qt ? 0 : tq_ + 1;
@@ -1097,6 +1184,14 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
         add_halves(dvacc);
         add_halves(dkacc);
         if (qw == 1) return;
+    }
+    if constexpr (QW > 2) {
+        const bool valid = kv < T;
+        const int64_t row = (int64_t)b * T + kv;
+        const float *cs = a.rope_cos ? a.rope_cos + (int64_t)kv * (HD / 2) : nullptr, *sn = a.rope_cos ? a.rope_sin + (int64_t)kv * (HD / 2) : nullptr;
+        store_summed<HD, KW, QW>(a.dk + row * a.lddk + (int64_t)hk * HD, dkacc, a.scale, kw, qw, lane, valid, cs, sn, lds);
+        store_summed<HD, KW, QW>(a.dv + row * a.lddv + (int64_t)hk * HD, dvacc, 1.0f, kw, qw, lane, valid, nullptr, nullptr, lds);
+        return;
     }
     if (kv0w < T) {
         const int n_valid = min(32, T - kv0w);
@@ -1133,7 +1228,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, C
     asm volatile("" : "+v"(stat_base));   // (one register, see BwdTile)
 
     bf16x8 kf[HD / 16];
-    TileStats stats;
+    TileStats<> stats;
     int n_valid = 0;
     const auto block_of = [&](const Block &blk) { return map.n_blocks - 1 - blk.qb; };   // the heaviest block is the first
     const auto request_keys = [&](const Block &blk) {
@@ -1222,8 +1317,9 @@ bool rope_tables_ok(const AttnArgs &a) {
 template <int HD, int QW, int KW, bool FAR = false>
 static hipError_t launch_fwd(const AttnArgs &a, hipStream_t s) {
     // two stages of K and V, or what the results need on their way out (out_region, the other half's sums)
-    constexpr size_t lds = std::max({(size_t)2 * 2 * 64 * HD * sizeof(bf16_t), (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
-                                     KW == 1 ? 0 : (size_t)QW * (HD / 32 * 16 + 2) * 64 * sizeof(float)});
+    constexpr size_t lds = std::max({(size_t)2 * 2 * walk_rows(KW) * HD * sizeof(bf16_t), (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
+                                     KW == 1 ? 0 : (size_t)(KW == 2 ? 1 : KW) * QW * (HD / 32 * 16 + 2) * 64 * sizeof(float)});
+    static_assert(lds <= 160 * 1024, "LDS");
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_fwd_kernel<HD, QW, KW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
@@ -1287,8 +1383,9 @@ static hipError_t launch_fwd_chain(const AttnArgs &a, hipStream_t s) {
 
 template <int HD, int QW, int KW, bool FAR = false>
 static hipError_t launch_dq(const AttnArgs &a, hipStream_t s) {
-    constexpr size_t lds = std::max({(size_t)2 * 2 * BwdTile<HD>::BYTES, (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
-                                     KW == 1 ? 0 : (size_t)QW * (HD / 32 * 16) * 64 * sizeof(float)});
+    constexpr size_t lds = std::max({(size_t)2 * 2 * BwdTile<HD>::rows(walk_rows(KW)), (size_t)QW * 32 * (HD + 8) * sizeof(bf16_t),
+                                     KW == 1 ? 0 : (size_t)(KW == 2 ? 1 : KW) * QW * (HD / 32 * 16) * 64 * sizeof(float)});
+    static_assert(lds <= 160 * 1024, "LDS");
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dq_kernel<HD, QW, KW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
@@ -1315,13 +1412,17 @@ static hipError_t launch_dq_chain(const AttnArgs &a, hipStream_t s) {
 // least as heavy (`share` < 1: two workgroups of the kernel share a compute unit).  `tile` and `full` are us per 64-row tile when
 // a walk decides and when the chip is full, `start` and `start_full` per block.  Fitted to 316 shapes (T 64 .. 4096, 24 .. 768 blocks of
 // 128 queries, 1 .. 8 query heads per KV head) on which the choice between the kernels comes out within 1 % of the best on average.
-struct AttnCost { int block; double start, tile, start_full, full, share; };
+// `rows`: of a tile (64 or more).
+struct AttnCost { int block, rows; double start, tile, start_full, full, share; };
 static double attn_time(const AttnArgs &a, const AttnCost &c, bool keys) {
-    const int G = a.Hq / a.Hkv, nt = (a.T + 63) / 64, nb = (a.T + c.block - 1) / c.block, tpb = c.block / 64, n_sets = a.B * a.Hkv;
+    const int G = a.Hq / a.Hkv, nt = (a.T + c.rows - 1) / c.rows, nb = (a.T + c.block - 1) / c.block, n_sets = a.B * a.Hkv;
     const int copies = keys ? 1 : G, per_set = copies * nb;
+    const double tpb = (double)c.block / c.rows, cut = nb > 1 ? 0.5 * std::max(0.0, 1.0 - tpb) : 0.0;   // (a block's first or last tile counts whole)
     const BlockMap map = block_map(per_set, n_sets, copies);
-    const auto tiles = [&](int inner) -> double { return keys ? (double)G * (nt - inner * tpb) : (double)std::min(nt, (nb - inner / G) * tpb); };
-    const double mean = keys ? G * (nt - (nb - 1) * tpb * 0.5) : ((nb - 1) * 0.5 * nb * tpb + nt) / nb;
+    const auto tiles = [&](int inner) -> double {
+        return keys ? (double)G * (nt - (int)((int64_t)inner * c.block / c.rows)) : (double)std::min(nt, (int)(((int64_t)(nb - inner / G) * c.block + c.rows - 1) / c.rows));
+    };
+    const double mean = keys ? G * (nt - (nb - 1) * tpb * 0.5 + cut) : ((nb - 1) * 0.5 * nb * tpb + nt) / nb + cut;
     double t = std::max(c.start + tiles(0) * c.tile, (double)n_sets * per_set / 256.0 * (c.start_full + mean * c.full));
     const int64_t slots = (int64_t)map.n_parts * map.per_part;
     if (slots <= kByRank)
@@ -1354,20 +1455,62 @@ static int cheapest(const AttnArgs &a, const AttnCost (&costs)[N], bool keys) {
 // the smaller workgroups' waves fit on a SIMD, and up to 4096 tokens they win (8 x 2048 x 16 156 -> 122, 4 x 4096 x 16 214 -> 207;
 // 1 x 8192 x 32 359 -> 377); head_dim 128 4 x 4096 x 32 610 -> 733; 830 -> 910.  (Some dQ would win there too: 8 x 2048 x 16, head_dim 64, 182 -> 168.)
 static bool split_keys(const AttnArgs &a, bool forward) {
-    static const AttnCost fwd64[] = {{256, 2.89, 1.15, 2.7, 1.13, 1.0}, {128, 3.18, 0.92, 1.96, 0.65, 0.55}};
-    static const AttnCost dq64[] = {{256, 3.4, 1.25, 3.4, 1.5, 1.0}, {128, 4.0, 0.85, 4.0, 0.95, 1.0}};
-    static const AttnCost hd128[] = {{256, 4.0, 1.62, 4.0, 1.9, 1.0}, {128, 5.2, 1.13, 5.2, 1.25, 1.0}};
+    static const AttnCost fwd64[] = {{256, 64, 2.89, 1.15, 2.7, 1.13, 1.0}, {128, 64, 3.18, 0.92, 1.96, 0.65, 0.55}};
+    static const AttnCost dq64[] = {{256, 64, 3.4, 1.25, 3.4, 1.5, 1.0}, {128, 64, 4.0, 0.85, 4.0, 0.95, 1.0}};
+    static const AttnCost hd128[] = {{256, 64, 4.0, 1.62, 4.0, 1.9, 1.0}, {128, 64, 5.2, 1.13, 5.2, 1.25, 1.0}};
     const BlockMap map = block_map(a.Hq / a.Hkv * ((a.T + 255) / 256), a.B * a.Hkv, a.Hq / a.Hkv);
     if ((int64_t)map.n_parts * map.per_part > kByRank)
         return forward && a.hd == 64 && a.T <= 4096 && (int64_t)a.B * a.Hq * ((a.T + 127) / 128) >= 1024;
     return cheapest(a, a.hd == 128 ? hd128 : forward ? fwd64 : dq64, false) == 1;
 }
 
+// Problems whose blocks do not fill the chip walk their rows with most of it idle.  Their blocks are cut further: 64 rows with the other side
+// split over four sets of waves, or 32 rows with eight sets (head_dim 128: four, which is what LDS holds tiles for); a tile has 32 rows for every set.
+// A walk takes a half to an eighth of the tiles, and what bounds it is a tile's own chain of loads, products and exponentials, 0.7-1.8 us.
+// Taken where the estimate is 6 % below that of the kernel chosen by the rules above (`own`: 0, 1, 2 for blocks of 256, 128, 64).  Fitted to 400 shapes (T 64 .. 8192,
+// up to 1200 blocks of 128 queries, 1 .. 8 query heads per KV head), over which the choice is within 0.6 % of the best on average, nowhere more than
+// 2 % behind the former kernels, and on average faster than they by (head_dim 64, 128): forward 16 and 13 %, dQ 14 and 18 %, dK/dV 33 and 22 %.  us:
+//   forward   1 x 4096, 4 heads on 1, head_dim 64 54 -> 26     1 x 2048, 4 heads, head_dim 128 43 -> 24
+//   backward, with dQ, dK/dV and the row sums   3 x 520, 8 on 2, 64 57 -> 33     1 x 4096, 4 on 1, 64 316 -> 123     1 x 1024, 40 on 10, 128 124 -> 96
+// One tile of 64 rows or less has nothing to share.
+template <int N>
+static int finer(const AttnArgs &a, const AttnCost (&costs)[N], int own, bool keys) {
+    if (a.T <= 64 || (int64_t)a.B * a.Hq * ((a.T + 127) / 128) > 1200) return own;
+    int best = own;
+    double best_t = 0.94 * attn_time(a, costs[own], keys);
+    for (int i = 3; i < N; ++i) {
+        const double t = attn_time(a, costs[i], keys);
+        if (t < best_t) {
+            best = i;
+            best_t = t;
+        }
+    }
+    return best;
+}
+// 0: blocks of 256 queries, 1: of 128, keys split in two, 3: of 64, in four, 4: of 32, in eight (head_dim 128: four)
+static int query_kernel(const AttnArgs &a, bool forward) {
+    static const AttnCost fwd64[] = {{256, 64, 4.17, 1.05, 4.35, 1.41, 1.12}, {128, 64, 4.65, 0.66, 2.95, 0.73, 0.6}, {},
+        {64, 128, 4.63, 0.71, 3.07, 0.73, 0.38}, {32, 256, 4.79, 0.84, 3.87, 0.96, 0.75}};
+    static const AttnCost fwd128[] = {{256, 64, 5.13, 1.49, 0.0, 1.19, 1.44}, {128, 64, 6.39, 0.88, 7.49, 1.12, 1.02}, {},
+        {64, 128, 6.36, 1.06, 6.59, 1.28, 0.99}, {32, 128, 5.14, 1.11, 4.84, 1.2, 0.88}};
+    static const AttnCost dq64[] = {{256, 64, 5.04, 1.3, 4.93, 1.76, 1.31}, {128, 64, 5.65, 0.7, 5.84, 0.82, 1.02}, {},
+        {64, 128, 5.56, 0.72, 5.1, 0.92, 0.82}, {32, 256, 5.68, 0.87, 4.81, 1.06, 0.81}};
+    static const AttnCost dq128[] = {{256, 64, 7.39, 2.09, 0.0, 0.5, 1.55}, {128, 64, 8.37, 1.11, 9.85, 1.42, 1.29}, {},
+        {64, 128, 8.39, 1.29, 8.5, 1.59, 1.04}, {32, 128, 5.91, 1.15, 5.79, 1.24, 0.91}};
+    const int own = split_keys(a, forward) ? 1 : 0;
+    return forward ? finer(a, a.hd == 64 ? fwd64 : fwd128, own, false) : finer(a, a.hd == 64 ? dq64 : dq128, own, false);
+}
+
 hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
     if (!attn_shape_ok(a) || (a.ldq & 7) || (a.ldk & 7) || (a.ldv & 7) || (a.ldo & 3)) return hipErrorInvalidValue;
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || ((uintptr_t)a.o & 7)) return hipErrorInvalidValue;
     if (!near_pitch(a.ldk) || !near_pitch(a.ldv)) return a.hd == 128 ? launch_fwd<128, 8, 1, true>(a, s) : launch_fwd<64, 8, 1, true>(a, s);
-    if (split_keys(a, true)) return a.hd == 128 ? launch_fwd<128, 4, 2>(a, s) : launch_fwd<64, 4, 2>(a, s);
+    switch (query_kernel(a, true)) {
+        case 1: return a.hd == 128 ? launch_fwd<128, 4, 2>(a, s) : launch_fwd<64, 4, 2>(a, s);
+        case 3: return a.hd == 128 ? launch_fwd<128, 2, 4>(a, s) : launch_fwd<64, 2, 4>(a, s);
+        case 4: return a.hd == 128 ? launch_fwd<128, 1, 4>(a, s) : launch_fwd<64, 1, 8>(a, s);
+        default: break;
+    }
     // (one tile of keys: nothing to fetch ahead, 5.4 us against 5.9)
     if (a.hd == 128 && a.T > 64 && near_pitch(a.ldq) && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256)))
         return launch_fwd_chain<128>(a, s);
@@ -1381,7 +1524,12 @@ hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.dout) || ((uintptr_t)a.dq & 7))
         return hipErrorInvalidValue;
     if (!near_pitch(a.ldk) || !near_pitch(a.ldv)) return a.hd == 128 ? launch_dq<128, 8, 1, true>(a, s) : launch_dq<64, 8, 1, true>(a, s);
-    if (split_keys(a, false)) return a.hd == 128 ? launch_dq<128, 4, 2>(a, s) : launch_dq<64, 4, 2>(a, s);
+    switch (query_kernel(a, false)) {
+        case 1: return a.hd == 128 ? launch_dq<128, 4, 2>(a, s) : launch_dq<64, 4, 2>(a, s);
+        case 3: return a.hd == 128 ? launch_dq<128, 2, 4>(a, s) : launch_dq<64, 2, 4>(a, s);
+        case 4: return a.hd == 128 ? launch_dq<128, 1, 4>(a, s) : launch_dq<64, 1, 8>(a, s);
+        default: break;
+    }
     if (a.hd == 128 && a.T > 64 && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256))) return launch_dq_chain<128>(a, s);   // (T: as for the forward)
     return a.hd == 128 ? launch_dq<128, 8, 1>(a, s) : launch_dq<64, 8, 1>(a, s);
 }
@@ -1389,9 +1537,10 @@ hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
 template <int HD, int KW, int QW, bool FAR = false>
 static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     constexpr int KB = 32 * KW;
-    constexpr size_t lds = KB / 64 * BwdTile<HD>::BYTES + 2 * (2 * BwdTile<HD>::BYTES + 512);
+    constexpr size_t lds = DkdvLds<HD, KW, QW>::BYTES;
+    static_assert(lds <= 160 * 1024, "LDS");
     static_assert((size_t)KW * 32 * (HD + 8) * sizeof(bf16_t) <= lds, "room for the results on their way out");
-    static_assert(QW == 1 || (size_t)KW * (HD / 32) * 16 * 64 * sizeof(float) <= lds, "room for the other half's sums");
+    static_assert(QW == 1 || (size_t)(QW == 2 ? 1 : QW) * KW * (HD / 32) * 16 * 64 * sizeof(float) <= lds, "room for the other sets' sums");
     static std::atomic<bool> done{false};
     const hipError_t e = ensure_lds(&flash_bwd_dkdv_kernel<HD, KW, QW, FAR>, lds, &done);
     if (e != hipSuccess) return e;
@@ -1419,10 +1568,19 @@ static hipError_t launch_dkdv_chain(const AttnArgs &a, hipStream_t s) {
 // Up to 128 keys and without groups of query heads, a walk of two tiles, the halves' merge costs more than it saves: 264 heads, 128
 // tokens, head_dim 128 50 / 53 / 54.
 static int choose_dkdv(const AttnArgs &a) {
-    static const AttnCost hd64[] = {{256, 2.0, 2.05, 14.0, 2.3, 1.0}, {128, 4.0, 1.22, 10.0, 1.27, 1.0}};
-    static const AttnCost hd128[] = {{256, 6.0, 3.32, 12.59, 3.68, 1.0}, {128, 9.0, 2.05, 8.33, 1.98, 1.0}, {64, 9.0, 1.57, 7.0, 1.69, 1.0}};
+    static const AttnCost hd64[] = {{256, 64, 2.0, 2.05, 14.0, 2.3, 1.0}, {128, 64, 4.0, 1.22, 10.0, 1.27, 1.0}};
+    static const AttnCost hd128[] = {{256, 64, 6.0, 3.32, 12.59, 3.68, 1.0}, {128, 64, 9.0, 2.05, 8.33, 1.98, 1.0}, {64, 64, 9.0, 1.57, 7.0, 1.69, 1.0}};
     if (a.T <= 128 && a.Hq == a.Hkv) return 0;
     return a.hd == 64 ? cheapest(a, hd64, true) : cheapest(a, hd128, true);
+}
+
+// 0, 1, 2: as above (blocks of 256, 128, 64 keys); 3: of 64, queries split over four sets of waves; 4: of 32, over eight (head_dim 128: four)
+static int dkdv_kernel(const AttnArgs &a) {
+    static const AttnCost hd64[] = {{256, 64, 4.18, 1.75, 8.54, 1.09, 1.76}, {128, 64, 5.97, 1.03, 6.32, 1.21, 0.56}, {},
+        {64, 128, 5.54, 1.15, 5.64, 1.32, 0.83}, {32, 256, 5.34, 1.35, 4.53, 1.57, 0.91}};
+    static const AttnCost hd128[] = {{256, 64, 6.52, 2.72, 2.41, 0.45, 2.44}, {128, 64, 9.01, 1.56, 10.89, 2.04, 0.74}, {64, 64, 8.38, 1.24, 9.33, 1.38, 1.09},
+        {64, 128, 8.78, 1.76, 8.92, 2.18, 0.86}, {32, 128, 6.25, 1.57, 6.34, 1.67, 0.95}};
+    return finer(a, a.hd == 64 ? hd64 : hd128, choose_dkdv(a), true);
 }
 
 hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
@@ -1435,7 +1593,7 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     if (!near_pitch(a.ldq) || !near_pitch(a.ldv) || !near_pitch(a.lddo))
         return a.hd == 128 ? launch_dkdv<128, 8, 1, true>(a, s) : launch_dkdv<64, 8, 1, true>(a, s);
-    switch (choose_dkdv(a)) {
+    switch (dkdv_kernel(a)) {
         case 0:
             // (lists of less than three blocks save less than they cost: 1 x 1536, 64 heads, 3 blocks 163 -> 165 us; 3.8 blocks 3 % faster,
             // 8 x 2048, 16 heads, 4 blocks 651 -> 547 together with dQ)
@@ -1445,7 +1603,10 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
             }
             return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
         case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);
-        default: return launch_dkdv<128, 2, 2>(a, s);
+        case 2: return launch_dkdv<128, 2, 2>(a, s);
+        case 3: return a.hd == 128 ? launch_dkdv<128, 2, 4>(a, s) : launch_dkdv<64, 2, 4>(a, s);
+        case 4: return a.hd == 128 ? launch_dkdv<128, 1, 4>(a, s) : launch_dkdv<64, 1, 8>(a, s);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -1454,6 +1615,16 @@ void flash_route(const AttnArgs &a, int *fwd, int *dq, int *dkdv) {
     *fwd = split_keys(a, true) ? 128 : 256;
     *dq = split_keys(a, false) ? 128 : 256;
     *dkdv = keys[choose_dkdv(a)];
+}
+
+void flash_sets(const AttnArgs &a, int *fwd, int *dq, int *dkdv) {
+    const int sets[] = {1, 2, 2, 4, a.hd == 64 ? 8 : 4}, rows[] = {256, 128, 64, 64, 32};
+    const int k[] = {query_kernel(a, true), query_kernel(a, false), dkdv_kernel(a)};
+    int *out[] = {fwd, dq, dkdv};
+    for (int i = 0; i < 3; ++i) {
+        out[i][0] = rows[k[i]];
+        out[i][1] = sets[k[i]];
+    }
 }
 
 }  // namespace mt

@@ -298,9 +298,11 @@ hipError_t attn_delta(float *delta, const bf16_t *dout, int64_t lddo, const bf16
                       int32_t H, int32_t hd, hipStream_t s);
 hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s);
 hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s);
-// The blocks that these three take: queries of the forward and of dQ (128: the keys split over two sets of waves; 256), keys of
-// dK/dV (256; 128 and 64: the queries split).  For tests and tools, no launch.
+// The blocks that these three take before small problems cut them further: queries of the forward and of dQ (128: the keys split over two sets
+// of waves; 256), keys of dK/dV (256; 128 and 64: the queries split).  For tests and tools, no launch.
 void flash_route(const AttnArgs &a, int *fwd, int *dq, int *dkdv);
+// The same with that cut: of each, rows of a block and sets of waves that share it.
+void flash_sets(const AttnArgs &a, int *fwd, int *dq, int *dkdv);
 
 hipError_t fill_u32(void *p, uint32_t value, size_t n_words, hipStream_t s);
 

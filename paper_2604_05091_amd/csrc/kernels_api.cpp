@@ -213,6 +213,14 @@ int32_t mt_k_flash_route(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t 
     return MT_OK;
 }
 
+int32_t mt_k_flash_sets(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *sets) {
+    if (B <= 0 || T <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || (hd != 64 && hd != 128) || !sets) return MT_ERR_INVALID_ARG;
+    AttnArgs a{};
+    a.B = B; a.T = T; a.Hq = Hq; a.Hkv = Hkv; a.hd = hd;
+    flash_sets(a, sets, sets + 2, sets + 4);
+    return MT_OK;
+}
+
 int32_t mt_k_flash_fwd(uint16_t *o, int64_t ldo, float *lse, const uint16_t *q, int64_t ldq, const uint16_t *k,
                        int64_t ldk, const uint16_t *v, int64_t ldv, int32_t B, int32_t T, int32_t Hq, int32_t Hkv,
                        int32_t hd, float scale, void *stream) {

@@ -880,6 +880,18 @@ def test_flash_attention_lists_of_blocks(orc64, B, T, Hq, Hkv, hd):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 264 else 0, dq_floor=2 * ROW_FLOOR)
 
 
+# Blocks cut further for small problems: four and eight sets of waves in the forward, dq, and dk and dv; a block's second wave past the end, tiles of
+# 128 and 256 rows with one row block of 8 rows, whole ones, groups of query heads, 8-byte aligned results.
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd,sets", [(1, 72, 2, 1, 64, (64, 4, 64, 4, 64, 4)), (1, 72, 2, 1, 128, (32, 4, 32, 4, 32, 4)), (5, 264, 2, 1, 64, (32, 8, 32, 8, 32, 8)),
+                               (1, 1032, 4, 1, 128, (32, 4, 32, 4, 32, 4)), (4, 392, 6, 3, 64, (64, 4, 64, 4, 32, 8)), (4, 392, 6, 3, 128, (64, 4, 32, 4, 32, 4)),
+                               (1, 800, 16, 16, 128, (64, 4, 64, 4, 64, 4)), (1, 2056, 2, 2, 64, (32, 8, 32, 8, 32, 8)), (1, 512, 2, 2, 64, (32, 8, 32, 8, 32, 8))])
+def test_flash_attention_blocks_cut_further(orc64, B, T, Hq, Hkv, hd, sets):
+    r = (ctypes.c_int32 * 6)()
+    ok(L.mt_k_flash_sets(B, T, Hq, Hkv, hd, ctypes.addressof(r)))
+    assert tuple(r) == sets
+    _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 392 else 0, dq_floor=2 * ROW_FLOOR)
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 72, 2, 1, 64), (1, 136, 2, 1, 128), (64, 136, 8, 8, 128)])
 def test_flash_attention_rows_in_reverse_order(B, T, Hq, Hkv, hd):
     """Rows may lie anywhere a 64-bit pitch reaches: stored last row first (negative pitches) they give the same results.  (Up to the
