@@ -198,7 +198,7 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
 // has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced; every
 // output is the sum of at least partial_sums partial sums.
-enum class RingTile { none, t256x128, t128x128, t128x64, t64x64 };
+enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, s128x64, s64x64, s32x64, s32x32 };   // s...: reductions shared among waves, NT only, first < 0
 // first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
 hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
 hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s);
@@ -221,6 +221,7 @@ int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu);
 // out).  nt: the first `whole` tiles of 256 x 256 go to that kernel, the others to tiles of tile_m x tile_n (0: there are none).
 // tn: tiles of tile_m x tile_n, `whole` of which a workgroup walks alone in the 256 x 256 kernel.
 void gemm_nt_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
+int gemm_nt_sharers(const GemmArgs &g);   // waves that share the reduction of such a tile
 void gemm_tn_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
 
 // out[b][c][r] = in[b][r][c] for r < rows, c < cols (bf16); leading dimensions in elements.

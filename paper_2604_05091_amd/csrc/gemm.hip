@@ -944,6 +944,32 @@ bool gemm_nt_fuses_glu_bwd(const GemmArgs &g) {
            !((uintptr_t)g.glu_bwd_gu & 15);
 }
 
+// Small grids with a long reduction: the waves of a workgroup share it (share_nt_kernel).  Measured, like the kernels it is compared with, on 600 shapes
+// (128 .. 8192 rows and columns, K 512 .. 20 000, up to 900 tiles of 64 x 64) with operands that come from memory; the estimates of the table above, of
+// operands in the caches, are 1.4 times too low there (two workgroups of 128 x 64 tiles on a compute unit: 1.7).  Taken from less of that on, 1.3 and 1.6 times
+// the other estimate, the choice is within 0.4 % of the best on average and nowhere more than 5 % behind the other kernels (240 x 3232 x 832), 1.34 times
+// faster than they over all shapes and up to 2.7 times.  At least a stage for every wave, 128 x 64 tiles with four waves eight: 4040 x 304 x 1152, 18
+// stages, 11.0 -> 12.9 us, but 4472 x 336 x 3520 28.9 -> 26.5.
+struct ShareCost { TileCost cost; int stages; double from_memory; };
+static const ShareCost kShareCosts[] = {{{RingTile::s32x32, 32, 32, 1, 0.122, 0.122, 2.7, 0.0}, 8, 1.3},
+                                        {{RingTile::s32x64, 32, 64, 1, 0.176, 0.184, 3.07, 0.0}, 8, 1.3},
+                                        {{RingTile::s64x64, 64, 64, 1, 0.242, 0.268, 3.5, 0.0}, 8, 1.3},
+                                        {{RingTile::s128x64, 128, 64, 1, 0.371, 0.419, 4.89, 0.0}, 32, 1.6}};
+constexpr int kShareTiles = 600;
+static const TileCost *share_tile(const GemmArgs &g, const TileCost &other) {
+    const double stages = (double)((g.K + BK - 1) / BK), other_t = tn_time(other, g.M, g.N, stages, 1, kComputeUnits);
+    double best = 1.0;
+    const TileCost *tile = nullptr;
+    for (const ShareCost &c : kShareCosts) {
+        const double tiles = tile_count(c.cost, g.M, g.N), t = tile_time(c.cost, tiles, stages, kComputeUnits) / (c.from_memory * other_t);
+        if (g.K / BK >= c.stages && tiles <= kShareTiles && t < best) {
+            tile = &c.cost;
+            best = t;
+        }
+    }
+    return tile;
+}
+
 // What takes an NT product without a fused store: the first `whole` tiles of 256 x 256 in the tile order the kernel above, the others
 // that of `tile` (null: there are none).
 struct NtRoute { int whole; const TileCost *tile; };
@@ -952,6 +978,7 @@ static NtRoute nt_route(const GemmArgs &g) {
     std::copy(std::begin(kNtCosts), std::end(kNtCosts), costs);
     costs[0].fixed += guarded_store(g);
     const TileCost &one = choose_tile(costs, g.M, g.N, g.K, 1);
+    if (const TileCost *share = share_tile(g, one)) return {0, share};
     // Or the full rounds of 256 x 256 tiles, and what is left in smaller ones that fill the chip (a launch of its own: 3 us).
     // 4096 x 5120 x 5120 (1.25 rounds) 204 -> 179 us; x 7168 253 -> 212; 3000 x 5632 x 1024 (1.03)
     // 50 -> 37; 12000 x 3072 x 3072 (2.2) 186 -> 162; 4096 x 7168 x 5120 (1.75) keeps its 208.
@@ -1008,6 +1035,11 @@ void gemm_nt_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n) {
     *whole = r.whole;
     *tile_m = r.tile ? r.tile->bm : 0;
     *tile_n = r.tile ? r.tile->bn : 0;
+}
+int gemm_nt_sharers(const GemmArgs &g) {
+    const NtRoute r = nt_route(g);
+    const RingTile t = r.tile ? r.tile->tile : RingTile::none;
+    return t == RingTile::s32x32 || t == RingTile::s32x64 ? 8 : t == RingTile::s64x64 || t == RingTile::s128x64 ? 4 : 1;
 }
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {

@@ -1,6 +1,7 @@
 // bf16 GEMM on the gfx950 matrix cores for grids that do not fill the chip with 256 x 256 tiles.
 //
 //   ring_nt_kernel   C[M,N] = A[M,K] . B[N,K]^T (+ bias) (+ R)     both operands with the reduction index contiguous
+//   share_nt_kernel  the same, the reduction of a tile shared among the waves of a workgroup
 //   ring_tn_kernel   C[M,N] = sum_k At[k][m] Bt[k][n]              both operands token-major (weight gradients)
 //
 // With one workgroup of four waves on a compute unit nothing but the kernel itself hides the latency of a load (1-2 us
@@ -56,25 +57,23 @@ __device__ __forceinline__ void ring_tile(int pid, int tiles_m, int tiles_n, int
     *tn = (pid % group) / gsz;
 }
 
-// The tile leaves through LDS as fp32 (the ring is free after the last stage), so that a store instruction covers whole
-// lines and bias, residual and accumulation read them the same way.  A lane owns row l16 of a 16 x 16 block and its columns
-// 4 hq .. + 3 (the MFMAs are issued with the operands swapped).  Row pitch BN + 4: the 16-byte writes of consecutive rows
-// fall on disjoint banks.
-template <int BM, int BN, int TM, int TN, bool F32>
-__device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)[TM][TN], int m0, int n0, int wm, int wn, float *st) {
+// An fp32 tile in LDS (row pitch BN + 4; NSUM of them are added up, each BM rows after the one before) -> C, by NT threads: a store instruction
+// covers whole lines, and bias, residual and accumulation read them the same way.
+template <int BM, int BN, int NT, int NSUM, bool F32>
+__device__ __forceinline__ void store_tile(const GemmArgs &g, const float *st, int m0, int n0) {
     constexpr int P = BN + 4;
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, hq = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-            *reinterpret_cast<f32x4 *>(st + (wm * TM * 16 + i * 16 + l16) * P + wn * TN * 16 + j * 16 + hq * 4) = acc[i][j];
-    __syncthreads();
+    const int tid = threadIdx.x;
     constexpr int CPL = F32 ? 4 : 8;                  // columns per lane
-    constexpr int LPR = BN / CPL, RPI = 256 / LPR;    // lanes per row, rows per pass
+    constexpr int LPR = BN / CPL, RPI = std::min(BM, NT / LPR);    // lanes per row, rows per pass
     const int r0 = tid / LPR, col = n0 + (tid % LPR) * CPL;
-    if (col >= g.N) return;
+    if (r0 >= RPI || col >= g.N) return;
     const float *sp = st + r0 * P + (tid % LPR) * CPL;
+    const auto sum = [](const float *p) {
+        f32x4 v = *reinterpret_cast<const f32x4 *>(p);
+#pragma unroll
+        for (int k = 1; k < NSUM; ++k) v += *reinterpret_cast<const f32x4 *>(p + k * BM * P);
+        return v;
+    };
     // Passes in groups of U: their LDS reads, and the reads of what is added, are in flight together (a pass that ends at the last row
     // by a branch would wait for its own read); rows past the end re-read the last one and are not stored.
     constexpr int N_PASS = BM / RPI, U = N_PASS < 4 ? N_PASS : 4;
@@ -86,7 +85,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
             if (m0 + it * RPI >= g.M) break;   // the same for the whole workgroup
             f32x4 v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P);
+            for (int u = 0; u < U; ++u) v[u] = sum(sp + (it + u) * RPI * P);
             if (vec) {
                 if (g.accumulate) {
                     f32x4 c[U];
@@ -122,7 +121,7 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
             float v[U][8];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const f32x4 lo = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P), hi = *reinterpret_cast<const f32x4 *>(sp + (it + u) * RPI * P + 4);
+                const f32x4 lo = sum(sp + (it + u) * RPI * P), hi = sum(sp + (it + u) * RPI * P + 4);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[u][e] = lo[e] + bias[e];
@@ -149,6 +148,22 @@ __device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)
                 if (m0 + r0 + (it + u) * RPI < g.M) row_store8(cp + (int64_t)(m0 + r0 + (it + u) * RPI) * g.ldc, v[u], access, col, g.N);
         }
     }
+}
+
+// The tile leaves through LDS as fp32 (the ring is free after the last stage).  A lane owns row l16 of a 16 x 16 block and its columns
+// 4 hq .. + 3 (the MFMAs are issued with the operands swapped).  Row pitch BN + 4: the 16-byte writes of consecutive rows
+// fall on disjoint banks.
+template <int BM, int BN, int TM, int TN, bool F32>
+__device__ __forceinline__ void ring_store(const GemmArgs &g, const f32x4 (&acc)[TM][TN], int m0, int n0, int wm, int wn, float *st) {
+    constexpr int P = BN + 4;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, hq = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            *reinterpret_cast<f32x4 *>(st + (wm * TM * 16 + i * 16 + l16) * P + wn * TN * 16 + j * 16 + hq * 4) = acc[i][j];
+    __syncthreads();
+    store_tile<BM, BN, 256, 1, F32>(g, st, m0, n0);
 }
 
 // The walk over the stages, shared by the two kernels.  LOAD(J, T, SLOT) requests load J of stage T, READ(SET, KS, F, SLOT)
@@ -449,6 +464,123 @@ __global__ __launch_bounds__(256) void ring_tn_kernel(GemmArgs g, int tiles_m, i
     ring_store<BM, BN, TM, TN, true>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
 }
 
+// Few tiles and a long reduction: the ring above walks it stage after stage (0.26 us each with 64 x 64 tiles) while most of the chip idles, and every
+// stage waits for the slowest of four waves.  Here the NW waves of a workgroup share the reduction of a tile: wave w multiplies the stages w, w + NW, ...
+// out of a ring of S stages of its own, which it fills and waits for without its neighbours; the sums are added in LDS, in order.  Together the rings
+// hold what LDS does: 128 KB in flight, 96 for 32 x 64 and 128 x 64 (whose accumulators leave room for four waves).  What bounds it is the path of a
+// compute unit for loads, (BM + BN) * 128 / 57 clocks a stage, and with most of the chip at work what an XCD can fetch beyond its L2.
+// us, operands from memory, before -> now: 200 x 128 x 10880 40 -> 17 (32 x 32 tiles, eight waves), 400 x 1088 x 17216 94 -> 47 (32 x 64, eight),
+// 1248 x 648 x 7040 41 -> 28 (64 x 64, four), 1992 x 864 x 17232 161 -> 134 (128 x 64, four).
+// A partial last stage (K % 64) belongs to the wave whose turn it is, first; it goes through registers, chunks at or beyond K as zeros.
+template <int TM, int TN, int NW, int S>
+struct ShareLds {
+    static constexpr uint32_t STAGE = 16 * (TM + TN) * 128, SUM = 16 * TM * (16 * TN + 4) * sizeof(float), BYTES = NW * std::max(S * STAGE, SUM);
+};
+template <int TM, int TN, int NW, int S, bool F32>
+__global__ __launch_bounds__(64 * NW) void share_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
+    constexpr int BM = 16 * TM, BN = 16 * TN, P = BN + 4, LA = BM / 8, LPS = (BM + BN) / 8;
+    constexpr uint32_t STAGE = ShareLds<TM, TN, NW, S>::STAGE;
+    int tm, tn;
+    ring_tile(ring_renumber(tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, hq = lane >> 4;
+    const bf16_t *abase = g.A + (int64_t)m0 * g.lda, *bbase = g.B + (int64_t)n0 * g.ldb;
+    // a load covers 8 rows of 128 bytes, in the layout of the ring above; rows past the edge re-read the last one
+    uint32_t off[LPS];
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) {
+        const int r = (j < LA ? j : j - LA) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+        off[j] = (uint32_t)((j < LA ? min(r, g.M - 1 - m0) * (int)g.lda : min(r, g.N - 1 - n0) * (int)g.ldb) + chunk * 8) * 2u;
+    }
+    char *const mine = ring + wave * (S * STAGE);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(ring_lptr)ring + wave * (S * STAGE);
+    uint32_t rd[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(l16 * 128 + (((4 * ks + hq) ^ ((l16 >> 1) & 7)) << 4));
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const auto request = [&](int i, int slot) {   // this wave's i-th stage
+        const int kn = (wave + i * NW) * RK;
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) ring_load((j < LA ? abase : bbase) + kn, off[j], lds0 + slot * STAGE + j * 1024u);
+    };
+    bf16x8 fr[2][TM + TN];
+    const auto read = [&](int slot) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int f = 0; f < TM + TN; ++f) fr[ks][f] = *reinterpret_cast<const bf16x8 *>(mine + slot * STAGE + rd[ks] + f * 2048);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the slot is free)
+    };
+    const auto multiply = [&]() {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int jj = i & 1 ? TN - 1 - j : j;
+                    mfma16_acc(acc[i][jj], fr[ks][TM + jj], fr[ks][i]);
+                }
+    };
+    const int whole = g.K / RK, n = (whole - wave + NW - 1) / NW;
+    if (g.K % RK && wave == whole % NW) {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) {
+            const int r = (j < LA ? j : j - LA) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+            const bool ok = whole * RK + chunk * 8 < g.K;   // otherwise column 0 of the row is read (in bounds) and replaced
+            ru32x4 v = *reinterpret_cast<const ru32x4 *>(reinterpret_cast<const char *>(j < LA ? abase : bbase) + off[j] + (ok ? whole * (RK * 2) : -chunk * 16));
+            if (!ok) v = ru32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<ru32x4 *>(mine + j * 1024 + lane * 16) = v;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        read(0);
+        multiply();
+        mfma16_drain();
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (s < n) request(s, s);
+    int slot = 0;
+    for (int i = 0; i < n; ++i) {
+        if (i + S <= n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"((S - 1) * LPS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        read(slot);
+        if (i + S < n) request(i + S, slot);
+        multiply();
+        slot = slot + 1 == S ? 0 : slot + 1;
+    }
+    mfma16_settle(acc);
+    __syncthreads();
+    float *sum = reinterpret_cast<float *>(ring) + wave * (BM * P) + l16 * P + hq * 4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4 *>(sum + i * 16 * P + j * 16) = acc[i][j];
+    __syncthreads();
+    store_tile<BM, BN, 64 * NW, NW, F32>(g, reinterpret_cast<float *>(ring), m0, n0);
+}
+template <int TM, int TN, int NW, int S, bool F32>
+hipError_t launch_share_one(const GemmArgs &g, hipStream_t s) {
+    static std::atomic<bool> attr{false};
+    constexpr size_t lds = ShareLds<TM, TN, NW, S>::BYTES;
+    static_assert(lds <= 160 * 1024, "LDS");
+    const hipError_t e = ensure_lds(share_nt_kernel<TM, TN, NW, S, F32>, lds, &attr);
+    if (e != hipSuccess) return e;
+    const int tiles_m = (g.M + 16 * TM - 1) / (16 * TM), tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
+    hipLaunchKernelGGL((share_nt_kernel<TM, TN, NW, S, F32>), dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), lds, s, g, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+template <int TM, int TN, int NW, int S>
+hipError_t launch_share(const GemmArgs &g, hipStream_t s) {
+    return g.out_fp32 ? launch_share_one<TM, TN, NW, S, true>(g, s) : launch_share_one<TM, TN, NW, S, false>(g, s);
+}
+
 template <int BM, int BN, int S, bool F32, bool TAIL>
 hipError_t launch_nt_one(const GemmArgs &g, int first, hipStream_t s) {
     static std::atomic<bool> attr{false};
@@ -494,6 +626,10 @@ hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t
         case RingTile::t128x128: return launch_nt<128, 128, 3>(g, first, s);
         case RingTile::t128x64: return launch_nt<128, 64, 3>(g, first, s);
         case RingTile::t64x64: return launch_nt<64, 64, 3>(g, first, s);
+        case RingTile::s128x64: return launch_share<8, 4, 4, 1>(g, s);
+        case RingTile::s64x64: return launch_share<4, 4, 4, 2>(g, s);
+        case RingTile::s32x64: return launch_share<2, 4, 8, 1>(g, s);
+        case RingTile::s32x32: return launch_share<2, 2, 8, 2>(g, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -116,6 +116,14 @@ int32_t mt_k_gemm_route(int32_t form, int32_t M, int32_t N, int32_t K, int64_t l
     return MT_OK;
 }
 
+int32_t mt_k_gemm_sharers(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc) {
+    if (form < 0 || form > 1 || M <= 0 || N <= 0 || K <= 0 || ldc < N) return MT_ERR_INVALID_ARG;
+    GemmArgs g;
+    g.A = g.B = g.R = nullptr; g.C = nullptr; g.lda = g.ldb = K; g.ldc = ldc; g.ldr = 0;
+    g.M = M; g.N = N; g.K = K; g.out_fp32 = form > 0; g.accumulate = 0;
+    return gemm_nt_sharers(g);
+}
+
 size_t mt_k_bias_grad_ws_bytes(int32_t cols) { return bias_grad_ws_floats(cols) * sizeof(float); }
 int32_t mt_k_bias_grad(float *db, const uint16_t *x, int64_t ld, int64_t n, int32_t cols, void *ws, void *stream) {
     if (!db || !x || !ws || !al16(x)) return MT_ERR_INVALID_ARG;

@@ -191,6 +191,38 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
     assert np.all(host(F)[:, N:] == 3)
 
 
+# Reductions shared among the waves of a workgroup: each tile, one whole stage a wave and several, uneven numbers of them, a partial last stage
+# that belongs to the first wave and to others, ragged and whole edges, columns and pitches that are whole 16-byte chunks and that are not.
+@pytest.mark.parametrize("M,N,K,pad,tile,sharers", [(8, 8, 512, 0, (32, 32), 8), (65, 63, 520, 1, (32, 32), 8), (333, 72, 584, 4, (32, 32), 8), (136, 320, 17464, 8, (32, 32), 8),
+                                                    (264, 1072, 1000, 8, (32, 64), 8), (400, 1088, 1160, 0, (32, 64), 8), (391, 1083, 1088, 2, (32, 64), 8),
+                                                    (1248, 648, 712, 0, T64, 4), (560, 1000, 4104, 4, T64, 4), (559, 997, 4096, 3, T64, 4),
+                                                    (1410, 945, 2056, 3, T128X64, 4), (1000, 2048, 5504, 8, T128X64, 4), (2050, 700, 2304, 4, T128X64, 4)])
+def test_gemm_reduction_shared_among_waves(M, N, K, pad, tile, sharers):
+    lda, ldb, ldc, ldr = K + 8, K + 16, N + pad, N + 3 * pad
+    for form in (NT_BF16, NT_F32):
+        assert gemm_route(form, M, N, K, ldc) == (0, tile) and L.mt_k_gemm_sharers(form, M, N, K, ldc) == sharers
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B, R, BI = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, lda), (N, ldb), (M, ldr), (1, N)))
+    ref = A[:, :K].double() @ B[:, :K].double().T.contiguous()
+    ops = (A.data_ptr(), lda, B.data_ptr(), ldb)
+    C = torch.zeros((M, ldc), dtype=torch.bfloat16, device="cuda")
+    for what, add in (("plain", 0), ("residual", R[:, :N].double()), ("bias", BI.double())):
+        if what == "bias":
+            ok(L.mt_k_gemm_nt_bias(*ops, C.data_ptr(), ldc, BI.data_ptr(), M, N, K, None))
+        else:
+            ok(L.mt_k_gemm_nt(*ops, C.data_ptr(), ldc, R.data_ptr() if what == "residual" else None, ldr, M, N, K, 0, 0, None))
+        want = ref + add
+        # one rounding to bf16 (2^-9 of the value) after fp32 sums
+        assert bool(((C[:, :N].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * K ** 0.5).all()), what
+        assert bool((C[:, N:] == 0).all()), what
+    F = torch.full((M, ldc), 3.0, dtype=torch.float32, device="cuda")
+    for acc in (0, 1):
+        ok(L.mt_k_gemm_nt(*ops, F.data_ptr(), ldc, None, 0, M, N, K, 1, acc, None))
+        # each of K additions rounds to 2^-24 of a partial sum of at most about 10 sqrt(K)
+        assert float((F[:, :N].double() - (1 + acc) * ref).abs().max()) <= K * 2.0 ** -24 * 10 * K ** 0.5
+    assert bool((F[:, N:] == 3).all())
+
+
 @pytest.mark.parametrize("M,N,K,whole,tile", [(4096, 5120, 128, 0, T128X64), (4360, 4352, 64, 0, T64), (4100, 4616, 192, 0, T128X64),
                                               (3000, 5632, 320, 256, T64), (3334, 5632, 256, 256, T128X64), (3340, 5632, 512, 256, T128),
                                               (3377, 5888, 1024, 256, T256X128),
