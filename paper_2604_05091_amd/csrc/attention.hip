@@ -728,6 +728,24 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 // Same ownership as the forward: a lane owns one query, loops over key tiles <= q.
 // KW = 2 splits the tiles' keys over two sets of waves as in the forward; their sums are added at the end.
 
+// dQ is the first kernel of the backward: it has the output gradients of its queries at hand, so it also works out delta = rowsum(dO * O),
+// which is stored for dK/dV (a pass of its own read dO once more.  us, forward and backward, with -> without it: 3 x 520, 8 heads of 64 on 2 40.6 -> 38.6;
+// 4 x 4096, 32 heads 2518 -> 2502; 1 x 32768, 40 heads on 8 43 830 -> 43 740).
+__device__ __forceinline__ float dot8(const bf16x8 &x, const bf16x8 &y) {
+    const u32x4 a = __builtin_bit_cast(u32x4, x), b = __builtin_bit_cast(u32x4, y);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s += bflo(a[i]) * bflo(b[i]) + bfhi(a[i]) * bfhi(b[i]);
+    return s;
+}
+template <int HD>
+__device__ __forceinline__ float row_delta(const bf16x8 (&dof)[HD / 16], const bf16x8 (&of)[HD / 16]) {
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < HD / 16; ++ks) s[ks & 1] += dot8(dof[ks], of[ks]);
+    return half_sum(s[0] + s[1]);
+}
+
 // the keys 32 rb .. + 31 (rb0 <= rb < rb0 + NR) of the tile that starts at key kv0
 template <int HD, int NR>
 __device__ __forceinline__ void dq_tile(f32x16 (&dqacc)[HD / 32], const bf16x8 (&qf)[HD / 16], const bf16x8 (&dof)[HD / 16], uint32_t Ks, uint32_t Vs,
@@ -845,7 +863,18 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
         }
     }
     const int64_t stat = ((int64_t)b * a.Hq + h) * T + qm;
-    const float lse2 = a.lse[stat] * kLog2e, dlt = a.delta[stat];
+    const float lse2 = a.lse[stat] * kLog2e;
+    float dlt;
+    if (a.o) {
+        bf16x8 of[HD / 16];
+        const bf16_t *op = a.o + ((int64_t)b * T + qm) * a.ldo + (int64_t)h * HD + hl * 8;
+#pragma unroll
+        for (int ks = 0; ks < HD / 16; ++ks) of[ks] = load_frag_global(op + ks * 16);
+        dlt = row_delta<HD>(dof, of);
+        if (qok && kw == 0 && hl == 0) a.delta[stat] = dlt;
+    } else {
+        dlt = a.delta[stat];
+    }
     const float c = a.scale * kLog2e;
     f32x16 dqacc[HD / 32];
 #pragma unroll
@@ -912,8 +941,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
     tk.init(smem, a.ldk, lane, wave);
     tv.init(smem, a.ldv, lane, wave);
 
-    bf16x8 qf[HD / 16], dof[HD / 16];
-    float lse, dlt;
+    bf16x8 qf[HD / 16], dof[HD / 16], of[HD / 16];
+    float lse;
     const auto request_tile = [&](const Block &blk, int kt, uint32_t stage) {
         tk.load(stage, a.k + (int64_t)blk.b * T * a.ldk + (int64_t)blk.hk * HD, a.ldk, kt * 64, T);
         tv.load(stage + TILE, a.v + (int64_t)blk.b * T * a.ldv + (int64_t)blk.hk * HD, a.ldv, kt * 64, T);
@@ -927,24 +956,38 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
             qf[ks] = load_frag_global(qp + ks * 16);
             dof[ks] = load_frag_global(dp + ks * 16);
         }
-        const int64_t stat = ((int64_t)blk.b * a.Hq + blk.h) * T + qm;
-        lse = a.lse[stat];
-        dlt = a.delta[stat];
+        lse = a.lse[((int64_t)blk.b * a.Hq + blk.h) * T + qm];
+    };
+    const auto request_outputs = [&](const Block &blk) {   // (without a condition: what may keep its value here would hold its registers through the whole block)
+        const int qm = min(blk.qb * BQ + wave * 32 + l32, T - 1);
+        const bf16_t *op = (a.o ? a.o : a.dout) + ((int64_t)blk.b * T + qm) * (a.o ? a.ldo : a.lddo) + (int64_t)blk.h * HD + hl * 8;
+#pragma unroll
+        for (int ks = 0; ks < HD / 16; ++ks) of[ks] = load_frag_global(op + ks * 16);
     };
     BlockList list;
     Block cur, nxt;
     if (!list.next(map, &cur)) return;
     request_tile(cur, 0, 0);
     request_queries(cur);
+    request_outputs(cur);
     tile_barrier();
     while (true) {
-        asm volatile("" : "+v"(lse), "+v"(dlt));
+        asm volatile("" : "+v"(lse));
         wave_barrier(qf);
         wave_barrier(dof);
+        wave_barrier(of);
         const bool more = list.next(map, &nxt);
         const int q0 = cur.qb * BQ + wave * 32, q = q0 + l32, qm = min(q, T - 1);
         const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = min(ntiles, (q0 + 31) / 64 + 1) - 1;
-        const float lse2 = lse * kLog2e, delta = dlt;
+        const int64_t stat = ((int64_t)cur.b * a.Hq + cur.h) * T + qm;
+        const float lse2 = lse * kLog2e;
+        float delta;
+        if (a.o) {
+            delta = row_delta<HD>(dof, of);
+            if (q < T && hl == 0) a.delta[stat] = delta;
+        } else {
+            delta = a.delta[stat];
+        }
         f32x16 dqacc[HD / 32];
 #pragma unroll
         for (int hb = 0; hb < HD / 32; ++hb) dqacc[hb] = zero16();
@@ -969,6 +1012,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
             write_rows_by_parts<HD, 64>(a.dq + ((int64_t)cur.b * T + q0) * a.lddq + (int64_t)cur.h * HD, a.lddq, dqacc, rope ? 1.0f : a.scale, l32, hl,
                                         min(32, T - q0), reinterpret_cast<char *>(smem) + O_OFF + wave * 4096);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        request_outputs(more ? nxt : cur);   // (in the place of the results)
         for (; kt < ntiles; kt += 2) {
             request_after(kt, 0);
             tile_barrier();
@@ -1517,7 +1562,7 @@ hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
     return a.hd == 128 ? launch_fwd<128, 8, 1>(a, s) : launch_fwd<64, 8, 1>(a, s);
 }
 
-hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
+static hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
     if (!rope_tables_ok(a)) return hipErrorInvalidValue;
     if (!attn_shape_ok(a) || (a.ldq & 7) || (a.ldk & 7) || (a.ldv & 7) || (a.lddo & 7) || (a.lddq & 3))
         return hipErrorInvalidValue;
@@ -1583,7 +1628,7 @@ static int dkdv_kernel(const AttnArgs &a) {
     return finer(a, a.hd == 64 ? hd64 : hd128, choose_dkdv(a), true);
 }
 
-hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
+static hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     if (!rope_tables_ok(a)) return hipErrorInvalidValue;
     if (!attn_shape_ok(a) || (a.ldq & 7) || (a.ldk & 7) || (a.ldv & 7) || (a.lddo & 7) || (a.lddk & 3) ||
         (a.lddv & 3))
@@ -1608,6 +1653,28 @@ hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
         case 4: return a.hd == 128 ? launch_dkdv<128, 1, 4>(a, s) : launch_dkdv<64, 1, 8>(a, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+// the rows of two [B T, H hd] arrays may share memory
+static bool overlap(const AttnArgs &a, const bf16_t *x, int64_t ldx, const bf16_t *y, int64_t ldy) {
+    const int64_t last = (int64_t)a.B * a.T - 1, cols = (int64_t)a.Hq * a.hd;
+    const bf16_t *x0 = x + std::min<int64_t>(0, last * ldx), *x1 = x + std::max<int64_t>(0, last * ldx) + cols;
+    const bf16_t *y0 = y + std::min<int64_t>(0, last * ldy), *y1 = y + std::max<int64_t>(0, last * ldy) + cols;
+    return x0 < y1 && y0 < x1;
+}
+hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
+    if (!aligned16(a.o) || (a.ldo & 7)) return hipErrorInvalidValue;
+    hipError_t e;
+    if (overlap(a, a.dq, a.lddq, a.q, a.ldq) || overlap(a, a.dq, a.lddq, a.dout, a.lddo) || overlap(a, a.dq, a.lddq, a.o, a.ldo)) {
+        // dq takes the place of something that dK/dV reads: it comes last
+        e = attn_delta(a.delta, a.dout, a.lddo, a.o, a.ldo, a.B, a.T, a.Hq, a.hd, s);
+        if (e == hipSuccess) e = flash_bwd_dkdv(a, s);
+        AttnArgs with_delta = a;
+        with_delta.o = nullptr;
+        return e == hipSuccess ? flash_bwd_dq(with_delta, s) : e;
+    }
+    e = flash_bwd_dq(a, s);
+    return e == hipSuccess ? flash_bwd_dkdv(a, s) : e;
 }
 
 void flash_route(const AttnArgs &a, int *fwd, int *dq, int *dkdv) {

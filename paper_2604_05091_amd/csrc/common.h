@@ -285,7 +285,7 @@ struct AttnArgs {
     float *lse;
     // backward only
     const bf16_t *dout; int64_t lddo;
-    const float *delta;  // [B,Hq,T] rowsum(do * o)
+    float *delta;  // [B,Hq,T] rowsum(do * o), written
     bf16_t *dq; int64_t lddq;
     bf16_t *dk; int64_t lddk;
     bf16_t *dv; int64_t lddv;
@@ -297,8 +297,7 @@ hipError_t flash_fwd(const AttnArgs &a, hipStream_t s);
 // delta[b,h,t] = sum_j do[b,t,h,j] * o[b,t,h,j]
 hipError_t attn_delta(float *delta, const bf16_t *dout, int64_t lddo, const bf16_t *o, int64_t ldo, int32_t B, int32_t T,
                       int32_t H, int32_t hd, hipStream_t s);
-hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s);
-hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s);
+hipError_t flash_bwd(const AttnArgs &a, hipStream_t s);   // delta, dq, dk, dv
 // The blocks that these three take before small problems cut them further: queries of the forward and of dQ (128: the keys split over two sets
 // of waves; 256), keys of dK/dV (256; 128 and 64: the queries split).  For tests and tools, no launch.
 void flash_route(const AttnArgs &a, int *fwd, int *dq, int *dkdv);

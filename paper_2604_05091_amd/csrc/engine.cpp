@@ -510,13 +510,11 @@ mt_status layer_backward(mt_handle *h, const LayerW &w, float *G, const uint16_t
     AttnArgs a = attn_args(h, B, T);
     a.rope_cos = h->rope_cos;  // dq and dk leave the kernels already rotated back
     a.rope_sin = h->rope_sin;
-    KCHK(attn_delta(h->delta, h->datt, D.Nq, h->att, D.Nq, B, T, D.Hq, D.hd, s));
     {
         // 7 tile products (4 in the dK/dV kernel, 3 in the dQ kernel), causal half of T^2
         Timed t(h, CLS_ATTN_BWD, 7.0 * (double)B * D.Hq * D.hd * (double)T * ((double)T + 1.0),
                 2.0 * (double)B * T * (4.0 * D.Nq + 4.0 * D.Nkv));
-        KCHK(flash_bwd_dkdv(a, s));
-        KCHK(flash_bwd_dq(a, s));
+        KCHK(flash_bwd(a, s));
     }
     if (D.bias) KCHK(bias_grad(G + o.bqkv, h->dqkv, D.Nqkv, n, (int32_t)D.Nqkv, h->bias_ws, s));
     // qkv = xn Wqkv^T + b

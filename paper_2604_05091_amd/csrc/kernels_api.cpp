@@ -256,12 +256,7 @@ int32_t mt_k_flash_bwd_rope(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t ld
     a.dout = dout; a.lddo = lddo; a.delta = delta;
     a.dq = dq; a.lddq = lddq; a.dk = dk; a.lddk = lddk; a.dv = dv; a.lddv = lddv;
     a.rope_cos = cos_tab; a.rope_sin = sin_tab;
-    hipStream_t s = S(stream);
-    hipError_t e = attn_delta(delta, dout, lddo, o, ldo, B, T, Hq, hd, s);
-    if (e != hipSuccess) return to_status(e);
-    e = flash_bwd_dkdv(a, s);
-    if (e != hipSuccess) return to_status(e);
-    return to_status(flash_bwd_dq(a, s));
+    return to_status(flash_bwd(a, S(stream)));
 }
 
 int32_t mt_k_flash_bwd(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t lddk, uint16_t *dv, int64_t lddv,

@@ -924,6 +924,28 @@ def test_flash_attention_blocks_cut_further(orc64, B, T, Hq, Hkv, hd, sets):
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 392 else 0, dq_floor=2 * ROW_FLOOR)
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(2, 136, 4, 2, 64), (17, 328, 24, 8, 128)])
+@pytest.mark.parametrize("place", ["q", "dout", "o"])
+def test_flash_attention_dq_in_the_place_of_an_input(B, T, Hq, Hkv, hd, place):
+    """dq may overwrite q, the gradient of the output or the output.  (Its delta is then summed in another order: results differ by a few
+    roundings to bf16, 2^-8 of an element each, of less than one in sixteen.)"""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    nq, nkv, n, scale = Hq * hd, Hkv * hd, B * T, hd ** -0.5
+    q, k, v, dout = (torch.randn((n, c), device="cuda", generator=g).to(torch.bfloat16) for c in (nq, nkv, nkv, nq))
+    O, LSE, DELTA = torch.zeros_like(q), torch.zeros((B, Hq, T), device="cuda"), torch.zeros((B, Hq, T), device="cuda")
+    ok(L.mt_k_flash_fwd(O.data_ptr(), nq, LSE.data_ptr(), q.data_ptr(), nq, k.data_ptr(), nkv, v.data_ptr(), nkv, B, T, Hq, Hkv, hd, scale, None))
+    got = []
+    for inplace in (False, True):
+        x = {"q": q.clone(), "dout": dout.clone(), "o": O.clone()}
+        dq = x[place] if inplace else torch.zeros_like(q)
+        dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+        ok(L.mt_k_flash_bwd(dq.data_ptr(), nq, dk.data_ptr(), nkv, dv.data_ptr(), nkv, x["dout"].data_ptr(), nq, x["q"].data_ptr(), nq, k.data_ptr(), nkv,
+                            v.data_ptr(), nkv, x["o"].data_ptr(), nq, LSE.data_ptr(), DELTA.data_ptr(), B, T, Hq, Hkv, hd, scale, None))
+        got.append((host(dq), host(dk), host(dv)))
+    for a, b in zip(*got):
+        assert rel_l2(b, a) < 2.0 ** -10
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(1, 72, 2, 1, 64), (1, 136, 2, 1, 128), (64, 136, 8, 8, 128)])
 def test_flash_attention_rows_in_reverse_order(B, T, Hq, Hkv, hd):
     """Rows may lie anywhere a 64-bit pitch reaches: stored last row first (negative pitches) they give the same results.  (Up to the
