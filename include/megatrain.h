@@ -117,7 +117,8 @@ typedef struct {
     uint32_t tie_embeddings;   /* 1: the output projection reuses the embedding table (Appendix A.1, tied weights):
                                 * the tensor list ends with final_norm (no lm_head); the table is streamed again for
                                 * the loss, and its gradient is the head's weight gradient plus the embedding's
-                                * scatter-add, summed on the host */
+                                * scatter-add, summed on the device, or on the host where max_device_bytes or the
+                                * device memory leaves no room to keep the former until the end of the step */
     uint32_t mlp_chunk;        /* 0: the MLP of a block runs on all tokens at once.  m > 0 (multiple of 8): it runs in chunks of m
                                 * tokens (chunked MLP of the long-context runs, Section 4.6): gate/up/activation buffers are chunk-sized, nothing of
                                 * the MLP is saved, and the backward recomputes each chunk right before differentiating it

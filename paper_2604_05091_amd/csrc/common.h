@@ -259,9 +259,9 @@ hipError_t swiglu_fwd(bf16_t *sout, const bf16_t *gu, int64_t n, int32_t F, hipS
 hipError_t swiglu_bwd(bf16_t *dgu, const bf16_t *ds, const bf16_t *gu, int64_t n, int32_t F, hipStream_t s);
 
 hipError_t embed_gather(bf16_t *h, const bf16_t *table, const int32_t *tokens, int64_t n, int32_t d, hipStream_t s);
-// dtable[V,d] fp32 fully written: row v = sum of dh rows listed in order[start[v] .. start[v+1])
+// dtable[V,d] fp32: row v = sum of dh rows listed in order[start[v] .. start[v+1]), added to what it holds or (fully) written
 hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
-                         int32_t d, hipStream_t s);
+                         int32_t d, bool add, hipStream_t s);
 
 // Per row: loss_rows[r] = logsumexp(z_r) - z_r[label] (0 for ignored rows); dlogits bf16 = (softmax - onehot) * inv_n
 hipError_t cross_entropy(float *loss_rows, bf16_t *dlogits, const float *logits, const int32_t *labels, int64_t n,

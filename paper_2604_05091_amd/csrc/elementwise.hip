@@ -430,9 +430,17 @@ __device__ __forceinline__ void scatter_add(float *a, const uint4 &v) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) a[k] += f[k];
 }
+template <bool ADD>
 __device__ __forceinline__ void scatter_store(float *o, const float *acc) {
-    reinterpret_cast<float4 *>(o)[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    reinterpret_cast<float4 *>(o)[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    float4 *p = reinterpret_cast<float4 *>(o);
+    float4 a = make_float4(acc[0], acc[1], acc[2], acc[3]), b = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    if (ADD) {
+        const float4 x = p[0], y = p[1];
+        a = make_float4(x.x + a.x, x.y + a.y, x.z + a.z, x.w + a.w);
+        b = make_float4(y.x + b.x, y.y + b.y, y.z + b.z, y.w + b.w);
+    }
+    p[0] = a;
+    p[1] = b;
 }
 
 // NR terms r[0..NR) of the list, added to acc[j] (columns col + 512 j) in order
@@ -451,7 +459,8 @@ __device__ __forceinline__ void scatter_terms(float (*acc)[8], const bf16_t *dh,
         for (int j = 0; j < NC; ++j) scatter_add(acc[j], v[u][j]);
 }
 
-template <int NC>
+// ADD: on top of what the table's gradient holds already (rows without a token are then left alone)
+template <int NC, bool ADD>
 __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float *dtable, const bf16_t *dh,
                                                                            const int32_t *row_start, const int32_t *order,
                                                                            int V, int d) {
@@ -469,14 +478,14 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
         const int v = x + (share * kScatterWaves + wave) * gx;
         if (v < V) {
             const int beg = row_start[v], end = row_start[v + 1];
-            if (end - beg <= kScatterShort) {
+            if (end - beg <= kScatterShort && (!ADD || beg < end)) {
                 float acc[NC][8] = {};
                 int i = beg;
                 for (; i + 1 < end; i += 2) scatter_terms<NC, 2>(acc, dh, order + i, d, col);
                 if (i < end) scatter_terms<NC, 1>(acc, dh, order + i, d, col);
 #pragma unroll
                 for (int j = 0; j < NC; ++j)
-                    if (col + 512 * j < d) scatter_store(dtable + (int64_t)v * d + col + 512 * j, acc[j]);
+                    if (col + 512 * j < d) scatter_store<ADD>(dtable + (int64_t)v * d + col + 512 * j, acc[j]);
             }
         }
     }
@@ -516,7 +525,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
             for (int q = 0; q < kScatterWaves - 1; ++q)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) acc[0][k] += part[q][k][lane];
-            if (c < d) scatter_store(dtable + (int64_t)v * d + c, acc[0]);
+            if (c < d) scatter_store<ADD>(dtable + (int64_t)v * d + c, acc[0]);
         }
         __syncthreads();
     }
@@ -778,7 +787,7 @@ hipError_t embed_gather(bf16_t *h, const bf16_t *table, const int32_t *tokens, i
 }
 
 hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
-                         int32_t d, hipStream_t s) {
+                         int32_t d, bool add, hipStream_t s) {
     if (V <= 0 || d <= 0 || (d & 7)) return hipErrorInvalidValue;
     // wide shares for big tables; smaller ones where the blocks would be too few for the chip (NC = 1 / 2 / 4 / a block per row, us):
     // 4848 uniform tokens, V = 1096, d = 1280 5.4 / 5.4 / 6.3 / 5.6; 4096 tokens, V = 1024, d = 1024 4.5 / 5.4 / 6.0 / 5.1; 65 536, 2000, 5120
@@ -787,9 +796,9 @@ hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_sta
     const auto blocks = [&](int nc) { return (int64_t)((V + 7) / 8) * ((d + 512 * nc - 1) / (512 * nc)); };
     const int nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
     const dim3 grid(nc * blocks_for(V, kScatterWaves * nc), blocks_for(d, 512 * nc)), block(64 * kScatterWaves);
-    if (nc == 1) hipLaunchKernelGGL(embed_scatter_kernel<1>, grid, block, 0, s, dtable, dh, row_start, order, V, d);
-    else if (nc == 2) hipLaunchKernelGGL(embed_scatter_kernel<2>, grid, block, 0, s, dtable, dh, row_start, order, V, d);
-    else hipLaunchKernelGGL(embed_scatter_kernel<4>, grid, block, 0, s, dtable, dh, row_start, order, V, d);
+    auto kernel = nc == 1 ? embed_scatter_kernel<1, false> : nc == 2 ? embed_scatter_kernel<2, false> : embed_scatter_kernel<4, false>;
+    if (add) kernel = nc == 1 ? embed_scatter_kernel<1, true> : nc == 2 ? embed_scatter_kernel<2, true> : embed_scatter_kernel<4, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d);
     return hipGetLastError();
 }
 

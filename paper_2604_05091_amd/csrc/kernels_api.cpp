@@ -196,7 +196,7 @@ int32_t mt_k_embed_gather(uint16_t *h, const uint16_t *table, const int32_t *tok
 int32_t mt_k_embed_scatter(float *dtable, const uint16_t *dh, const int32_t *row_start, const int32_t *order,
                            int32_t V, int32_t d, void *stream) {
     if (!dtable || !dh || !row_start || !order || !al16(dtable) || !al16(dh)) return MT_ERR_INVALID_ARG;
-    return to_status(embed_scatter(dtable, dh, row_start, order, V, d, S(stream)));
+    return to_status(embed_scatter(dtable, dh, row_start, order, V, d, false, S(stream)));
 }
 
 int32_t mt_k_cross_entropy(float *loss_rows, uint16_t *dlogits, const float *logits, const int32_t *labels, int64_t n,

@@ -275,6 +275,25 @@ def test_tied_embeddings_match_oracle(orc64, K, flags):
                 assert np.array_equal(a, g + g)
 
 
+@pytest.mark.parametrize("adam", [False, True])
+def test_tied_table_gradient_without_room_for_the_heads_part(adam):
+    """The head's part of a tied table's gradient waits on the device for the embedding's, or, where a cap on the device memory leaves no
+    room for it, on the host: the same sums."""
+    shape = ModelShape(2, 128, 4, 2, 64, 264, 520, tie_embeddings=True)
+    params = mt_inputs.make_params(shape, seed=73, std=0.05)
+    tok, lab = mt_inputs.make_batch(shape.vocab, 2, 72, seed=74)
+    got, arena = [], 0
+    for cap in (0, 1):
+        ps = [p.copy() for p in params]
+        with mt.TrainHandle(make_cfg(shape, 2, 72, max_device_bytes=arena - 1 if cap else 0), ps) as h:
+            assert not cap or arena - h.stats()["device_arena_bytes"] >= 4 * shape.vocab * shape.hidden
+            arena = h.stats()["device_arena_bytes"]
+            loss = h.train_step_adam(tok, lab, 1e-3, step=1) if adam else h.train_step(tok, lab)
+            got.append([np.float64(loss)] + [g.copy() for g in h.grads()] + ps)
+    for i, (a, b) in enumerate(zip(*got)):
+        assert np.array_equal(a, b), i
+
+
 def test_chunked_mlp_matches_unchunked_and_oracle(orc64):
     """cfg.mlp_chunk: the MLP runs (and is recomputed in the backward) in token chunks, ragged last chunk.  The
     forward is row-wise identical, so the loss is bit-identical; weight gradients are sums over chunks in a
