@@ -524,7 +524,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
             dk.load(STAGE - stage, kbase, a.ldk, kv0 + TK, T);
             dv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + TK, T);
         }
-        if (kv0 + key0 <= q0 + 31) {  // otherwise the wave's keys lie after every one of its queries
+        if (kv0 + key0 <= q0 + 31 && q0 < T) {  // otherwise the wave's keys lie after every one of its queries, or it has none
             const char *Ks = reinterpret_cast<const char *>(smem) + stage;
             fwd_tile<HD, NR>(oacc, m, lsum, qf, Ks, Ks + TILE, roff, toff, key0, kv0, q0, qm, hl, c, tau);
         }
@@ -648,6 +648,7 @@ __device__ __forceinline__ void rotate_back(f32x16 *acc, float mul, int hl, cons
 // writes its results as soon as its own last tile is done, while the waves with later queries still work on theirs, and the lists
 // share the work evenly.  us, a workgroup per block (with tiles through registers) -> now: 4 x 4096, 32 heads 650 -> 554 (995 TFLOP/s);
 // 8 x 2048, 16 heads 212 -> 153; 8 x 1024, 32 heads 141 -> 98; 1 x 32768, 40 heads on 8 10 927 -> 9869 (6 % of it by loads that write LDS).
+// head_dim 64, blocks of 128 -> lists: 8 x 2048, 16 heads 129 -> 94 (backward, lists there too, 406 -> 282); 8 x 1024, 32 heads 70 -> 53 (245 -> 170).
 // What bounds it now: matrix pipes busy for half of the cycles at 2.04 GHz, i.e. their issue, the softmax's and the power limit.
 // LDS: two stages of K and V | the wave's queries of the next block | the wave's results on their way out
 template <int HD>
@@ -689,7 +690,7 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
         const bool more = list.next(map, &nxt);
         if (more) request_queries(nxt);
         const int q0 = cur.qb * BQ + wave * 32, q = q0 + l32, qm = min(q, T - 1);  // padded queries behave like the last row; never stored
-        const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = min(ntiles, (q0 + 31) / 64 + 1) - 1;
+        const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = q0 < T ? min(ntiles, (q0 + 31) / 64 + 1) - 1 : -1;   // (no tile for queries past the end)
         f32x16 oacc[HD / 32];
 #pragma unroll
         for (int hb = 0; hb < HD / 32; ++hb) oacc[hb] = zero16();
@@ -887,7 +888,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
             tk.load(STAGE - stage, kbase, a.ldk, kv0 + TK, T);
             tv.load(STAGE - stage + TILE, vbase, a.ldv, kv0 + TK, T);
         }
-        if (kv0 + (KW > 1 ? kw * 32 : 0) <= q0 + 31) {
+        if (kv0 + (KW > 1 ? kw * 32 : 0) <= q0 + 31 && q0 < T) {
             dq_tile<HD, TK / 32 / KW>(dqacc, qf, dof, stage, stage + TILE, t, kw, kv0, q0, qm, hl, c, lse2, dlt);
         }
         tile_barrier();
@@ -978,7 +979,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
         wave_barrier(of);
         const bool more = list.next(map, &nxt);
         const int q0 = cur.qb * BQ + wave * 32, q = q0 + l32, qm = min(q, T - 1);
-        const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = min(ntiles, (q0 + 31) / 64 + 1) - 1;
+        const int ntiles = (min(T, cur.qb * BQ + BQ) + 63) / 64, last = q0 < T ? min(ntiles, (q0 + 31) / 64 + 1) - 1 : -1;   // (no tile for queries past the end)
         const int64_t stat = ((int64_t)cur.b * a.Hq + cur.h) * T + qm;
         const float lse2 = lse * kLog2e;
         float delta;
@@ -1201,7 +1202,7 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
         const bool more = j + 1 < total;
         if (more) request_next(STAGE - stage);
         const int q0t = (qt_first + tq_) * TQ;
-        if (QW <= 2 || q0t + qw * 32 < T)
+        if ((QW <= 2 || q0t + qw * 32 < T) && kv0w < T)
             dkdv_tile<HD, TQ / 32 / QW, HD == 128 && NW == 8, TQ>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? Lds::STATS : 0), Vw, t, qw,
                               q0t, kv0w, kv, hl, c);
         if (more) commit(STAGE - stage);
@@ -1320,7 +1321,7 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, C
             const bool here = j + 1 < total, there = !here && more && (j & 1);
             if (here) request_tile(cur, head, tile, STAGE - stage);
             if (there) request_tile(nxt, 0, block_of(nxt) * (KB / 64), STAGE - stage);
-            if (j < total) dkdv_tile<HD, 2, HD == 128>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? 512 : 0), Vw, t, 0, tile_ * 64, kv0w, kv, hl, c);
+            if (j < total && kv0w < T) dkdv_tile<HD, 2, HD == 128>(dvacc, dkacc, kf, stage, stage + TILE, stat_base + (stage ? 512 : 0), Vw, t, 0, tile_ * 64, kv0w, kv, hl, c);
             if (here || there) commit(STAGE - stage);
             tile_barrier();
         };
@@ -1496,16 +1497,15 @@ static int cheapest(const AttnArgs &a, const AttnCost (&costs)[N], bool keys) {
 //   256 blocks of 128: 1 x 1024 x 32 heads 30 -> 23; 81 -> 69     1 x 2048 x 16 51 -> 37; 133 -> 108     1 x 4096 x 8 95 -> 65; 238 -> 186
 //   264 .. 320: 1 x 384 x 101 15 -> 19; 52 -> 56    1 x 768 x 48 23 -> 19; 67 -> 60    1 x 1536 x 25 40 -> 30; 108 -> 93
 //   512: 1 x 1024 x 64 32 -> 32; 107 -> 104    1 x 2048 x 32 55 -> 47; 159 -> 146      768: 1 x 1536 x 64 49 -> 61; 166 -> 177
-// In grids beyond kByRank the line is drawn by sizes: with head_dim 64 the forward is bound by its vector arithmetic, four of
-// the smaller workgroups' waves fit on a SIMD, and up to 4096 tokens they win (8 x 2048 x 16 156 -> 122, 4 x 4096 x 16 214 -> 207;
-// 1 x 8192 x 32 359 -> 377); head_dim 128 4 x 4096 x 32 610 -> 733; 830 -> 910.  (Some dQ would win there too: 8 x 2048 x 16, head_dim 64, 182 -> 168.)
+// In grids beyond kByRank blocks of 256 go through lists, only that short sequences of head_dim 64 keep blocks of 128 in the forward: blocks of 128 -> lists, forward, head_dim 64: 8 x 2048 x 16 129 -> 94, 4 x 4096 x 16
+// 183 -> 159, 8 x 1024 x 32 70 -> 53; head_dim 128 4 x 4096 x 32 733 -> 554.
 static bool split_keys(const AttnArgs &a, bool forward) {
     static const AttnCost fwd64[] = {{256, 64, 2.89, 1.15, 2.7, 1.13, 1.0}, {128, 64, 3.18, 0.92, 1.96, 0.65, 0.55}};
     static const AttnCost dq64[] = {{256, 64, 3.4, 1.25, 3.4, 1.5, 1.0}, {128, 64, 4.0, 0.85, 4.0, 0.95, 1.0}};
     static const AttnCost hd128[] = {{256, 64, 4.0, 1.62, 4.0, 1.9, 1.0}, {128, 64, 5.2, 1.13, 5.2, 1.25, 1.0}};
     const BlockMap map = block_map(a.Hq / a.Hkv * ((a.T + 255) / 256), a.B * a.Hkv, a.Hq / a.Hkv);
     if ((int64_t)map.n_parts * map.per_part > kByRank)
-        return forward && a.hd == 64 && a.T <= 4096 && (int64_t)a.B * a.Hq * ((a.T + 127) / 128) >= 1024;
+        return forward && a.hd == 64 && a.T < 512 && (int64_t)a.B * a.Hq * ((a.T + 127) / 128) >= 1024;
     return cheapest(a, a.hd == 128 ? hd128 : forward ? fwd64 : dq64, false) == 1;
 }
 
@@ -1557,8 +1557,8 @@ hipError_t flash_fwd(const AttnArgs &a, hipStream_t s) {
         default: break;
     }
     // (one tile of keys: nothing to fetch ahead, 5.4 us against 5.9)
-    if (a.hd == 128 && a.T > 64 && near_pitch(a.ldq) && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256)))
-        return launch_fwd_chain<128>(a, s);
+    if (a.T > 64 && near_pitch(a.ldq) && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256)))
+        return a.hd == 128 ? launch_fwd_chain<128>(a, s) : launch_fwd_chain<64>(a, s);
     return a.hd == 128 ? launch_fwd<128, 8, 1>(a, s) : launch_fwd<64, 8, 1>(a, s);
 }
 
@@ -1575,7 +1575,12 @@ static hipError_t flash_bwd_dq(const AttnArgs &a, hipStream_t s) {
         case 4: return a.hd == 128 ? launch_dq<128, 1, 4>(a, s) : launch_dq<64, 1, 8>(a, s);
         default: break;
     }
-    if (a.hd == 128 && a.T > 64 && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256))) return launch_dq_chain<128>(a, s);   // (T: as for the forward)
+    if (a.T > 64 && chain_fits(a, a.Hq / a.Hkv * ((a.T + 255) / 256))) {   // (T: as for the forward)
+        if (a.hd == 128) return launch_dq_chain<128>(a, s);
+        // (head_dim 64, lists of up to three blocks: 2 x 2048, 32 heads, two, 140 -> 144 us; four: 8 x 1024, 32 heads 245 -> 215)
+        const BlockMap m = block_map(a.Hq / a.Hkv * ((a.T + 255) / 256), a.B * a.Hkv, 1);
+        if (m.n_parts * m.per_part > 3 * kWorkers) return launch_dq_chain<64>(a, s);
+    }
     return a.hd == 128 ? launch_dq<128, 8, 1>(a, s) : launch_dq<64, 8, 1>(a, s);
 }
 
@@ -1641,10 +1646,12 @@ static hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     switch (dkdv_kernel(a)) {
         case 0:
             // (lists of less than three blocks save less than they cost: 1 x 1536, 64 heads, 3 blocks 163 -> 165 us; 3.8 blocks 3 % faster,
-            // 8 x 2048, 16 heads, 4 blocks 651 -> 547 together with dQ)
-            if (a.hd == 128 && chain_fits(a, (a.T + 255) / 256)) {
+            // 8 x 2048, 16 heads, 4 blocks 651 -> 547 together with dQ; head_dim 64, dK/dV alone 406 -> 319)
+            if (chain_fits(a, (a.T + 255) / 256)) {
                 const BlockMap m = block_map((a.T + 255) / 256, a.B * a.Hkv, 1);
-                if (m.n_parts * m.per_part > 3 * kWorkers) return launch_dkdv_chain<128>(a, s);
+                // (head_dim 64: not for long sequences, 10 x 15 320, 8 heads on 4 8310 -> 8480)
+                if (m.n_parts * m.per_part > 3 * kWorkers && (a.hd == 128 || a.T <= 6144))
+                    return a.hd == 128 ? launch_dkdv_chain<128>(a, s) : launch_dkdv_chain<64>(a, s);
             }
             return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
         case 1: return a.hd == 128 ? launch_dkdv<128, 4, 2>(a, s) : launch_dkdv<64, 4, 2>(a, s);

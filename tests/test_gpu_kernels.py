@@ -906,7 +906,8 @@ def test_flash_attention_block_shapes(orc64, B, T, Hq, Hkv, hd, route):
 
 # A workgroup that goes through a list of blocks: one to four of them, odd numbers of tiles, lists of different lengths, padding between
 # the sets of an XCD (sets no multiple of 8), blocks with fewer rows than a wave owns.
-@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(64, 72, 12, 12, 128), (17, 328, 24, 8, 128), (41, 264, 8, 4, 128), (20, 1032, 8, 8, 128), (4, 840, 33, 33, 128)])
+@pytest.mark.parametrize("B,T,Hq,Hkv,hd", [(64, 72, 12, 12, 128), (17, 328, 24, 8, 128), (41, 264, 8, 4, 128), (20, 1032, 8, 8, 128), (4, 840, 33, 33, 128),
+                                           (20, 1032, 8, 8, 64), (33, 600, 8, 8, 64), (64, 520, 6, 6, 64)])
 def test_flash_attention_lists_of_blocks(orc64, B, T, Hq, Hkv, hd):
     assert attention_route(B, T, Hq, Hkv, hd)[0] == 256
     _attention_case(orc64, B, T, Hq, Hkv, hd, seed=T + Hq, out_pad=4 if T == 264 else 0, dq_floor=2 * ROW_FLOOR)
