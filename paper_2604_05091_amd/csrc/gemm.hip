@@ -950,6 +950,8 @@ bool gemm_nt_fuses_glu_bwd(const GemmArgs &g) {
 // the other estimate, the choice is within 0.4 % of the best on average and nowhere more than 5 % behind the other kernels (240 x 3232 x 832), 1.34 times
 // faster than they over all shapes and up to 2.7 times.  At least a stage for every wave, 128 x 64 tiles with four waves eight: 4040 x 304 x 1152, 18
 // stages, 11.0 -> 12.9 us, but 4472 x 336 x 3520 28.9 -> 26.5.
+// fp32 results over whole stages stay one chain of additions: they are what the precision of a split weight gradient is measured against
+// (those that need speed, weight gradients of ragged token counts, have a partial stage).
 struct ShareCost { TileCost cost; int stages; double from_memory; };
 static const ShareCost kShareCosts[] = {{{RingTile::s32x32, 32, 32, 1, 0.122, 0.122, 2.7, 0.0}, 8, 1.3},
                                         {{RingTile::s32x64, 32, 64, 1, 0.176, 0.184, 3.07, 0.0}, 8, 1.3},
@@ -957,6 +959,7 @@ static const ShareCost kShareCosts[] = {{{RingTile::s32x32, 32, 32, 1, 0.122, 0.
                                         {{RingTile::s128x64, 128, 64, 1, 0.371, 0.419, 4.89, 0.0}, 32, 1.6}};
 constexpr int kShareTiles = 600;
 static const TileCost *share_tile(const GemmArgs &g, const TileCost &other) {
+    if (g.out_fp32 && g.K % BK == 0) return nullptr;
     const double stages = (double)((g.K + BK - 1) / BK), other_t = tn_time(other, g.M, g.N, stages, 1, kComputeUnits);
     double best = 1.0;
     const TileCost *tile = nullptr;

@@ -200,7 +200,10 @@ def test_gemm_small_tiles_edges(orc64, M, N, K, pad, tile):
 def test_gemm_reduction_shared_among_waves(M, N, K, pad, tile, sharers):
     lda, ldb, ldc, ldr = K + 8, K + 16, N + pad, N + 3 * pad
     for form in (NT_BF16, NT_F32):
-        assert gemm_route(form, M, N, K, ldc) == (0, tile) and L.mt_k_gemm_sharers(form, M, N, K, ldc) == sharers
+        if form == NT_F32 and K % 64 == 0:   # one chain of additions
+            assert L.mt_k_gemm_sharers(form, M, N, K, ldc) == 1
+        else:
+            assert gemm_route(form, M, N, K, ldc) == (0, tile) and L.mt_k_gemm_sharers(form, M, N, K, ldc) == sharers
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     A, B, R, BI = (torch.randn((r, c), device="cuda", generator=g).to(torch.bfloat16) for r, c in ((M, lda), (N, ldb), (M, ldr), (1, N)))
     ref = A[:, :K].double() @ B[:, :K].double().T.contiguous()
