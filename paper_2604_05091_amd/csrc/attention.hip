@@ -106,6 +106,15 @@ struct DirectTile {
             }
         }
     }
+    // the pieces that this lane delivers, into registers instead
+    __device__ __forceinline__ void load_to(u32x4 (&v)[N], const bf16_t *src, int64_t ld, int row0, int row_end) const {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bf16_t *p = src + (int64_t)min(row0 + RPL * (wave + NW * j), row_end - RPL) * ld;
+            const uint32_t c = GS == 1024 && RPL * NW % 16 ? chunk ^ (swz<HD>(RPL * NW * j) << 4) : chunk;
+            v[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(p) + (FAR ? (int64_t)r * ld * 2 : row_bytes) + c);
+        }
+    }
 };
 // (in a scalar register: what depends on it is a scalar branch)
 __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
@@ -188,6 +197,17 @@ __device__ __forceinline__ float half_max(float v) {
 __device__ __forceinline__ float half_sum(float v) {
     const auto u = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(u[0]) + __uint_as_float(u[1]);
+}
+
+// sum over the 8 or 16 neighbouring lanes of a group, in all of them
+template <int N>
+__device__ __forceinline__ float group_sum(float v) {
+    const auto add = [&](auto ctrl) { v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    add(std::integral_constant<int, 0xb1>());    // lane ^ 1
+    add(std::integral_constant<int, 0x4e>());    // lane ^ 2
+    add(std::integral_constant<int, 0x141>());   // 7 - lane of 8: the other four
+    if (N == 16) add(std::integral_constant<int, 0x140>());   // 15 - lane of 16: the other eight
+    return v;
 }
 
 __device__ __forceinline__ bf16x8 pack_frag(const f32x16 &v, int cch) {
@@ -316,8 +336,8 @@ inline BlockMap block_map(int per_set, int n_sets, int copies) {
     m.by_rank = (int64_t)m.n_parts * m.per_part <= kByRank && m.n_parts * copies > 1;
     return m;
 }
-__device__ __forceinline__ bool decode_block(const BlockMap &m, int *set, int *inner) {
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, by = m.by_rank ? m.n_parts : m.per_part, quot = slot / by, rest = slot - quot * by;
+__device__ __forceinline__ bool decode_block(const BlockMap &m, uint32_t id, int *set, int *inner) {
+    const int xcd = id % kXcds, slot = id / kXcds, by = m.by_rank ? m.n_parts : m.per_part, quot = slot / by, rest = slot - quot * by;
     const int i = m.by_rank ? quot : rest, part_id = (m.by_rank ? rest : quot) * kXcds + xcd, p = 1 << m.log_parts, part = part_id & (p - 1);
     *set = part_id >> m.log_parts;
     *inner = i * p + (i & 1 ? p - 1 - part : part);
@@ -485,7 +505,7 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_fwd_kernel(AttnArgs a, Blo
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
     int set, inner;
-    if (!decode_block(map, &set, &inner)) return;
+    if (!decode_block(map, blockIdx.x, &set, &inner)) return;
     const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
     const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));  // heaviest query blocks first (in alternating rows of 8)
     const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
@@ -734,11 +754,12 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 // dQ is the first kernel of the backward: it has the output gradients of its queries at hand, so it also works out delta = rowsum(dO * O),
 // which is stored for dK/dV (a pass of its own read dO once more.  us, forward and backward, with -> without it: 3 x 520, 8 heads of 64 on 2 40.6 -> 38.6;
 // 4 x 4096, 32 heads 2518 -> 2502; 1 x 32768, 40 heads on 8 43 830 -> 43 740).
+// (v_dot2c_f32_bf16: its error against 64 bits is that of two fused multiply-adds)
 __device__ __forceinline__ float dot8(const bf16x8 &x, const bf16x8 &y) {
-    const u32x4 a = __builtin_bit_cast(u32x4, x), b = __builtin_bit_cast(u32x4, y);
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s += bflo(a[i]) * bflo(b[i]) + bfhi(a[i]) * bfhi(b[i]);
+    for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{x[2 * i], x[2 * i + 1]}, bf16x2{y[2 * i], y[2 * i + 1]}, s, false);
     return s;
 }
 template <int HD>
@@ -826,15 +847,15 @@ __device__ __forceinline__ void store_summed(bf16_t *out, const f32x16 *acc, flo
         *reinterpret_cast<uint2 *>(out + j + HD / 2) = uint2{pack2bf(y[0], y[1]), pack2bf(y[2], y[3])};
     }
 }
+// (a block; the kernel follows)
 template <int HD, int QW, int KW, bool FAR>
-__global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, BlockMap map) {
+__device__ __forceinline__ void dq_block(const AttnArgs &a, const BlockMap &map, uint32_t id, bf16_t *smem) {
     constexpr int BQ = 32 * QW, TK = walk_rows(KW);
     constexpr uint32_t TILE = BwdTile<HD>::rows(TK), STAGE = 2 * TILE;   // a stage is K, V
-    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
 
     const int T = a.T, G = a.Hq / a.Hkv, nqb = (T + BQ - 1) / BQ;
     int set, inner;
-    if (!decode_block(map, &set, &inner)) return;
+    if (!decode_block(map, id, &set, &inner)) return;
     const int b = set / a.Hkv, hk = set % a.Hkv, h = hk * G + (map.by_rank ? inner % G : inner / nqb);
     const int qb = nqb - 1 - (map.by_rank ? inner / G : snake8(inner % nqb, nqb));
     const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
@@ -924,6 +945,11 @@ __global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, 
         write_owned_rows<HD>(a.dq + ((int64_t)b * T + q0) * a.lddq + (int64_t)h * HD, a.lddq, dqacc, a.scale, l32, hl,
                              min(32, T - q0), a.rope_cos ? a.rope_cos + (int64_t)q0 * (HD / 2) : nullptr,
                              a.rope_cos ? a.rope_sin + (int64_t)q0 * (HD / 2) : nullptr, out_region<HD>(smem, qw));
+}
+template <int HD, int QW, int KW, bool FAR>
+__global__ __launch_bounds__(64 * QW * KW) void flash_bwd_dq_kernel(AttnArgs a, BlockMap map) {
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    dq_block<HD, QW, KW, FAR>(a, map, blockIdx.x, smem);
 }
 
 // The same in blocks of 256 queries with one workgroup per compute unit that goes through a list of them (see flash_fwd_chain_kernel).  The
@@ -1048,9 +1074,11 @@ __global__ __launch_bounds__(512) void flash_bwd_dq_chain_kernel(AttnArgs a, Cha
 
 // the queries 32 rb .. + 31 (rb0 <= rb < rb0 + NR) of the tile that starts at query q0t; kv0w: the wave's first key, kv: the lane's;
 // stats: lse * log2e [TQ], delta [TQ] from the lane half's first query on; Vw: the wave's rows of V
-template <int HD, int NR, bool TIGHT, int TQ = 64>
+// (VREG: vf instead)
+template <int HD, int NR, bool TIGHT, int TQ = 64, bool VREG = false>
 __device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dkacc)[HD / 32], const bf16x8 (&kf)[HD / 16], uint32_t Qs, uint32_t dOs,
-                                          uint32_t stats, uint32_t Vw, const BwdTile<HD> &t, int rb0, int q0t, int kv0w, int kv, int hl, float c) {
+                                          uint32_t stats, uint32_t Vw, const BwdTile<HD> &t, int rb0, int q0t, int kv0w, int kv, int hl, float c,
+                                          const bf16x8 *vf = nullptr) {
     typedef __attribute__((address_space(3))) const f32x4 *lds_f4;
 #pragma unroll
     for (int u = 0; u < NR; ++u) {
@@ -1074,7 +1102,7 @@ __device__ __forceinline__ void dkdv_tile(f32x16 (&dvacc)[HD / 32], f32x16 (&dka
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 dd[i] = t.row_frag(dor, half * 4 + i);
-                vv[i] = t.row_frag(Vw, half * 4 + i);
+                vv[i] = VREG ? vf[half * 4 + i] : t.row_frag(Vw, half * 4 + i);
             }
             if constexpr (!TIGHT) {
 #pragma unroll
@@ -1144,7 +1172,7 @@ __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_dkdv_kernel(AttnArgs a
 
     const int T = a.T, G = a.Hq / a.Hkv, nkb = (T + KB - 1) / KB;
     int set, kvb;
-    if (!decode_block(map, &set, &kvb)) return;
+    if (!decode_block(map, blockIdx.x, &set, &kvb)) return;
     if (!map.by_rank) kvb = snake8(kvb, nkb);
     const int b = set / a.Hkv, hk = set % a.Hkv;
     const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
@@ -1344,6 +1372,133 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, C
         if (!more) break;
         cur = nxt;
     }
+}
+
+// Small problems: dQ and dK/dV side by side in one launch, each working out the row sums of dO * O for itself, so that neither waits for the other.
+// What bounds them is latency: each alone leaves most of the chip idle for the 8-60 us of its longest walk.  The blocks of keys come first, theirs
+// is the longer walk.
+//
+// A block's KW x QW waves own 32 keys each and walk pieces of 32 queries; those of all the group's heads are dealt to the QW sets in turn.  A wave
+// fetches its pieces into LDS of its own, one ahead, and waits for nobody until the sets' sums are added.  A tile shared by the waves
+// (flash_bwd_dkdv_kernel) holds rows of one head only and ends with a barrier: 3 x 520, 8 heads of 64 on 2, are 12 steps of it and 9 here.  The row sums
+// come from the chunks of dO and O that a lane itself fetched (a fragment's layout would take 32 lines per load: 26 us against 21 of this kernel alone).
+// us, backward, two launches -> one: 3 x 520, 8 heads on 2, head_dim 64 30.2 -> 19.3; 7 x 128, 10 on 2 19.4 -> 14.7; 4 x 512, 2 on 2 16.6 -> 9.7;
+// head_dim 128: 2 x 88, 20 on 4 22.7 -> 15.0; 1 x 560, 8 on 2 49.6 -> 40.4; 3 x 1120, 2 on 2 38.4 -> 27.5.
+// LDS: a wave's two stages of Q, dO | the waves' lse * log2e, delta of 32 queries, twice | head_dim 128: V (64: the lane's values fit into registers)
+template <int HD, int NW>
+struct UnitLds {
+    static constexpr uint32_t TILE = BwdTile<HD>::rows(32), WAVE = 4 * TILE, STAT_OFF = NW * WAVE, V_OFF = STAT_OFF + NW * 512, BYTES = V_OFF + (HD == 128 ? TILE : 0);
+};
+template <int HD, int KW, int QW>
+__device__ __forceinline__ void dkdv_units_block(const AttnArgs &a, const BlockMap &map, uint32_t id, bf16_t *smem) {
+    constexpr int HB = HD / 32, GS = BwdTile<HD>::GS, LPR = HD / 8, N = 32 * LPR / 64;   // lanes of a row, chunks that a lane fetches
+    using Lds = UnitLds<HD, KW * QW>;
+    static_assert(HD == 64 || KW == 1, "one wave's values in LDS");
+    constexpr uint32_t TILE = Lds::TILE, STAGE = 2 * TILE;
+    char *lds = reinterpret_cast<char *>(smem);
+
+    const int T = a.T, G = a.Hq / a.Hkv, nt = (T + 31) / 32, nkb = (T + 32 * KW - 1) / (32 * KW);
+    int set, kvb;
+    if (!decode_block(map, id, &set, &kvb)) return;
+    if (!map.by_rank) kvb = snake8(kvb, nkb);
+    const int b = set / a.Hkv, hk = set % a.Hkv;
+    const int lane = threadIdx.x & 63, wave = wave_index(), l32 = lane & 31, hl = lane >> 5;
+    BwdTile<HD> t;
+    t.init(smem, lane);
+    const int kw = wave % KW, qw = wave / KW, key_unit = kvb * KW + kw, kv0 = key_unit * 32, kv = kv0 + l32;
+    const float c = scalar(a.scale * kLog2e);
+    const uint32_t wave_lds = lds_address(smem) + wave * Lds::WAVE;
+    DirectTile<32, HD, 1, false, GS> tq, tdo, to;
+    tq.init(lds + wave * Lds::WAVE, a.ldq, lane, 0);
+    tdo.init(lds + wave * Lds::WAVE, a.lddo, lane, 0);
+    to.init(lds, a.ldo, lane, 0);
+
+    f32x16 dvacc[HB], dkacc[HB];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) {
+        dvacc[hb] = zero16();
+        dkacc[hb] = zero16();
+    }
+    bf16x8 kf[HD / 16], vf[HD / 16];
+    u32x4 of[N];
+    float lse = 0.f;
+    int head = key_unit < nt ? 0 : G, unit = key_unit + qw;   // of the next piece (none for keys past the end)
+    const auto settle = [&]() {
+        while (unit >= nt && head < G) {
+            unit -= nt - key_unit;
+            ++head;
+        }
+    };
+    const auto request = [&](uint32_t stage) {
+        const int h = hk * G + head, q0 = unit * 32;
+        tq.load(stage, a.q + (int64_t)b * T * a.ldq + (int64_t)h * HD, a.ldq, q0, T);
+        tdo.load(stage + TILE, a.dout + (int64_t)b * T * a.lddo + (int64_t)h * HD, a.lddo, q0, T);
+        to.load_to(of, a.o + (int64_t)b * T * a.ldo + (int64_t)h * HD, a.ldo, q0, T);
+        lse = a.lse[((int64_t)b * a.Hq + h) * T + min(q0 + l32, T - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // The row sums of dO * O of a piece that has landed, from the chunks of dO and O that this lane fetched; LPR neighbouring lanes have a row.
+    // Queries past T: lse = +inf makes their P (and with it dS) exactly zero.
+    const auto commit = [&](int q0, uint32_t stage, uint32_t stats) {
+        typedef __attribute__((address_space(3))) const bf16x8 *lds_frag;
+        typedef __attribute__((address_space(3))) float *lds_float;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        float mine = 0.f;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bf16x8 dof = *(lds_frag)(wave_lds + stage + TILE + j * GS + lane * 16);
+            const float d = group_sum<LPR>(dot8(dof, __builtin_bit_cast(bf16x8, of[j])));
+            mine = lane % LPR == j ? d : mine;
+        }
+        if (lane % LPR < N) *(lds_float)(stats + (32 + lane % LPR * (64 / LPR) + lane / LPR) * 4) = mine;
+        if (lane < 32) *(lds_float)(stats + lane * 4) = q0 + lane < T ? lse * kLog2e : INFINITY;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    settle();
+    if (head < G) request(0);
+    {
+        const bf16_t *kp = a.k + ((int64_t)b * T + min(kv, T - 1)) * a.ldk + (int64_t)hk * HD + hl * 8;
+        const bf16_t *vp = a.v + ((int64_t)b * T + min(kv, T - 1)) * a.ldv + (int64_t)hk * HD + hl * 8;
+#pragma unroll
+        for (int i = 0; i < HD / 16; ++i) {
+            kf[i] = load_frag_global(kp + i * 16);
+            if constexpr (HD == 64) vf[i] = load_frag_global(vp + i * 16);
+        }
+        if constexpr (HD == 128) {
+            DirectTile<32, HD, QW, false, GS> tv;
+            tv.init(smem, a.ldv, lane, wave);
+            tv.load(Lds::V_OFF, a.v + (int64_t)b * T * a.ldv + (int64_t)hk * HD, a.ldv, kv0, T);
+            tile_barrier();
+        }
+    }
+    const uint32_t mine = wave * Lds::WAVE, stats = lds_address(smem) + Lds::STAT_OFF + wave * 512;
+    if (head < G) commit(unit * 32, 0, stats);
+    for (uint32_t stage = 0; head < G; stage ^= 1) {
+        const int q0 = unit * 32;
+        unit += QW;
+        settle();
+        const bool more = head < G;
+        if (more) request(stage ? 0 : STAGE);
+        dkdv_tile<HD, 1, false, 32, HD == 64>(dvacc, dkacc, kf, mine + stage * STAGE, mine + stage * STAGE + TILE, stats + stage * 256 + hl * 16, Lds::V_OFF, t, 0, q0, kv0, kv, hl, c, vf);
+        if constexpr (HD == 128) {   // (in the accumulation registers: left to itself the compiler brings them back and forth, 300 moves a piece)
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb) asm volatile("" : "+a"(dvacc[hb]), "+a"(dkacc[hb]));
+        }
+        if (more) commit(unit * 32, stage ? 0 : STAGE, stats + (stage ^ 1) * 256);
+    }
+    const bool valid = kv < T;
+    const int64_t row = (int64_t)b * T + kv;
+    const float *cs = a.rope_cos ? a.rope_cos + (int64_t)kv * (HD / 2) : nullptr, *sn = a.rope_cos ? a.rope_sin + (int64_t)kv * (HD / 2) : nullptr;
+    store_summed<HD, KW, QW>(a.dk + row * a.lddk + (int64_t)hk * HD, dkacc, a.scale, kw, qw, lane, valid, cs, sn, lds);
+    store_summed<HD, KW, QW>(a.dv + row * a.lddv + (int64_t)hk * HD, dvacc, 1.0f, kw, qw, lane, valid, nullptr, nullptr, lds);
+}
+// the first n_keys workgroups take blocks of keys, the others blocks of queries
+template <int HD, int DQ_QW, int DQ_KW, int KW, int QW>
+__global__ __launch_bounds__(64 * KW * QW) void flash_bwd_both_kernel(AttnArgs a, BlockMap keys, BlockMap queries, int n_keys) {
+    static_assert(DQ_QW * DQ_KW == KW * QW, "workgroups of one size");
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    if ((int)blockIdx.x < n_keys) dkdv_units_block<HD, KW, QW>(a, keys, blockIdx.x, smem);
+    else dq_block<HD, DQ_QW, DQ_KW, false>(a, queries, blockIdx.x - n_keys, smem);
 }
 
 bool attn_shape_ok(const AttnArgs &a) {
@@ -1649,6 +1804,22 @@ static hipError_t launch_dkdv(const AttnArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int HD, int DQ_QW, int DQ_KW, int KW, int QW>
+static hipError_t launch_both(const AttnArgs &a, hipStream_t s) {
+    // either kind of block, and the sums of the sets that share one
+    constexpr size_t lds = std::max({(size_t)UnitLds<HD, KW * QW>::BYTES, (size_t)KW * QW * (HD / 32 * 16) * 64 * sizeof(float),
+                                     (size_t)2 * 2 * BwdTile<HD>::rows(walk_rows(DQ_KW)), (size_t)DQ_QW * 32 * (HD + 8) * sizeof(bf16_t)});
+    static_assert(lds <= 160 * 1024, "LDS");
+    static std::atomic<bool> done{false};
+    const hipError_t e = ensure_lds(&flash_bwd_both_kernel<HD, DQ_QW, DQ_KW, KW, QW>, lds, &done);
+    if (e != hipSuccess) return e;
+    const int G = a.Hq / a.Hkv, kb = 32 * KW, qb = 32 * DQ_QW;
+    const BlockMap keys = block_map((a.T + kb - 1) / kb, a.B * a.Hkv, 1), queries = block_map(G * ((a.T + qb - 1) / qb), a.B * a.Hkv, G);
+    hipLaunchKernelGGL((flash_bwd_both_kernel<HD, DQ_QW, DQ_KW, KW, QW>), dim3(grid_blocks(keys) + grid_blocks(queries)), dim3(64 * KW * QW), lds, s, a, keys,
+                       queries, (int)grid_blocks(keys));
+    return hipGetLastError();
+}
+
 template <int HD>
 static hipError_t launch_dkdv_chain(const AttnArgs &a, hipStream_t s) {
     constexpr size_t lds = 4 * BwdTile<HD>::BYTES + 2 * 2 * BwdTile<HD>::BYTES + 1024 + 8 * 2048;
@@ -1708,13 +1879,39 @@ static hipError_t flash_bwd_dkdv(const AttnArgs &a, hipStream_t s) {
     return a.hd == 128 ? launch_dkdv<128, 8, 1>(a, s) : launch_dkdv<64, 8, 1>(a, s);
 }
 
-// the rows of two [B T, H hd] arrays may share memory
-static bool overlap(const AttnArgs &a, const bf16_t *x, int64_t ldx, const bf16_t *y, int64_t ldy) {
-    const int64_t last = (int64_t)a.B * a.T - 1, cols = (int64_t)a.Hq * a.hd;
-    const bf16_t *x0 = x + std::min<int64_t>(0, last * ldx), *x1 = x + std::max<int64_t>(0, last * ldx) + cols;
-    const bf16_t *y0 = y + std::min<int64_t>(0, last * ldy), *y1 = y + std::max<int64_t>(0, last * ldy) + cols;
+// the rows of two arrays of B T rows may share memory: elements of their rows, pitches
+static bool overlap(const AttnArgs &a, const bf16_t *x, int64_t ldx, int64_t cols_x, const bf16_t *y, int64_t ldy, int64_t cols_y) {
+    const int64_t last = (int64_t)a.B * a.T - 1;
+    const bf16_t *x0 = x + std::min<int64_t>(0, last * ldx), *x1 = x + std::max<int64_t>(0, last * ldx) + cols_x;
+    const bf16_t *y0 = y + std::min<int64_t>(0, last * ldy), *y1 = y + std::max<int64_t>(0, last * ldy) + cols_y;
     return x0 < y1 && y0 < x1;
 }
+// dQ and dK/dV in one launch: where dK/dV takes blocks of 32 keys (head_dim 64: or of 64, shared by four sets) and dQ workgroups of the same size, up to
+// kTogether workgroups.  Two launches against one, 240 shapes: 1.0 to 1.9 times faster up to 700 workgroups (1.26 on average);
+// 700 to 1100: 0.88 to 1.12, slower where the walks are long (1 x 3528, 16 heads on 8 of 64, 896 workgroups 131 -> 145 us).
+constexpr int kTogether = 700;
+static bool runs_together(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv) {
+    if (!(dkdv.rows == 32 || (dkdv.rows == 64 && dkdv.sets == 4 && a.hd == 64)) || dq.list || (a.hd == 128 && dq.rows != 32)) return false;
+    const int64_t blocks = (int64_t)a.B * a.Hkv * ((a.T + dkdv.rows - 1) / dkdv.rows) + (int64_t)a.B * a.Hq * ((a.T + dq.rows - 1) / dq.rows);
+    if (blocks > kTogether) return false;
+    // dK and dV may take the place of keys and values, but not while dQ reads them
+    const int64_t nq = (int64_t)a.Hq * a.hd, nkv = (int64_t)a.Hkv * a.hd;
+    const auto apart = [&](const bf16_t *x, int64_t ldx) {
+        return !overlap(a, x, ldx, nkv, a.k, a.ldk, nkv) && !overlap(a, x, ldx, nkv, a.v, a.ldv, nkv) && !overlap(a, x, ldx, nkv, a.q, a.ldq, nq) &&
+               !overlap(a, x, ldx, nkv, a.dout, a.lddo, nq) && !overlap(a, x, ldx, nkv, a.o, a.ldo, nq);
+    };
+    return near_pitch(a.ldk) && near_pitch(a.ldo) && apart(a.dk, a.lddk) && apart(a.dv, a.lddv);
+}
+static hipError_t flash_bwd_both(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv, hipStream_t s) {
+    if (a.hd == 128) return launch_both<128, 1, 4, 1, 4>(a, s);
+    switch (dq.rows) {
+        case 256: return dkdv.rows == 64 ? launch_both<64, 8, 1, 2, 4>(a, s) : launch_both<64, 8, 1, 1, 8>(a, s);
+        case 128: return dkdv.rows == 64 ? launch_both<64, 4, 2, 2, 4>(a, s) : launch_both<64, 4, 2, 1, 8>(a, s);
+        case 64: return dkdv.rows == 64 ? launch_both<64, 2, 4, 2, 4>(a, s) : launch_both<64, 2, 4, 1, 8>(a, s);
+        default: return dkdv.rows == 64 ? launch_both<64, 1, 8, 2, 4>(a, s) : launch_both<64, 1, 8, 1, 8>(a, s);
+    }
+}
+
 hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
     // everything that either kernel asks for, before one of them has written a result
     if (!attn_shape_ok(a) || !rope_tables_ok(a)) return hipErrorInvalidValue;
@@ -1722,7 +1919,8 @@ hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
     if (!aligned16(a.q) || !aligned16(a.k) || !aligned16(a.v) || !aligned16(a.o) || !aligned16(a.dout)) return hipErrorInvalidValue;
     if (((uintptr_t)a.dq & 7) || ((uintptr_t)a.dk & 7) || ((uintptr_t)a.dv & 7)) return hipErrorInvalidValue;
     hipError_t e;
-    if (overlap(a, a.dq, a.lddq, a.q, a.ldq) || overlap(a, a.dq, a.lddq, a.dout, a.lddo) || overlap(a, a.dq, a.lddq, a.o, a.ldo)) {
+    const int64_t nq = (int64_t)a.Hq * a.hd;
+    if (overlap(a, a.dq, a.lddq, nq, a.q, a.ldq, nq) || overlap(a, a.dq, a.lddq, nq, a.dout, a.lddo, nq) || overlap(a, a.dq, a.lddq, nq, a.o, a.ldo, nq)) {
         // dq takes the place of something that dK/dV reads: it comes last
         e = attn_delta(a.delta, a.dout, a.lddo, a.o, a.ldo, a.B, a.T, a.Hq, a.hd, s);
         if (e == hipSuccess) e = flash_bwd_dkdv(a, s);
@@ -1730,6 +1928,8 @@ hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
         with_delta.o = nullptr;
         return e == hipSuccess ? flash_bwd_dq(with_delta, s) : e;
     }
+    const AttnKernel dq = dq_kernel(a), dkdv = dkdv_kernel(a);
+    if (runs_together(a, dq, dkdv)) return flash_bwd_both(a, dq, dkdv, s);
     e = flash_bwd_dq(a, s);
     return e == hipSuccess ? flash_bwd_dkdv(a, s) : e;
 }
