@@ -76,7 +76,7 @@ int32_t mt_k_gemm_tn(const uint16_t *At, int64_t lda, const uint16_t *Bt, int64_
 int32_t mt_k_gemm_tn_split(const uint16_t *At, int64_t lda, const uint16_t *Bt, int64_t ldb, float *C, int64_t ldc, int32_t M,
                            int32_t N, int32_t K, int32_t accumulate, int32_t split_k, float *ws, void *stream);
 int32_t mt_k_gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int32_t n_cu);
-/* Which tiles compute a product of this size (host only, launches nothing; C 16-byte aligned, row pitch ldc): route[0] = number
+/* Which tiles compute a product of this size (host only, launches nothing; operands' rows K apart, C 16-byte aligned, row pitch ldc): route[0] = number
  * of 256 x 256 tiles that are left to one workgroup each of the kernel for large grids, route[1] x route[2] = tile of all others.
  * form = 0, 1: mt_k_gemm_nt (and mt_k_gemm_nt_bias) with bf16 and fp32 results (split_k = 1; route[1] = route[2] = 0: there are no
  * others); 2: mt_k_gemm_tn_split, whose others have a workgroup for each of the split_k chunks. */

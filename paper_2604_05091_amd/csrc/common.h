@@ -68,7 +68,16 @@ __device__ __forceinline__ void mfma16_drain() {
     asm volatile("s_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
-// The same, for the compiler too.  Where two paths with these instructions meet in front of it, the compiler may move accumulators at
+// The accumulators have been set (before the first of these instructions, where the compiler would set them right in front of it).
+template <int I, int J>
+__device__ __forceinline__ void mfma16_begin(f32x4 (&acc)[I][J]) {
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j) asm volatile("" : "+a"(acc[i][j]));
+    mfma16_drain();
+}
+// The same as mfma16_drain, for the compiler too.  Where two paths with these instructions meet in front of it, the compiler may move accumulators at
 // the end of one of them: that path ends with a mfma16_drain of its own (tests/test_matrix_hazards.py looks for such moves).
 template <int I, int J>
 __device__ __forceinline__ void mfma16_settle(f32x4 (&acc)[I][J]) {
@@ -200,7 +209,7 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s, int32_t of_rows = 0);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
 // has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced; every
 // output is the sum of at least partial_sums partial sums.
-enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, s128x64, s64x64, s32x64, s32x32 };   // s...: reductions shared among waves, NT only, first < 0
+enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, l128x128, l128x64, l64x64, s128x64, s64x64, s32x64, s32x32 };   // s...: reductions shared among waves, NT only, first < 0
 // first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
 hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
 hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s);

@@ -11,6 +11,8 @@
 // MFMAs of the present one run (two register sets), so neither the LDS latency nor the barrier (one per stage) is
 // exposed.  16 x 16 x 32 MFMAs with accumulators updated in place, as in the 256 x 256 kernel.  The path into LDS takes about 57 bytes a clock, which makes (BM + BN) * 128 / 57 clocks the floor of a
 // stage: 575 for 128 x 128 (MFMA: 515), 431 for 128 x 64 (257), 287 for 64 x 64 (129).
+#include <type_traits>
+
 #include "common.h"
 
 namespace mt {
@@ -333,6 +335,159 @@ __global__ __launch_bounds__(256) void ring_nt_kernel(GemmArgs g, int tiles_m, i
     ring_store<BM, BN, TM, TN, F32>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
 }
 
+// The ring for rows that are not whole lines (K % 64, pitches as tight as K).  A piece of 128 bytes of such a row touches two lines, and a
+// line is asked for twice, by the stage that needs its beginning and by the one that needs its end: 1.14 to 1.43 times the time.  Here whole lines are
+// fetched, each once, and put together when LDS is read: row r begins s_r chunks of 16 bytes behind the start of a line, so chunk c of
+// stage T lies in line T + (c + s_r) / 8 of the row.  A lane's rows are 16 apart and begin alike, so that is one choice between two slots per lane,
+// operand and half stage.  Chunk c + s_r of its line lies at position (c + (r >> 1)) & 7: reads are free of bank conflicts whatever s_r.
+// The partial stage comes first, as in the other kernels (same order of additions, same bits): the lines are v = 0, 1 (the end of the row) and
+// then 2, 3, .. (its lines 0, 1, ..), stage u = 0 (the partial one) takes lines 0 and 1, stage u > 0 lines u + 1 and u + 2.  Line v lives in slot v % S.
+// At the top of stage u lines up to u + 3 have landed and every wave has read its fragments of stage u: slot (u + 1) % S takes line u + 1 + S.
+// Chunks before or behind the row are replaced by ones inside, those behind are zeros in the fragments.
+template <int BM, int BN, int S, bool F32>
+__global__ __launch_bounds__(256) void line_nt_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
+    constexpr int TM = BM / 32, TN = BN / 32, MPS = TM * TN;         // 16 x 16 blocks of a wave (2 x 2 waves)
+    constexpr int LA = BM / 32, LB = BN / 32, LPS = LA + LB;         // loads of a wave per stage
+    constexpr int STAGE = (BM + BN) * 128;
+    static_assert(S >= 4 && BM * (BN + 4) * 4 <= S * STAGE && S * STAGE <= 160 * 1024, "LDS");
+    int tm, tn;
+    ring_tile(ring_renumber(tiles_m * tiles_n), tiles_m, tiles_n, &tm, &tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, hq = lane >> 4;
+
+    const bf16_t *abase = g.A + (int64_t)m0 * g.lda, *bbase = g.B + (int64_t)n0 * g.ldb;
+    const int nk = (g.K + RK - 1) / RK, nv = nk > 1 ? nk + 2 : 2;
+    const auto start_of = [&](bool a, int row) { return (int)(((uintptr_t)(a ? abase : bbase) >> 4) + (uint32_t)row * (uint32_t)((a ? g.lda : g.ldb) >> 3)) & 7; };
+    // wave w fills rows (BM / 4) w .. of A and (BN / 4) w .. of B, 8 rows per load; rows past the edge re-read the last one
+    uint32_t off[LPS];   // from 128 bytes in front of a line 0
+    const auto row_of = [&](int j) { return j < LA ? wave * (BM / 4) + j * 8 + (lane >> 3) : wave * (BN / 4) + (j - LA) * 8 + (lane >> 3); };
+    const auto row_off = [&](int j) {
+        return (uint32_t)((j < LA ? min(row_of(j), g.M - 1 - m0) : min(row_of(j), g.N - 1 - n0)) * (int)(j < LA ? g.lda : g.ldb)) * 2u;
+    };
+#pragma unroll
+    for (int j = 0; j < LPS; ++j) {
+        const int r = row_of(j), s = start_of(j < LA, r);
+        off[j] = row_off(j) + 128u + (((lane - (r >> 1) + s) & 7) - s) * 16u;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(ring_lptr)ring;
+    const uint32_t fill_a = (uint32_t)(wave * (BM / 4) * 128), fill_b = (uint32_t)(BM * 128 + wave * (BN / 4) * 128);
+    uint32_t rda[2], rdb[2];
+    bool ca[2], cb[2];   // the chunk lies in the second line
+    {
+        const int sa = start_of(true, wm * TM * 16 + l16), sb = start_of(false, wn * TN * 16 + l16);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint32_t pos = (uint32_t)(((4 * ks + hq + (l16 >> 1)) & 7) * 16);
+            rda[ks] = (uint32_t)((wm * TM * 16 + l16) * 128) + pos;
+            rdb[ks] = (uint32_t)(BM * 128 + (wn * TN * 16 + l16) * 128) + pos;
+            ca[ks] = 4 * ks + hq + sa >= 8;
+            cb[ks] = 4 * ks + hq + sb >= 8;
+        }
+    }
+    bf16x8 fr[2][2][TM + TN];
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const auto load = [&](int j, int line, int slot) {   // a line in the middle of the rows: 0 < line < nk - 1
+        ring_load((j < LA ? abase : bbase) + (line - 1) * 64, off[j], lds0 + (uint32_t)slot * STAGE + (j < LA ? fill_a + j * 1024u : fill_b + (j - LA) * 1024u));
+    };
+    const auto load_any = [&](int line, int slot) {
+#pragma unroll
+        for (int j = 0; j < LPS; ++j) {
+            const int first = (int)row_off(j), at = (int)off[j] + (line - 1) * 128;
+            ring_load(j < LA ? abase : bbase, (uint32_t)min(max(at, first), first + (g.K - 8) * 2),
+                      lds0 + (uint32_t)slot * STAGE + (j < LA ? fill_a + j * 1024u : fill_b + (j - LA) * 1024u));
+        }
+    };
+    const auto line_of = [&](int v) { return v < 2 ? nk - 1 + v : v - 2; };
+    uint32_t ra[2], rb[2];
+    const auto aim = [&](int slot) {   // the reads of the stage whose first line is in this slot
+        const uint32_t lo = (uint32_t)slot * STAGE, hi = (uint32_t)(slot + 1 == S ? 0 : slot + 1) * STAGE;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            ra[ks] = rda[ks] + (ca[ks] ? hi : lo);
+            rb[ks] = rdb[ks] + (cb[ks] ? hi : lo);
+        }
+    };
+    const auto read = [&](auto set, int ks, int f) {
+        fr[set()][ks][f] = *reinterpret_cast<const bf16x8 *>(ring + (f < TM ? ra[ks] + f * 2048 : rb[ks] + (f - TM) * 2048));
+    };
+    const auto next = [&](int slot) { return slot + 1 == S ? 0 : slot + 1; };
+
+#pragma unroll
+    for (int v = 0; v < S; ++v)
+        if (v < nv) load_any(line_of(v), v);
+    ring_wait_steps<LPS, S + 1>(min(S, nv) - 2);
+    aim(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const bool there = (nk - 1) * RK + (4 * ks + hq) * 8 < g.K;
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f) {
+            read(std::integral_constant<int, 0>(), ks, f);
+            ru32x4 w = __builtin_bit_cast(ru32x4, fr[0][ks][f]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = there ? w[e] : 0u;
+            fr[0][ks][f] = __builtin_bit_cast(bf16x8, w);
+        }
+    }
+    mfma16_begin(acc);
+    int u = 0, slot = 1;   // slot: (u + 1) % S, what is free at the top of stage u
+    // the products of stage u, the fragments of the next one, and line u + 1 + S if it lies in the middle of the rows
+    const auto stage = [&](auto set, auto loads) {
+        constexpr int C = set();
+        aim(next(slot));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int m = 0; m < MPS; ++m) {
+                const int w = ks * MPS + m;
+                if constexpr (loads()) {
+#pragma unroll
+                    for (int j = w * LPS / (2 * MPS); j < (w + 1) * LPS / (2 * MPS); ++j) load(j, u + S - 1, slot);
+                }
+#pragma unroll
+                for (int f = m * (TM + TN) / MPS; f < (m + 1) * (TM + TN) / MPS; ++f) read(std::integral_constant<int, 1 - C>(), ks, f);
+                const int i = m / TN, j = i & 1 ? TN - 1 - m % TN : m % TN;
+                mfma16_acc(acc[i][j], fr[C][ks][TM + j], fr[C][ks][i]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        slot = next(slot);
+        ++u;
+    };
+    const auto last_stage = [&](auto set) {
+        ring_wait_steps<LPS, S>(min(u == 0 ? S - 1 : u + S, nv - 1) - (u + 3));
+        if (u == 0 && S < nv) load_any(line_of(S), 0);
+        if (u + 1 + S < nv) load_any(line_of(u + 1 + S), slot);
+        stage(set, std::false_type());
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    last_stage(even);
+    const int whole = nv - 2 - S;   // stages below this one load lines in the middle
+    while (u + 1 < whole) {
+        ring_wait<(S - 3) * LPS>();
+        stage(odd, std::true_type());
+        ring_wait<(S - 3) * LPS>();
+        stage(even, std::true_type());
+    }
+    while (u < nk) {
+        last_stage(odd);
+        if (u == nk) break;
+        last_stage(even);
+    }
+    mfma16_settle(acc);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    ring_store<BM, BN, TM, TN, F32>(g, acc, m0, n0, wm, wn, reinterpret_cast<float *>(ring));
+}
+
 // LDS stage: A [64][BM] | B [64][BN] bf16 as in memory; fragments are read with the transposing load: lane (hq, i) supplies k
 // row 8 hq + (i >> 2) (and + 4) of the 32-row slice, 8 bytes at column 4 (i & 3) of the block's 16.  Half a wave reads rows 0 .. 3
 // and 8 .. 11, 32 bytes each: 32-byte column group c of row r sits at group position c ^ ring_swz(r), which puts those
@@ -593,6 +748,20 @@ hipError_t launch_nt_one(const GemmArgs &g, int first, hipStream_t s) {
     hipLaunchKernelGGL((ring_nt_kernel<BM, BN, S, F32, TAIL>), dim3((unsigned)blocks), dim3(256), lds, s, g, tiles_m, tiles_n, first);
     return hipGetLastError();
 }
+template <int BM, int BN, int S, bool F32>
+hipError_t launch_line_one(const GemmArgs &g, hipStream_t s) {
+    static std::atomic<bool> attr{false};
+    constexpr size_t lds = (size_t)S * (BM + BN) * 128;
+    const hipError_t e = ensure_lds(line_nt_kernel<BM, BN, S, F32>, lds, &attr);
+    if (e != hipSuccess) return e;
+    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    hipLaunchKernelGGL((line_nt_kernel<BM, BN, S, F32>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, s, g, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+template <int BM, int BN, int S>
+hipError_t launch_line(const GemmArgs &g, hipStream_t s) {
+    return g.out_fp32 ? launch_line_one<BM, BN, S, true>(g, s) : launch_line_one<BM, BN, S, false>(g, s);
+}
 template <int BM, int BN, int S>
 hipError_t launch_nt(const GemmArgs &g, int first, hipStream_t s) {
     if (g.K % RK) return g.out_fp32 ? launch_nt_one<BM, BN, S, true, true>(g, first, s) : launch_nt_one<BM, BN, S, false, true>(g, first, s);
@@ -626,6 +795,9 @@ hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t
         case RingTile::t128x128: return launch_nt<128, 128, 3>(g, first, s);
         case RingTile::t128x64: return launch_nt<128, 64, 3>(g, first, s);
         case RingTile::t64x64: return launch_nt<64, 64, 3>(g, first, s);
+        case RingTile::l128x128: return launch_line<128, 128, 5>(g, s);
+        case RingTile::l128x64: return launch_line<128, 64, 6>(g, s);
+        case RingTile::l64x64: return launch_line<64, 64, 5>(g, s);
         case RingTile::s128x64: return launch_share<8, 4, 4, 1>(g, s);
         case RingTile::s64x64: return launch_share<4, 4, 4, 2>(g, s);
         case RingTile::s32x64: return launch_share<2, 4, 8, 1>(g, s);

@@ -69,3 +69,33 @@ def test_no_accumulator_is_touched_too_early():
         for source, text in zip(("gemm.hip", "gemm_ring.hip"), ex.map(assembly, ("gemm.hip", "gemm_ring.hip"))):
             assert "v_mfma_f32_16x16x32_bf16" in text
             assert findings(text) == [], source
+
+
+def set_too_late(assembly):
+    """(function, instruction) for every product whose accumulator a vector instruction wrote less than two wait states before."""
+    out, function, writes = [], None, []
+    for line in assembly.split("\n"):
+        if m := re.match(r"(_Z\w+):", line):
+            function, writes = m.group(1), []
+            continue
+        text = line.split(";")[0].strip()
+        if not text or text.startswith(".") or text.endswith(":"):
+            continue
+        op, _, rest = text.partition(" ")
+        args = [a.strip() for a in rest.split(",")]
+        if op.startswith("v_mfma") and any(w & registers(args[3]) and d < 2 for d, w in writes):
+            out.append((function, text))
+        states = int(args[0]) + 1 if op == "s_nop" else 1
+        writes = [(d + states, w) for d, w in writes if d + states < 2]
+        if op.startswith("v_") and not op.startswith("v_mfma"):
+            writes.append((0, registers(args[0].split(" ")[0])))
+    return out
+
+
+def test_no_accumulator_is_set_too_late():
+    late = "_Z1k:\n v_accvgpr_write_b32 a0, 0\n v_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n"
+    assert set_too_late(late) != [] and set_too_late(late.replace("0\n", "0\n s_nop 1\n")) == []
+    for source in ("gemm.hip", "gemm_ring.hip"):
+        text = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-o", "-", os.path.join(build.CSRC, source)], capture_output=True, text=True,
+                              check=True).stdout
+        assert set_too_late(text) == [], source
