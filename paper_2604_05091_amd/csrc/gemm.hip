@@ -998,14 +998,16 @@ static double straddling_rows(const bf16_t *p, int64_t ld) {
 }
 // Such stages take 1 + kStraddle times that share longer (K % 64 = 32: 1.20, 16 and 48: 1.32, odd multiples of 8: 1.38 measured on 2000 x 1024 x 2816 ..
 // 4096 x 4096 x 14 976).  Fitted, with the line kernels' figures, to 420 shapes of down and weight-gradient products, heads and their gradients (K 128 ..
-// 24 000, operands from memory, compared with the kernels that the rules above choose): the choice is within 0.6 % of the best on average, 1.07 times faster than
-// without line kernels, nowhere more than 5 % slower.  us: 2048 x 2048 x 10 008 138 -> 97, 5120 x 2048 x 4008 139 -> 108, 2000 x 2048 x 5528 66 -> 54,
-// 1024 x 2816 x 3000 32.5 -> 25.7, 1536 x 1024 x 3000 24.7 -> 19.3; but 8000 x 2048 x 5520 keeps 256 x 256 tiles, 166 (207).  A shared reduction stays shared.
+// 24 000, operands from memory, compared with the kernels that the rules above choose), so that the choice is nowhere more than 1 % slower than without line
+// kernels.  us: 2048 x 2048 x 10 008 138 -> 97, 2000 x 2048 x 5528 66 -> 54, 1024 x 2816 x 3000 32.5 -> 25.7; in a chain of products, where operands come
+// from the caches, less: the MLP of 512 tokens, 4160 x 12 400, forward 259 -> 231, a head of 3008 tokens, 640 x 1080 49.8 -> 47.8, most others even.  Products
+// that 256 x 256 tiles take keep them: they would gain up to 1.3 times alone (5120 x 2048 x 4008 139 -> 108) and lose 1 % in a chain under the power
+// limit (the projections of 2 x 1480 tokens, 3136 wide, 922 -> 931 us).  A shared reduction stays shared.
 constexpr double kStraddle = 0.40;
 constexpr int kLineStages = 10;   // (they start later: 256 x 256 x 472 4.9 us, 5.2 with them)
-static const TileCost kLineCosts[] = {{RingTile::l128x128, 128, 128, 1, 0.20, 0.48, 4.9, 0.0},
-                                      {RingTile::l128x64, 128, 64, 1, 0.32, 0.304, 2.9, 0.0},
-                                      {RingTile::l64x64, 64, 64, 2, 0.24, 0.194, 2.75, 0.85}};
+static const TileCost kLineCosts[] = {{RingTile::l128x128, 128, 128, 1, 0.40, 0.48, 4.0, 0.0},
+                                      {RingTile::l128x64, 128, 64, 1, 0.30, 0.28, 2.7, 0.0},
+                                      {RingTile::l64x64, 64, 64, 2, 0.22, 0.175, 3.0, 0.9}};
 
 // What takes an NT product without a fused store: the first `whole` tiles of 256 x 256 in the tile order the kernel above, the others
 // that of `tile` (null: there are none).
@@ -1030,28 +1032,23 @@ static NtRoute nt_route(const GemmArgs &g, int32_t of_rows = 0) {
     const double tiles = tile_count(costs[0], g.M, g.N);
     const int whole = (int)(std::floor(tiles / kRound) * kRound), rest = (int)tiles - whole;
     NtRoute route = one.tile == RingTile::none ? NtRoute{(int)tiles, nullptr} : NtRoute{0, &kNtCosts[&one - costs]};
-    const auto with_rest = [&](const TileCost &big, const TileCost &c, double slower) {
-        return tile_time(big, whole, stages * slower, kComputeUnits) + 3.0 + tile_time(c, (double)rest * (256 / c.bm) * (256 / c.bn), stages * slower, kComputeUnits);
-    };
     if (g.K >= BK && whole > 0 && rest > 0) {
         double best_t = 0.97 * tn_time(one, g.M, g.N, stages, 1, kComputeUnits);
         for (int i = 1; i < (int)std::size(kNtCosts); ++i) {
-            const double t = with_rest(costs[0], kNtCosts[i], 1.0);
+            const TileCost &c = kNtCosts[i];
+            const double t = tile_time(costs[0], whole, stages, kComputeUnits) + 3.0 +
+                             tile_time(c, (double)rest * (256 / c.bm) * (256 / c.bn), stages, kComputeUnits);
             if (t < best_t) {
                 best_t = t;
-                route = {whole, &kNtCosts[i]};
+                route = {whole, &c};
             }
         }
     }
-    if (straddle > 1.0) {
-        // Instead of 256 x 256 tiles only by a clear margin, with results whose rows are aligned, up to 256 stages (8192 x 1152 x 25 648 677 -> 717 us), and not
-        // with a last round that is nearly empty.
-        const bool big = route.whole > 0, rows = !(g.ldc & (g.out_fp32 ? 3 : 7)) && !((uintptr_t)g.C & 15);
-        double best_t = (big ? 0.93 : 0.97) * (big && route.tile ? with_rest(costs[0], *route.tile, straddle) : tn_time(one, g.M, g.N, stages * straddle, 1, kComputeUnits));
+    if (straddle > 1.0 && route.whole == 0) {
+        double best_t = 0.92 * tn_time(one, g.M, g.N, stages * straddle, 1, kComputeUnits);
         for (const TileCost &c : kLineCosts) {
             const double t = tn_time(c, g.M, g.N, stages, 1, kComputeUnits);
-            const int last = (int)std::fmod(tile_count(c, g.M, g.N), kRound);
-            if (t < best_t && (!big || (rows && stages <= 256 && (last == 0 || last >= kRound / 10)))) {
+            if (t < best_t) {
                 best_t = t;
                 route = {0, &c};
             }
