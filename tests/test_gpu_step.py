@@ -15,7 +15,7 @@ import mt_inputs
 import paper_2604_05091_amd as mt
 from gpu_util import cosine, rel_l2
 from mt_inputs import ModelShape
-from paper_2604_05091_amd.binding import KIND_ADAM_M, KIND_ADAM_V, ModelCfg
+from paper_2604_05091_amd.binding import FLAG_GRAD_SLABS, FLAG_STAGED_WEIGHTS, KIND_ADAM_M, KIND_ADAM_V, ModelCfg
 
 pytestmark = pytest.mark.gpu
 
@@ -123,6 +123,36 @@ def test_overlapped_adam_equals_separate_calls_bitwise():
                 assert np.array_equal(ha.tensor(i), hb.tensor(i))
         assert hb.stats()["adam_ms"] > 0
     assert not np.array_equal(pa[1], params[1])
+
+
+@pytest.mark.parametrize("flags", [0, FLAG_GRAD_SLABS, FLAG_STAGED_WEIGHTS])
+@pytest.mark.parametrize("vocab,sub", [(8264, None), (8320, 1000), (8328, 70000)])
+def test_rows_of_the_table_without_a_token_are_updated_ahead(monkeypatch, vocab, sub, flags):
+    """A table of more than 2^20 elements without a token in their row: those rows are updated before any gradient has arrived, the others as it lands, in pieces
+    that cut through rows and runs of rows.  The first and the last row with and without a token, runs longer than a piece, single rows; three steps
+    with other tokens equal the separate calls bitwise."""
+    shape = ModelShape(1, 128, 2, 2, 64, 136, vocab)
+    params = mt_inputs.make_params(shape, seed=41, std=0.05)
+    pa, pb = [p.copy() for p in params], [p.copy() for p in params]
+    rng = np.random.default_rng(vocab)
+    with mt.TrainHandle(make_cfg(shape, 1, 64, flags=flags), pa) as ha, mt.TrainHandle(make_cfg(shape, 1, 64, flags=flags), pb) as hb:
+        for step in (1, 2, 3):
+            tok = rng.integers(11, vocab - 1, (1, 64)).astype(np.int32)
+            lab = rng.integers(0, vocab, (1, 64)).astype(np.int32)
+            tok[0, :6] = [7, 8, 8, 10, 4000, 4002]
+            tok[0, 6:8] = [0, 5] if step == 2 else [1, vocab - 1]
+            assert (vocab - len(np.unique(tok))) * 128 >= 1 << 20 and (0 in tok) == (step == 2)
+            monkeypatch.delenv("MT_SUBPIECE_ELEMS", raising=False)
+            la = ha.train_step(tok, lab)
+            ha.adam_step(3e-4, wd=0.01, step=step)
+            if sub:
+                monkeypatch.setenv("MT_SUBPIECE_ELEMS", str(sub))
+            assert hb.train_step_adam(tok, lab, 3e-4, wd=0.01, step=step) == la
+            for i, (a, b) in enumerate(zip(pa, pb)):
+                assert np.array_equal(a, b), (step, i)
+                for kind in (KIND_ADAM_M, KIND_ADAM_V):
+                    assert np.array_equal(ha.tensor(i, kind), hb.tensor(i, kind)), (step, i)
+                assert np.array_equal(ha.tensor(i), hb.tensor(i)), (step, i)
 
 
 def test_gradient_pieces_in_sub_ranges_give_the_same_update(monkeypatch):
