@@ -62,6 +62,10 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 __device__ __forceinline__ void mfma16_acc(f32x4 &acc, const bf16x8 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+// the same with the accumulator among the vector registers (there are 256 of either kind, and a wave that is alone on its SIMD may use all)
+__device__ __forceinline__ void mfma16_acc_v(f32x4 &acc, const bf16x8 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
 // every accumulator has been written (16 wait states, the slowest of these instructions needs 11) and may be read
 __device__ __forceinline__ void mfma16_drain() {
     __builtin_amdgcn_sched_barrier(0);
@@ -209,7 +213,8 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s, int32_t of_rows = 0);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
 // has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced; every
 // output is the sum of at least partial_sums partial sums.
-enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, l128x128, l128x64, l64x64, s128x64, s64x64, s32x64, s32x32 };   // s...: reductions shared among waves, NT only, first < 0
+// l...: rows that are not whole lines, s...: reductions shared among waves (both NT only, first < 0); wide: gemm_nt's own 256 x 320.
+enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, l128x128, l128x64, l64x64, wide, s128x64, s64x64, s32x64, s32x32 };
 // first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
 hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
 hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s);
