@@ -213,8 +213,8 @@ hipError_t gemm_nt(const GemmArgs &g, hipStream_t s, int32_t of_rows = 0);
 // The kernels with smaller tiles behind gemm_nt and gemm_tn (same arguments, no fused rotary / SwiGLU stores; the caller
 // has checked the operands).  gemm_nt_ring takes any K % 8 == 0; gemm_tn_ring leaves the chunks of a split unreduced; every
 // output is the sum of at least partial_sums partial sums.
-// l...: rows that are not whole lines, s...: reductions shared among waves (both NT only, first < 0); wide: gemm_nt's own 256 x 320.
-enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, l128x128, l128x64, l64x64, wide, s128x64, s64x64, s32x64, s32x32 };
+// l...: rows that are not whole lines, s...: reductions shared among waves (both NT only, first < 0); wide...: gemm_nt's own 256 x 320, 256 x 192.
+enum class RingTile { none, t256x128, t128x128, t128x64, t64x64, l128x128, l128x64, l64x64, wide320, wide192, s128x64, s64x64, s32x64, s32x32 };
 // first >= 0: only the 256 x 256 tiles from position `first` of that kernel's tile order on (gemm_nt has covered the others).
 hipError_t gemm_nt_ring(const GemmArgs &g, RingTile tile, int first, hipStream_t s);
 hipError_t gemm_tn_ring(const GemmArgs &g, RingTile tile, int partial_sums, hipStream_t s);

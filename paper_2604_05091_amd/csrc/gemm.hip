@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <cmath>
 #include <iterator>
+#include <type_traits>
 
 #include "common.h"
 
@@ -518,29 +519,24 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_w4e_kernel(GemmArgs g, int tile
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same in tiles of 256 x 320, bf16 results, for widths that are multiples of 320 and grids that 256 x 256 tiles fill badly: 4096 x 5120 is one
-// round of these and 1.25 of those.  4 waves x 128 x 160: 80 accumulators of which 64 lie in the accumulation registers and 16 (columns 128 .. 159 of the
-// wave) among the vector registers, where the fragments leave room because a column block's fragment is given up before the other slice's are all there
-// (the blocks are walked column by column).  Two slots of 72 KB.  Loads, waits and reads as above: 18 of each to a slice's 80 MFMAs, one per four.
-// The results leave in two halves of 64 rows.
-constexpr int WX_BN = 320, WX_A = 256 * 64 * 2, WX_SLOT = WX_A + WX_BN * 64 * 2, WX_PITCH = 160 + 8;
-static_assert(2 * 64 * WX_PITCH * 2 <= WX_SLOT, "two staging blocks in a slot");
+// The same in tiles of 256 x 32 NB, bf16 results, for grids that 256 x 256 tiles fill badly.  NB = 10: 4096 x 5120 is one round of 256 x 320 and 1.25 of 256 x 256;
+// NB = 6: 1000 x 11008 fills 0.91 of a round of 256 x 192 and 0.67 of one of 256 x 256.  4 waves x 128 x 16 NB.  NB = 10 has 80 accumulators, of which 64 lie in
+// the accumulation registers and 16 (columns 128 .. 159 of the wave) among the vector registers, where the fragments leave room because a column block's
+// fragment is given up before the other slice's are all there (the blocks are walked column by column).  Two slots of 72 (56) KB.  Loads, waits and reads as
+// above, spread evenly over a slice's MFMAs.  The results leave in two halves of 64 rows; columns are whole groups of 8.
+template <int NB>
+struct Wide {
+    static constexpr int BN = 32 * NB, A = 256 * 64 * 2, SLOT = A + BN * 64 * 2, COLS = 16 * NB, PITCH = COLS + 8, LB = BN / 32, N = 8 + LB;   // N: loads, and reads, of a wave
+    static constexpr int GROUPS = 2 * NB;   // of four MFMAs in a slice
+    static_assert(2 * 64 * PITCH * 2 <= SLOT, "two staging blocks in a slot");
+};
 
-// MFMAs 4 U .. 4 U + 3 of a slice's 80
-template <int U>
-__device__ __forceinline__ void wx_mfma_group(f32x4 (&acc)[8][8], f32x4 (&accv)[8][2], const bf16x8 (&fr)[18]) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int m = 4 * U + e, j = m / 8, i = j & 1 ? 7 - m % 8 : m % 8;
-        if (j < 8) mfma16_acc(acc[i][j < 8 ? j : 0], fr[8 + j], fr[i]);
-        else mfma16_acc_v(accv[i][j < 8 ? 0 : j - 8], fr[8 + j], fr[i]);
-    }
-}
-
-template <bool BIAS, bool RES>
+template <int NB, bool BIAS, bool RES>
 __global__ __launch_bounds__(W4_NT) void gemm_nt_wide_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    __shared__ __attribute__((aligned(1024))) char sl0[WX_SLOT];
-    __shared__ __attribute__((aligned(1024))) char sl1[WX_SLOT];
+    using W = Wide<NB>;
+    constexpr int NA = NB < 8 ? NB : 8, NV = NB - NA;   // column blocks with accumulators of either kind
+    __shared__ __attribute__((aligned(1024))) char sl0[W::SLOT];
+    __shared__ __attribute__((aligned(1024))) char sl1[W::SLOT];
     typedef __attribute__((address_space(3))) void *lptr;
     int pid = blockIdx.x;
     {
@@ -549,125 +545,120 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_wide_kernel(GemmArgs g, int til
     }
     int tm, tn;
     gemm_tile_of(pid, tiles_m, tiles_n, g.group_m, &tm, &tn);
-    const int m0 = tm * W4_BM, n0 = tn * WX_BN;
+    const int m0 = tm * W4_BM, n0 = tn * W::BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, hq = lane >> 4;
 
-    // loader: wave w fills rows 64 w .. of the A part and 80 w .. of the B part of a slot, 8 rows per load
+    // loader: wave w fills rows 64 w .. of the A part and 8 LB w .. of the B part of a slot, 8 rows per load; rows past the edge re-read the last one
     const bf16_t *abase = g.A + (int64_t)m0 * g.lda, *bbase = g.B + (int64_t)n0 * g.ldb;
-    uint32_t off[18];   // byte offsets from abase (0..7) / bbase (8..17)
+    uint32_t off[W::N];   // byte offsets from abase (0..7) / bbase
 #pragma unroll
-    for (int j = 0; j < 18; ++j) {
-        const int r = j < 8 ? wave * 64 + j * 8 + (lane >> 3) : wave * 80 + (j - 8) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
-        off[j] = (uint32_t)((j < 8 ? min(r, g.M - 1 - m0) * (int)g.lda : r * (int)g.ldb) + chunk * 8) * 2u;
+    for (int j = 0; j < W::N; ++j) {
+        const int r = j < 8 ? wave * 64 + j * 8 + (lane >> 3) : wave * (8 * W::LB) + (j - 8) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((r >> 1) & 7);
+        off[j] = (uint32_t)((j < 8 ? min(r, g.M - 1 - m0) * (int)g.lda : min(r, g.N - 1 - n0) * (int)g.ldb) + chunk * 8) * 2u;
     }
-    const uint32_t fill_a = (uint32_t)(wave * 64 * 128), fill_b = (uint32_t)(WX_A + wave * 80 * 128);
+    const uint32_t fill_a = (uint32_t)(wave * 64 * 128), fill_b = (uint32_t)(W::A + wave * 8 * W::LB * 128);
     uint32_t rda[2], rdb[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         const uint32_t pos = (uint32_t)(((4 * ks + hq) ^ ((l16 >> 1) & 7)) * 16);
         rda[ks] = (uint32_t)((wm * 128 + l16) * 128) + pos;
-        rdb[ks] = (uint32_t)(WX_A + (wn * 160 + l16) * 128) + pos;
+        rdb[ks] = (uint32_t)(W::A + (wn * W::COLS + l16) * 128) + pos;
     }
-    bf16x8 fr[2][18];   // [set][A block 0..7 | B block 0..9]
-    f32x4 acc[8][8], accv[8][2];
+    bf16x8 fr[2][W::N];   // [set][A block 0..7 | B blocks]
+    f32x4 acc[8][NA], accv[8][NV > 0 ? NV : 1];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NA; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 2; ++j) accv[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NV; ++j) accv[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-#define WX_LOAD1(SLOT, J, T)                                                                            \
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"                       \
-                 :                                                                                      \
-                 : "v"(off[J]), "s"(((J) < 8 ? abase : bbase) + (T) * 64),                              \
-                   "s"((uint32_t)(uintptr_t)(lptr)(SLOT) + ((J) < 8 ? fill_a + (J) * 1024u : fill_b + ((J) - 8) * 1024u)) \
-                 : "memory")
-#define WX_READ1(SET, SLOT, KS, IDX)                                                                    \
-    fr[SET][IDX] = *reinterpret_cast<const bf16x8 *>((SLOT) + ((IDX) < 8 ? rda[KS] + (IDX) * 2048 : rdb[KS] + ((IDX) - 8) * 2048))
-#define WX_WAIT(N) asm volatile("s_waitcnt vmcnt(" #N ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
-    // (the first B fragments and all of A are what the next slice starts with)
-#define WX_GROUP(SET, RSET, RSLOT, KS, U, LD, LSLOT, TL)                                                \
-    {                                                                                                   \
-        if (LD && (U) < 18) WX_LOAD1(LSLOT, (U) < 18 ? (U) : 0, TL);                                    \
-        if ((U) < 18) WX_READ1(RSET, RSLOT, KS, (U) < 18 ? (U) : 0);                                    \
-        wx_mfma_group<U>(acc, accv, fr[SET]);                                                           \
-        __builtin_amdgcn_sched_barrier(0);                                                              \
-    }
-#define WX_FOUR(SET, RSET, RSLOT, KS, U, LD, LSLOT, TL)                                                 \
-    WX_GROUP(SET, RSET, RSLOT, KS, U, LD, LSLOT, TL); WX_GROUP(SET, RSET, RSLOT, KS, (U) + 1, LD, LSLOT, TL); \
-    WX_GROUP(SET, RSET, RSLOT, KS, (U) + 2, LD, LSLOT, TL); WX_GROUP(SET, RSET, RSLOT, KS, (U) + 3, LD, LSLOT, TL)
-#define WX_SLICE(SET, RSET, RSLOT, KS, LD, LSLOT, TL)                                                   \
-    {                                                                                                   \
-        WX_FOUR(SET, RSET, RSLOT, KS, 0, LD, LSLOT, TL); WX_FOUR(SET, RSET, RSLOT, KS, 4, LD, LSLOT, TL); \
-        WX_FOUR(SET, RSET, RSLOT, KS, 8, LD, LSLOT, TL); WX_FOUR(SET, RSET, RSLOT, KS, 12, LD, LSLOT, TL); \
-        WX_FOUR(SET, RSET, RSLOT, KS, 16, LD, LSLOT, TL);                                               \
-    }
-#define WX_STEP(CUR, NXT, T)                                                                            \
-    {                                                                                                   \
-        const int t2_ = at(min((T) + 2, nk - 1));                                                       \
-        WX_SLICE(0, 1, CUR, 1, false, CUR, 0);                                                          \
-        WX_WAIT(0);                                                                                     \
-        WX_SLICE(1, 0, NXT, 0, true, CUR, t2_);                                                         \
-    }
+    const auto load = [&](const char *slot, int j, int t) {   // (as assembly, ordered by hand: see gemm_nt_w4e_kernel)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(off[j]), "s"((j < 8 ? abase : bbase) + t * 64),
+                       "s"((uint32_t)(uintptr_t)(lptr)slot + (j < 8 ? fill_a + j * 1024u : fill_b + (j - 8) * 1024u))
+                     : "memory");
+    };
+    const auto read = [&](auto set, const char *slot, int ks, int f) {
+        fr[set()][f] = *reinterpret_cast<const bf16x8 *>(slot + (f < 8 ? rda[ks] + f * 2048 : rdb[ks] + (f - 8) * 2048));
+    };
+#define WX_WAIT(N) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory")
+    // the products of the slice in `set`, the reads of the next one (out of rslot) and, with lslot, the loads of step t into it
+    const auto slice = [&](auto set, const char *rslot, int ks, auto loads, const char *lslot, int t) {
+        constexpr int C = set();
+#pragma unroll
+        for (int u = 0; u < W::GROUPS; ++u) {
+#pragma unroll
+            for (int f = u * W::N / W::GROUPS; f < (u + 1) * W::N / W::GROUPS; ++f) {
+                if constexpr (loads()) load(lslot, f, t);
+                read(std::integral_constant<int, 1 - C>(), rslot, ks, f);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int m = 4 * u + e, j = m / 8, i = j & 1 ? 7 - m % 8 : m % 8;
+                if (j < NA) mfma16_acc(acc[i][j < NA ? j : 0], fr[C][8 + j], fr[C][i]);
+                else mfma16_acc_v(accv[i][j < NA ? 0 : j - NA], fr[C][8 + j], fr[C][i]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    constexpr std::integral_constant<int, 0> first{};
+    constexpr std::integral_constant<int, 1> second{};
     const int nk = g.K / BK, start = gemm_walk_start(tm, nk);
     const auto at = [&](int t) { return t + start - (t + start >= nk ? nk : 0); };   // k-step walked as number t
-    {
-        const int t0_ = at(0), t1_ = at(min(1, nk - 1));
+    const auto step = [&](const char *cur, const char *nxt, int t) {
+        slice(first, cur, 1, std::false_type(), cur, 0);
+        WX_WAIT(0);
+        slice(second, nxt, 0, std::true_type(), cur, at(min(t + 2, nk - 1)));
+    };
 #pragma unroll
-        for (int j = 0; j < 18; ++j) WX_LOAD1(sl0, j, t0_);
+    for (int j = 0; j < W::N; ++j) load(sl0, j, at(0));
 #pragma unroll
-        for (int j = 0; j < 18; ++j) WX_LOAD1(sl1, j, t1_);
-    }
-    WX_WAIT(18);
+    for (int j = 0; j < W::N; ++j) load(sl1, j, at(min(1, nk - 1)));
+    WX_WAIT(W::N);
 #pragma unroll
-    for (int u = 0; u < 18; ++u) WX_READ1(0, sl0, 0, u);
+    for (int f = 0; f < W::N; ++f) read(first, sl0, 0, f);
     int kt = 0;
     for (; kt + 2 <= nk; kt += 2) {
-        WX_STEP(sl0, sl1, kt);
-        WX_STEP(sl1, sl0, kt + 1);
+        step(sl0, sl1, kt);
+        step(sl1, sl0, kt + 1);
     }
     if (kt < nk) {
-        WX_STEP(sl0, sl1, kt);
+        step(sl0, sl1, kt);
         mfma16_drain();
     }
     WX_WAIT(0);   // the loads requested past the end have landed before the store staging reuses the arrays
-#undef WX_LOAD1
-#undef WX_READ1
 #undef WX_WAIT
-#undef WX_GROUP
-#undef WX_FOUR
-#undef WX_SLICE
-#undef WX_STEP
     mfma16_settle(acc);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(accv[i][j]));
+        for (int j = 0; j < NV; ++j) asm volatile("" : "+v"(accv[i][j]));
 
-    bf16_t *region = reinterpret_cast<bf16_t *>((wave < 2 ? sl0 : sl1) + (wave & 1) * (64 * WX_PITCH * 2));
-    const int col_w = n0 + wn * 160, row_w = m0 + wm * 128;
-    uint2 bv[BIAS ? 10 : 1];
+    bf16_t *region = reinterpret_cast<bf16_t *>((wave < 2 ? sl0 : sl1) + (wave & 1) * (64 * W::PITCH * 2));
+    const int col_w = n0 + wn * W::COLS, row_w = m0 + wm * 128, col_l = col_w + hq * 4;
+    uint2 bv[BIAS ? NB : 1];   // (columns past the last ones re-read these and are not stored)
     if constexpr (BIAS) {
 #pragma unroll
-        for (int j = 0; j < 10; ++j) bv[j] = *reinterpret_cast<const uint2 *>(g.bias + col_w + j * 16 + hq * 4);
+        for (int j = 0; j < NB; ++j) bv[j] = *reinterpret_cast<const uint2 *>(g.bias + min(col_l + j * 16, g.N - 4));
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int i = half * 4 + k;
-            bf16_t *lp = region + (k * 16 + l16) * WX_PITCH + hq * 4;
-            uint2 rv[RES ? 10 : 1];
-            if constexpr (RES) {   // (rows past the last one re-read it and are not stored)
-                const bf16_t *rp = g.R + (int64_t)min(row_w + i * 16 + l16, g.M - 1) * g.ldr + col_w + hq * 4;
+            bf16_t *lp = region + (k * 16 + l16) * W::PITCH + hq * 4;
+            uint2 rv[RES ? NB : 1];
+            if constexpr (RES) {
+                const bf16_t *rp = g.R + (int64_t)min(row_w + i * 16 + l16, g.M - 1) * g.ldr;
 #pragma unroll
-                for (int j = 0; j < 10; ++j) rv[j] = *reinterpret_cast<const uint2 *>(rp + j * 16);
+                for (int j = 0; j < NB; ++j) rv[j] = *reinterpret_cast<const uint2 *>(rp + min(col_l + j * 16, g.N - 4));
             }
 #pragma unroll
-            for (int j = 0; j < 10; ++j) {
-                f32x4 v = j < 8 ? acc[i][j < 8 ? j : 0] : accv[i][j < 8 ? 0 : j - 8];
+            for (int j = 0; j < NB; ++j) {
+                f32x4 v = j < NA ? acc[i][j < NA ? j : 0] : accv[i][j < NA ? 0 : j - NA];
                 if constexpr (BIAS) {
                     v[0] += bflo(bv[j].x); v[1] += bfhi(bv[j].x); v[2] += bflo(bv[j].y); v[3] += bfhi(bv[j].y);
                 }
@@ -679,10 +670,12 @@ __global__ __launch_bounds__(W4_NT) void gemm_nt_wide_kernel(GemmArgs g, int til
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own LDS writes have landed
         bf16_t *C = reinterpret_cast<bf16_t *>(g.C) + (int64_t)(row_w + half * 64) * g.ldc + col_w;
+        constexpr int LPR = 2 * NB;   // lanes of a row
 #pragma unroll 5
-        for (int it = 0; it < 20; ++it) {
-            const int at16 = it * 64 + lane, r = at16 / 20, c = at16 % 20 * 8;
-            if (row_w + half * 64 + r < g.M) *reinterpret_cast<uint4 *>(C + r * g.ldc + c) = *reinterpret_cast<const uint4 *>(region + r * WX_PITCH + c);
+        for (int it = 0; it < LPR; ++it) {
+            const int at16 = it * 64 + lane, r = at16 / LPR, c = at16 % LPR * 8;
+            if (row_w + half * 64 + r < g.M && col_w + c < g.N)
+                *reinterpret_cast<uint4 *>(C + r * g.ldc + c) = *reinterpret_cast<const uint4 *>(region + r * W::PITCH + c);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // and its reads
     }
@@ -716,12 +709,13 @@ hipError_t launch_w4e_epi(const GemmArgs &g, hipStream_t s, int n_tiles = 0) {
 }
 
 bool takes_wide(const GemmArgs &g) {
-    return g.K % BK == 0 && g.N % WX_BN == 0 && !g.out_fp32 && !(g.ldc & 7) && !((uintptr_t)g.C & 15) && (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) &&
+    return g.K % BK == 0 && g.N % 8 == 0 && !g.out_fp32 && !(g.ldc & 7) && !((uintptr_t)g.C & 15) && (!g.R || (!(g.ldr & 3) && !((uintptr_t)g.R & 7))) &&
            !((uintptr_t)g.bias & 7) && !(g.bias && g.R);
 }
+template <int NB>
 hipError_t launch_wide(const GemmArgs &g, hipStream_t s) {
-    const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = g.N / WX_BN;
-    const auto kernel = g.R ? gemm_nt_wide_kernel<false, true> : g.bias ? gemm_nt_wide_kernel<true, false> : gemm_nt_wide_kernel<false, false>;
+    const int tiles_m = (g.M + W4_BM - 1) / W4_BM, tiles_n = (g.N + 32 * NB - 1) / (32 * NB);
+    const auto kernel = g.R ? gemm_nt_wide_kernel<NB, false, true> : g.bias ? gemm_nt_wide_kernel<NB, true, false> : gemm_nt_wide_kernel<NB, false, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_m * tiles_n)), dim3(W4_NT), 0, s, g, tiles_m, tiles_n);
     return hipGetLastError();
 }
@@ -1191,12 +1185,14 @@ static const TileCost kLineCosts[] = {{RingTile::l128x128, 128, 128, 1, 0.40, 0.
                                       {RingTile::l128x64, 128, 64, 1, 0.30, 0.28, 2.7, 0.0},
                                       {RingTile::l64x64, 64, 64, 2, 0.22, 0.175, 3.0, 0.9}};
 
-// 256 x 320 tiles.  A stage takes 1.21 times that of 256 x 256 (its operands are 1.125 times the bytes), the start and the store of a tile longer.  Taken from an
-// estimated gain of 1.5 % on, us with residual: 4096 x 5120 x 5120 (one round instead of 1.25) 155 -> 143, x 7168 210 -> 194, x 27 648 897 -> 774, 8192 x 2560 x 2560
-// 89 -> 80, 5120 x 3840 x 1024 47 -> 42; 65 536 x 5120 x 5120 (16 rounds instead of 20) 2524 -> 2452, x 13 824 6523 -> 6283 (1477 TFLOP/s);
-// 16 384 x 5120 x 5120 even; 2000 x 5120 x 5120 (half a round) 94, 115 here, and 8200 x 2560 x 6400 (1.03 rounds) 213, 301 here, keep theirs.
+// Tiles of 256 x 320 (widths that are multiples of 320) and of 256 x 192 (of 64).  Fitted to 263 plain products of MLPs, projections and heads (K 512 .. 15 000,
+// half a round to eight): taken from an estimated gain of 3 and 4 % on, nowhere slower, 1.02 times faster over all of them (the best choice: 1.024).  us, before ->
+// here: 4096 x 5120 x 5120 (one round of 256 x 320 instead of 1.25) 155 -> 143, x 7168 210 -> 194, x 27 648 897 -> 774, 8192 x 2560 x 2560 89 -> 80, 65 536 x 5120 x 5120
+// (16 rounds instead of 20) 2524 -> 2452, x 13 824 6523 -> 6283 (1477 TFLOP/s); the projections of 5 x 512
+// tokens, 3712 wide, forward (2560 x 11 136 in one round of 256 x 192 and a little of 128 x 128 before) 291 -> 269, in other chains under the power limit even;
+// 2000 x 5120 x 5120 (half a round) 94, in 256 x 320 115, and 8200 x 2560 x 6400 (1.03 rounds) 213, 301, keep theirs.
 constexpr int kWideStages = 8;   // (shorter walks were not looked at)
-static const TileCost kWideCost = {RingTile::wide, 256, WX_BN, 1, 1.20, 1.57, 13.0, 0.0};
+static const TileCost kWideCosts[] = {{RingTile::wide320, 256, 320, 1, 1.03, 1.545, 12.5, 0.0}, {RingTile::wide192, 256, 192, 1, 0.55, 1.09, 9.8, 0.0}};
 
 // What takes an NT product without a fused store: the first `whole` tiles of 256 x 256 in the tile order the kernel above, the others
 // that of `tile` (null: there are none).
@@ -1234,7 +1230,18 @@ static NtRoute nt_route(const GemmArgs &g, int32_t of_rows = 0) {
             }
         }
     }
-    if (takes_wide(g) && stages >= kWideStages && tile_time(kWideCost, tile_count(kWideCost, g.M, g.N), stages, kComputeUnits) < 0.985 * route_t) return {0, &kWideCost};
+    if (takes_wide(g) && stages >= kWideStages) {
+        const TileCost *wide = nullptr;
+        double best_t = route_t;
+        for (const TileCost &c : kWideCosts) {
+            const double t = tile_time(c, tile_count(c, g.M, g.N), stages, kComputeUnits);
+            if (t < best_t && g.N % (c.bn == 320 ? 320 : 64) == 0 && t < (c.bn == 320 ? 0.97 : 0.96) * route_t) {
+                best_t = t;
+                wide = &c;
+            }
+        }
+        if (wide) return {0, wide};
+    }
     if (straddle > 1.0 && route.whole == 0) {
         double best_t = 0.92 * tn_time(one, g.M, g.N, stages * straddle, 1, kComputeUnits);
         for (const TileCost &c : kLineCosts) {
@@ -1268,11 +1275,13 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s, int32_t of_rows) {
         case 2: return gemm_nt_ring(g, RingTile::t256x128, -1, s);
         case 3: return gemm_nt_ring(g, RingTile::t128x128, -1, s);
         case 6: if (g.K >= BK) return launch_w4e(g, s); break;          // 256 x 256 kernel on any grid
-        case 7: if (takes_wide(g)) return launch_wide(g, s); break;
+        case 7: if (takes_wide(g)) return launch_wide<10>(g, s); break;   // 256 x 320
+        case 8: if (takes_wide(g)) return launch_wide<6>(g, s); break;    // 256 x 192
         default: break;
     }
     const NtRoute r = nt_route(g, of_rows);
-    if (r.whole == 0) return r.tile->tile == RingTile::wide ? launch_wide(g, s) : gemm_nt_ring(g, r.tile->tile, -1, s);
+    if (r.whole == 0)
+        return r.tile->tile == RingTile::wide320 ? launch_wide<10>(g, s) : r.tile->tile == RingTile::wide192 ? launch_wide<6>(g, s) : gemm_nt_ring(g, r.tile->tile, -1, s);
     const hipError_t e = launch_w4e(g, s, r.whole);
     return e == hipSuccess && r.tile ? gemm_nt_ring(g, r.tile->tile, r.whole, s) : e;
 }
