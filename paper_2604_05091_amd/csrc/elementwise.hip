@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void embed_gather_kernel(bf16_t *h, const bf16
 // atomics, a fixed order.
 // 65 536 Zipf-distributed tokens, d = 4096, V = 32 000: one block per row with one serial sum 3690 us, this one 239 us with
 // scattered ids and 275 us with ids in order of frequency (1.06 GB: 4.45 and 3.86 TB/s; a copy reaches 4.9); uniform tokens
-// 219 and 213 us.  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
+// 219 and 213 us (over three sets of buffers in turn: 326, 327 and 214; with the column ranges side by side 309, 282 and 216).  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
 constexpr int kScatterWaves = 8, kScatterShort = 32;
 
 __device__ __forceinline__ void scatter_add(float *a, const uint4 &v) {
@@ -459,15 +459,19 @@ __device__ __forceinline__ void scatter_terms(float (*acc)[8], const bf16_t *dh,
         for (int j = 0; j < NC; ++j) scatter_add(acc[j], v[u][j]);
 }
 
-// ADD: on top of what the table's gradient holds already (rows without a token are then left alone)
-template <int NC, bool ADD>
+// ADD: on top of what the table's gradient holds already (rows without a token are then left alone).  SIDE: the blocks come by groups of
+// rows, all column ranges of a group side by side; else by column ranges, all groups of one.
+template <int NC, bool ADD, bool SIDE>
 __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float *dtable, const bf16_t *dh,
                                                                            const int32_t *row_start, const int32_t *order,
-                                                                           int V, int d) {
+                                                                           int V, int d, int groups) {
     __shared__ float part[kScatterWaves - 1][8][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gx = gridDim.x / NC, x = blockIdx.x / NC, share = blockIdx.x % NC;
-    const int col = blockIdx.y * (512 * NC) + lane * 8;
+    const int x = SIDE ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.x / NC, share = blockIdx.x % NC;
+    const int gx = SIDE ? groups : gridDim.x / NC;
+    if (SIDE && x >= gx) return;
+    const int y = SIDE ? (blockIdx.x / NC + x) % (gridDim.x / NC) : blockIdx.y;   // (turned, so that a narrow last range comes to every XCD)
+    const int col = y * (512 * NC) + lane * 8;
     // which of the group's rows are long: one row per lane, so that the usual block does not pay for looking
     int g_beg = 0, g_cnt = 0;
     if (lane < NC * kScatterWaves && x + lane * gx < V) {
@@ -795,10 +799,20 @@ hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_sta
     // 297 / 260 / 213 / 217
     const auto blocks = [&](int nc) { return (int64_t)((V + 7) / 8) * ((d + 512 * nc - 1) / (512 * nc)); };
     const int nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
-    const dim3 grid(nc * blocks_for(V, kScatterWaves * nc), blocks_for(d, 512 * nc)), block(64 * kScatterWaves);
-    auto kernel = nc == 1 ? embed_scatter_kernel<1, false> : nc == 2 ? embed_scatter_kernel<2, false> : embed_scatter_kernel<4, false>;
-    if (add) kernel = nc == 1 ? embed_scatter_kernel<1, true> : nc == 2 ? embed_scatter_kernel<2, true> : embed_scatter_kernel<4, true>;
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d);
+    const int gx = (int)blocks_for(V, kScatterWaves * nc);
+    const unsigned ny = blocks_for(d, 512 * nc), gy = std::min(gx, 1 << 15);
+    // Several column ranges come side by side: by ranges, the heavy rows of the later ones begin late, and all shares of such a row fall on NC XCDs.
+    // Zipf-distributed ids in order of frequency, by ranges -> side by side, us: 65 536 tokens, V = 32 000, d = 4096 328 -> 284 (uniform ids
+    // 215 -> 217), d = 5120 418 -> 345, 4096 tokens, V = 1024, d = 4096 30.2 -> 21-23.  Not where narrow blocks come out even or as the better
+    // end: with one whole range and a narrower one (65 536, 32 000, 2560) 309 with the lookup, side by side 323; 8192, 4000, 3584 (NC = 2) 60.7,
+    // 61.6; nor two ranges of NC = 2 (4096, 1500, 2048: 18.1, 18.7) and NC = 1, tables small enough to be at work all at once.
+    const bool side = nc == 4 ? d >= 2 * 512 * nc : nc == 2 && d > 2 * 512 * nc && d % (512 * nc) == 0;
+    const dim3 grid = side ? dim3(nc * ny, gy, blocks_for(gx, gy)) : dim3(nc * gx, ny), block(64 * kScatterWaves);
+    auto kernel = nc == 1 ? embed_scatter_kernel<1, false, false> : nc == 2 ? embed_scatter_kernel<2, false, false> : embed_scatter_kernel<4, false, false>;
+    if (add) kernel = nc == 1 ? embed_scatter_kernel<1, true, false> : nc == 2 ? embed_scatter_kernel<2, true, false> : embed_scatter_kernel<4, true, false>;
+    if (side && nc == 2) kernel = add ? embed_scatter_kernel<2, true, true> : embed_scatter_kernel<2, false, true>;
+    if (side && nc == 4) kernel = add ? embed_scatter_kernel<4, true, true> : embed_scatter_kernel<4, false, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d, gx);
     return hipGetLastError();
 }
 
