@@ -421,7 +421,8 @@ __global__ __launch_bounds__(256) void embed_gather_kernel(bf16_t *h, const bf16
 // atomics, a fixed order.
 // 65 536 Zipf-distributed tokens, d = 4096, V = 32 000: one block per row with one serial sum 3690 us, this one 239 us with
 // scattered ids and 275 us with ids in order of frequency (1.06 GB: 4.45 and 3.86 TB/s; a copy reaches 4.9); uniform tokens
-// 219 and 213 us (over three sets of buffers in turn: 326, 327 and 214; with the column ranges side by side 309, 282 and 216).  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
+// 219 and 213 us (over three sets of buffers in turn: 326, 327 and 214; with the column ranges side by side and
+// whole lines per store ids in order of frequency 269, uniform ones 211).  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
 constexpr int kScatterWaves = 8, kScatterShort = 32;
 
 __device__ __forceinline__ void scatter_add(float *a, const uint4 &v) {
@@ -430,17 +431,28 @@ __device__ __forceinline__ void scatter_add(float *a, const uint4 &v) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) a[k] += f[k];
 }
+// A lane's 8 sums as fp32.  Lanes 2 k and 2 k + 1 exchange halves, so that the 8 lanes that loaded a line of dh (in the order 0, 4, 1, 5, ..) store a
+// whole line each time, past the caches: with 32 bytes per lane every store covered half of each line.  us, before -> here: 16 384 Zipf tokens, 32 000 x
+// 4096 193 -> 157, 65 536 tokens, 152 064 x 4096 832 -> 682, 4096 tokens, 16 000 x 768 26 -> 12.5; of these the caches' share 7, 23, 0.
+// o: where the lane's first four go, left: columns from there to the end of the row.
 template <bool ADD>
-__device__ __forceinline__ void scatter_store(float *o, const float *acc) {
-    float4 *p = reinterpret_cast<float4 *>(o);
-    float4 a = make_float4(acc[0], acc[1], acc[2], acc[3]), b = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    if (ADD) {
-        const float4 x = p[0], y = p[1];
-        a = make_float4(x.x + a.x, x.y + a.y, x.z + a.z, x.w + a.w);
-        b = make_float4(y.x + b.x, y.y + b.y, y.z + b.z, y.w + b.w);
+__device__ __forceinline__ void scatter_store(float *o, const float *acc, int left) {
+    const bool odd = threadIdx.x & 1;
+    float a[2][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float give = odd ? acc[k] : acc[4 + k];
+        const float got = __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(give), 0xb1, 0xf, 0xf, true));   // quad_perm 1, 0, 3, 2
+        a[0][k] = odd ? got : acc[k];
+        a[1][k] = odd ? acc[4 + k] : got;
     }
-    p[0] = a;
-    p[1] = b;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (32 * h >= left) return;
+        f32x4 *p = reinterpret_cast<f32x4 *>(o + 32 * h), v = {a[h][0], a[h][1], a[h][2], a[h][3]};
+        if (ADD) v = *p + v;
+        __builtin_nontemporal_store(v, p);
+    }
 }
 
 // NR terms r[0..NR) of the list, added to acc[j] (columns col + 512 j) in order
@@ -471,7 +483,8 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
     const int gx = SIDE ? groups : gridDim.x / NC;
     if (SIDE && x >= gx) return;
     const int y = SIDE ? (blockIdx.x / NC + x) % (gridDim.x / NC) : blockIdx.y;   // (turned, so that a narrow last range comes to every XCD)
-    const int col = y * (512 * NC) + lane * 8;
+    const int col0 = y * (512 * NC), col = col0 + (lane >> 3) * 64 + (lane & 1) * 32 + (lane & 6) * 4;   // (what scatter_store wants)
+    const int out0 = (lane >> 3) * 64 + (lane & 7) * 4;
     // which of the group's rows are long: one row per lane, so that the usual block does not pay for looking
     int g_beg = 0, g_cnt = 0;
     if (lane < NC * kScatterWaves && x + lane * gx < V) {
@@ -485,16 +498,19 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
             if (end - beg <= kScatterShort && (!ADD || beg < end)) {
                 float acc[NC][8] = {};
                 int i = beg;
-                for (; i + 1 < end; i += 2) scatter_terms<NC, 2>(acc, dh, order + i, d, col);
+                // 8 loads in flight; two terms at a time whatever NC: 16 384 uniform tokens, 1024 x 1024 (NC = 1) 11.2 us, here 9.2
+                for (; i + 8 / NC <= end; i += 8 / NC) scatter_terms<NC, 8 / NC>(acc, dh, order + i, d, col);
+                if (NC == 1 && i + 4 <= end) scatter_terms<NC, 4>(acc, dh, order + i, d, col), i += 4;
+                if (NC <= 2 && i + 2 <= end) scatter_terms<NC, 2>(acc, dh, order + i, d, col), i += 2;
                 if (i < end) scatter_terms<NC, 1>(acc, dh, order + i, d, col);
 #pragma unroll
                 for (int j = 0; j < NC; ++j)
-                    if (col + 512 * j < d) scatter_store<ADD>(dtable + (int64_t)v * d + col + 512 * j, acc[j]);
+                    scatter_store<ADD>(dtable + (int64_t)v * d + col0 + out0 + 512 * j, acc[j], d - (col0 + out0 + 512 * j));
             }
         }
     }
     const int c = col + 512 * share;
-    if (c - lane * 8 >= d) return;   // uniform over the block
+    if (col0 + 512 * share >= d) return;   // uniform over the block
     for (uint64_t todo = __builtin_amdgcn_ballot_w64(g_cnt > kScatterShort); todo; todo &= todo - 1) {   // the same in every wave
         const int w = __builtin_ctzll(todo), v = x + w * gx;
         const int beg = __builtin_amdgcn_readlane(g_beg, w), cnt = __builtin_amdgcn_readlane(g_cnt, w);
@@ -529,7 +545,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
             for (int q = 0; q < kScatterWaves - 1; ++q)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) acc[0][k] += part[q][k][lane];
-            if (c < d) scatter_store<ADD>(dtable + (int64_t)v * d + c, acc[0]);
+            scatter_store<ADD>(dtable + (int64_t)v * d + col0 + out0 + 512 * share, acc[0], d - (col0 + out0 + 512 * share));
         }
         __syncthreads();
     }
