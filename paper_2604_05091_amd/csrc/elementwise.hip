@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256) void embed_gather_kernel(bf16_t *h, const bf16
 // Gradient of the table: row v of dtable = sum of the dh rows listed for token v.  HBM-bound (every dh row read once,
 // every table row written once), if the rows of frequent tokens do not become a serial chain: token ids in text follow
 // Zipf's law, so at 65 536 tokens one row has some 2000 terms while most have none to three.
-// NC blocks of 8 waves share 8 NC rows (x, x + gridDim.x, ...: tokenizers give frequent words neighbouring ids) of
+// NC blocks of 8 waves share 8 NC rows (x, x + groups, ...: tokenizers give frequent words neighbouring ids) of
 // NC x 512 columns.  Rows of up to kScatterShort terms: a wave sums one row in list order over all NC x 512 columns, so
 // that the chain row_start -> list -> dh is paid once for 4 KB.  Longer rows: every block sums its own 512 columns with
 // all waves, wave w taking the w-th eighth of the list, 16 loads in flight, and the 8 sums are added in wave order.  No
@@ -422,8 +422,8 @@ __global__ __launch_bounds__(256) void embed_gather_kernel(bf16_t *h, const bf16
 // 65 536 Zipf-distributed tokens, d = 4096, V = 32 000: one block per row with one serial sum 3690 us, this one 239 us with
 // scattered ids and 275 us with ids in order of frequency (1.06 GB: 4.45 and 3.86 TB/s; a copy reaches 4.9); uniform tokens
 // 219 and 213 us (over three sets of buffers in turn: 326, 327 and 214; with the column ranges side by side and
-// whole lines per store ids in order of frequency 269, uniform ones 211).  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
-constexpr int kScatterWaves = 8, kScatterShort = 32;
+// whole lines per store ids in order of frequency 269, uniform ones 211; the heaviest rows first 265, 214).  Without sharing (every block its own 512 columns of 8 rows) uniform tokens took 370 us.
+constexpr int kScatterWaves = 8, kScatterShort = 32, kScatterHeavy = 256, kScatterLook = 4;
 
 __device__ __forceinline__ void scatter_add(float *a, const uint4 &v) {
     float f[8];
@@ -476,22 +476,32 @@ __device__ __forceinline__ void scatter_terms(float (*acc)[8], const bf16_t *dh,
 template <int NC, bool ADD, bool SIDE>
 __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float *dtable, const bf16_t *dh,
                                                                            const int32_t *row_start, const int32_t *order,
-                                                                           int V, int d, int groups) {
+                                                                           int V, int d, int groups, int heavy) {
     __shared__ float part[kScatterWaves - 1][8][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int x = SIDE ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.x / NC, share = blockIdx.x % NC;
-    const int gx = SIDE ? groups : gridDim.x / NC;
-    if (SIDE && x >= gx) return;
-    const int y = SIDE ? (blockIdx.x / NC + x) % (gridDim.x / NC) : blockIdx.y;   // (turned, so that a narrow last range comes to every XCD)
+    const int bx = SIDE ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.x / NC, x = bx - heavy, share = blockIdx.x % NC;
+    const int gx = groups;
+    if (x >= gx) return;
+    const int y = SIDE ? (blockIdx.x / NC + bx) % (gridDim.x / NC) : blockIdx.y;   // (turned, so that a narrow last range comes to every XCD)
     const int col0 = y * (512 * NC), col = col0 + (lane >> 3) * 64 + (lane & 1) * 32 + (lane & 6) * 4;   // (what scatter_store wants)
     const int out0 = (lane >> 3) * 64 + (lane & 7) * 4;
-    // which of the group's rows are long: one row per lane, so that the usual block does not pay for looking
+    const int c = col + 512 * share;
+    // the blocks below heavy sum the longest rows of 64 kScatterLook, before all others; the other blocks theirs of a group
+    int first = x >= 0 ? x : bx;
+    const int step = x >= 0 ? gx : heavy, n_rows = x >= 0 ? NC * kScatterWaves : 64;
+    const int more = x >= 0 ? kScatterShort : kScatterHeavy, most = x >= 0 && heavy > 0 ? kScatterHeavy : INT32_MAX;
+    // which of these rows are long: one row per lane, so that the usual block does not pay for looking
     int g_beg = 0, g_cnt = 0;
-    if (lane < NC * kScatterWaves && x + lane * gx < V) {
-        g_beg = row_start[x + lane * gx];
-        g_cnt = row_start[x + lane * gx + 1] - g_beg;
-    }
-    {
+    const auto look = [&]() {
+        const int v = first + lane * step;
+        g_cnt = 0;
+        if (lane < n_rows && v < V) {
+            g_beg = row_start[v];
+            g_cnt = row_start[v + 1] - g_beg;
+        }
+    };
+    look();
+    if (x >= 0) {
         const int v = x + (share * kScatterWaves + wave) * gx;
         if (v < V) {
             const int beg = row_start[v], end = row_start[v + 1];
@@ -509,45 +519,50 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
             }
         }
     }
-    const int c = col + 512 * share;
     if (col0 + 512 * share >= d) return;   // uniform over the block
-    for (uint64_t todo = __builtin_amdgcn_ballot_w64(g_cnt > kScatterShort); todo; todo &= todo - 1) {   // the same in every wave
-        const int w = __builtin_ctzll(todo), v = x + w * gx;
-        const int beg = __builtin_amdgcn_readlane(g_beg, w), cnt = __builtin_amdgcn_readlane(g_cnt, w);
-        const int i0 = beg + (int)((int64_t)cnt * wave / kScatterWaves), i1 = beg + (int)((int64_t)cnt * (wave + 1) / kScatterWaves);
-        float acc[1][8] = {};
-        for (int ib = i0; ib < i1; ib += 64) {
-            const int idx = order[min(ib + lane, i1 - 1)], m = min(64, i1 - ib);   // the next 64 terms, one per lane
-            int i = 0;
-            for (; i + 16 <= m; i += 16) {
-                int32_t r[16];
+    for (int k = 1;; ++k) {
+        uint64_t todo = __builtin_amdgcn_ballot_w64(g_cnt > more && g_cnt <= most);
+        for (; todo; todo &= todo - 1) {   // the same in every wave
+            const int w = __builtin_ctzll(todo), v = first + w * step;
+            const int beg = __builtin_amdgcn_readlane(g_beg, w), cnt = __builtin_amdgcn_readlane(g_cnt, w);
+            const int i0 = beg + (int)((int64_t)cnt * wave / kScatterWaves), i1 = beg + (int)((int64_t)cnt * (wave + 1) / kScatterWaves);
+            float acc[1][8] = {};
+            for (int ib = i0; ib < i1; ib += 64) {
+                const int idx = order[min(ib + lane, i1 - 1)], m = min(64, i1 - ib);   // the next 64 terms, one per lane
+                int i = 0;
+                for (; i + 16 <= m; i += 16) {
+                    int32_t r[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) r[u] = __builtin_amdgcn_readlane(idx, i + u);
-                scatter_terms<1, 16>(acc, dh, r, d, c);
-            }
-            for (; i + 4 <= m; i += 4) {
-                int32_t r[4];
+                    for (int u = 0; u < 16; ++u) r[u] = __builtin_amdgcn_readlane(idx, i + u);
+                    scatter_terms<1, 16>(acc, dh, r, d, c);
+                }
+                for (; i + 4 <= m; i += 4) {
+                    int32_t r[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) r[u] = __builtin_amdgcn_readlane(idx, i + u);
-                scatter_terms<1, 4>(acc, dh, r, d, c);
+                    for (int u = 0; u < 4; ++u) r[u] = __builtin_amdgcn_readlane(idx, i + u);
+                    scatter_terms<1, 4>(acc, dh, r, d, c);
+                }
+                for (; i < m; ++i) {
+                    const int32_t r[1] = {__builtin_amdgcn_readlane(idx, i)};
+                    scatter_terms<1, 1>(acc, dh, r, d, c);
+                }
             }
-            for (; i < m; ++i) {
-                const int32_t r[1] = {__builtin_amdgcn_readlane(idx, i)};
-                scatter_terms<1, 1>(acc, dh, r, d, c);
+            if (wave > 0)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) part[wave - 1][k][lane] = acc[0][k];
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll
+                for (int q = 0; q < kScatterWaves - 1; ++q)
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) acc[0][k] += part[q][k][lane];
+                scatter_store<ADD>(dtable + (int64_t)v * d + col0 + out0 + 512 * share, acc[0], d - (col0 + out0 + 512 * share));
             }
+            __syncthreads();
         }
-        if (wave > 0)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) part[wave - 1][k][lane] = acc[0][k];
-        __syncthreads();
-        if (wave == 0) {
-#pragma unroll
-            for (int q = 0; q < kScatterWaves - 1; ++q)
-#pragma unroll
-                for (int k = 0; k < 8; ++k) acc[0][k] += part[q][k][lane];
-            scatter_store<ADD>(dtable + (int64_t)v * d + col0 + out0 + 512 * share, acc[0], d - (col0 + out0 + 512 * share));
-        }
-        __syncthreads();
+        if (x >= 0 || k == kScatterLook) return;
+        first += 64 * heavy;
+        look();
     }
 }
 
@@ -816,19 +831,25 @@ hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_sta
     const auto blocks = [&](int nc) { return (int64_t)((V + 7) / 8) * ((d + 512 * nc - 1) / (512 * nc)); };
     const int nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
     const int gx = (int)blocks_for(V, kScatterWaves * nc);
-    const unsigned ny = blocks_for(d, 512 * nc), gy = std::min(gx, 1 << 15);
+    const unsigned ny = blocks_for(d, 512 * nc);
+    // Rows of more than kScatterHeavy terms first, in blocks of their own that look through 64 kScatterLook rows: a frequent token's row that comes
+    // late is summed alone at the end.  Ids of a Zipf law scattered over the table, with the lookup, us: 65 536 tokens, 32 000 x 4096 425 -> 412,
+    // x 2048 239 -> 219, x 1280 170 -> 154; where no row is that long it costs 1 to 3 % (16 384 tokens, 32 000 x 4096 187 -> 192, 213 before whole
+    // lines per store).  From 125 such groups on: fewer hold too many long rows each (65 536 tokens, 5000 x 640 99, 129 in 20 groups of two shares).
+    const int heavy_groups = (int)blocks_for(V, 64 * kScatterLook), heavy = nc == 4 && heavy_groups * ny >= 125 ? heavy_groups : 0;
+    const int gy = std::min(gx + heavy, 1 << 15);
     // Several column ranges come side by side: by ranges, the heavy rows of the later ones begin late, and all shares of such a row fall on NC XCDs.
     // Zipf-distributed ids in order of frequency, by ranges -> side by side, us: 65 536 tokens, V = 32 000, d = 4096 328 -> 284 (uniform ids
     // 215 -> 217), d = 5120 418 -> 345, 4096 tokens, V = 1024, d = 4096 30.2 -> 21-23.  Not where narrow blocks come out even or as the better
     // end: with one whole range and a narrower one (65 536, 32 000, 2560) 309 with the lookup, side by side 323; 8192, 4000, 3584 (NC = 2) 60.7,
     // 61.6; nor two ranges of NC = 2 (4096, 1500, 2048: 18.1, 18.7) and NC = 1, tables small enough to be at work all at once.
     const bool side = nc == 4 ? d >= 2 * 512 * nc : nc == 2 && d > 2 * 512 * nc && d % (512 * nc) == 0;
-    const dim3 grid = side ? dim3(nc * ny, gy, blocks_for(gx, gy)) : dim3(nc * gx, ny), block(64 * kScatterWaves);
+    const dim3 grid = side ? dim3(nc * ny, gy, blocks_for(gx + heavy, gy)) : dim3(nc * (gx + heavy), ny), block(64 * kScatterWaves);
     auto kernel = nc == 1 ? embed_scatter_kernel<1, false, false> : nc == 2 ? embed_scatter_kernel<2, false, false> : embed_scatter_kernel<4, false, false>;
     if (add) kernel = nc == 1 ? embed_scatter_kernel<1, true, false> : nc == 2 ? embed_scatter_kernel<2, true, false> : embed_scatter_kernel<4, true, false>;
     if (side && nc == 2) kernel = add ? embed_scatter_kernel<2, true, true> : embed_scatter_kernel<2, false, true>;
     if (side && nc == 4) kernel = add ? embed_scatter_kernel<4, true, true> : embed_scatter_kernel<4, false, true>;
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d, gx);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d, gx, heavy);
     return hipGetLastError();
 }
 
