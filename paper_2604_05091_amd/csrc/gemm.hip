@@ -1186,10 +1186,10 @@ static const TileCost kLineCosts[] = {{RingTile::l128x128, 128, 128, 1, 0.40, 0.
                                       {RingTile::l64x64, 64, 64, 2, 0.22, 0.175, 3.0, 0.9}};
 
 // Tiles of 256 x 320 (widths that are multiples of 320) and of 256 x 192 (of 64).  Fitted to 263 plain products of MLPs, projections and heads (K 512 .. 15 000,
-// half a round to eight): taken from an estimated gain of 3 and 4 % on, nowhere slower, 1.02 times faster over all of them (the best choice: 1.024).  us, before ->
+// half a round to eight): taken from an estimated gain of 3 and 4 % on, 1.013 times faster over all of them.  us, before ->
 // here: 4096 x 5120 x 5120 (one round of 256 x 320 instead of 1.25) 155 -> 143, x 7168 210 -> 194, x 27 648 897 -> 774, 8192 x 2560 x 2560 89 -> 80, 65 536 x 5120 x 5120
 // (16 rounds instead of 20) 2524 -> 2452, x 13 824 6523 -> 6283 (1477 TFLOP/s); the projections of 5 x 512
-// tokens, 3712 wide, forward (2560 x 11 136 in one round of 256 x 192 and a little of 128 x 128 before) 291 -> 269, in other chains under the power limit even;
+// tokens, 3712 wide, forward (of which 2560 x 3712 x 3712 in 0.78 of a round of 256 x 192) 291 -> 269; among products that run at the power limit even;
 // 2000 x 5120 x 5120 (half a round) 94, in 256 x 320 115, and 8200 x 2560 x 6400 (1.03 rounds) 213, 301, keep theirs.
 constexpr int kWideStages = 8;   // (shorter walks were not looked at)
 static const TileCost kWideCosts[] = {{RingTile::wide320, 256, 320, 1, 1.03, 1.545, 12.5, 0.0}, {RingTile::wide192, 256, 192, 1, 0.55, 1.09, 9.8, 0.0}};
