@@ -5,6 +5,7 @@
 // arithmetic in fp32 and reduce inside a 64-lane wave with cross-lane shuffles.
 // None uses atomics, so every result is bit-reproducible from run to run.
 #include <algorithm>
+#include <type_traits>
 #include <atomic>
 
 #include "common.h"
@@ -72,11 +73,21 @@ __global__ __launch_bounds__(256) void transpose_kernel(TransposeArgs t) {
     }
 }
 
+// NT: past the caches.  For results that the L2 caches (32 MB in all) cannot hold for their reader: the lines written take no place from those read.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+template <bool NT>
+__device__ __forceinline__ void norm_store(uint4 *p, const uint4 &v) {
+    if constexpr (NT)
+        __builtin_nontemporal_store((u32x4){v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
+    else
+        *p = v;
+}
+
 // ------------------------------------------------------------------ RMSNorm forward
 // One wave per row; the row is held in registers (NCH chunks of 8 per lane).  PACKED: as it was loaded; otherwise the compiler keeps
 // the unpacked row, and fewer waves fit on a SIMD (NCH = 8: five instead of eight).  A launch of few rounds is the faster for more
 // waves, one of many for fewer (see rmsnorm_fwd).
-template <int NCH, bool PACKED>
+template <int NCH, bool PACKED, bool NT>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n,
                                                           int d, float eps) {
     const int lane = threadIdx.x & 63;
@@ -116,7 +127,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
             unpack8(gr[c], gf);
 #pragma unroll
             for (int k = 0; k < 8; ++k) f[k] = f[k] * r * gf[k];
-            yr[c] = pack8(f);
+            norm_store<NT>(yr + c, pack8(f));
         }
     }
 }
@@ -138,7 +149,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(bf16_t *y, const bf16_
 // it has one: 65 536 x 6144 639 -> 602 us, x 5120 (with dres) 518 -> 488, 45 448 x 6016 427 -> 410; x 2048 stays at 189 (238).
 constexpr int kNormBwdBlocks = 512, kNormChain = 32;
 
-template <int NCH, int WPR>
+template <int NCH, int WPR, bool NT>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *partial, const bf16_t *dy, const bf16_t *x,
                                                           const bf16_t *gain, const bf16_t *dres, int64_t n, int d, float eps) {
     static_assert(WPR == 1 || WPR == 4, "a row belongs to one wave or to the whole block");
@@ -250,7 +261,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(bf16_t *dx, float *par
                 of[k] += r * gf[k] * yf[k] - xf[k] * cc;
                 dg[i][k] += yf[k] * xf[k] * r;
             }
-            if (c < nch) reinterpret_cast<uint4 *>(dx + row * d)[c] = pack8(of);
+            if (c < nch) norm_store<NT>(reinterpret_cast<uint4 *>(dx + row * d) + c, pack8(of));
         }
     }
     if constexpr (WPR == 4) end_chain();
@@ -721,6 +732,9 @@ hipError_t transpose_bf16(const TransposeArgs &t, hipStream_t s) {
     return hipGetLastError();
 }
 
+// (norm_store) forward and backward, us: 65 536 x 5120 738 -> 714, 16 384 x 4096 159 -> 142, 65 536 x 1024 152 -> 134, 8192 x 8192 169 -> 148; results of
+// less than twice the caches may be there yet when their reader comes.
+static bool past_caches(int64_t n, int32_t d) { return n * d * 2 >= (int64_t)64 << 20; }
 hipError_t rmsnorm_fwd(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n, int32_t d, float eps,
                        hipStream_t s) {
     if (n <= 0 || d <= 0 || (d & 7) || d > 8192) return hipErrorInvalidValue;
@@ -729,10 +743,15 @@ hipError_t rmsnorm_fwd(bf16_t *y, const bf16_t *x, const bf16_t *gain, int64_t n
     // packed: 5136 x 3904 14.7 -> 13.4 us, 8192 x 5120 25.9 -> 24.1, 3117 x 6144 16.7 -> 13.8, 4026 x 7368 22.0 -> 18.4.  Many: with fewer waves,
     // 24 576 x 5120 98 -> 94, 65 536 x 3072 146 -> 141, x 5120 248 -> 241, x 6144 298 -> 288; 16 384 x 4096 39.5 -> 40.6.
     const int k = (d - 1) / 1024;
-    decltype(&rmsnorm_fwd_kernel<2, false>) const few[8] = {rmsnorm_fwd_kernel<2, false>, rmsnorm_fwd_kernel<4, false>, rmsnorm_fwd_kernel<6, true>, rmsnorm_fwd_kernel<8, true>,
-                                                            rmsnorm_fwd_kernel<10, true>, rmsnorm_fwd_kernel<12, true>, rmsnorm_fwd_kernel<14, true>, rmsnorm_fwd_kernel<16, true>};
-    const auto many = k <= 1 ? few[k] : k <= 3 ? rmsnorm_fwd_kernel<8, false> : k == 4 ? rmsnorm_fwd_kernel<10, false> : rmsnorm_fwd_kernel<16, false>;
-    const auto kernel = n < 20480 ? few[k] : many;
+    const auto pick = [&](auto nt) {
+        constexpr bool NT = decltype(nt)::value;
+        decltype(&rmsnorm_fwd_kernel<2, false, NT>) const few[8] = {
+            rmsnorm_fwd_kernel<2, false, NT>, rmsnorm_fwd_kernel<4, false, NT>, rmsnorm_fwd_kernel<6, true, NT>, rmsnorm_fwd_kernel<8, true, NT>,
+            rmsnorm_fwd_kernel<10, true, NT>, rmsnorm_fwd_kernel<12, true, NT>, rmsnorm_fwd_kernel<14, true, NT>, rmsnorm_fwd_kernel<16, true, NT>};
+        const auto many = k <= 1 ? few[k] : k <= 3 ? rmsnorm_fwd_kernel<8, false, NT> : k == 4 ? rmsnorm_fwd_kernel<10, false, NT> : rmsnorm_fwd_kernel<16, false, NT>;
+        return n < 20480 ? few[k] : many;
+    };
+    const auto kernel = past_caches(n, d) ? pick(std::true_type{}) : pick(std::false_type{});
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, y, x, gain, n, d, eps);
     return hipGetLastError();
 }
@@ -745,8 +764,12 @@ hipError_t rmsnorm_bwd(bf16_t *dx_out, float *dgain, const bf16_t *dy, const bf1
     if (n <= 0 || d <= 0 || (d & 7) || d > 8192) return hipErrorInvalidValue;
     const int rpb = d <= 1024 ? 4 : 1;   // rows a block has in hand
     const unsigned grid = (unsigned)std::min<int64_t>((n + rpb - 1) / rpb, kNormBwdBlocks);
-    auto kernel = d <= 512 ? rmsnorm_bwd_kernel<1, 1> : d <= 1024 ? rmsnorm_bwd_kernel<2, 1> : d <= 2048 ? rmsnorm_bwd_kernel<1, 4>
-                : d <= 4096 ? rmsnorm_bwd_kernel<2, 4> : d <= 6144 ? rmsnorm_bwd_kernel<3, 4> : rmsnorm_bwd_kernel<4, 4>;
+    const auto pick = [&](auto nt) {
+        constexpr bool NT = decltype(nt)::value;
+        return d <= 512 ? rmsnorm_bwd_kernel<1, 1, NT> : d <= 1024 ? rmsnorm_bwd_kernel<2, 1, NT> : d <= 2048 ? rmsnorm_bwd_kernel<1, 4, NT>
+             : d <= 4096 ? rmsnorm_bwd_kernel<2, 4, NT> : d <= 6144 ? rmsnorm_bwd_kernel<3, 4, NT> : rmsnorm_bwd_kernel<4, 4, NT>;
+    };
+    const auto kernel = past_caches(n, d) ? pick(std::true_type{}) : pick(std::false_type{});
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, dx_out, partial, dy, x, gain, dres, n, d, eps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
