@@ -757,12 +757,13 @@ __global__ __launch_bounds__(512) void flash_fwd_chain_kernel(AttnArgs a, ChainM
 // dQ is the first kernel of the backward: it has the output gradients of its queries at hand, so it also works out delta = rowsum(dO * O),
 // which is stored for dK/dV (a pass of its own read dO once more.  us, forward and backward, with -> without it: 3 x 520, 8 heads of 64 on 2 40.6 -> 38.6;
 // 4 x 4096, 32 heads 2518 -> 2502; 1 x 32768, 40 heads on 8 43 830 -> 43 740).
-// (v_dot2c_f32_bf16: its error against 64 bits is that of two fused multiply-adds)
+// (A product of two bf16 is exact in fp32, so a pair of terms is rounded once.  The two-element dot product instruction adds the terms one by one instead:
+// where neighbouring terms cancel it loses what was there before.)
 __device__ __forceinline__ float dot8(const bf16x8 &x, const bf16x8 &y) {
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const u32x4 a = __builtin_bit_cast(u32x4, x), b = __builtin_bit_cast(u32x4, y);
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{x[2 * i], x[2 * i + 1]}, bf16x2{y[2 * i], y[2 * i + 1]}, s, false);
+    for (int i = 0; i < 4; ++i) s += bflo(a[i]) * bflo(b[i]) + bfhi(a[i]) * bfhi(b[i]);
     return s;
 }
 template <int HD>
@@ -1385,8 +1386,8 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, C
 // fetches its pieces into LDS of its own, one ahead, and waits for nobody until the sets' sums are added.  A tile shared by the waves
 // (flash_bwd_dkdv_kernel) holds rows of one head only and ends with a barrier: 3 x 520, 8 heads of 64 on 2, are 12 steps of it and 9 here.  The row sums
 // come from the chunks of dO and O that a lane itself fetched (a fragment's layout would take 32 lines per load: 26 us against 21 of this kernel alone).
-// us, backward, two launches -> one: 3 x 520, 8 heads on 2, head_dim 64 30.2 -> 19.3; 7 x 128, 10 on 2 19.4 -> 14.7; 4 x 512, 2 on 2 16.6 -> 9.7;
-// head_dim 128: 2 x 88, 20 on 4 22.7 -> 15.0; 1 x 560, 8 on 2 49.6 -> 40.4; 3 x 1120, 2 on 2 38.4 -> 27.5.
+// us, backward, two launches -> one: 3 x 520, 8 heads on 2, head_dim 64 30.2 -> 20.4; 7 x 128, 10 on 2 19.4 -> 15.2; 4 x 512, 2 on 2 16.6 -> 9.8;
+// head_dim 128: 2 x 88, 20 on 4 22.7 -> 15.7; 1 x 560, 8 on 2 49.6 -> 45.8; 3 x 1120, 2 on 2 38.4 -> 29.6.
 // LDS: a wave's two stages of Q, dO | the waves' lse * log2e, delta of 32 queries, twice | head_dim 128: V (64: the lane's values fit into registers)
 template <int HD, int NW>
 struct UnitLds {
@@ -1890,13 +1891,18 @@ static bool overlap(const AttnArgs &a, const bf16_t *x, int64_t ldx, int64_t col
     return x0 < y1 && y0 < x1;
 }
 // dQ and dK/dV in one launch: where dK/dV takes blocks of 32 keys (head_dim 64: or of 64, shared by four sets) and dQ workgroups of the same size, up to
-// kTogether workgroups.  Two launches against one, 240 shapes: 1.0 to 1.9 times faster up to 700 workgroups (1.26 on average);
-// 700 to 1100: 0.88 to 1.12, slower where the walks are long (1 x 3528, 16 heads on 8 of 64, 896 workgroups 131 -> 145 us).
+// kTogether workgroups.  Two launches against one, 150 shapes up to there: 1.0 to 1.9 times faster (1.39 on average);
+// 700 to 1100 (with row sums that took less time): 0.88 to 1.12, slower where the walks are long (1 x 3528, 16 heads on 8 of 64, 896 workgroups 131 -> 145 us).
+// Head_dim 128, where a piece's row sums take 0.55 us: only while those of the longest walk take less than dQ, which no longer comes first (5.9 us and 1.15 a tile
+// of 128 rows).  us, 1 x 1120, 8 heads on 1 136 (159 in one launch), 1 x 744, 16 on 2 100 (113), 1 x 232, 16 on 2 40.4 (42.0), 1 x 960, 8 on 2 72.0 (72.6), but
+// 3 x 616, 4 on 1 50.9 -> 51.1, 2 x 216, 16 on 2 40.6 -> 37.6, 1 x 2992, 4 on 2 116 -> 110.
 constexpr int kTogether = 700;
+constexpr double kPieceSums = 0.55;
 static bool runs_together(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv) {
     if (!(dkdv.rows == 32 || (dkdv.rows == 64 && dkdv.sets == 4 && a.hd == 64)) || dq.list || (a.hd == 128 && dq.rows != 32)) return false;
     const int64_t blocks = (int64_t)a.B * a.Hkv * ((a.T + dkdv.rows - 1) / dkdv.rows) + (int64_t)a.B * a.Hq * ((a.T + dq.rows - 1) / dq.rows);
     if (blocks > kTogether) return false;
+    if (a.hd == 128 && kPieceSums * ((a.Hq / a.Hkv * ((a.T + 31) / 32) + 3) / 4) > 5.9 + 1.15 * ((a.T + 127) / 128)) return false;
     // dK and dV may take the place of keys and values, but not while dQ reads them
     const int64_t nq = (int64_t)a.Hq * a.hd, nkv = (int64_t)a.Hkv * a.hd;
     const auto apart = [&](const bf16_t *x, int64_t ldx) {
