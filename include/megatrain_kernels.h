@@ -152,7 +152,8 @@ int32_t mt_k_flash_fwd(uint16_t *o, int64_t ldo, float *lse, const uint16_t *q, 
                        int32_t hd, float scale, void *stream);
 /* Causal attention backward: dq, dk, dv from dout, the forward's inputs, o and lse.  dk, dv of a KV head are
  * summed over the query heads of its group.  delta [B,Hq,T] fp32 is scratch written by this call
- * (delta = rowsum(dout * o)).  Deterministic: no atomics. */
+ * (delta = rowsum(dout * o)).  Deterministic: no atomics.  dk and dv may take the place of k and v
+ * (same pitch), with the same bits; dq that of q, dout or o (its delta is then summed in another order). */
 int32_t mt_k_flash_bwd(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t lddk, uint16_t *dv, int64_t lddv,
                        const uint16_t *dout, int64_t lddo, const uint16_t *q, int64_t ldq, const uint16_t *k,
                        int64_t ldk, const uint16_t *v, int64_t ldv, const uint16_t *o, int64_t ldo, const float *lse,
@@ -177,6 +178,9 @@ int32_t mt_k_flash_bwd_rope(uint16_t *dq, int64_t lddq, uint16_t *dk, int64_t ld
 int32_t mt_k_flash_route(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *route);
 int32_t mt_k_flash_sets(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *sets);
 int32_t mt_k_flash_lists(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd, int32_t *lists);
+/* 1 where dk and dv come from a kernel that walks the queries in pieces of 32 and works out delta for itself; it takes dq's blocks into its launch
+ * unless a result takes the place of an input.  0 where dk and dv follow dq's launch and use its delta. */
+int32_t mt_k_flash_together(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd);
 
 /* Host Adam on one array (the arithmetic of mt_adam_step; all HOST pointers).  shadow may be
  * NULL, otherwise it receives the updated parameters rounded to bf16 (nearest even). */

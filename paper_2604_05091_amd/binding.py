@@ -132,6 +132,7 @@ def lib():
         "mt_k_flash_route": ([c_int32, c_int32, c_int32, c_int32, c_int32, pi], c_int32),
         "mt_k_flash_sets": ([c_int32, c_int32, c_int32, c_int32, c_int32, pi], c_int32),
         "mt_k_flash_lists": ([c_int32, c_int32, c_int32, c_int32, c_int32, pi], c_int32),
+        "mt_k_flash_together": ([c_int32, c_int32, c_int32, c_int32, c_int32], c_int32),
         "mt_k_gemm_route": ([c_int32, c_int32, c_int32, c_int32, c_int64, c_int32, pi], c_int32),
         "mt_k_gemm_sharers": ([c_int32, c_int32, c_int32, c_int32, c_int64], c_int32),
         "mt_k_bias_grad_ws_bytes": ([c_int32], c_size_t),

@@ -199,17 +199,6 @@ __device__ __forceinline__ float half_sum(float v) {
     return __uint_as_float(u[0]) + __uint_as_float(u[1]);
 }
 
-// sum over the 8 or 16 neighbouring lanes of a group, in all of them
-template <int N>
-__device__ __forceinline__ float group_sum(float v) {
-    const auto add = [&](auto ctrl) { v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true)); };
-    add(std::integral_constant<int, 0xb1>());    // lane ^ 1
-    add(std::integral_constant<int, 0x4e>());    // lane ^ 2
-    add(std::integral_constant<int, 0x141>());   // 7 - lane of 8: the other four
-    if (N == 16) add(std::integral_constant<int, 0x140>());   // 15 - lane of 16: the other eight
-    return v;
-}
-
 __device__ __forceinline__ bf16x8 pack_frag(const f32x16 &v, int cch) {
     const int o = cch * 8;
     const uint4 u = {pack2bf(v[o + 0], v[o + 1]), pack2bf(v[o + 2], v[o + 3]), pack2bf(v[o + 4], v[o + 5]),
@@ -1385,15 +1374,33 @@ __global__ __launch_bounds__(512) void flash_bwd_dkdv_chain_kernel(AttnArgs a, C
 // A block's KW x QW waves own 32 keys each and walk pieces of 32 queries; those of all the group's heads are dealt to the QW sets in turn.  A wave
 // fetches its pieces into LDS of its own, one ahead, and waits for nobody until the sets' sums are added.  A tile shared by the waves
 // (flash_bwd_dkdv_kernel) holds rows of one head only and ends with a barrier: 3 x 520, 8 heads of 64 on 2, are 12 steps of it and 9 here.  The row sums
-// come from the chunks of dO and O that a lane itself fetched (a fragment's layout would take 32 lines per load: 26 us against 21 of this kernel alone).
-// us, backward, two launches -> one: 3 x 520, 8 heads on 2, head_dim 64 30.2 -> 20.4; 7 x 128, 10 on 2 19.4 -> 15.2; 4 x 512, 2 on 2 16.6 -> 9.8;
-// head_dim 128: 2 x 88, 20 on 4 22.7 -> 15.7; 1 x 560, 8 on 2 49.6 -> 45.8; 3 x 1120, 2 on 2 38.4 -> 29.6.
+// come from the chunks of dO and O that a lane itself fetched (a fragment's layout would take 32 lines per load: 26 us against 21 of this kernel alone), added
+// in dQ's order, so that both have the same delta.  OWN = false: delta is dQ's, which came before (dK, dV in the place of K, V).
+// us, backward, two launches -> one: 3 x 520, 8 heads on 2, head_dim 64 30.1 -> 20.6; 7 x 128, 10 on 2 19.4 -> 15.5; 4 x 512, 2 on 2 16.5 -> 10.0;
+// head_dim 128: 2 x 88, 20 on 4 22.6 -> 16.0; 1 x 560, 8 on 2 49.5 -> 47.7; 3 x 1120, 2 on 2 38.4 -> 30.3.  In the place of the inputs, both in two launches, tiles -> pieces:
+// 1.04 times faster over 125 shapes, 0.94 (T of about 100, head_dim 64, 17.0 -> 18.0) to 1.3.
 // LDS: a wave's two stages of Q, dO | the waves' lse * log2e, delta of 32 queries, twice | head_dim 128: V (64: the lane's values fit into registers)
 template <int HD, int NW>
 struct UnitLds {
     static constexpr uint32_t TILE = BwdTile<HD>::rows(32), WAVE = 4 * TILE, STAT_OFF = NW * WAVE, V_OFF = STAT_OFF + NW * 512, BYTES = V_OFF + (HD == 128 ? TILE : 0);
 };
-template <int HD, int KW, int QW>
+// The sum of a row's chunks, one to each of the HD / 8 lanes that fetched it, in the order of row_delta, whose lane half h has the chunks 2 ks + h: the even and
+// the odd ks apart, then these two, then the halves.  The lanes are those of the chunks up to an xor, so a step is one between lanes.  head_dim 64: in all
+// lanes; 128, where four chunks follow each other: in those whose chunk is one of the first four.
+template <int HD>
+__device__ __forceinline__ float chunk_sum(float v) {
+    const auto from = [](float x, auto ctrl) { return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    uint32_t far = __builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x104, 0xf, 0x5, false);   // lane ^ 4: from + 4
+    far = __builtin_amdgcn_update_dpp(far, __float_as_uint(v), 0x114, 0xf, 0xa, false);          // and from - 4
+    float s = v + __uint_as_float(far);
+    if constexpr (HD == 128) {
+        s += from(v, std::integral_constant<int, 0x128>());                      // lane ^ 8
+        s += from(__uint_as_float(far), std::integral_constant<int, 0x128>());   // lane ^ 12
+    }
+    s += from(s, std::integral_constant<int, 0x4e>());   // lane ^ 2
+    return s + from(s, std::integral_constant<int, 0xb1>());   // lane ^ 1
+}
+template <int HD, int KW, int QW, bool OWN>
 __device__ __forceinline__ void dkdv_units_block(const AttnArgs &a, const BlockMap &map, uint32_t id, bf16_t *smem) {
     constexpr int HB = HD / 32, GS = BwdTile<HD>::GS, LPR = HD / 8, N = 32 * LPR / 64;   // lanes of a row, chunks that a lane fetches
     using Lds = UnitLds<HD, KW * QW>;
@@ -1425,7 +1432,7 @@ __device__ __forceinline__ void dkdv_units_block(const AttnArgs &a, const BlockM
     }
     bf16x8 kf[HD / 16], vf[HD / 16];
     u32x4 of[N];
-    float lse = 0.f;
+    float stat = 0.f;   // lse (and, not OWN, delta in the lanes from 32 on)
     int head = key_unit < nt ? 0 : G, unit = key_unit + qw;   // of the next piece (none for keys past the end)
     const auto settle = [&]() {
         while (unit >= nt && head < G) {
@@ -1437,25 +1444,33 @@ __device__ __forceinline__ void dkdv_units_block(const AttnArgs &a, const BlockM
         const int h = hk * G + head, q0 = unit * 32;
         tq.load(stage, a.q + (int64_t)b * T * a.ldq + (int64_t)h * HD, a.ldq, q0, T);
         tdo.load(stage + TILE, a.dout + (int64_t)b * T * a.lddo + (int64_t)h * HD, a.lddo, q0, T);
-        to.load_to(of, a.o + (int64_t)b * T * a.ldo + (int64_t)h * HD, a.ldo, q0, T);
-        lse = a.lse[((int64_t)b * a.Hq + h) * T + min(q0 + l32, T - 1)];
+        if constexpr (OWN) to.load_to(of, a.o + (int64_t)b * T * a.ldo + (int64_t)h * HD, a.ldo, q0, T);
+        stat = (OWN || lane < 32 ? a.lse : a.delta)[((int64_t)b * a.Hq + h) * T + min(q0 + l32, T - 1)];
         __builtin_amdgcn_sched_barrier(0);
     };
-    // The row sums of dO * O of a piece that has landed, from the chunks of dO and O that this lane fetched; LPR neighbouring lanes have a row.
-    // Queries past T: lse = +inf makes their P (and with it dS) exactly zero.
+    // The row sums of dO * O of a piece that has landed, from the chunks of dO and O that this lane fetched.  Of the lanes that have a row's sum one takes it for
+    // load j (head_dim 128: four take two loads each).  Queries past T: lse = +inf makes their P (and with it dS) exactly zero.
+    const int taker = HD == 64 ? lane & 7 : lane & 3;
     const auto commit = [&](int q0, uint32_t stage, uint32_t stats) {
         typedef __attribute__((address_space(3))) const bf16x8 *lds_frag;
         typedef __attribute__((address_space(3))) float *lds_float;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        float mine = 0.f;
+        if constexpr (OWN) {
+            float mine[N / 4] = {};
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const bf16x8 dof = *(lds_frag)(wave_lds + stage + TILE + j * GS + lane * 16);
-            const float d = group_sum<LPR>(dot8(dof, __builtin_bit_cast(bf16x8, of[j])));
-            mine = lane % LPR == j ? d : mine;
+            for (int j = 0; j < N; ++j) {
+                const bf16x8 dof = *(lds_frag)(wave_lds + stage + TILE + j * GS + lane * 16);
+                const float d = chunk_sum<HD>(dot8(dof, __builtin_bit_cast(bf16x8, of[j])));
+                mine[j / 4] = taker == j % 4 ? d : mine[j / 4];
+            }
+            if (HD == 64 ? taker < 4 : (lane >> 2 & 3) == lane >> 4) {
+#pragma unroll
+                for (int m = 0; m < N / 4; ++m) *(lds_float)(stats + (32 + (m * 4 + taker) * (64 / LPR) + lane / LPR) * 4) = mine[m];
+            }
+        } else if (lane >= 32) {
+            *(lds_float)(stats + lane * 4) = stat;
         }
-        if (lane % LPR < N) *(lds_float)(stats + (32 + lane % LPR * (64 / LPR) + lane / LPR) * 4) = mine;
-        if (lane < 32) *(lds_float)(stats + lane * 4) = q0 + lane < T ? lse * kLog2e : INFINITY;
+        if (lane < 32) *(lds_float)(stats + lane * 4) = q0 + lane < T ? stat * kLog2e : INFINITY;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     settle();
@@ -1501,8 +1516,14 @@ template <int HD, int DQ_QW, int DQ_KW, int KW, int QW>
 __global__ __launch_bounds__(64 * KW * QW) void flash_bwd_both_kernel(AttnArgs a, BlockMap keys, BlockMap queries, int n_keys) {
     static_assert(DQ_QW * DQ_KW == KW * QW, "workgroups of one size");
     extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
-    if ((int)blockIdx.x < n_keys) dkdv_units_block<HD, KW, QW>(a, keys, blockIdx.x, smem);
+    if ((int)blockIdx.x < n_keys) dkdv_units_block<HD, KW, QW, true>(a, keys, blockIdx.x, smem);
     else dq_block<HD, DQ_QW, DQ_KW, false>(a, queries, blockIdx.x - n_keys, smem);
+}
+
+template <int HD, int KW, int QW>
+__global__ __launch_bounds__(64 * KW * QW) void flash_bwd_pieces_kernel(AttnArgs a, BlockMap keys) {
+    extern __shared__ __attribute__((aligned(256))) bf16_t smem[];
+    dkdv_units_block<HD, KW, QW, false>(a, keys, blockIdx.x, smem);
 }
 
 bool attn_shape_ok(const AttnArgs &a) {
@@ -1823,6 +1844,17 @@ static hipError_t launch_both(const AttnArgs &a, hipStream_t s) {
                        queries, (int)grid_blocks(keys));
     return hipGetLastError();
 }
+template <int HD, int KW, int QW>
+static hipError_t launch_pieces(const AttnArgs &a, hipStream_t s) {
+    constexpr size_t lds = std::max((size_t)UnitLds<HD, KW * QW>::BYTES, (size_t)KW * QW * (HD / 32 * 16) * 64 * sizeof(float));
+    static_assert(lds <= 160 * 1024, "LDS");
+    static std::atomic<bool> done{false};
+    const hipError_t e = ensure_lds(&flash_bwd_pieces_kernel<HD, KW, QW>, lds, &done);
+    if (e != hipSuccess) return e;
+    const BlockMap keys = block_map((a.T + 32 * KW - 1) / (32 * KW), a.B * a.Hkv, 1);
+    hipLaunchKernelGGL((flash_bwd_pieces_kernel<HD, KW, QW>), dim3(grid_blocks(keys)), dim3(64 * KW * QW), lds, s, a, keys);
+    return hipGetLastError();
+}
 
 template <int HD>
 static hipError_t launch_dkdv_chain(const AttnArgs &a, hipStream_t s) {
@@ -1891,25 +1923,29 @@ static bool overlap(const AttnArgs &a, const bf16_t *x, int64_t ldx, int64_t col
     return x0 < y1 && y0 < x1;
 }
 // dQ and dK/dV in one launch: where dK/dV takes blocks of 32 keys (head_dim 64: or of 64, shared by four sets) and dQ workgroups of the same size, up to
-// kTogether workgroups.  Two launches against one, 150 shapes up to there: 1.0 to 1.9 times faster (1.39 on average);
+// kTogether workgroups.  Two launches against one, 125 shapes up to there: 1.0 to 1.8 times faster (1.27 on average);
 // 700 to 1100 (with row sums that took less time): 0.88 to 1.12, slower where the walks are long (1 x 3528, 16 heads on 8 of 64, 896 workgroups 131 -> 145 us).
-// Head_dim 128, where a piece's row sums take 0.55 us: only while those of the longest walk take less than dQ, which no longer comes first (5.9 us and 1.15 a tile
-// of 128 rows).  us, 1 x 1120, 8 heads on 1 136 (159 in one launch), 1 x 744, 16 on 2 100 (113), 1 x 232, 16 on 2 40.4 (42.0), 1 x 960, 8 on 2 72.0 (72.6), but
-// 3 x 616, 4 on 1 50.9 -> 51.1, 2 x 216, 16 on 2 40.6 -> 37.6, 1 x 2992, 4 on 2 116 -> 110.
+// Head_dim 128, where a piece's row sums take 0.6 us: only while those of the longest walk take less than dQ, which no longer comes first (5.9 us and 1.15 a tile
+// of 128 rows).  us, 1 x 1120, 8 heads on 1 136 (159 in one launch), 1 x 744, 16 on 2 100 (113), 1 x 232, 16 on 2 40.4 (42.1), 3 x 616, 4 on 1 51.1 (53.2), but
+// 3 x 816, 3 on 1 54.6 -> 53.5, 4 x 128, 16 on 2 27.6 -> 25.9, 1 x 2992, 4 on 2 116.0 -> 115.2.
 constexpr int kTogether = 700;
-constexpr double kPieceSums = 0.55;
-static bool runs_together(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv) {
+constexpr double kPieceSums = 0.63;
+static bool walks_pieces(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv) {
     if (!(dkdv.rows == 32 || (dkdv.rows == 64 && dkdv.sets == 4 && a.hd == 64)) || dq.list || (a.hd == 128 && dq.rows != 32)) return false;
     const int64_t blocks = (int64_t)a.B * a.Hkv * ((a.T + dkdv.rows - 1) / dkdv.rows) + (int64_t)a.B * a.Hq * ((a.T + dq.rows - 1) / dq.rows);
     if (blocks > kTogether) return false;
     if (a.hd == 128 && kPieceSums * ((a.Hq / a.Hkv * ((a.T + 31) / 32) + 3) / 4) > 5.9 + 1.15 * ((a.T + 127) / 128)) return false;
-    // dK and dV may take the place of keys and values, but not while dQ reads them
+    return near_pitch(a.ldk) && near_pitch(a.ldo);
+}
+// dK and dV may take the place of keys and values, but not while dQ reads them: dK/dV then has a launch of its own behind dQ, with the same walk, so that
+// its results do not depend on where they go.
+static bool apart_from_inputs(const AttnArgs &a) {
     const int64_t nq = (int64_t)a.Hq * a.hd, nkv = (int64_t)a.Hkv * a.hd;
     const auto apart = [&](const bf16_t *x, int64_t ldx) {
         return !overlap(a, x, ldx, nkv, a.k, a.ldk, nkv) && !overlap(a, x, ldx, nkv, a.v, a.ldv, nkv) && !overlap(a, x, ldx, nkv, a.q, a.ldq, nq) &&
                !overlap(a, x, ldx, nkv, a.dout, a.lddo, nq) && !overlap(a, x, ldx, nkv, a.o, a.ldo, nq);
     };
-    return near_pitch(a.ldk) && near_pitch(a.ldo) && apart(a.dk, a.lddk) && apart(a.dv, a.lddv);
+    return apart(a.dk, a.lddk) && apart(a.dv, a.lddv);
 }
 static hipError_t flash_bwd_both(const AttnArgs &a, const AttnKernel &dq, const AttnKernel &dkdv, hipStream_t s) {
     if (a.hd == 128) return launch_both<128, 1, 4, 1, 4>(a, s);
@@ -1919,6 +1955,10 @@ static hipError_t flash_bwd_both(const AttnArgs &a, const AttnKernel &dq, const 
         case 64: return dkdv.rows == 64 ? launch_both<64, 2, 4, 2, 4>(a, s) : launch_both<64, 2, 4, 1, 8>(a, s);
         default: return dkdv.rows == 64 ? launch_both<64, 1, 8, 2, 4>(a, s) : launch_both<64, 1, 8, 1, 8>(a, s);
     }
+}
+static hipError_t flash_bwd_pieces(const AttnArgs &a, const AttnKernel &dkdv, hipStream_t s) {
+    if (a.hd == 128) return launch_pieces<128, 1, 4>(a, s);
+    return dkdv.rows == 64 ? launch_pieces<64, 2, 4>(a, s) : launch_pieces<64, 1, 8>(a, s);
 }
 
 hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
@@ -1938,9 +1978,11 @@ hipError_t flash_bwd(const AttnArgs &a, hipStream_t s) {
         return e == hipSuccess ? flash_bwd_dq(with_delta, s) : e;
     }
     const AttnKernel dq = dq_kernel(a), dkdv = dkdv_kernel(a);
-    if (runs_together(a, dq, dkdv)) return flash_bwd_both(a, dq, dkdv, s);
+    const bool pieces = walks_pieces(a, dq, dkdv);
+    if (pieces && apart_from_inputs(a)) return flash_bwd_both(a, dq, dkdv, s);
     e = flash_bwd_dq(a, s);
-    return e == hipSuccess ? flash_bwd_dkdv(a, s) : e;
+    if (e != hipSuccess) return e;
+    return pieces ? flash_bwd_pieces(a, dkdv, s) : flash_bwd_dkdv(a, s);
 }
 
 void flash_kernels(const AttnArgs &a, AttnKernel (&k)[3]) {
@@ -1949,5 +1991,6 @@ void flash_kernels(const AttnArgs &a, AttnKernel (&k)[3]) {
     k[2] = dkdv_kernel(a);
     for (int i = 0; i < 3; ++i) k[i].group = k[i].list ? (int)(i < 2 ? query_lists(a) : key_lists(a)).group_size.d : 0;
 }
+bool flash_bwd_together(const AttnArgs &a) { return walks_pieces(a, dq_kernel(a), dkdv_kernel(a)); }
 
 }  // namespace mt

@@ -322,6 +322,8 @@ struct AttnKernel {
     int group;
 };
 void flash_kernels(const AttnArgs &a, AttnKernel (&k)[3]);
+// dQ and dK/dV share a launch (where dK and dV are apart from the inputs)
+bool flash_bwd_together(const AttnArgs &a);
 
 hipError_t fill_u32(void *p, uint32_t value, size_t n_words, hipStream_t s);
 

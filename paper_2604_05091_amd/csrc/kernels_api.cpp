@@ -239,6 +239,12 @@ int32_t mt_k_flash_lists(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t 
     for (int i = 0; i < 3 && st == MT_OK; ++i) lists[i] = k[i].group;
     return st;
 }
+int32_t mt_k_flash_together(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t hd) {
+    if (B <= 0 || T <= 0 || Hq <= 0 || Hkv <= 0 || Hq % Hkv || (hd != 64 && hd != 128)) return MT_ERR_INVALID_ARG;
+    AttnArgs a{};
+    a.B = B; a.T = T; a.Hq = Hq; a.Hkv = Hkv; a.hd = hd;
+    return flash_bwd_together(a);
+}
 
 int32_t mt_k_flash_fwd(uint16_t *o, int64_t ldo, float *lse, const uint16_t *q, int64_t ldq, const uint16_t *k,
                        int64_t ldk, const uint16_t *v, int64_t ldv, int32_t B, int32_t T, int32_t Hq, int32_t Hkv,

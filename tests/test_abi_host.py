@@ -207,6 +207,7 @@ def test_attention_queries_agree():
     r = (ctypes.c_int32 * 3)()
     assert L.mt_k_flash_route(1, 1032, 4, 1, 128, ctypes.addressof(r)) == 0 and list(r) == [32, 32, 32]
     assert L.mt_k_flash_lists(1, 1032, 3, 2, 128, ctypes.addressof(r)) != 0
+    assert L.mt_k_flash_together(1, 520, 8, 2, 64) == 1 and L.mt_k_flash_together(16, 4096, 32, 32, 128) == 0 and L.mt_k_flash_together(1, 520, 3, 2, 64) < 0
 
 
 def _dealt_group(n_sets, copies, n_blocks, tiles):
