@@ -683,8 +683,9 @@ void adam_empty_rows(mt_handle *h, const int32_t *row_start, const AdamHyper &hp
 
 // The rows of the table without a token are updated ahead of the others from this many elements on (a fork and a join of the host threads, which the thread that
 // launches the step's first kernels shares its cores with, cost it more than a smaller job saves).  The host update bounds such a step, and until the
-// backward's first gradient it had nothing to do: two layers 2048 wide, 32 000 rows, 16 384 tokens 48.3 -> 40.6 ms; three layers 128 wide, 22 040 rows, 2472
-// tokens 2.38 -> 2.11.
+// backward's first gradient it had nothing to do: two layers 2048 wide, 32 000 rows, 16 384 tokens 44.5 -> 39.3 ms; three layers 128 wide, 22 040 rows, 2464
+// tokens 2.38 -> 2.12.  Not with staged weights: the host threads are then packing the next units' weights while the forward runs, and the two jobs held each other
+// up (the same models 44.8 -> 46.9 and 3.20 -> 3.52).
 constexpr size_t kEmptyElems = (size_t)1 << 20;
 
 // Host optimizer running beside the GPU (Algorithm 1, optimizer phase; Section 3.3: a background CPU thread
@@ -1609,7 +1610,7 @@ mt_status train_step_core(mt_handle *h, const int32_t *tokens, const int32_t *la
 
     // ---- Phase 1: streaming forward
     STEP(issue_load(0));
-    if (apply_opt && !D.tied) {   // (a tied table has the head's gradient as well)
+    if (apply_opt && !D.tied && !h->staged) {   // (a tied table has the head's gradient as well)
         size_t empty = 0;
         for (int v = 0; v < D.V; ++v) empty += st_rs[v] == st_rs[v + 1];
         if (empty * (size_t)D.d >= kEmptyElems) worker->push_empty_rows(h->w_ready[0], st_rs);

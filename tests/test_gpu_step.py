@@ -129,7 +129,7 @@ def test_overlapped_adam_equals_separate_calls_bitwise():
 @pytest.mark.parametrize("vocab,sub", [(8264, None), (8320, 1000), (8328, 70000)])
 def test_rows_of_the_table_without_a_token_are_updated_ahead(monkeypatch, vocab, sub, flags):
     """A table of more than 2^20 elements without a token in their row: those rows are updated before any gradient has arrived, the others as it lands, in pieces
-    that cut through rows and runs of rows.  The first and the last row with and without a token, runs longer than a piece, single rows; three steps
+    that cut through rows and runs of rows (staged weights: all of them as the gradient lands).  The first and the last row with and without a token, runs longer than a piece, single rows; three steps
     with other tokens equal the separate calls bitwise."""
     shape = ModelShape(1, 128, 2, 2, 64, 136, vocab)
     params = mt_inputs.make_params(shape, seed=41, std=0.05)
