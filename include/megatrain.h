@@ -204,7 +204,9 @@ mt_status mt_adam_step(mt_handle *h, float lr, float beta1, float beta2, float e
  * moments and bf16 copy are updated.  With MT_FLAG_COMPUTE_ONLY / MT_FLAG_COPY_ONLY no update is applied.
  * Failure: argument, shape and token-range errors are found before anything runs and leave every state untouched.
  * An error after that (MT_ERR_HIP) can leave the update applied to the units whose gradients had already landed
- * (the head and the later blocks) and not to the others; nothing is rolled back.  The handle then refuses
+ * (the head and the later blocks), and to any of those rows of the embedding table that this step's tokens do not name (their
+ * gradient is zero, so their update waits for nothing: it may have been applied even if no gradient had landed, parameters and
+ * moments), and not to the others; nothing is rolled back.  The handle then refuses
  * mt_train_step_adam and mt_adam_step with MT_ERR_STATE, so that a retry cannot apply the same step twice to some
  * units, until the caller has restored the parameters (its own arrays) and the moments (through mt_get_tensor)
  * from a copy of its own and called mt_refresh_shadow, which acknowledges the state.  mt_train_step alone stays

@@ -692,7 +692,8 @@ constexpr size_t kEmptyElems = (size_t)1 << 20;
 // applies the update as gradient blocks land).  The step pushes
 // (copy-done event, unit u, element range) right after enqueueing a device-to-host copy of gradients; the worker
 // waits for that event and updates the tensors of the unit inside the range.  A unit's weights are never streamed again in the same
-// step once its gradients exist, so updating its master copy and bf16 copy in place is safe.
+// step once its gradients exist, so updating its master copy and bf16 copy in place is safe.  The table's rows without a token do not wait for
+// gradients: they are safe because an untied table is streamed by the step's first load and by no later one (train_step_core makes sure of it).
 class HostWorker {
   public:
     // opt == nullptr: no optimizer, the worker only drains gradient slabs
@@ -1610,7 +1611,8 @@ mt_status train_step_core(mt_handle *h, const int32_t *tokens, const int32_t *la
 
     // ---- Phase 1: streaming forward
     STEP(issue_load(0));
-    if (apply_opt && !D.tied && !h->staged) {   // (a tied table has the head's gradient as well)
+    // (a tied table has the head's gradient as well, and is streamed twice)
+    if (apply_opt && !D.tied && !h->staged && std::count(load_unit.begin(), load_unit.end(), 0) == 1) {
         size_t empty = 0;
         for (int v = 0; v < D.V; ++v) empty += st_rs[v] == st_rs[v + 1];
         if (empty * (size_t)D.d >= kEmptyElems) worker->push_empty_rows(h->w_ready[0], st_rs);
