@@ -135,6 +135,10 @@ int32_t mt_k_embed_gather(uint16_t *h, const uint16_t *table, const int32_t *tok
  * row_start has V+1 entries. */
 int32_t mt_k_embed_scatter(float *dtable, const uint16_t *dh, const int32_t *row_start, const int32_t *order,
                            int32_t V, int32_t d, void *stream);
+/* How a table of this size is summed (host only, launches nothing): route[0] = 1, 2 or 4 times 512 columns to a block, route[1] = ranges of so many
+ * columns, route[2] = 1 if the ranges of a group of rows are at work side by side, 0 if range after range, route[3] = blocks in front of each range's
+ * for rows of more than 256 terms (0: none) and route[4] = terms in all (row_start[V]) from which on those take part.  The sums are the same whatever the route. */
+int32_t mt_k_embed_scatter_route(int32_t V, int32_t d, int32_t *route);
 
 /* Per row r of logits fp32 [n,V] (V % 4 == 0): loss_rows[r] = logsumexp(z_r) - z_r[label_r];
  * dlogits bf16 [n,V] = (softmax(z_r) - onehot(label_r)) * inv_n.  A negative label gives a zero

@@ -113,6 +113,7 @@ def lib():
         "mt_k_swiglu_bwd": ([p16, p16, p16, c_int64, c_int32, c_void_p], c_int32),
         "mt_k_embed_gather": ([p16, p16, pi, c_int64, c_int32, c_void_p], c_int32),
         "mt_k_embed_scatter": ([pf, p16, pi, pi, c_int32, c_int32, c_void_p], c_int32),
+        "mt_k_embed_scatter_route": ([c_int32, c_int32, pi], c_int32),
         "mt_k_cross_entropy": ([pf, p16, pf, pi, c_int64, c_int32, c_float, c_void_p], c_int32),
         "mt_k_reduce_sum": ([pf, pf, c_int64, c_float, c_int32, c_void_p], c_int32),
         "mt_k_gemm_nt_bias": ([p16, c_int64, p16, c_int64, p16, c_int64, p16, c_int32, c_int32, c_int32, c_void_p], c_int32),

@@ -278,6 +278,14 @@ hipError_t embed_gather(bf16_t *h, const bf16_t *table, const int32_t *tokens, i
 // dtable[V,d] fp32: row v = sum of dh rows listed in order[start[v] .. start[v+1]), added to what it holds or (fully) written
 hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
                          int32_t d, bool add, hipStream_t s);
+// Its kernel: blocks of 512 nc columns in so many ranges, side by side or one after the other; blocks in front (a range's) for the longest rows, if the lists
+// have `enough` terms
+struct ScatterRoute {
+    int nc, ranges;
+    bool side;
+    int heavy, enough;
+};
+ScatterRoute embed_scatter_route(int32_t V, int32_t d);
 
 // Per row: loss_rows[r] = logsumexp(z_r) - z_r[label] (0 for ignored rows); dlogits bf16 = (softmax - onehot) * inv_n
 hipError_t cross_entropy(float *loss_rows, bf16_t *dlogits, const float *logits, const int32_t *labels, int64_t n,

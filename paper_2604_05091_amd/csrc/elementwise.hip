@@ -487,7 +487,7 @@ __device__ __forceinline__ void scatter_terms(float (*acc)[8], const bf16_t *dh,
 template <int NC, bool ADD, bool SIDE>
 __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float *dtable, const bf16_t *dh,
                                                                            const int32_t *row_start, const int32_t *order,
-                                                                           int V, int d, int groups, int heavy) {
+                                                                           int V, int d, int groups, int heavy, int enough) {
     __shared__ float part[kScatterWaves - 1][8][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int bx = SIDE ? blockIdx.z * gridDim.y + blockIdx.y : blockIdx.x / NC, x = bx - heavy, share = blockIdx.x % NC;
@@ -497,10 +497,12 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
     const int col0 = y * (512 * NC), col = col0 + (lane >> 3) * 64 + (lane & 1) * 32 + (lane & 6) * 4;   // (what scatter_store wants)
     const int out0 = (lane >> 3) * 64 + (lane & 7) * 4;
     const int c = col + 512 * share;
-    // the blocks below heavy sum the longest rows of 64 kScatterLook, before all others; the other blocks theirs of a group
+    // the blocks below heavy sum the longest rows of 64 kScatterLook, before all others, if the list has `enough` terms; the other blocks theirs of a group
+    const bool ahead = heavy > 0 && row_start[V] >= enough;
+    if (x < 0 && !ahead) return;
     int first = x >= 0 ? x : bx;
     const int step = x >= 0 ? gx : heavy, n_rows = x >= 0 ? NC * kScatterWaves : 64;
-    const int more = x >= 0 ? kScatterShort : kScatterHeavy, most = x >= 0 && heavy > 0 ? kScatterHeavy : INT32_MAX;
+    const int more = x >= 0 ? kScatterShort : kScatterHeavy, most = x >= 0 && ahead ? kScatterHeavy : INT32_MAX;
     // which of these rows are long: one row per lane, so that the usual block does not pay for looking
     int g_beg = 0, g_cnt = 0;
     const auto look = [&]() {
@@ -844,35 +846,46 @@ hipError_t embed_gather(bf16_t *h, const bf16_t *table, const int32_t *tokens, i
     return hipGetLastError();
 }
 
-hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
-                         int32_t d, bool add, hipStream_t s) {
-    if (V <= 0 || d <= 0 || (d & 7)) return hipErrorInvalidValue;
+ScatterRoute embed_scatter_route(int32_t V, int32_t d) {
+    ScatterRoute r;
     // wide shares for big tables; smaller ones where the blocks would be too few for the chip (NC = 1 / 2 / 4 / a block per row, us):
     // 4848 uniform tokens, V = 1096, d = 1280 5.4 / 5.4 / 6.3 / 5.6; 4096 tokens, V = 1024, d = 1024 4.5 / 5.4 / 6.0 / 5.1; 65 536, 2000, 5120
     // 173 / 167 / 188 / 207; 4096, 4000, 4096 16.5 / 16.1 / 16.5 / 18.9; 800, 11 704, 1600 17.8 / 16.0 / 15.6 / 15.2; 65 536, 32 000, 4096
     // 297 / 260 / 213 / 217
     const auto blocks = [&](int nc) { return (int64_t)((V + 7) / 8) * ((d + 512 * nc - 1) / (512 * nc)); };
-    const int nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
-    const int gx = (int)blocks_for(V, kScatterWaves * nc);
-    const unsigned ny = blocks_for(d, 512 * nc);
-    // Rows of more than kScatterHeavy terms first, in blocks of their own that look through 64 kScatterLook rows: a frequent token's row that comes
-    // late is summed alone at the end.  Ids of a Zipf law scattered over the table, with the lookup, us: 65 536 tokens, 32 000 x 4096 425 -> 412,
-    // x 2048 239 -> 219, x 1280 170 -> 154; where no row is that long it costs 1 to 3 % (16 384 tokens, 32 000 x 4096 187 -> 192, 213 before whole
-    // lines per store).  From 125 such groups on: fewer hold too many long rows each (65 536 tokens, 5000 x 640 99, 129 in 20 groups of two shares).
-    const int heavy_groups = (int)blocks_for(V, 64 * kScatterLook), heavy = nc == 4 && heavy_groups * ny >= 125 ? heavy_groups : 0;
-    const int gy = std::min(gx + heavy, 1 << 15);
+    r.nc = d > 1024 && blocks(4) >= 1200 ? 4 : d > 512 && blocks(2) >= 260 ? 2 : 1;
+    r.ranges = (int)blocks_for(d, 512 * r.nc);
+    // Rows of more than kScatterHeavy terms first, in blocks of their own that look through 64 kScatterLook rows of a column range: a frequent token's row that
+    // comes late is summed alone at the end.  Measured on 288 tables (V 5000 .. 64 000, one to three ranges, 4096 .. 65 536 ids of a Zipf law scattered over the table,
+    // or uniform ones), without -> with such blocks.
+    // Their number is groups x ranges x 4.  From 46 groups x ranges on, three quarters of a block per compute unit: 47 .. 64 1.06 times faster on average (65 536 ids,
+    // 12 000 x 1280 88 -> 78 us, 8000 x 4096 162 -> 149); fewer hold too many long rows each: at 40 from 10 000 x 1280
+    // 82 -> 95 to 5000 x 4096 173 -> 166.
+    // And from two terms to three rows x ranges on, which only the device knows: what the long rows save grows with the terms, what the looking costs with rows x
+    // ranges.  1.04 times faster on average (32 000 x 4096, 65 536 ids 230 -> 218; uniform ids 211 -> 214); below that it costs 2 to 4 % (16 384 ids, 32 000 x 4096 137 -> 142,
+    // 64 000 x 4096 235 -> 246), and blocks that leave at once up to 1 % (235 -> 236).
+    const int groups = (int)blocks_for(V, 64 * kScatterLook);
+    r.heavy = r.nc == 4 && (int64_t)groups * r.ranges >= 46 ? groups : 0;
+    r.enough = (int)std::min<int64_t>(INT32_MAX, (int64_t)V * r.ranges * 2 / 3);
     // Several column ranges come side by side: by ranges, the heavy rows of the later ones begin late, and all shares of such a row fall on NC XCDs.
     // Zipf-distributed ids in order of frequency, by ranges -> side by side, us: 65 536 tokens, V = 32 000, d = 4096 328 -> 284 (uniform ids
     // 215 -> 217), d = 5120 418 -> 345, 4096 tokens, V = 1024, d = 4096 30.2 -> 21-23.  Not where narrow blocks come out even or as the better
     // end: with one whole range and a narrower one (65 536, 32 000, 2560) 309 with the lookup, side by side 323; 8192, 4000, 3584 (NC = 2) 60.7,
     // 61.6; nor two ranges of NC = 2 (4096, 1500, 2048: 18.1, 18.7) and NC = 1, tables small enough to be at work all at once.
-    const bool side = nc == 4 ? d >= 2 * 512 * nc : nc == 2 && d > 2 * 512 * nc && d % (512 * nc) == 0;
-    const dim3 grid = side ? dim3(nc * ny, gy, blocks_for(gx + heavy, gy)) : dim3(nc * (gx + heavy), ny), block(64 * kScatterWaves);
-    auto kernel = nc == 1 ? embed_scatter_kernel<1, false, false> : nc == 2 ? embed_scatter_kernel<2, false, false> : embed_scatter_kernel<4, false, false>;
-    if (add) kernel = nc == 1 ? embed_scatter_kernel<1, true, false> : nc == 2 ? embed_scatter_kernel<2, true, false> : embed_scatter_kernel<4, true, false>;
-    if (side && nc == 2) kernel = add ? embed_scatter_kernel<2, true, true> : embed_scatter_kernel<2, false, true>;
-    if (side && nc == 4) kernel = add ? embed_scatter_kernel<4, true, true> : embed_scatter_kernel<4, false, true>;
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d, gx, heavy);
+    r.side = r.nc == 4 ? d >= 2 * 512 * r.nc : r.nc == 2 && d > 2 * 512 * r.nc && d % (512 * r.nc) == 0;
+    return r;
+}
+hipError_t embed_scatter(float *dtable, const bf16_t *dh, const int32_t *row_start, const int32_t *order, int32_t V,
+                         int32_t d, bool add, hipStream_t s) {
+    if (V <= 0 || d <= 0 || (d & 7)) return hipErrorInvalidValue;
+    const ScatterRoute r = embed_scatter_route(V, d);
+    const int gx = (int)blocks_for(V, kScatterWaves * r.nc), gy = std::min(gx + r.heavy, 1 << 15);
+    const dim3 grid = r.side ? dim3(r.nc * r.ranges, gy, blocks_for(gx + r.heavy, gy)) : dim3(r.nc * (gx + r.heavy), r.ranges), block(64 * kScatterWaves);
+    auto kernel = r.nc == 1 ? embed_scatter_kernel<1, false, false> : r.nc == 2 ? embed_scatter_kernel<2, false, false> : embed_scatter_kernel<4, false, false>;
+    if (add) kernel = r.nc == 1 ? embed_scatter_kernel<1, true, false> : r.nc == 2 ? embed_scatter_kernel<2, true, false> : embed_scatter_kernel<4, true, false>;
+    if (r.side && r.nc == 2) kernel = add ? embed_scatter_kernel<2, true, true> : embed_scatter_kernel<2, false, true>;
+    if (r.side && r.nc == 4) kernel = add ? embed_scatter_kernel<4, true, true> : embed_scatter_kernel<4, false, true>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, dtable, dh, row_start, order, V, d, gx, r.heavy, r.enough);
     return hipGetLastError();
 }
 

@@ -199,6 +199,13 @@ int32_t mt_k_embed_scatter(float *dtable, const uint16_t *dh, const int32_t *row
     return to_status(embed_scatter(dtable, dh, row_start, order, V, d, false, S(stream)));
 }
 
+int32_t mt_k_embed_scatter_route(int32_t V, int32_t d, int32_t *route) {
+    if (V <= 0 || d <= 0 || (d & 7) || !route) return MT_ERR_INVALID_ARG;
+    const ScatterRoute r = embed_scatter_route(V, d);
+    route[0] = r.nc; route[1] = r.ranges; route[2] = r.side; route[3] = r.heavy; route[4] = r.heavy ? r.enough : 0;
+    return MT_OK;
+}
+
 int32_t mt_k_cross_entropy(float *loss_rows, uint16_t *dlogits, const float *logits, const int32_t *labels, int64_t n,
                            int32_t V, float inv_n, void *stream) {
     if (!loss_rows || !dlogits || !logits || !labels || !al16(logits) || ((uintptr_t)dlogits & 7))

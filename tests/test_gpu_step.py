@@ -318,7 +318,9 @@ def test_tied_embeddings_match_oracle(orc64, K, flags, on_host):
 
 # The embedding's part of a tied table's gradient is added to the head's on the device by a kernel that takes one, two or four times 512 columns: d and
 # the vocabulary choose.  Ids that no token has, that one to 32 tokens have (a wave adds them) and more (a block does).
-@pytest.mark.parametrize("d,vocab,T", [(128, 520, 72), (1024, 2088, 136), (1032, 2088, 136), (1088, 9608, 200), (2048, 9608, 200)])
+# Column ranges side by side, two of 2048 and three of 1024 columns; the longest rows first, in one range and in two side by side.
+@pytest.mark.parametrize("d,vocab,T", [(128, 520, 72), (1024, 2088, 136), (1032, 2088, 136), (1088, 9608, 200), (2048, 9608, 200), (3072, 704, 72), (4096, 4808, 72),
+                                       (1032, 12040, 4016), (4096, 5896, 3936)])
 @pytest.mark.parametrize("adam", [False, True])
 def test_tied_table_gradient_without_room_for_the_heads_part(adam, d, vocab, T):
     """The head's part of a tied table's gradient waits on the device for the embedding's, or, where a cap on the device memory leaves no
@@ -326,6 +328,11 @@ def test_tied_table_gradient_without_room_for_the_heads_part(adam, d, vocab, T):
     shape = ModelShape(1, d, 4, 2, 64, 264, vocab, tie_embeddings=True)
     params = mt_inputs.make_params(shape, seed=73, std=0.05)
     tok, lab = mt_inputs.make_batch(shape.vocab, 2, T, seed=74)
+    route = (ctypes.c_int32 * 5)()
+    assert mt.lib().mt_k_embed_scatter_route(vocab, d, ctypes.addressof(route)) == 0
+    assert route[2] == (d >= 3072) and (route[3] > 0) == (T > 1000) and route[4] <= 2 * T
+    if route[3]:
+        tok.ravel()[200:500], tok.ravel()[600:857], tok.ravel()[900:1156] = 9, 64 * route[3], 3 * 64 * route[3] + 1   # (more than 256 terms, as many)
     tok.ravel()[:65] = 7                # (more than a wave adds alone)
     tok.ravel()[70:102] = vocab - 1     # (as many as it does)
     assert (tok == 7).sum() > 32 and len(np.unique(tok)) < vocab
