@@ -84,6 +84,8 @@ int32_t mt_k_gemm_route(int32_t form, int32_t M, int32_t N, int32_t K, int64_t l
 /* Waves of a workgroup among which mt_k_gemm_nt (form 0, 1 as above) shares the reduction of a tile: 8 or 4 on small grids with a long
  * reduction (up to 8192 rows and columns, or more columns in one round of tiles), otherwise (and for fp32 results with K % 64 == 0) 1. */
 int32_t mt_k_gemm_sharers(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc);
+/* 1 where mt_k_gemm_nt (form 0, 1 as above) fetches whole lines of rows that are not whole lines (K % 64 != 0) and puts them together, else 0. */
+int32_t mt_k_gemm_fetches_lines(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc);
 /* db[cols] fp32 (written) = sum over the n rows of x [n, ld] bf16 (the gradient of such a bias); cols % 8 == 0;
  * ws: device scratch of at least mt_k_bias_grad_ws_bytes(cols) bytes.  Fixed summation order. */
 size_t mt_k_bias_grad_ws_bytes(int32_t cols);

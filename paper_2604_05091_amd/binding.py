@@ -136,6 +136,7 @@ def lib():
         "mt_k_flash_together": ([c_int32, c_int32, c_int32, c_int32, c_int32], c_int32),
         "mt_k_gemm_route": ([c_int32, c_int32, c_int32, c_int32, c_int64, c_int32, pi], c_int32),
         "mt_k_gemm_sharers": ([c_int32, c_int32, c_int32, c_int32, c_int64], c_int32),
+        "mt_k_gemm_fetches_lines": ([c_int32, c_int32, c_int32, c_int32, c_int64], c_int32),
         "mt_k_bias_grad_ws_bytes": ([c_int32], c_size_t),
         "mt_k_bias_grad": ([pf, p16, c_int64, c_int64, c_int32, c_void_p, c_void_p], c_int32),
         "mt_k_flash_fwd": ([p16, c_int64, pf, p16, c_int64, p16, c_int64, p16, c_int64, c_int32, c_int32, c_int32,

@@ -238,6 +238,8 @@ int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu);
 // tn: tiles of tile_m x tile_n, `whole` of which a workgroup walks alone in the 256 x 256 kernel.
 void gemm_nt_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
 int gemm_nt_sharers(const GemmArgs &g);   // waves that share the reduction of such a tile
+// its tile fetches whole lines of rows that are not whole lines (line_nt_kernel)
+bool gemm_nt_fetches_lines(const GemmArgs &g);
 void gemm_tn_route(const GemmArgs &g, int *whole, int *tile_m, int *tile_n);
 
 // out[b][c][r] = in[b][r][c] for r < rows, c < cols (bf16); leading dimensions in elements.

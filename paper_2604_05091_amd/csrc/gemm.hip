@@ -1298,6 +1298,10 @@ int gemm_nt_sharers(const GemmArgs &g) {
         if (r.tile && c.cost.tile == r.tile->tile) return c.waves;
     return 1;
 }
+bool gemm_nt_fetches_lines(const GemmArgs &g) {
+    const TileCost *tile = nt_route(g).tile;
+    return tile >= std::begin(kLineCosts) && tile < std::end(kLineCosts);
+}
 
 int gemm_tn_pick_split(int64_t M, int64_t N, int64_t K, int n_cu) {
     if (M <= 0 || N <= 0 || K < BK || n_cu <= 0) return 1;

@@ -116,12 +116,20 @@ int32_t mt_k_gemm_route(int32_t form, int32_t M, int32_t N, int32_t K, int64_t l
     return MT_OK;
 }
 
+// an NT product whose operands have rows as tight as K, for the queries about it
+static bool nt_query(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc, GemmArgs *g) {
+    if (form < 0 || form > 1 || M <= 0 || N <= 0 || K <= 0 || ldc < N) return false;
+    g->A = g->B = g->R = nullptr; g->C = nullptr; g->lda = g->ldb = K; g->ldc = ldc; g->ldr = 0;
+    g->M = M; g->N = N; g->K = K; g->out_fp32 = form > 0; g->accumulate = 0;
+    return true;
+}
 int32_t mt_k_gemm_sharers(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc) {
-    if (form < 0 || form > 1 || M <= 0 || N <= 0 || K <= 0 || ldc < N) return MT_ERR_INVALID_ARG;
     GemmArgs g;
-    g.A = g.B = g.R = nullptr; g.C = nullptr; g.lda = g.ldb = K; g.ldc = ldc; g.ldr = 0;
-    g.M = M; g.N = N; g.K = K; g.out_fp32 = form > 0; g.accumulate = 0;
-    return gemm_nt_sharers(g);
+    return nt_query(form, M, N, K, ldc, &g) ? gemm_nt_sharers(g) : MT_ERR_INVALID_ARG;
+}
+int32_t mt_k_gemm_fetches_lines(int32_t form, int32_t M, int32_t N, int32_t K, int64_t ldc) {
+    GemmArgs g;
+    return nt_query(form, M, N, K, ldc, &g) ? gemm_nt_fetches_lines(g) : MT_ERR_INVALID_ARG;
 }
 
 size_t mt_k_bias_grad_ws_bytes(int32_t cols) { return bias_grad_ws_floats(cols) * sizeof(float); }

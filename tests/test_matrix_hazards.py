@@ -1,6 +1,7 @@
 """The GEMM kernels update their accumulators with matrix instructions written in assembly, whose latency the compiler does not
 know: it may place a move of an accumulator right behind the instruction that writes it.  This looks through the assembly of
 the library's own kernels for such moves, and for vector instructions that write an operand right in front of one."""
+import functools
 import os
 import re
 import subprocess
@@ -59,16 +60,22 @@ def test_findings_on_small_texts():
     assert findings("_Z1k:\n v_mov_b32 v5, v9\n v_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n") != []
 
 
-def test_no_accumulator_is_touched_too_early():
+@functools.cache
+def assemblies():
     def assembly(source):
         r = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-o", "-", os.path.join(build.CSRC, source)],
                            capture_output=True, text=True, check=True)
         return r.stdout
 
+    sources = ("gemm.hip", "gemm_ring.hip")
     with ThreadPoolExecutor() as ex:
-        for source, text in zip(("gemm.hip", "gemm_ring.hip"), ex.map(assembly, ("gemm.hip", "gemm_ring.hip"))):
-            assert "v_mfma_f32_16x16x32_bf16" in text
-            assert findings(text) == [], source
+        return list(zip(sources, ex.map(assembly, sources)))
+
+
+def test_no_accumulator_is_touched_too_early():
+    for source, text in assemblies():
+        assert "v_mfma_f32_16x16x32_bf16" in text
+        assert findings(text) == [], source
 
 
 def set_too_late(assembly):
@@ -95,7 +102,5 @@ def set_too_late(assembly):
 def test_no_accumulator_is_set_too_late():
     late = "_Z1k:\n v_accvgpr_write_b32 a0, 0\n v_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n"
     assert set_too_late(late) != [] and set_too_late(late.replace("0\n", "0\n s_nop 1\n")) == []
-    for source in ("gemm.hip", "gemm_ring.hip"):
-        text = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-o", "-", os.path.join(build.CSRC, source)], capture_output=True, text=True,
-                              check=True).stdout
+    for source, text in assemblies():
         assert set_too_late(text) == [], source
