@@ -498,7 +498,7 @@ __global__ __launch_bounds__(64 * kScatterWaves) void embed_scatter_kernel(float
     const int out0 = (lane >> 3) * 64 + (lane & 7) * 4;
     const int c = col + 512 * share;
     // the blocks below heavy sum the longest rows of 64 kScatterLook, before all others, if the list has `enough` terms; the other blocks theirs of a group
-    const bool ahead = heavy > 0 && row_start[V] >= enough;
+    const bool ahead = NC == 4 && heavy > 0 && row_start[V] >= enough;   // (heavy = 0 where NC < 4; unread there, which is 0.1 us of 4)
     if (x < 0 && !ahead) return;
     int first = x >= 0 ? x : bx;
     const int step = x >= 0 ? gx : heavy, n_rows = x >= 0 ? NC * kScatterWaves : 64;
