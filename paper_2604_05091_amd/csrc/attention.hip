@@ -21,7 +21,7 @@
 // they are read from the natural row-major LDS tiles with the gfx950 transposing LDS read
 // (ds_read_b64_tr_b16), which hands each lane four consecutive rows of one column; two such
 // reads give exactly the eight reduction indices of the accumulator permutation.
-// dQ and dK/dV are separate kernels: no atomics, results are bit-reproducible.
+// dQ and dK/dV walk the scores apart, in kernels of their own or side by side in one launch (small problems): no atomics, results are bit-reproducible.
 //
 // Tiles go from memory to LDS without passing through registers (DirectTile); where their 16-byte chunks lie is chosen so that
 // row-wise and transposing reads are free of bank conflicts.  Against tiles that were fetched into registers and written to LDS

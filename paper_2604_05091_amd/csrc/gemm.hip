@@ -1191,6 +1191,9 @@ static const TileCost kLineCosts[] = {{RingTile::l128x128, 128, 128, 1, 0.40, 0.
 // (16 rounds instead of 20) 2524 -> 2452, x 13 824 6523 -> 6283 (1477 TFLOP/s); the projections of 5 x 512
 // tokens, 3712 wide, forward (of which 2560 x 3712 x 3712 in 0.78 of a round of 256 x 192) 291 -> 269; among products that run at the power limit even;
 // 2000 x 5120 x 5120 (half a round) 94, in 256 x 320 115, and 8200 x 2560 x 6400 (1.03 rounds) 213, 301, keep theirs.
+// The kernel takes any width of whole groups of 8.  Other widths, by the same estimate but alone, operands from memory: 256 x 320 where N % 64 == 0 1.02 to 1.36 times faster
+// (24 products, 1.14 on average: 4152 x 4672 x 2304 93 -> 74 us), any N 1.01 to 1.27 (12, 1.09), 256 x 192 with any N 1.08 to 1.26 (8, 1.15).  They keep their
+// tiles: among the other products of a block, at the power limit, that has not been measured.
 constexpr int kWideStages = 8;   // (shorter walks were not looked at)
 static const TileCost kWideCosts[] = {{RingTile::wide320, 256, 320, 1, 1.03, 1.545, 12.5, 0.0}, {RingTile::wide192, 256, 192, 1, 0.55, 1.09, 9.8, 0.0}};
 
@@ -1268,7 +1271,7 @@ hipError_t gemm_nt(const GemmArgs &g0, hipStream_t s, int32_t of_rows) {
     if (g.lda < g.K || g.ldb < g.K || (g.C && g.ldc < g.N)) return hipErrorInvalidValue;
     if (g.R && (g.out_fp32 || g.ldr < g.N)) return hipErrorInvalidValue;
     if (g.bias && g.out_fp32) return hipErrorInvalidValue;
-    // offsets inside one tile are 32-bit: 256 rows of either operand must stay below 2^31 elements
+    // offsets inside one tile are 32-bit: 256 rows of A, and the 320 of B that the widest tile has, must stay below 2^31 elements
     if (g.lda >= (1 << 22) || g.ldb >= (1 << 22)) return hipErrorInvalidValue;
     if (g.rope_cos || g.glu_F || g.glu_bwd_gu) return launch_w4e(g, s);
     switch (variant_override()) {   // diagnostic override (MT_GEMM_VARIANT), 0 = the estimate
